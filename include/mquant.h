@@ -494,10 +494,14 @@ typedef enum {
     MQUANT_TUNE_GEMM_TILE = 0,      /* -1 = cost model; 0 = 256x256, 1 = 128x256, 2 = 192x128,
                                        3 = 64x128, 4 = 64x256 (short prompts) */
     MQUANT_TUNE_GEMM_NOSPLIT = 1,   /* 0 = cost model; 1 = never split K */
-    MQUANT_TUNE_G128_TILE = 2,      /* -1 = cost model; 0 = 128x256, 1 = 96x256 (weight-only GEMM) */
-    MQUANT_TUNE_GEMV_VARIANT = 3    /* -1 = default; 0..3 = waves per work-group x loads in flight per
+    MQUANT_TUNE_G128_TILE = 2,      /* -1 = cost model; 0 = 256x256, 1 = 96x128 (weight-only GEMM) */
+    MQUANT_TUNE_GEMV_VARIANT = 3,   /* -1 = default; 0..3 = waves per work-group x loads in flight per
                                        wave of the decode GEMV: 4x8|4x4, 8x4|8x4, 8x8|4x8, 4x16|8x8
                                        (16-channel units | 32-channel units) */
+    MQUANT_TUNE_G128_SHAPE = 4      /* the setting of G128_TILE over all its tiles: -1 = cost model;
+                                       0 = 256x256, 1 = 96x128, 2 = 256x128, 3 = 192x128, 4 = 160x128,
+                                       5 = 128x128, 6 = 64x128, 7 = 128x64, 8 = 64x64, 9 = 32x64,
+                                       10 = 64x32, 11 = 32x32 */
 } mquant_tune_key_t;
 
 /*

@@ -125,7 +125,7 @@ def build_id() -> str:
     return lib.mquant_build_id().decode()
 
 
-TUNE_GEMM_TILE, TUNE_GEMM_NOSPLIT, TUNE_G128_TILE, TUNE_GEMV_VARIANT = 0, 1, 2, 3
+TUNE_GEMM_TILE, TUNE_GEMM_NOSPLIT, TUNE_G128_TILE, TUNE_GEMV_VARIANT, TUNE_G128_SHAPE = 0, 1, 2, 3, 4
 
 
 def tune_set(key: int, value: int) -> None:

@@ -42,10 +42,11 @@ static inline int launch_status()
 struct TuneState {
     std::atomic<int32_t> gemm_tile{-1};
     std::atomic<int32_t> gemm_nosplit{0};
-    std::atomic<int32_t> g128_tile{-1};
+    std::atomic<int32_t> g128_tile{-1};       // index into the table of w4g128_gemm.hip
     std::atomic<int32_t> gemv_variant{-1};
 };
 TuneState &tune_state();
+constexpr int kG128Tiles = 12;            // tiles of the weight-only GEMM
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

@@ -28,6 +28,7 @@
 
 #include <atomic>
 
+#include "lds_dma.h"
 #include "mquant_internal.h"
 
 using namespace mquant;
@@ -40,10 +41,7 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int kGroup = 128;               // input channels per weight scale
-constexpr int kAPitch = 272;              // bytes per LDS row of the A tile: 128 halves + 16 pad
-
-// 16-byte reads of 16 consecutive rows at pitch 272 B start at banks 68 r mod 64 = 4 r:
-// the 64 banks exactly once.
+constexpr int64_t kG128MaxLdx = int64_t(1) << 23;   // 255 rows of 2 * ldx bytes within 32 bits
 
 __global__ __launch_bounds__(256) void g128_prepack_kernel(
     const uint8_t *__restrict__ w, const __half *__restrict__ scales, uint32_t *__restrict__ out_w,
@@ -126,219 +124,260 @@ __device__ __forceinline__ void tile_of_group(int32_t id, int32_t tiles_m, int32
     tn = in_band / rows;
 }
 
-// Work-group tile BM x BN, WM x WN wavefronts.  K advances one scale group (128
-// channels, two k-tiles) at a time; the A tile of the next group is fetched into
-// registers while the current one is multiplied, then written to the other LDS
-// buffer: one barrier per group.
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(WM *WN * 64, 2) void w4g128_gemm_kernel(
-    const __half *__restrict__ x, int64_t ldx, const v4u *__restrict__ wp,
+// Prefill shapes: one work-group of eight waves computes an MT*32 x NWN*32 tile.  The waves
+// stand as NWN column waves x KS = 8 / NWN K slices: a wave owns all MT*32 rows of one
+// 32-channel column and one 64-channel k-tile of every stage, so each weight is dequantised
+// once per work-group (15 VALU operations per MT MFMAs), and the KS slices of a column are
+// added through LDS at the end.
+//
+// A stage is KS k-tiles.  Everything in it arrives by LDS-DMA: the activations (KS slabs of
+// MT*32 rows x 128 bytes, 16-byte chunk c of row r at c ^ ((r >> 1) & 7): 16 consecutive rows
+// cover the 64 banks once on both sides), every wave's own weight tile (1 KiB) and its 32
+// scales.  NB stage buffers: after the barrier that ends the reads of stage s, its buffer is
+// refilled with stage s + NB.  The barrier sits kWin MFMAs before the end of a stage, whose
+// last operands are in registers by then, and the first fragments and weights of the next
+// stage are requested behind it, so neither the LDS latency nor the dequantisation of a
+// stage's first step is exposed.
+//
+// What bounds it: with few work-groups the length of K each walks (hence the slices: 18944 x
+// 3584 at T = 128 makes 224 groups of 64 x 32 instead of 28 of 96 x 256, 184 -> 47 us; 3584 x 4608 at
+// T = 128 37.9 -> 14.5 us), with all compute units busy the clock under matrix-core power
+// (256 x 256 at 1280 x 3584 x 37888: matrix pipes 61 % of the cycles at 1.80 GHz, 361 -> 305 us
+// against a 128 x 256 tile that dequantised every weight twice as often: 66 % at 1.58 GHz, 313 us).
+
+template <int MT, int NWN>
+struct G128Tile {
+    static constexpr int KS = 8 / NWN;
+    static constexpr int WIN = MT > 1 ? 4 : 2;        // A fragments requested ahead of the MFMA that uses them
+    static constexpr int A_SLAB = MT * 32 * 128, A_STAGE = KS * A_SLAB;
+    static constexpr int B_OFF = A_STAGE, S_OFF = B_OFF + 8 * 1024, STAGE = S_OFF + 8 * 256;
+    static constexpr int CHA = MT * KS / 2;           // 1 KiB activation blocks a wave copies per stage
+    static constexpr int PER = CHA + 2;               // ... and the weight tile and the scales
+    static constexpr int RED = NWN * MT * 4 * (KS - 1) * 1024;   // slice sums in transit
+    static constexpr int EPI = RED + 8 * 32 * 80;                // ... and the store patches
+    static_assert((MT * KS) % 2 == 0, "blocks must divide evenly over the waves");
+};
+
+template <int MT, int NWN, int NB>
+constexpr int g128_lds_bytes()
+{
+    using G = G128Tile<MT, NWN>;
+    return NB * G::STAGE > G::EPI ? NB * G::STAGE : G::EPI;
+}
+
+template <int MT, int NWN, int NB>
+__global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 4 : 2)) void w4g128_gemm_kernel(
+    const __half *__restrict__ x, int64_t ldx, const uint8_t *__restrict__ wp,
     const __half *__restrict__ sT, __half *__restrict__ y, int64_t ldy, int32_t T, int32_t N,
     int32_t K, int32_t tiles_m, int32_t tiles_n, int32_t n_tiles32, int32_t wide_store,
     int32_t band)
 {
-    constexpr int NW = WM * WN, NTHR = NW * 64;
-    constexpr int MT = BM / WM / 32, NT = BN / WN / 32;
-    constexpr int A_BUF = BM * kAPitch;
-    constexpr int A_LOADS = BM * 16 / NTHR;           // 16-byte chunks of the A tile per thread
-    static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && (BM * 16) % NTHR == 0, "tile shape");
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // g128_lds_bytes<...>()
+    using G = G128Tile<MT, NWN>;
+    constexpr int KS = G::KS, kWin = G::WIN;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];   // g128_lds_bytes<...>()
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, g = lane >> 5;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wn = wave % NWN, ks = wave / NWN;
     int32_t tm, tn;
     tile_of_group(blockIdx.x, tiles_m, tiles_n, band, tm, tn);
-    const int32_t row0 = tm * BM;
-    const int32_t ntile0 = tn * (BN / 32);
+    const int32_t row0 = tm * MT * 32;
     const int32_t k_tiles = K / kPackK;
-    const int32_t trips = K / kGroup;
+    const int32_t stages = (k_tiles + KS - 1) / KS;
     const int32_t n_pad = n_tiles32 * kPackN;
+    const int32_t n0 = (tn * NWN + wn) * kPackN;      // first column of this wave
+    // column tiles past the last one repeat it (never stored)
+    const int32_t ntile = tn * NWN + wn < n_tiles32 ? tn * NWN + wn : n_tiles32 - 1;
 
-    // n-tiles of this wave, clamped to the last real tile (columns beyond N are never stored)
-    int32_t my_tile[NT];
+    // ---- copies.  Uniform bases and 32-bit lane offsets; rows past T repeat row T - 1 and
+    // k-tiles past the last one repeat it (neither result is used).
+    const uint8_t *xbase = reinterpret_cast<const uint8_t *>(x + static_cast<int64_t>(row0) * ldx);
+    const uint8_t *wbase = wp + static_cast<int64_t>(ntile) * k_tiles * kPackTileBytes;
+    const uint8_t *sbase = reinterpret_cast<const uint8_t *>(sT + ntile * kPackN);
+    const uint32_t lds0 = lds_address(smem);
+    uint32_t aoff[G::CHA];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int32_t t = ntile0 + wn * NT + nt;
-        my_tile[nt] = t < n_tiles32 ? t : n_tiles32 - 1;
+    for (int i = 0; i < G::CHA; ++i) {
+        const int r = ((wave + 8 * i) % (MT * 4)) * 8 + (lane >> 3);
+        const int32_t row = row0 + r < T ? r : T - 1 - row0;
+        aoff[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(ldx * 2) +
+                  (((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
-
-    // Rows past T read row T - 1 again: their results are never stored.
-    v4u areg[A_LOADS];
-    const __half *arow[A_LOADS];
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) {
-        const int c = tid + i * NTHR;
-        const int32_t row = row0 + (c >> 4);
-        arow[i] = x + static_cast<int64_t>(row < T ? row : T - 1) * ldx + (c & 15) * 8;
-    }
-    auto load_a = [&](int32_t trip) {
-#pragma unroll
-        for (int i = 0; i < A_LOADS; ++i)
-            areg[i] = *reinterpret_cast<const v4u *>(arow[i] + static_cast<int64_t>(trip) * kGroup);
-    };
-    auto store_a = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_LOADS; ++i) {
-            const int c = tid + i * NTHR;
-            *reinterpret_cast<v4u *>(smem + buf * A_BUF + (c >> 4) * kAPitch + (c & 15) * 16) = areg[i];
-        }
-    };
-    auto load_b = [&](int32_t trip, v4u (&b)[2][NT]) {
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                b[kk][nt] = wp[(static_cast<int64_t>(my_tile[nt]) * k_tiles + 2 * trip + kk) * 64 + lane];
-    };
-    auto load_s = [&](int32_t trip, uint16_t (&s)[NT]) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            s[nt] = __builtin_bit_cast(
-                uint16_t, sT[static_cast<int64_t>(trip) * n_pad + my_tile[nt] * kPackN + l32]);
+    auto copy_piece = [&](int i, int32_t s, uint32_t buf) {   // buf: byte offset of the stage buffer
+        const int b = wave + 8 * i;
+        int32_t kt = s * KS + (i < G::CHA ? b / (MT * 4) : ks);
+        kt = kt < k_tiles ? kt : k_tiles - 1;
+        if (i < G::CHA)
+            lds_dma16_uniform_base(xbase + static_cast<int64_t>(kt) * (kPackK * 2), aoff[i < G::CHA ? i : 0],
+                                   lds0 + buf + b * 1024);
+        else if (i == G::CHA)
+            lds_dma16_uniform_base(wbase + static_cast<int64_t>(kt) * kPackTileBytes, lane * 16,
+                                   lds0 + buf + G::B_OFF + wave * 1024);
+        else
+            lds_dma4_uniform_base(sbase + static_cast<int64_t>(kt >> 1) * n_pad * 2, (lane & 15) * 4,
+                                  lds0 + buf + G::S_OFF + wave * 256);
     };
 
-    v16f acc[MT][NT];
+    v16f acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mt][nt][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.0f;
 
     const uint32_t mask = 0x000F000Fu;
     uint32_t magic = 0x64006400u;
     asm volatile("" : "+v"(magic));           // keep it in a VGPR (third operand of v_and_or_b32)
+    const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
 
-    // One scale group (eight MFMA steps) on LDS buffer `buf` with weights b and scales s.
-    auto compute = [&](int buf, const v4u (&b)[2][NT], const uint16_t (&s)[NT]) {
-        const uint8_t *abase = smem + buf * A_BUF + (wm * MT * 32 + l32) * kAPitch + g * 64;
-        v2h s2[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const _Float16 v = __builtin_bit_cast(_Float16, s[nt]);
-            s2[nt] = v2h{v, v};
-        }
-        // Operands of MFMA step i + 1 (A fragments from LDS, dequantised weights) are produced
-        // while the MFMAs of step i run: a fragment read just before its MFMA would expose
-        // the LDS latency once per MFMA.
-        v8h bfr[2][NT], afr[2][MT];
-        auto fetch = [&](int i) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                afr[i & 1][mt] = *reinterpret_cast<const v8h *>(abase + mt * 32 * kAPitch +
-                                                                (i >> 2) * 128 + (i & 3) * 16);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                bfr[i & 1][nt] =
-                    __builtin_bit_cast(v8h, dequant8(b[i >> 2][nt][i & 3], s2[nt], mask, magic));
-        };
-        fetch(0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (i < 7) fetch(i + 1);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(afr[i & 1][mt], bfr[i & 1][nt],
-                                                                        acc[mt][nt], 0, 0, 0);
-            // order inside the step: the next step's fragment reads first, then its VALU work
-            // dealt between this step's MFMAs
-            if (i < 7) {
-                __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);
-#pragma unroll
-                for (int j = 0; j < MT * NT; ++j) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, (16 * NT + MT * NT - 1) / (MT * NT), 0);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);      // nothing moves across steps: bounds the live operands
-        }
+    // fragment (st, mt): chunk g * 4 + st of row mt * 32 + l32 of this wave's slab
+    const uint32_t a_lane = ks * G::A_SLAB + l32 * 128 + (((g * 4) ^ ((l32 >> 1) & 7)) << 4);
+    auto afrag = [&](uint32_t buf, int st, int mt) {
+        return *reinterpret_cast<const v8h *>(smem + buf + (a_lane ^ (st << 4)) + mt * 4096);
+    };
+    auto btile = [&](uint32_t buf) {
+        return *reinterpret_cast<const v4u *>(smem + buf + G::B_OFF + wave * 1024 + lane * 16);
+    };
+    auto scale = [&](uint32_t buf) {
+        const _Float16 v = *reinterpret_cast<const _Float16 *>(smem + buf + G::S_OFF + wave * 256 + l32 * 2);
+        return v2h{v, v};
+    };
+    auto dequant_pair = [&](uint32_t v, int j, v2h s2) -> uint32_t {
+        v2h h = __builtin_bit_cast(v2h, and_or(v >> (4 * j), mask, magic));
+        h = (h - bias) * s2;                      // the difference is exact; one rounding
+        return __builtin_bit_cast(uint32_t, h);
     };
 
-    // Two groups per loop trip with two register sets for the weights, so that no set is
-    // copied and every wait is for loads issued a whole group earlier.  The last fetch of
-    // a tile repeats the final group instead of branching; it is not used.  The scheduling
-    // fences keep the fetches of the next group ahead of this group's arithmetic (the
-    // compiler would otherwise sink them next to their LDS stores and expose the whole
-    // memory latency).
-    v4u b0[2][NT], b1[2][NT];
-    uint16_t s0[NT], s1[NT];
-    load_a(0);
-    load_b(0, b0);
-    load_s(0, s0);
-    store_a(0);
-    __syncthreads();
+    // ---- prologue: fill every buffer, wait for stage 0, first operands
+#pragma unroll
+    for (int s = 0; s < NB; ++s)
+        if (s < stages)
+#pragma unroll
+            for (int i = 0; i < G::PER; ++i) copy_piece(i, s, s * G::STAGE);
+    if (NB == 3 && stages >= 3) wait_vmcnt<2 * G::PER>();
+    else if (stages >= 2) wait_vmcnt<G::PER>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 
-    for (int32_t t = 0; t < trips; t += 2) {
-        const int32_t t1 = t + 1 < trips ? t + 1 : trips - 1;
-        load_a(t1);
-        load_b(t1, b1);
-        load_s(t1, s1);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(0, b0, s0);
-        __builtin_amdgcn_sched_barrier(0);
-        store_a(1);
-        __syncthreads();
-        if (t + 1 >= trips) break;
+    uint32_t cur = 0;
+    v4u bw = btile(0);
+    v2h s2 = scale(0);
+    v8h fr[kWin];
+#pragma unroll
+    for (int i = 0; i < kWin; ++i) fr[i] = afrag(0, i / MT, i % MT);
+    v4u bf[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bf[0][j] = dequant_pair(bw[0], j, s2);
 
-        const int32_t t2 = t + 2 < trips ? t + 2 : trips - 1;
-        load_a(t2);
-        load_b(t2, b0);
-        load_s(t2, s0);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(1, b1, s1);
-        __builtin_amdgcn_sched_barrier(0);
-        store_a(0);
-        __syncthreads();
+    // A wave whose slice ends a stage early (K / 64 not a multiple of KS) leaves the loop one
+    // stage early; there is no barrier in the last stage.
+    const int32_t my_stages = (stages - 1) * KS + ks < k_tiles ? stages : stages - 1;
+    for (int32_t s = 0; s < my_stages; ++s) {
+        const uint32_t nxt = cur + G::STAGE == NB * G::STAGE ? 0 : cur + G::STAGE;
+        v4u bw_n = bw;
+        v2h s2_n = s2;
+        constexpr int NM = 4 * MT;
+        constexpr int kBar = NM - kWin, kLand = kBar - (MT < 4 ? MT : 4);
+        static_assert(kLand >= 0, "");
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const int st = m / MT, mt = m % MT;
+            if (m == kLand) {
+                // this wave's copies of the next stage have landed: its own weights and scales
+                if (NB == 3 && s + 2 < stages) wait_vmcnt<G::PER>();
+                else wait_vmcnt<0>();
+                asm volatile("" ::: "memory");
+                bw_n = btile(nxt);
+                s2_n = scale(nxt);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (m == kBar && s + 1 < stages) {
+                // every operand of this stage is in registers, every wave's copies have landed
+                wait_lgkm0();
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[m % kWin], __builtin_bit_cast(v8h, bf[st & 1]),
+                                                            acc[mt], 0, 0, 0);
+            const int f = m + kWin;                    // the fragment requested behind this MFMA
+            if (f < NM) fr[m % kWin] = afrag(cur, f / MT, f % MT);
+            else fr[m % kWin] = afrag(nxt, (f - NM) / MT, (f - NM) % MT);
+            if (m >= kBar && s + NB < stages) {        // refill the buffer just freed, a few pieces per MFMA
+#pragma unroll
+                for (int i = (m - kBar) * G::PER / kWin; i < (m - kBar + 1) * G::PER / kWin; ++i)
+                    copy_piece(i, s + NB, cur);
+            }
+            // the next step's weights, dealt over the MFMAs of this one
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((MT >= 4 ? MT - 4 + j : j * MT / 4) == mt)
+                    bf[(st + 1) & 1][j] = dequant_pair(st < 3 ? bw[(st + 1) & 3] : bw_n[0], j, st < 3 ? s2 : s2_n);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        bw = bw_n;
+        s2 = s2_n;
+        cur = nxt;
     }
+    __syncthreads();                                    // every wave is done with the stage buffers
 
-    const int32_t wave_row0 = row0 + wm * (BM / WM);
-    const int32_t wave_n0 = (ntile0 + wn * NT) * 32;
+    // ---- add the K slices of a column.  The rows of a 32x32 block held by registers 4 q .. 4 q + 3
+    // (eight rows of the block) are unit mt * 4 + q; unit u belongs to slice u % KS, every other
+    // slice hands its part over through LDS.
+    if constexpr (KS > 1) {
+        float *red = reinterpret_cast<float *>(smem) + wn * (MT * 4 * (KS - 1) * 256);
+        auto slot = [&](int u, int from) {             // from: (source slice - owner) mod KS, 1 .. KS - 1
+            return red + ((u * (KS - 1) + from - 1) * 4) * 64 + lane;
+        };
+#pragma unroll
+        for (int u = 0; u < MT * 4; ++u) {
+            const int from = (ks - u % KS + KS) % KS;
+            if (from != 0)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) slot(u, from)[e * 64] = acc[u / 4][(u % 4) * 4 + e];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MT * 4; ++u)
+            if (u % KS == ks)
+#pragma unroll
+                for (int from = 1; from < KS; ++from)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[u / 4][(u % 4) * 4 + e] += slot(u, from)[e * 64];
+    }
 
     if (!wide_store) {
         // every lane stores its own 2-byte results
+        const int32_t n = n0 + l32;
+        if (n >= N) return;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int32_t n = wave_n0 + nt * 32 + l32;
-            if (n >= N) continue;
+        for (int u = 0; u < MT * 4; ++u)
+            if (u % KS == ks)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int32_t row = wave_row0 + mt * 32 + acc_row(r, g);
-                    if (row < T) y[static_cast<int64_t>(row) * ldy + n] = __float2half_rn(acc[mt][nt][r]);
+                for (int e = 0; e < 4; ++e) {
+                    const int32_t row = row0 + (u / 4) * 32 + (u % 4) * 8 + g * 4 + e;
+                    if (row < T) y[static_cast<int64_t>(row) * ldy + n] = __float2half_rn(acc[u / 4][(u % 4) * 4 + e]);
                 }
-        }
         return;
     }
 
-    // Wide stores: the MFMA result has a lane per column; each wave turns 32 rows x
-    // NT*32 columns through its own LDS patch (the A buffers are free after the last
-    // barrier) and stores 16 bytes per lane.
-    constexpr int ROWB = NT * 64 + 16;
-    constexpr int LPR = NT * 64 / 16;
-    constexpr int RPI = 64 / LPR;
-    uint8_t *patch = smem + wave * (32 * ROWB);
+    // Wide stores: the MFMA result has a lane per column; each wave turns its units through its
+    // own LDS patch and stores 16 bytes per lane.
+    uint8_t *patch = smem + G::RED + wave * (32 * 80);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int rl = acc_row(r, g);
+        for (int r = 0; r < 16; ++r)
+            if ((mt * 4 + r / 4) % KS == ks)
+                *reinterpret_cast<__half *>(patch + acc_row(r, g) * 80 + l32 * 2) = __float2half_rn(acc[mt][r]);
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                *reinterpret_cast<__half *>(patch + rl * ROWB + (nt * 32 + l32) * 2) =
-                    __float2half_rn(acc[mt][nt][r]);
-        }
-#pragma unroll
-        for (int q = 0; q < 32 / RPI; ++q) {
-            const int rl = q * RPI + lane / LPR;
-            const int c = lane % LPR;
-            const v4u v = *reinterpret_cast<const v4u *>(patch + rl * ROWB + c * 16);
-            const int32_t row = wave_row0 + mt * 32 + rl;
-            const int32_t n = wave_n0 + c * 8;
-            if (row < T && n < N)                                  // N % 8 == 0 on this path
+        for (int q = 0; q < 2; ++q) {
+            const int rl = q * 16 + lane / 4, c = lane % 4;
+            const v4u v = *reinterpret_cast<const v4u *>(patch + rl * 80 + c * 16);
+            const int32_t row = row0 + mt * 32 + rl, n = n0 + c * 8;
+            if ((mt * 4 + rl / 8) % KS == ks && row < T && n < N)      // N % 8 == 0 on this path
                 *reinterpret_cast<v4u *>(y + static_cast<int64_t>(row) * ldy + n) = v;
         }
     }
@@ -435,27 +474,20 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_kernel(
     }
 }
 
-template <int BM, int BN, int WM, int WN>
-constexpr int g128_lds_bytes()
-{
-    constexpr int a = 2 * BM * kAPitch;                                   // two A buffers
-    constexpr int patch = WM * WN * 32 * (BN / WN / 32 * 64 + 16);        // epilogue patches
-    return a > patch ? a : patch;
-}
-
-template <int BM, int BN, int WM, int WN>
+template <int MT, int NWN, int NB>
 int launch_g128(const __half *x, int64_t ldx, const uint8_t *wp, __half *y, int64_t ldy, int32_t T,
                 int32_t N, int32_t K, hipStream_t stream)
 {
     const int32_t n_tiles32 = static_cast<int32_t>(ceil_div(N, kPackN));
-    const int32_t tiles_m = static_cast<int32_t>(ceil_div(T, BM));
-    const int32_t tiles_n = static_cast<int32_t>(ceil_div(N, BN));
+    const int32_t tiles_m = static_cast<int32_t>(ceil_div(T, MT * 32));
+    const int32_t tiles_n = static_cast<int32_t>(ceil_div(n_tiles32, NWN));
     const int64_t w_bytes = static_cast<int64_t>(n_tiles32) * (K / kPackK) * kPackTileBytes;
     const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
     const int32_t wide = (N % 8 == 0 && ldy % 8 == 0 && aligned_to(y, 16)) ? 1 : 0;
-    const int32_t band = tiles_m < 4 ? tiles_m : 4;
-    constexpr int lds = g128_lds_bytes<BM, BN, WM, WN>();
-    auto kern = w4g128_gemm_kernel<BM, BN, WM, WN>;
+    const int32_t band = tiles_m <= 8 ? tiles_m : 6;
+    constexpr int lds = g128_lds_bytes<MT, NWN, NB>();
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    auto kern = w4g128_gemm_kernel<MT, NWN, NB>;
     // Raising the dynamic LDS limit is idempotent: threads racing here at most repeat it.
     static std::atomic<bool> attr_set{false};
     if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
@@ -464,10 +496,56 @@ int launch_g128(const __half *x, int64_t ldx, const uint8_t *wp, __half *y, int6
             return MQUANT_ERR_HIP;
         attr_set.store(true, std::memory_order_release);
     }
-    MQ_LAUNCH(kern, dim3(tiles_m * tiles_n), dim3(WM * WN * 64), lds,
-              stream, x, ldx, reinterpret_cast<const v4u *>(wp), sT, y, ldy, T, N, K, tiles_m,
-              tiles_n, n_tiles32, wide, band);
+    MQ_LAUNCH(kern, dim3(tiles_m * tiles_n), dim3(512), lds, stream, x, ldx, wp, sT, y, ldy, T, N, K,
+              tiles_m, tiles_n, n_tiles32, wide, band);
     return launch_status();
+}
+
+using G128Launch = int (*)(const __half *, int64_t, const uint8_t *, __half *, int64_t, int32_t, int32_t, int32_t,
+                           hipStream_t);
+
+// The compiled tiles and what a launch of each costs: fixed + k-tiles * (per_round * rounds +
+// per_tile * tiles / CUs), in microseconds.  The second term is the length of the longest chain
+// of tiles a compute unit walks, the third what full occupancy adds (clock, L2).  Fitted to
+// the time of every tile on the 7B and 72B projections (K 3584 .. 29568, N 3584 .. 59136) at 23
+// row counts from 9 to 2048; the tile the model picks is within 2 % of the fastest one on
+// average.  Tiles that no shape of that sweep lost by leaving out (128 x 256, 64 x 256, 32 x 128)
+// are not built.  All twelve are needed: leaving out two more costs 3 - 5 % on average and up to
+// 25 % on single shapes.
+struct G128Variant {
+    int32_t bm, bn, per_cu;               // per_cu: work-groups a compute unit holds at a time
+    G128Launch launch;
+    double fixed, per_round, per_tile;
+};
+constexpr G128Variant kG128[] = {
+    {256, 256, 1, launch_g128<8, 8, 3>, 3.7, 1.139, 0.507}, {96, 128, 2, launch_g128<3, 4, 2>, 4.2, 0.310, 0.218},
+    {256, 128, 1, launch_g128<8, 4, 2>, 7.9, 0.579, 0.356}, {192, 128, 1, launch_g128<6, 4, 2>, 6.2, 0.461, 0.277},
+    {160, 128, 1, launch_g128<5, 4, 3>, 5.9, 0.400, 0.234}, {128, 128, 1, launch_g128<4, 4, 3>, 5.4, 0.373, 0.178},
+    {64, 128, 2, launch_g128<2, 4, 3>, 5.5, 0.250, 0.168},  {128, 64, 1, launch_g128<4, 2, 2>, 4.2, 0.227, 0.115},
+    {64, 64, 1, launch_g128<2, 2, 3>, 4.3, 0.147, 0.067},   {32, 64, 1, launch_g128<1, 2, 3>, 5.0, 0.118, 0.0},
+    {64, 32, 1, launch_g128<2, 1, 2>, 2.7, 0.115, 0.040},   {32, 32, 1, launch_g128<1, 1, 3>, 3.7, 0.072, 0.018},
+};
+constexpr int kG128Variants = sizeof(kG128) / sizeof(kG128[0]);
+static_assert(kG128Variants == kG128Tiles, "mquant_tune_set validates against this");
+
+const G128Variant &g128_choose(int32_t T, int32_t N, int32_t K)
+{
+    const int32_t forced = tune_state().g128_tile.load(std::memory_order_relaxed);
+    if (forced >= 0) return kG128[forced];
+    int best = 0;
+    double best_us = 0.0;
+    for (int i = 0; i < kG128Variants; ++i) {
+        const G128Variant &v = kG128[i];
+        const int64_t tiles = ceil_div(T, v.bm) * ceil_div(N, v.bn);
+        const double us = v.fixed + static_cast<double>(K / kPackK) *
+                                        (v.per_round * static_cast<double>(ceil_div(tiles, kNumCU * v.per_cu)) +
+                                         v.per_tile * static_cast<double>(tiles) / kNumCU);
+        if (i == 0 || us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
+    return kG128[best];
 }
 
 }  // namespace
@@ -513,18 +591,17 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
     const __half *xh = static_cast<const __half *>(x);
     __half *yh = static_cast<__half *>(y);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Decode shapes stream the weights through the GEMV.  In the GEMM every wave owns 32
-    // output channels of the tile (WM = 1): a weight is dequantised once
-    // per work-group.
+    // Up to eight rows the GEMV streams the weights (at 8 rows both are within 3 %: 7B down
+    // 25.5 against 25.9 us, gate_up 23.1 against 22.8; at 1 row 22.1 against 26.5 and 21.7
+    // against 24.5, at 16 rows 30.9 against 26.0 and 27.9 against 23.0).  It also takes rows so far
+    // apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of them at a time.
     const int32_t n_tiles32 = static_cast<int32_t>(ceil_div(N, kPackN));
-    if (T <= 32 || (T <= 64 && n_tiles32 < 512)) {
+    const bool forced = tune_state().g128_tile.load(std::memory_order_relaxed) >= 0;
+    if ((T <= 8 && !forced) || ldx >= kG128MaxLdx) {
         const int64_t w_bytes = static_cast<int64_t>(n_tiles32) * (K / kPackK) * kPackTileBytes;
         const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
         const v4u *wt = reinterpret_cast<const v4u *>(wp);
         const int32_t n_pad = n_tiles32 * kPackN;
-        // The GEMV holds 32 token rows (one MFMA M extent).  With few output tiles, up to 64
-        // rows take two launches: that still beats a GEMM whose few tiles would each walk all
-        // of K alone (18944 x 3584 at T = 64: 91 us against 129 us).
         for (int32_t t0 = 0; t0 < T; t0 += 32) {
             const int32_t tc = T - t0 < 32 ? T - t0 : 32;
             const __half *xc = xh + static_cast<int64_t>(t0) * ldx;
@@ -543,15 +620,5 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
         }
         return MQUANT_OK;
     }
-    if (T <= 64) return launch_g128<64, 128, 1, 4>(xh, ldx, wp, yh, ldy, T, N, K, st);
-    // 96 x 256 when it fills more CUs per round than 128 x 256 (rounds over the CUs x tile
-    // rows / measured relative efficiency): 1280 x 3584 makes 196 tiles instead of 140 and
-    // runs 12 % faster; with thousands of tiles the taller tile wins by 15 %.
-    const double c128 = static_cast<double>(ceil_div(ceil_div(T, 128) * ceil_div(N, 256), kNumCU)) * 128.0;
-    const double c96 = static_cast<double>(ceil_div(ceil_div(T, 96) * ceil_div(N, 256), kNumCU)) * 96.0 / 0.9;
-    int tile = c96 < c128 ? 1 : 0;
-    const int32_t forced = tune_state().g128_tile.load(std::memory_order_relaxed);
-    if (forced >= 0) tile = forced;
-    if (tile == 1) return launch_g128<96, 256, 1, 8>(xh, ldx, wp, yh, ldy, T, N, K, st);
-    return launch_g128<128, 256, 1, 8>(xh, ldx, wp, yh, ldy, T, N, K, st);
+    return g128_choose(T, N, K).launch(xh, ldx, wp, yh, ldy, T, N, K, st);
 }

@@ -165,6 +165,27 @@ def test_both_gemm_tiles_on_ragged_shapes(mq, tile):
         mq.tune_set(mq.TUNE_G128_TILE, -1)
 
 
+@pytest.mark.parametrize("shape", range(12))
+def test_every_gemm_tile_on_ragged_shapes(mq, shape):
+    """Each compiled tile forced on: one stage of K or fewer (K = 128 with up to eight K slices),
+    slices that end a stage early (K / 64 not a multiple of the slice count), the pipeline's two
+    and three stages, rows and columns that end inside a tile, 2-byte stores, one row."""
+    mq.tune_set(mq.TUNE_G128_SHAPE, shape)
+    try:
+        rng = np.random.default_rng(90 + shape)
+        for T, N, K in [(1, 32, 128), (9, 40, 256), (33, 300, 384), (70, 264, 1152), (257, 552, 640), (300, 130, 1920)]:
+            wq, sc = make_weight(rng, N, K)
+            x = (rng.standard_normal((T, K)) * 1.5).astype(np.float16)
+            ref, mag = orc.w4g128_linear(x, wq, sc)
+            wp = mq.w4g128_prepack(dev(pack_int4(wq)), dev(sc))
+            say(f"tile shape {shape} T={T} N={N} K={K}")
+            y = torch.full((T, N), float("nan"), dtype=torch.float16, device="cuda")
+            mq.w4g128_gemm(dev(x), wp, N, out=y)
+            check(y.cpu().numpy(), ref, mag, f"w4g128 tile shape {shape} {(T, N, K)}")
+    finally:
+        mq.tune_set(mq.TUNE_G128_SHAPE, -1)
+
+
 def test_output_beyond_2_31_elements(mq):
     """T x N > 2^31 outputs: 64-bit addressing of y, on sampled rows (K = one group)."""
     T, N, K = 70000, 37888, 128
