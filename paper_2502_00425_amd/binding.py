@@ -126,6 +126,7 @@ def build_id() -> str:
 
 
 TUNE_GEMM_TILE, TUNE_GEMM_NOSPLIT, TUNE_G128_TILE, TUNE_GEMV_VARIANT, TUNE_G128_SHAPE = 0, 1, 2, 3, 4
+TUNE_GEMM_SHAPE = 5
 
 
 def tune_set(key: int, value: int) -> None:

@@ -44,11 +44,15 @@ struct TuneState {
     std::atomic<int32_t> gemm_nosplit{0};
     std::atomic<int32_t> g128_tile{-1};       // index into the table of w4g128_gemm.hip
     std::atomic<int32_t> gemv_variant{-1};
+    std::atomic<int32_t> gemm_sliced{-1};     // index into the table of w4a8_sliced.hip
 };
 TuneState &tune_state();
+constexpr int kSlicedTiles = 11;          // tiles of the sliced W4A8 GEMM
 constexpr int kG128Tiles = 12;            // tiles of the weight-only GEMM
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// The same for sizes and tile edges in 32 bits: the cost models ask dozens of times per call.
+static inline uint32_t ceil_div32(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 
 // Geometry of the prepacked int4 weight layout (see w4a8_gemm.hip).
 constexpr int kPackN = 32;                // output channels per packed tile (one MFMA N extent)

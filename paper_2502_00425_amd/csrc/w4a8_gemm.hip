@@ -856,27 +856,14 @@ int launch_gemm(const int8_t *xq, const uint8_t *wp, const void *w_scale, void *
     return launch_status();
 }
 
-// Tile choice.  256x256 (one work-group per CU, three stages) has the best
-// steady-state rate; 128x256 with two stages fits two work-groups per CU, which
-// hides one group's prologue and epilogue under the other's main loop and
-// halves the tile-count granularity.  Cost model: rounds over the 256 CUs times
-// tile area, the smaller tile derated by its measured relative rate.
-//
-// Short prompts on matrices with many output channels (up to 128 rows; the few-channel ones
-// go to the tile GEMV): one or two rows of 64-row tiles, three stages, several work-groups per
-// CU.  With one row of 128- or 256-row tiles the k-loop of a lone, mostly empty work-group per
-// CU sets the time.  Measured at T = 64, 64x128 / 64x256 against the 128x256 tile the cost
-// model below would pick: 3584 -> 18944 15.3 / 19.1 against 22.6 us, 3584 -> 37888 23.0 / 20.7
-// against 32.7, 8192 -> 59136 53.6 / 48.9 against 72.8; at T = 128: 3584 -> 18944 20.5
-// against 23.2, 8192 -> 10240 28.4 against 37.9, 3584 -> 37888 no difference (30.5).
+// Tile choice of the prefill GEMM.  256x256 (one work-group per CU, three stages) has the best
+// steady-state rate; 128x256 with two stages fits two work-groups per CU, which hides one
+// group's prologue and epilogue under the other's main loop and halves the tile-count
+// granularity; 192x128 when 128x256 tiles leave a third of the CUs idle (1280 x 4608: 252 tiles
+// instead of 180; 28 us against 31 us).  Rounds of work-groups over the CUs x tile area /
+// measured relative efficiency of the tile.
 int pick_gemm_tile(int32_t T, int32_t N)
 {
-    if (T <= 128) {
-        const int64_t groups = ceil_div(T, 64) * ceil_div(N, 128);       // of 64x128 tiles
-        if (T <= 64) return groups <= kNumCU ? 3 : 4;
-        if (groups <= kNumCU + kNumCU / 4) return 3;
-    }
-    // rounds of work-groups over the CUs x tile area / measured relative efficiency of the tile
     const double a = static_cast<double>(ceil_div(ceil_div(T, 256) * ceil_div(N, 256), kNumCU)) *
                      256.0 * 256.0;
     const double b = static_cast<double>(ceil_div(ceil_div(T, 128) * ceil_div(N, 256), kNumCU)) *
@@ -885,6 +872,21 @@ int pick_gemm_tile(int32_t T, int32_t N)
                      192.0 * 128.0 / 0.78;
     if (a <= b && a <= c) return 0;
     return b <= c ? 1 : 2;
+}
+
+// What the plan above costs in microseconds (split-K with its reduction, or the tile), for the
+// comparison with the sliced GEMM; fitted to the same sweep as the table of w4a8_sliced.hip
+// (rms 2 - 4 %).
+double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
+{
+    if (splits > 1)
+        return 6.62 + 1.561 * static_cast<double>(ceil_div(K / 128, splits)) +
+               1.163e-6 * splits * static_cast<double>(T) * N;
+    static constexpr TileCost cost[3] = {{256, 256, 1, 0.0, 7.34, 1.070, 0.0, 0.472},
+                                         {128, 256, 2, 2.23, 4.55, 1.023, 0.493, 0.386},
+                                         {192, 128, 1, 2.33, 1.53, 0.615, 0.0, 0.154}};
+    const TileCost &c = cost[pick_gemm_tile(T, N)];
+    return c.us(static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn), K);
 }
 
 }  // namespace
@@ -917,22 +919,22 @@ extern "C" int mquant_w4_prepack(const uint8_t *w, uint8_t *out, int32_t N, int3
 
 namespace {
 
-// Shapes the tile GEMV takes instead of the prefill GEMM: up to 32 rows (one pass), every K
-// the prefill kernel does not handle, and short prompts against matrices with few output
-// channels, where the GEMM would run a single, mostly empty row of tiles at its fixed cost
-// while the GEMV streams the weights once per 64 rows (two row blocks per weight tile).
-// Measured at 33..64 rows, GEMV against GEMM: 3584 x 3584 and 3584 x 4608 9 against 22 us,
-// 18944 x 3584 24-30 against 33-35, 8192 x 8192 15 against 31, 8192 x 10240 23-25 against 32,
-// 29568 x 8192 39-43 against 60; with 18944 or more output channels the GEMM fills enough
-// compute units to win (3584 x 18944: 22-23 us either way, x 37888: 38 against 32).  At
-// 65..128 rows the second pass pays for small matrices only (3584 x 3584: 14-16 against 22 us,
-// 8192 x 8192 24-29 against 34; 18944 x 3584 49 against 36).
-bool gemv_tile_takes(int32_t T, int32_t N, int32_t K)
+// Shapes the tile GEMV takes: up to 16 rows, where its smaller fixed cost wins (T = 16, tile or
+// streaming GEMV against the sliced GEMM: 3584 x 3584 5.0 against 6.1 us, 3584 x 37888 16.8
+// against 18.2, 8192 x 59136 44.2 against 46.6; at 24 rows 6.0 / 6.1, 19.8 / 18.6, 51.9 / 49.5 and
+// 18944 x 3584 18.9 / 14.0), and every K the GEMM kernels do not handle.
+bool gemv_tile_takes(int32_t T, int32_t K) { return T < kGemmMinT || K % 128 != 0; }
+
+// Pieces of the split-K plan that the caller's workspace has to hold (1: none).  Short prompts
+// on few channels ask for no workspace: the sliced GEMM is far ahead there.
+int workspace_splits(int32_t T, int32_t N, int32_t K)
 {
-    if (T <= kGemvMaxT || K % 128 != 0) return true;
-    if (tune_state().gemm_tile.load(std::memory_order_relaxed) >= 0) return false;   // a forced GEMM tile
-    if (T <= 2 * kGemvMaxT) return N <= 12288;
-    return T <= 4 * kGemvMaxT && N <= 8192 && static_cast<int64_t>(N) * K <= (int64_t{1} << 26);
+    if (T <= kGemvMaxT || K % 128 != 0) return 1;
+    if (tune_state().gemm_tile.load(std::memory_order_relaxed) < 0) {
+        if (T <= 2 * kGemvMaxT && N <= 12288) return 1;
+        if (T <= 4 * kGemvMaxT && N <= 8192 && static_cast<int64_t>(N) * K <= (int64_t{1} << 26)) return 1;
+    }
+    return plan_splits(T, N, K);
 }
 
 }  // namespace
@@ -1007,8 +1009,7 @@ extern "C" int64_t mquant_w4a8_workspace_bytes(int32_t T, int32_t N, int32_t K)
 {
     if (T < 0 || N < 0 || K < 0) return MQUANT_ERR_BAD_SHAPE;
     if (K % kPackK != 0 || K > kMaxK) return MQUANT_ERR_UNSUPPORTED;
-    if (gemv_tile_takes(T, N, K)) return 0;
-    const int splits = plan_splits(T, N, K);
+    const int splits = workspace_splits(T, N, K);
     return splits > 1 ? static_cast<int64_t>(splits) * T * N * 4 : 0;
 }
 
@@ -1021,50 +1022,43 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
                   int32_t *acc_out, int32_t T, int32_t N, int32_t K, Epilogue ep, void *workspace,
                   int64_t workspace_bytes, hipStream_t stream)
 {
-    if (gemv_stream_takes(T, K, ceil_div(N, kPackN))) {
-        GemvGroup grp = {};
-        grp.n = 1;
-        grp.p[0].wp = reinterpret_cast<const uint4 *>(wp);
-        grp.p[0].w_scale = static_cast<const __half *>(w_scale);
-        grp.p[0].y = static_cast<__half *>(y);
-        grp.p[0].acc_out = acc_out;
-        grp.p[0].ldy = ldy;
-        grp.p[0].N = N;
-        return gemv_stream_dispatch<EPI>(xq, T, K, grp, ep, stream);
+    GemvGroup grp = {};
+    grp.n = 1;
+    grp.p[0].wp = reinterpret_cast<const uint4 *>(wp);
+    grp.p[0].w_scale = static_cast<const __half *>(w_scale);
+    grp.p[0].y = static_cast<__half *>(y);
+    grp.p[0].acc_out = acc_out;
+    grp.p[0].ldy = ldy;
+    grp.p[0].N = N;
+    const bool force_sliced = tune_state().gemm_sliced.load(std::memory_order_relaxed) >= 0 && K % 128 == 0;
+    if (!force_sliced) {
+        if (gemv_stream_takes(T, K, ceil_div(N, kPackN)))
+            return gemv_stream_dispatch<EPI>(xq, T, K, grp, ep, stream);
+        if (gemv_tile_takes(T, K)) return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);
     }
-    if (gemv_tile_takes(T, N, K)) {
-        GemvGroup grp = {};
-        grp.n = 1;
-        grp.p[0].wp = reinterpret_cast<const uint4 *>(wp);
-        grp.p[0].w_scale = static_cast<const __half *>(w_scale);
-        grp.p[0].y = static_cast<__half *>(y);
-        grp.p[0].acc_out = acc_out;
-        grp.p[0].ldy = ldy;
-        grp.p[0].N = N;
-        return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);
-    }
-    int splits = plan_splits(T, N, K);
-    const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
-    if (tune_state().gemm_nosplit.load(std::memory_order_relaxed)) splits = 1;
+    const int splits = tune_state().gemm_nosplit.load(std::memory_order_relaxed) ? 1 : workspace_splits(T, N, K);
     if (splits > 1) {
         const int64_t need = static_cast<int64_t>(splits) * T * N * 4;
         if (!workspace || workspace_bytes < need) return MQUANT_ERR_WORKSPACE;
         if (!aligned_to(workspace, 256)) return MQUANT_ERR_ALIGNMENT;
+    }
+    // The sliced GEMM where it is expected to be clearly ahead: few tiles (T = 128: 3584 x 4608 17.1
+    // -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1 -> 15.9; T = 512: 22.8 -> 16.2 on 3584
+    // x 4608).  Closer calls go to the tiles below: where every CU is busy the clock is bound by
+    // power, and their waves, 64 columns wide, read each activation fragment from LDS for two
+    // MFMAs instead of one (T = 1280 over the four 7B projections: the sliced tiles 2 - 6 % ahead in
+    // short bursts, 3 % behind in a continuous run).
+    const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
+    if (force_sliced || force_tile >= kPrefillTiles ||
+        (force_tile < 0 && sliced_cost_us(T, K, grp) < 0.88 * prefill_cost_us(T, N, K, splits)))
+        return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
+    if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,
                                                  static_cast<int32_t *>(workspace), stream);
-    }
     const int tile = force_tile < 0 ? pick_gemm_tile(T, N) : force_tile;
-    if (tile == 3)
-        return launch_gemm<64, 128, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
-                                                nullptr, stream);
-    if (tile == 4)
-        return launch_gemm<64, 256, 1, 8, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
-                                                nullptr, stream);
     if (tile == 0)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
                                                  nullptr, stream);
-    // 192 x 128 (wave tile 96 x 32): the middle ground when 128 x 256 tiles leave a third of
-    // the CUs idle (1280 x 4608: 252 tiles instead of 180; 28 us against 31 us).
     if (tile == 2)
         return launch_gemm<192, 128, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
                                                  nullptr, stream);

@@ -599,7 +599,10 @@ extern "C" int mquant_w4a8_gemv_grouped(const int8_t *xq, int32_t T, int32_t K, 
     ep.n_vis = n_vis, ep.s_vis = s_vis, ep.s_txt = s_txt, ep.K = K, ep.xq = xq;
     int64_t group_tiles = 0;
     for (int32_t i = 0; i < grp.n; ++i) group_tiles += ceil_div(grp.p[i].N, kPackN);
-    // outside the streaming kernels' range: the tile kernel, still one launch for the group
+    // outside the streaming kernels' range: the sliced GEMM or the tile kernel, still one launch
+    // for the group
+    if (T >= kGemmMinT && K % 128 == 0)
+        return sliced_dispatch<kEpiStatic>(xq, T, K, grp, ep, static_cast<hipStream_t>(stream));
     if (!gemv_stream_takes(T, K, group_tiles))
         return gemv_tile_dispatch<kEpiStatic>(xq, T, K, grp, ep, static_cast<hipStream_t>(stream));
     return gemv_stream_dispatch<kEpiStatic>(xq, T, K, grp, ep, static_cast<hipStream_t>(stream));

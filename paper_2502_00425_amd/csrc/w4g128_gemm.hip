@@ -536,10 +536,12 @@ const G128Variant &g128_choose(int32_t T, int32_t N, int32_t K)
     double best_us = 0.0;
     for (int i = 0; i < kG128Variants; ++i) {
         const G128Variant &v = kG128[i];
-        const int64_t tiles = ceil_div(T, v.bm) * ceil_div(N, v.bn);
+        const int64_t tiles = static_cast<int64_t>(ceil_div32(T, v.bm)) * ceil_div32(N, v.bn);
+        const int shift = v.per_cu == 2 ? 9 : 8;          // work-groups per round: per_cu (1 or 2) x 256
+        const int64_t rounds = (tiles + (int64_t{1} << shift) - 1) >> shift;
         const double us = v.fixed + static_cast<double>(K / kPackK) *
-                                        (v.per_round * static_cast<double>(ceil_div(tiles, kNumCU * v.per_cu)) +
-                                         v.per_tile * static_cast<double>(tiles) / kNumCU);
+                                        (v.per_round * static_cast<double>(rounds) +
+                                         v.per_tile * static_cast<double>(tiles) * (1.0 / kNumCU));
         if (i == 0 || us < best_us) {
             best = i;
             best_us = us;
