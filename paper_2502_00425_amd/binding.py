@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
@@ -152,10 +153,15 @@ def _dp(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _rows(t, what: str) -> None:
-    """A 2-D operand the ABI addresses through a leading dimension: unit stride along a row."""
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1) or (t.shape[0] > 1 and t.stride(0) < t.shape[1]):
-        raise MQuantError(ERR_BAD_SHAPE, f"{what}: expected a 2-D tensor with unit column stride")
+def _rows(t, what: str) -> int:
+    """A 2-D operand the ABI addresses through a leading dimension, which is returned: unit
+    stride along a row."""
+    st = t.stride()
+    if len(st) == 2:
+        rows, cols = t.shape
+        if (st[1] == 1 or cols <= 1) and (st[0] >= cols or rows <= 1):
+            return st[0]
+    raise MQuantError(ERR_BAD_SHAPE, f"{what}: expected a 2-D tensor with unit column stride")
 
 
 def _dense(t, what: str) -> None:
@@ -164,9 +170,34 @@ def _dense(t, what: str) -> None:
         raise MQuantError(ERR_BAD_SHAPE, f"{what}: expected a contiguous tensor")
 
 
+# torch.cuda.current_stream() builds a stream object around the handle (2.8 us a call against 0.2 us
+# for the handle, of about 8 us that a launch through this module costs the host); a build of
+# torch without the accessors takes the long way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> Optional[int]:
-    import torch
-    return torch.cuda.current_stream().cuda_stream or None
+    """Handle of this thread's current stream on its current device; None for the default stream."""
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream or None
+    return _raw_stream(_device()) or None
+
+
+_linear_packers = [struct.Struct("@" + "PPPqi4x" * n) for n in range(9)]
+assert _linear_packers[1].size == ctypes.sizeof(Linear)
+
+
+def _linears(linears) -> bytes:
+    """An array of mquant_linear_t (the layout of Linear), packed in one go: filling ctypes
+    structures field by field costs 1.3 us per linear on the way to a launch."""
+    vals = []
+    for wp, ws, N, out in linears:
+        ld = _rows(out, "y")
+        _dense(ws, "w_scale")
+        vals += (_dp(wp) or 0, _dp(ws) or 0, _dp(out) or 0, ld, N)
+    n = len(linears)
+    return (_linear_packers[n] if n < len(_linear_packers) else struct.Struct("@" + "PPPqi4x" * n)).pack(*vals)
 
 
 # ------------------------------------------------------------------- host
@@ -190,7 +221,6 @@ def aifs_build_perm(T: int, vis_spans: Sequence[Tuple[int, int]]):
 # ----------------------------------------------------------------- device
 
 def aifs_permute(x, perm_dev, out=None):
-    import torch
     T, K = x.shape
     if out is None:
         out = torch.empty((T, K), dtype=x.dtype, device=x.device)
@@ -201,7 +231,6 @@ def aifs_permute(x, perm_dev, out=None):
 
 
 def aifs_remap_mask(mask, perm_dev, out=None):
-    import torch
     T = mask.shape[0]
     if out is None:
         out = torch.empty((T, T), dtype=torch.uint8, device=mask.device)
@@ -213,7 +242,6 @@ def aifs_remap_mask(mask, perm_dev, out=None):
 
 def hadamard_quant_act(x, n_vis: int, s_vis: float, s_txt: float, had_block: int,
                        perm_dev=None, out=None, T: Optional[int] = None, act_bits: Optional[int] = None):
-    import torch
     rows, K = x.shape
     T = rows if T is None else T
     if out is None:
@@ -246,7 +274,6 @@ def w4_prepacked_bytes(N: int, K: int) -> int:
 
 
 def w4_prepack(w_canonical, out=None):
-    import torch
     N, K2 = w_canonical.shape
     K = 2 * K2
     if out is None:
@@ -265,7 +292,6 @@ def w4a8_workspace_bytes(T: int, N: int, K: int) -> int:
 
 def w4a8_gemm(xq, w_prepacked, w_scale, N: int, n_vis: int, s_vis: float, s_txt: float,
               out=None, acc_out=None, workspace=None):
-    import torch
     T, K = xq.shape
     if out is None:
         out = torch.empty((T, N), dtype=torch.float16, device=xq.device)
@@ -282,7 +308,6 @@ def w4a8_gemm(xq, w_prepacked, w_scale, N: int, n_vis: int, s_vis: float, s_txt:
 
 
 def hadamard_dynquant_act(x, had_block: int, perm_dev=None, out=None, row_scale=None):
-    import torch
     T, K = x.shape
     if out is None:
         out = torch.empty((T, K), dtype=torch.int8, device=x.device)
@@ -297,7 +322,6 @@ def hadamard_dynquant_act(x, had_block: int, perm_dev=None, out=None, row_scale=
 
 def w4a8_gemm_rowscale(xq, w_prepacked, w_scale, row_scale, N: int, out=None, acc_out=None,
                        workspace=None):
-    import torch
     T, K = xq.shape
     if out is None:
         out = torch.empty((T, N), dtype=torch.float16, device=xq.device)
@@ -318,7 +342,6 @@ def w4a8_gemm_rms(xq, w_prepacked, w_scale, N: int, n_vis: int, s_vis: float, s_
                   split_idx, split_w, split_scale, out=None, acc_out=None, workspace=None):
     """split_idx (int32) and split_scale (fp32) are HOST arrays (per-layer constants),
     split_w is a device tensor int8 [n_split, N]."""
-    import torch
     T, K = xq.shape
     if split_idx is None:
         n_split, idx_p, sc_p = 0, None, None
@@ -351,7 +374,6 @@ def w4a8_linear_prefill_workspace_bytes(T: int, N: int, K: int) -> int:
 
 def w4a8_linear_prefill(x, perm_dev, w_prepacked, w_scale, N: int, n_vis: int, s_vis: float,
                         s_txt: float, had_block: int, workspace, out=None):
-    import torch
     T, K = x.shape
     if out is None:
         out = torch.empty((T, N), dtype=torch.float16, device=x.device)
@@ -369,14 +391,8 @@ def w4a8_gemv_grouped(xq, linears, n_vis: int, s_vis: float, s_txt: float):
     one launch computes every out [T, N]."""
     T, K = xq.shape
     _dense(xq, "xq")
-    arr = (Linear * max(len(linears), 1))()
-    for i, (wp, ws, N, out) in enumerate(linears):
-        _rows(out, "y"), _dense(ws, "w_scale")
-        arr[i].w_prepacked_dev, arr[i].w_scale_dev, arr[i].y_dev = _dp(wp), _dp(ws), _dp(out)
-        arr[i].ldy, arr[i].N = out.stride(0), N
-    _check(lib.mquant_w4a8_gemv_grouped(_dp(xq), T, K, n_vis, s_vis, s_txt,
-                                        ctypes.cast(arr, ctypes.c_void_p), len(linears), _stream()),
-           "mquant_w4a8_gemv_grouped")
+    _check(lib.mquant_w4a8_gemv_grouped(_dp(xq), T, K, n_vis, s_vis, s_txt, _linears(linears), len(linears),
+                                        _stream()), "mquant_w4a8_gemv_grouped")
     return [l[3] for l in linears]
 
 
@@ -414,7 +430,6 @@ def aifs_attention_workspace_bytes(T: int, n_kv_heads: int, head_dim: int = 128)
 def aifs_attention(q, k, v, pos_dev, n_q_heads: int, n_kv_heads: int, head_dim: int = 128,
                    out=None, workspace=None):
     """q [T, >= Hq*D], k, v [T, >= Hkv*D] fp16 views (row strides are passed on)."""
-    import torch
     T = q.shape[0]
     if out is None:
         out = torch.empty((T, n_q_heads * head_dim), dtype=torch.float16, device=q.device)
@@ -432,7 +447,6 @@ def aifs_attention(q, k, v, pos_dev, n_q_heads: int, n_kv_heads: int, head_dim: 
 def w4a8_linear_decode(x, w_prepacked, w_scale, N: int, n_vis: int, s_vis: float, s_txt: float,
                        had_block: int, out=None):
     """x fp16 [T <= 4, K] -> y fp16 [T, N]: rotate, quantize, GEMV and dequant in one launch."""
-    import torch
     T, K = x.shape
     if out is None:
         out = torch.empty((T, N), dtype=torch.float16, device=x.device)
@@ -446,15 +460,10 @@ def w4a8_linear_decode_grouped(x, linears, n_vis: int, s_vis: float, s_txt: floa
     """x fp16 [T <= 4, K]; linears: sequence of (w_prepacked, w_scale, N, out) sharing x.
     One launch rotates and quantizes x and computes every out [T, N]."""
     T, K = x.shape
-    _rows(x, "x")
-    arr = (Linear * max(len(linears), 1))()
-    for i, (wp, ws, N, out) in enumerate(linears):
-        _rows(out, "y"), _dense(ws, "w_scale")
-        arr[i].w_prepacked_dev, arr[i].w_scale_dev, arr[i].y_dev = _dp(wp), _dp(ws), _dp(out)
-        arr[i].ldy, arr[i].N = out.stride(0), N
-    _check(lib.mquant_w4a8_linear_decode_grouped(_dp(x), x.stride(0), T, K, n_vis, s_vis, s_txt, had_block,
-                                                 ctypes.cast(arr, ctypes.c_void_p), len(linears),
-                                                 _stream()), "mquant_w4a8_linear_decode_grouped")
+    ldx = _rows(x, "x")
+    _check(lib.mquant_w4a8_linear_decode_grouped(_dp(x), ldx, T, K, n_vis, s_vis, s_txt, had_block,
+                                                 _linears(linears), len(linears), _stream()),
+           "mquant_w4a8_linear_decode_grouped")
     return [l[3] for l in linears]
 
 
@@ -467,7 +476,6 @@ def w4g128_prepacked_bytes(N: int, K: int) -> int:
 
 def w4g128_prepack(w_canonical, scales, out=None):
     """w_canonical uint8 [N, K/2], scales fp16 [N, K/128] -> the weight-only kernel's layout."""
-    import torch
     N, K2 = w_canonical.shape
     K = 2 * K2
     if out is None:
@@ -481,7 +489,6 @@ def w4g128_prepack(w_canonical, scales, out=None):
 
 def w4g128_gemm(x, w_prepacked, N: int, out=None):
     """x fp16 [T, K] (row stride in elements) -> y fp16 [T, N] = x W~^T, group-wise dequantised weight."""
-    import torch
     T, K = x.shape
     if out is None:
         out = torch.empty((T, N), dtype=torch.float16, device=x.device)
