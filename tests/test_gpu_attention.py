@@ -276,3 +276,23 @@ def test_rope_leaves_the_rest_of_the_row_alone(mq):
     assert (got[:, 256:] == x[:, 256:]).all()
     assert (got[0] == x[0]).all()                                   # position 0: identity
     assert not (got[1:, :256] == x[1:, :256]).all()
+
+
+@pytest.mark.parametrize("T,H", [(1, 1), (3, 31), (5, 32), (66, 33), (9, 70)])
+def test_rope_wide_and_narrow_rows_agree(mq, T, H):
+    """Rows that start on 16 bytes take the 16-byte kernel, others the 4-byte one: the same
+    arithmetic, so the same bits; heads that end inside, at and after a batch of chunks."""
+    rng = np.random.default_rng(T + H)
+    x = (rng.standard_normal((T, H * 128)) * 2.0).astype(np.float16)
+    pos = rng.permutation(16384)[:T].astype(np.int32)
+    say(f"rope wide/narrow T={T} H={H}")
+    got = []
+    for pad, start in ((8, 0), (8, 2)):                    # rows 16-byte aligned, then 4 bytes off
+        buf = torch.full((T, H * 128 + pad), 7.0, dtype=torch.float16, device="cuda")
+        view = buf[:, start:start + H * 128]
+        view.copy_(dev(x))
+        mq.rope_apply(view, dev(pos), H)
+        got.append(view.cpu().numpy())
+        rest = torch.cat((buf[:, :start], buf[:, start + H * 128:]), dim=1)
+        assert bool((rest == 7.0).all().item())
+    assert (got[0].view(np.uint16) == got[1].view(np.uint16)).all()
