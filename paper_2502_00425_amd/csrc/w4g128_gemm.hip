@@ -35,6 +35,7 @@ using namespace mquant;
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
@@ -474,6 +475,111 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_kernel(
     }
 }
 
+// The same for a few rows whose activations fit LDS: half a tile (16 output channels) per
+// work-group, so that few output tiles still reach every compute unit (18944 -> 3584: 224 groups
+// instead of 112), and v_mfma_f32_16x16x32_f16.  Lane n % 16 + 16 * kg holds the 32 channels
+// 64 * (kg / 2) + 32 * (kg % 2) .. + 31 of its scale group (two k-tiles) of output row n; MFMA
+// step s contracts channels s * 8 .. + 7 of the four lane groups.  The activations are copied to
+// LDS once (read per k-tile from L2 they are four of six vector-memory instructions); every wave
+// keeps DEPTH weight loads in flight, the first of them issued before that copy.
+template <int NWAVES, int DEPTH>
+__global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_half_kernel(
+    const __half *__restrict__ x, int64_t ldx, const v4u *__restrict__ wp,
+    const __half *__restrict__ sT, __half *__restrict__ y, int64_t ldy, int32_t T, int32_t N,
+    int32_t K, int32_t n_pad)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];   // max(T * pitch, NWAVES * 1024)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kg = lane >> 4;
+    const int32_t pitch = K * 2 + 16;
+    const int32_t ntile = blockIdx.x >> 1, h = blockIdx.x & 1;
+    const int32_t n = ntile * kPackN + h * 16 + n16;
+    const int32_t groups = K / kGroup;
+    const int32_t per_wave = (groups + NWAVES - 1) / NWAVES;
+    const int32_t begin = wave * per_wave;
+    const int32_t end = begin + per_wave < groups ? begin + per_wave : groups;
+
+    const v4u *wlane = wp + static_cast<int64_t>(ntile) * (2 * groups) * 64 + (kg >> 1) * 64 + (kg & 1) * 32 + h * 16 + n16;
+    const __half *scol = sT + n;
+    v4u b[DEPTH];
+    uint16_t sc[DEPTH];
+    auto request = [&](int j, int32_t u) {                 // past the end: the last group again, not used
+        u = u < groups ? u : groups - 1;
+        b[j] = __builtin_nontemporal_load(wlane + static_cast<int64_t>(u) * 128);
+        sc[j] = __builtin_bit_cast(uint16_t, scol[static_cast<int64_t>(u) * n_pad]);
+    };
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) request(j, begin + j);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int32_t t = 0; t < T; ++t)
+        for (int32_t c = tid; c < K / 8; c += NWAVES * 64)
+            *reinterpret_cast<v4u *>(smem + t * pitch + c * 16) =
+                *reinterpret_cast<const v4u *>(x + static_cast<int64_t>(t) * ldx + c * 8);
+    __syncthreads();
+
+    const uint8_t *xlane = smem + (n16 < T ? n16 : T - 1) * pitch + kg * 64;   // rows >= T are never stored
+    const uint32_t mask = 0x000F000Fu;
+    uint32_t magic = 0x64006400u;
+    asm volatile("" : "+v"(magic));
+    v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains
+    for (int32_t base = begin; base < end; base += DEPTH) {
+#pragma unroll
+        for (int j = 0; j < DEPTH; ++j) {
+            if (base + j >= end) break;                    // wave-uniform
+            const _Float16 sv = __builtin_bit_cast(_Float16, sc[j]);
+            const v2h s2 = {sv, sv};
+            const v4u bw = b[j];
+            request(j, base + j + DEPTH);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const v8h af = *reinterpret_cast<const v8h *>(xlane + (base + j) * (kGroup * 2) + st * 16);
+                const v8h bf = __builtin_bit_cast(v8h, dequant8(bw[st], s2, mask, magic));
+                acc[st & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, bf, acc[st & 1], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();                                       // the sums reuse the activations' LDS
+
+    // MFMA 16x16 result register r of lane group kg holds row 4 * kg + r
+    float(*red)[4][64] = reinterpret_cast<float(*)[4][64]>(smem);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][r][lane] = acc[0][r] + acc[1][r];
+    __syncthreads();
+    for (int r = wave; r < 4; r += NWAVES) {
+        const int32_t row = kg * 4 + r;
+        if (row < T && n < N) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NWAVES; ++w) sum += red[w][r][lane];
+            y[static_cast<int64_t>(row) * ldy + n] = __float2half_rn(sum);
+        }
+    }
+}
+
+constexpr int kGemvHalfLds = 150 * 1024;
+
+template <int NWAVES, int DEPTH>
+int launch_gemv_half(const __half *x, int64_t ldx, const v4u *wt, const __half *sT, __half *y, int64_t ldy, int32_t T,
+                     int32_t N, int32_t K, int32_t n_pad, hipStream_t stream)
+{
+    auto kern = w4g128_gemv_half_kernel<NWAVES, DEPTH>;
+    const int64_t xb = static_cast<int64_t>(T) * (static_cast<int64_t>(K) * 2 + 16);
+    const int lds = static_cast<int>(xb > NWAVES * 1024 ? xb : NWAVES * 1024);
+    // Raising the dynamic LDS limit is idempotent: threads racing here at most repeat it.
+    static std::atomic<bool> attr_set{false};
+    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kGemvHalfLds) != hipSuccess)
+            return MQUANT_ERR_HIP;
+        attr_set.store(true, std::memory_order_release);
+    }
+    MQ_LAUNCH(kern, dim3(static_cast<unsigned>(n_pad / 16)), dim3(NWAVES * 64), lds, stream, x, ldx, wt, sT, y, ldy, T,
+              N, K, n_pad);
+    return launch_status();
+}
+
 template <int MT, int NWN, int NB>
 int launch_g128(const __half *x, int64_t ldx, const uint8_t *wp, __half *y, int64_t ldy, int32_t T,
                 int32_t N, int32_t K, hipStream_t stream)
@@ -594,8 +700,8 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
     __half *yh = static_cast<__half *>(y);
     hipStream_t st = static_cast<hipStream_t>(stream);
     // Up to eight rows the GEMV streams the weights (at 8 rows both are within 3 %: 7B down
-    // 25.5 against 25.9 us, gate_up 23.1 against 22.8; at 1 row 22.1 against 26.5 and 21.7
-    // against 24.5, at 16 rows 30.9 against 26.0 and 27.9 against 23.0).  It also takes rows so far
+    // 25.5 against 25.9 us, gate_up 23.1 against 22.8; at 16 rows 30.9 against 26.0 and 27.9
+    // against 23.0).  It also takes rows so far
     // apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of them at a time.
     const int32_t n_tiles32 = static_cast<int32_t>(ceil_div(N, kPackN));
     const bool forced = tune_state().g128_tile.load(std::memory_order_relaxed) >= 0;
@@ -604,6 +710,21 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
         const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
         const v4u *wt = reinterpret_cast<const v4u *>(wp);
         const int32_t n_pad = n_tiles32 * kPackN;
+        // Up to four rows that fit LDS take the half-tile form.  At 1 row, half tiles against whole
+        // ones: 18944 x 3584 10.8 / 22.3 us, 3584 x 3584 4.5 / 6.5, 3584 x 37888 18.9 / 22.0,
+        // 8192 x 59136 50.5 / 67; at 4 rows 12.0 / 23.0, 5.2 / 6.8, 21.6 / 21.7, 66.9 / 68.5; at 6 the
+        // copy of the rows costs more than it saves on wide matrices (3584 x 37888 27.9 / 22.2).
+        // Sixteen waves where there are few tiles or the rows leave room for one group per CU,
+        // four where there are many tiles and several groups fit (3584 x 37888: 18.9 us with 4, 20.1
+        // with 8, 24.4 with 16; 8192 x 8192: 11.4, 10.2, 10.6; 18944 x 3584: 17.5, 12.2, 10.8).
+        const int64_t row_bytes = static_cast<int64_t>(T) * (static_cast<int64_t>(K) * 2 + 16);
+        if (T <= 4 && row_bytes <= kGemvHalfLds) {
+            if (n_tiles32 < 200 || row_bytes > 80 * 1024)
+                return launch_gemv_half<16, 2>(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
+            if (n_tiles32 >= 512 && row_bytes <= 36 * 1024)
+                return launch_gemv_half<4, 2>(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
+            return launch_gemv_half<8, 2>(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
+        }
         for (int32_t t0 = 0; t0 < T; t0 += 32) {
             const int32_t tc = T - t0 < 32 ? T - t0 : 32;
             const __half *xc = xh + static_cast<int64_t>(t0) * ldx;

@@ -165,6 +165,28 @@ def test_both_gemm_tiles_on_ragged_shapes(mq, tile):
         mq.tune_set(mq.TUNE_G128_TILE, -1)
 
 
+@pytest.mark.parametrize("T,N,K", [
+    (1, 16, 128), (2, 40, 256), (3, 200, 2176), (4, 17, 4224),      # 16 waves: idle, uneven and full K ranges
+    (1, 8200, 384), (4, 6408, 8192),                                # 8 waves
+    (1, 16400, 256), (4, 16392, 1152), (3, 16385, 640),             # 4 waves; 2-byte rows
+    (4, 64, 18944), (4, 40, 19200), (1, 40, 76672),                 # the largest rows in LDS and what no longer fits
+])
+def test_few_rows_in_half_tiles(mq, T, N, K):
+    """One to four rows: every work-group size, K ranges that do not divide over the waves, the
+    last half tile, strided x and y with untouched padding."""
+    rng = np.random.default_rng(T * 11 + N + K)
+    wq, sc = make_weight(rng, N, K)
+    xb = (rng.standard_normal((T, K + 8)) * 1.5).astype(np.float16)
+    ref, mag = orc.w4g128_linear(np.ascontiguousarray(xb[:, :K]), wq, sc)
+    wp = mq.w4g128_prepack(dev(pack_int4(wq)), dev(sc))
+    yb = torch.full((T, N + 3), 7.0, dtype=torch.float16, device="cuda")
+    say(f"few rows T={T} N={N} K={K}")
+    mq.w4g128_gemm(dev(xb)[:, :K], wp, N, out=yb[:, :N])
+    got = yb.cpu().numpy()
+    check(got[:, :N], ref, mag, f"few rows {(T, N, K)}")
+    assert (got[:, N:] == 7.0).all()
+
+
 @pytest.mark.parametrize("shape", range(12))
 def test_every_gemm_tile_on_ragged_shapes(mq, shape):
     """Each compiled tile forced on: one stage of K or fewer (K = 128 with up to eight K slices),
