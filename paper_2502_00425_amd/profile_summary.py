@@ -81,7 +81,7 @@ def copy_factor(table, what: str) -> float:
 
 def trace_table(directory: str, projections=None,
                 only=("w4a8_", "splitk_", "hadamard_", "permute_rows", "remap_mask", "aifs_attention",
-                      "vt_kernel", "rope_kernel", "w4g128_")) -> str:
+                      "vt_kernel", "rope_", "w4g128_")) -> str:
     """Per (kernel, launch shape) durations of a `rocprofv3 --kernel-trace` run, from its
     *_kernel_trace.csv: dispatches, average / min / max microseconds.  With `projections`
     (the order in which a step launches its linears) the GEMM and rotate+quant dispatches of a
@@ -107,7 +107,7 @@ def trace_table(directory: str, projections=None,
     for _, name, wgs, us in rows:
         label = ""
         if projections:
-            kind = "gemm" if name.startswith("w4a8_gemm_kernel") else ("quant" if name.startswith("hadamard_quant_kernel") and "false" in name else None)
+            kind = "gemm" if name.startswith(("w4a8_gemm_kernel", "w4a8_sliced_kernel")) else ("quant" if name.startswith("hadamard_quant_kernel") and "false" in name else None)
             if kind:
                 label = projections[seen[kind] % len(projections)]
                 seen[kind] += 1
@@ -201,12 +201,12 @@ def main():
         f_avg = sum(fv) / len(fv) * ff if fv else 0.0
         w_avg = sum(wv) / len(wv) * wf if wv else 0.0
         rows.append((name, grid // wg, n, f_avg, w_avg))
-        if name.startswith("w4a8_gemm_kernel") or name.startswith("splitk_reduce_kernel"):
+        if name.startswith(("w4a8_gemm_kernel", "w4a8_sliced_kernel", "splitk_reduce_kernel")):
             gemm_bytes += (f_avg + w_avg) * 1024.0 * n
-            if name.startswith("w4a8_gemm_kernel"):
+            if not name.startswith("splitk_reduce_kernel"):
                 gemm_launches += n
     if gemm_launches == 0:
-        raise SystemExit("no w4a8_gemm_kernel dispatch in the counter output")
+        raise SystemExit("no GEMM dispatch in the counter output")
     per_launch = gemm_bytes / gemm_launches
     per_step = gemm_bytes / args.steps
 
@@ -220,7 +220,7 @@ def main():
     data["configs"][f"c{args.config}"] = {
         "bytes_per_gemm_launch": round(per_launch, 1), "bytes_per_step": round(per_step, 1),
         "gemm_launches_counted": gemm_launches, "steps": args.steps,
-        "includes": "w4a8_gemm_kernel fetch + write, plus the split-K reduce kernel's",
+        "includes": "GEMM kernel fetch + write, plus the split-K reduce kernel's",
     }
     os.makedirs(os.path.dirname(args.json), exist_ok=True)
     with open(args.json, "w") as fh:
