@@ -179,7 +179,13 @@ struct TileCost {
 };
 
 // ---- the K-sliced GEMM of w4a8_sliced.hip for the same kind of group; K % 128 == 0
-constexpr int kGemmMinT = 17;               // rows from which the GEMM kernels replace the GEMVs
+// Rows from which the GEMM kernels replace the GEMVs: 17 on few output tiles, 21 on many (weights
+// from HBM, whole decode steps, GEMV against sliced GEMM: the 7B linears at 17 rows 337 / 253 us for
+// four layers; the 72B linears at 17 rows 108.7 / 111.1, at 24 rows 120.2 / 118.1).
+inline bool gemm_takes(int32_t T, int32_t K, int64_t n_tiles)
+{
+    return K % 128 == 0 && (T > 20 || (T > 16 && n_tiles <= kNumCU / 2));
+}
 constexpr int kPrefillTiles = 3;            // tiles of the prefill GEMM; GEMM_TILE counts on with the sliced ones
 
 template <int EPI>

@@ -498,7 +498,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(
 // Several linears that share xq (q/k/v, gate/up) can go into one launch: the grid is the
 // concatenation of their tiles (units = 32-channel tiles of each problem).
 //
-// MROWS = 2 (33..64 rows, short prompts): two 32-row blocks share every weight tile -- the
+// MROWS = 2 (33..64 rows of a K the GEMM kernels do not take): two 32-row blocks share every weight tile -- the
 // weights are still read once, unpacked once and feed two MFMA pairs.
 template <int NWAVES, int KT, int EPI, int AROWS, int MROWS>
 __global__ __launch_bounds__(NWAVES * 64) void w4a8_gemv_kernel(
@@ -919,12 +919,6 @@ extern "C" int mquant_w4_prepack(const uint8_t *w, uint8_t *out, int32_t N, int3
 
 namespace {
 
-// Shapes the tile GEMV takes: up to 16 rows, where its smaller fixed cost wins (T = 16, tile or
-// streaming GEMV against the sliced GEMM: 3584 x 3584 5.0 against 6.1 us, 3584 x 37888 16.8
-// against 18.2, 8192 x 59136 44.2 against 46.6; at 24 rows 6.0 / 6.1, 19.8 / 18.6, 51.9 / 49.5 and
-// 18944 x 3584 18.9 / 14.0), and every K the GEMM kernels do not handle.
-bool gemv_tile_takes(int32_t T, int32_t K) { return T < kGemmMinT || K % 128 != 0; }
-
 // Pieces of the split-K plan that the caller's workspace has to hold (1: none).  Short prompts
 // on few channels ask for no workspace: the sliced GEMM is far ahead there.
 int workspace_splits(int32_t T, int32_t N, int32_t K)
@@ -955,8 +949,8 @@ int gemv_tile_dispatch(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, co
     }
     if (total <= 0 || total > 0x7fffffff) return MQUANT_ERR_BAD_SHAPE;
     const unsigned n_tiles = static_cast<unsigned>(total);
-    // 32 rows per pass, 64 with two row blocks per weight tile (rows beyond 32 come here only
-    // for short prompts and for K % 128 != 0)
+    // 32 rows per pass, 64 with two row blocks per weight tile (rows beyond 20 come here only
+    // for K % 128 != 0)
     for (int32_t t0 = 0; t0 < T;) {
         const int32_t left = T - t0;
         const int32_t tt = left > kGemvMaxT ? (left < 2 * kGemvMaxT ? left : 2 * kGemvMaxT) : left;
@@ -1034,7 +1028,7 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     if (!force_sliced) {
         if (gemv_stream_takes(T, K, ceil_div(N, kPackN)))
             return gemv_stream_dispatch<EPI>(xq, T, K, grp, ep, stream);
-        if (gemv_tile_takes(T, K)) return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);
+        if (!gemm_takes(T, K, ceil_div(N, kPackN))) return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);
     }
     const int splits = tune_state().gemm_nosplit.load(std::memory_order_relaxed) ? 1 : workspace_splits(T, N, K);
     if (splits > 1) {

@@ -699,13 +699,13 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
     const __half *xh = static_cast<const __half *>(x);
     __half *yh = static_cast<__half *>(y);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Up to eight rows the GEMV streams the weights (at 8 rows both are within 3 %: 7B down
-    // 25.5 against 25.9 us, gate_up 23.1 against 22.8; at 16 rows 30.9 against 26.0 and 27.9
-    // against 23.0).  It also takes rows so far
-    // apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of them at a time.
+    // Up to twelve rows the GEMV streams the weights (the four 7B linears with weights from HBM, GEMV
+    // against GEMM: 9 rows 62 / 68 us, 16 rows 75 / 69; the 72B ones 148 / 151 and 178 / 153).  It
+    // also takes rows so far apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of
+    // them at a time.
     const int32_t n_tiles32 = static_cast<int32_t>(ceil_div(N, kPackN));
     const bool forced = tune_state().g128_tile.load(std::memory_order_relaxed) >= 0;
-    if ((T <= 8 && !forced) || ldx >= kG128MaxLdx) {
+    if ((T <= 12 && !forced) || ldx >= kG128MaxLdx) {
         const int64_t w_bytes = static_cast<int64_t>(n_tiles32) * (K / kPackK) * kPackTileBytes;
         const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
         const v4u *wt = reinterpret_cast<const v4u *>(wp);
