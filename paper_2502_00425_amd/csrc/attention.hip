@@ -532,7 +532,12 @@ extern "C" int mquant_rope_apply(void *x, int64_t ldx, const int32_t *pos, int32
     if (ldx % 2 != 0 || !aligned_to(x, 4) || !aligned_to(pos, 4)) return MQUANT_ERR_ALIGNMENT;
     InvFreq inv;
     for (int j = 0; j < kHeadDim / 2; ++j) inv.f[j] = pow(base, -2.0 * j / kHeadDim);
-    if (ldx % 8 == 0 && aligned_to(x, 16) && n_heads <= 65535) {
+    // A wave of the 16-byte kernel forms 64 angles for its token whatever the number of heads, and with
+    // few heads most of its lanes hold no data: 4-byte kernel against 16-byte one at 16384 tokens, 1 / 2
+    // / 4 / 5 / 6 / 8 heads: 5.7 / 8.1, 6.5 / 8.6, 8.3 / 9.7, 8.7 / 10.2, 11.1 / 10.7, 13.2 / 11.7 us; at 4096 tokens
+    // 3.4 / 3.8, 3.6 / 3.8, 4.3 / 4.2, 4.6 / 4.4, 4.9 / 4.5, 5.5 / 4.8.
+    const bool wide = n_heads >= 6 || (n_heads >= 3 && T <= 4096);
+    if (wide && ldx % 8 == 0 && aligned_to(x, 16) && n_heads <= 65535) {
         const dim3 grid(static_cast<unsigned>(ceil_div(T, 4) < 65536 ? ceil_div(T, 4) : 65536),
                         static_cast<unsigned>(ceil_div(n_heads * (kHeadDim / 8), 64 * kRopeChunks)));
         MQ_LAUNCH(rope_wide_kernel, grid, dim3(256), 0, static_cast<hipStream_t>(stream),

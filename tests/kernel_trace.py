@@ -1,0 +1,20 @@
+"""Names of the kernels that a call launches on the GPU, for tests of the dispatch: results alone
+do not show which kernel made them."""
+import re
+
+import pytest
+import torch
+
+
+def kernels(fn):
+    """Kernels launched by fn(), in order, as 'name<template arguments>' without their namespace."""
+    fn()                                   # first-use work of the runtime stays out of the trace
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    names = [e.name for e in sorted(prof.events(), key=lambda e: e.time_range.start)]
+    out = [m.group(1) for m in (re.search(r"(\w+_kernel(?:<[^(]*>)?)\(", n) for n in names) if m]
+    if not out:
+        pytest.skip("the profiler saw no kernel")
+    return out

@@ -21,6 +21,8 @@ import pytest
 from oracle import mquant_oracle as orc
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
+
 pytestmark = pytest.mark.gpu
 
 
@@ -278,7 +280,18 @@ def test_rope_leaves_the_rest_of_the_row_alone(mq):
     assert not (got[1:, :256] == x[1:, :256]).all()
 
 
-@pytest.mark.parametrize("T,H", [(1, 1), (3, 31), (5, 32), (66, 33), (9, 70)])
+@pytest.mark.parametrize("T,H,name", [(1, 1, "rope_kernel"), (16384, 2, "rope_kernel"), (4096, 3, "rope_wide_kernel"),
+                                      (4097, 5, "rope_kernel"), (16384, 6, "rope_wide_kernel")])
+def test_rope_kernel_by_heads_and_tokens(mq, T, H, name):
+    """Aligned rows: few heads leave most lanes of the 16-byte kernel without data, so they take the
+    4-byte one (16384 tokens, 1 head: 5.7 against 8.1 us)."""
+    say(f"rope route T={T} H={H}")
+    x = torch.zeros((T, H * 128), dtype=torch.float16, device="cuda")
+    pos = torch.arange(T, dtype=torch.int32, device="cuda")
+    assert kernels(lambda: mq.rope_apply(x, pos, H)) == [name]
+
+
+@pytest.mark.parametrize("T,H", [(1, 1), (3, 31), (5, 32), (66, 33), (9, 70), (40, 3), (5, 5)])
 def test_rope_wide_and_narrow_rows_agree(mq, T, H):
     """Rows that start on 16 bytes take the 16-byte kernel, others the 4-byte one: the same
     arithmetic, so the same bits; heads that end inside, at and after a batch of chunks."""
