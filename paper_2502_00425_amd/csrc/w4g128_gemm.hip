@@ -580,6 +580,51 @@ int launch_gemv_half(const __half *x, int64_t ldx, const v4u *wt, const __half *
     return launch_status();
 }
 
+// What a launch of the whole-tile GEMV takes in microseconds, up to 32 rows on n 32-channel
+// tiles.  A wave walks `steps` batches of its k-tiles, `busy` of the waves have any; sixteen waves fill
+// a compute unit, of the eight-wave form four groups fit.  Fitted to 18 tile counts x 10 lengths of K
+// (128 .. 8192) at 1 to 4 rows and to 53 matrices (K 128 .. 29568, N 32 .. 59136) at 5 to 32 rows,
+// weights from HBM; rms 8 %.
+double gemv_us(int32_t T, int32_t n, int32_t K)
+{
+    const bool many = n >= 512;
+    const int32_t k_tiles = K / kPackK, waves = many ? 8 : 16;
+    const uint32_t per_wave = ceil_div32(k_tiles, waves);
+    const double steps = many ? per_wave : ceil_div32(per_wave, 2), busy = ceil_div32(k_tiles, per_wave);
+    const double rounds = ceil_div32(n, many ? 4 * kNumCU : kNumCU), tiles = n * (1.0 / kNumCU), q = T * (1.0 / 16);
+    if (many)
+        return 1.41 + steps * (0.208 + 0.152 * q) + busy * (0.011 + 0.034 * q) + 0.372 * rounds +
+               tiles * (0.176 + 0.163 * steps + k_tiles * (0.0384 + 0.0357 * q));
+    return steps * (0.532 + 0.520 * q) + busy * (0.045 + 0.051 * q) + rounds * (1.406 * steps + 0.071 * busy) +
+           tiles * (0.508 + k_tiles * (0.0095 + 0.0226 * q));
+}
+
+// The forms of the half-tile GEMV and the same for them, up to four rows: every group copies
+// the rows to LDS (per round and row), then its waves walk their scale groups.  rms 6 % over the
+// same sweep.
+struct HalfForm {
+    int waves;
+    int (*launch)(const __half *, int64_t, const v4u *, const __half *, __half *, int64_t, int32_t, int32_t, int32_t,
+                  int32_t, hipStream_t);
+    double fixed, step, half, half_row, half_group, half_busy, round_row, round_step;
+};
+constexpr HalfForm kHalf[] = {
+    {16, launch_gemv_half<16, 2>, 1.463, 0.396, 0.460, 0.052, 0.038, 0.035, 0.169, 0.329},
+    {8, launch_gemv_half<8, 2>, 1.729, 0.226, 0.257, 0.029, 0.042, 0.028, 0.179, 0.160},
+    {4, launch_gemv_half<4, 2>, 1.738, 0.061, 0.099, 0.011, 0.038, 0.039, 0.177, 0.267},
+};
+
+double half_us(const HalfForm &f, int32_t T, int32_t n, int32_t K)
+{
+    const uint32_t groups = K / kGroup, steps = ceil_div32(groups, f.waves);
+    const double busy = ceil_div32(groups, steps);
+    const uint32_t xb = static_cast<uint32_t>(T) * (2 * K + 16), rb = f.waves * 1024;
+    const uint32_t lds = xb > rb ? xb : rb, fit = (160 * 1024) / lds, slots = 32 / f.waves;
+    const double rounds = ceil_div32(2 * n, kNumCU * (fit < slots ? fit : slots)), halves = 2 * n * (1.0 / kNumCU);
+    return f.fixed + f.step * steps + halves * (f.half + f.half_row * T + f.half_group * groups + f.half_busy * busy) +
+           rounds * (f.round_row * T + f.round_step * steps);
+}
+
 template <int MT, int NWN, int NB>
 int launch_g128(const __half *x, int64_t ldx, const uint8_t *wp, __half *y, int64_t ldy, int32_t T,
                 int32_t N, int32_t K, hipStream_t stream)
@@ -710,20 +755,22 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
         const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
         const v4u *wt = reinterpret_cast<const v4u *>(wp);
         const int32_t n_pad = n_tiles32 * kPackN;
-        // Up to four rows that fit LDS take the half-tile form.  At 1 row, half tiles against whole
-        // ones: 18944 x 3584 10.8 / 22.3 us, 3584 x 3584 4.5 / 6.5, 3584 x 37888 18.9 / 22.0,
-        // 8192 x 59136 50.5 / 67; at 4 rows 12.0 / 23.0, 5.2 / 6.8, 21.6 / 21.7, 66.9 / 68.5; at 6 the
-        // copy of the rows costs more than it saves on wide matrices (3584 x 37888 27.9 / 22.2).
-        // Sixteen waves where there are few tiles or the rows leave room for one group per CU,
-        // four where there are many tiles and several groups fit (3584 x 37888: 18.9 us with 4, 20.1
-        // with 8, 24.4 with 16; 8192 x 8192: 11.4, 10.2, 10.6; 18944 x 3584: 17.5, 12.2, 10.8).
-        const int64_t row_bytes = static_cast<int64_t>(T) * (static_cast<int64_t>(K) * 2 + 16);
-        if (T <= 4 && row_bytes <= kGemvHalfLds) {
-            if (n_tiles32 < 200 || row_bytes > 80 * 1024)
-                return launch_gemv_half<16, 2>(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
-            if (n_tiles32 >= 512 && row_bytes <= 36 * 1024)
-                return launch_gemv_half<4, 2>(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
-            return launch_gemv_half<8, 2>(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
+        // Up to four rows that fit LDS take the half-tile form with the number of waves that is expected
+        // to be fastest, or the whole-tile one: half tiles against whole ones at 1 / 4 rows: 18944 x 3584
+        // 11.3 / 22.5 us and 12.4 / 23.3, 3584 x 3584 4.8 / 6.6 and 5.5 / 6.9; whole ones where every
+        // group would copy rows for little work: 128 x 37888 4.2 / 4.6 and 4.3 / 6.0, 2048 x 5120 4.5 / 4.6 and 4.6 / 5.8.
+        // At 6 rows the copy costs more than it saves on wide matrices (3584 x 37888 27.9 / 22.2).
+        if (T <= 4 && static_cast<int64_t>(T) * (static_cast<int64_t>(K) * 2 + 16) <= kGemvHalfLds) {
+            const HalfForm *best = nullptr;
+            double best_us = gemv_us(T, n_tiles32, K);
+            for (const HalfForm &f : kHalf) {
+                const double us = half_us(f, T, n_tiles32, K);
+                if (us < best_us) {
+                    best = &f;
+                    best_us = us;
+                }
+            }
+            if (best) return best->launch(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
         }
         for (int32_t t0 = 0; t0 < T; t0 += 32) {
             const int32_t tc = T - t0 < 32 ? T - t0 : 32;

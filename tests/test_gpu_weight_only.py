@@ -14,6 +14,8 @@ import pytest
 from oracle import mquant_oracle as orc
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
+
 pytestmark = pytest.mark.gpu
 
 
@@ -165,23 +167,27 @@ def test_both_gemm_tiles_on_ragged_shapes(mq, tile):
         mq.tune_set(mq.TUNE_G128_TILE, -1)
 
 
-@pytest.mark.parametrize("T,N,K", [
-    (1, 16, 128), (2, 40, 256), (3, 200, 2176), (4, 17, 4224),      # 16 waves: idle, uneven and full K ranges
-    (1, 8200, 384), (4, 6408, 8192),                                # 8 waves
-    (1, 16400, 256), (4, 16392, 1152), (3, 16385, 640),             # 4 waves; 2-byte rows
-    (4, 64, 18944), (4, 40, 19200), (1, 40, 76672),                 # the largest rows in LDS and what no longer fits
+@pytest.mark.parametrize("T,N,K,waves", [
+    (1, 17, 1152, 16), (4, 17, 4224, 16), (1, 200, 18944, 16),      # 16 waves: idle, uneven and full K ranges
+    (4, 64, 18944, 16), (1, 40, 76672, 16),                         # ... and the largest rows in LDS
+    (1, 200, 640, 8), (3, 200, 2176, 8), (2, 4100, 2176, 8), (4, 4100, 4224, 8), (4, 6408, 8192, 8),
+    (2, 40, 256, 4), (1, 8200, 384, 4), (1, 16392, 2176, 4), (3, 18950, 4224, 4),
+    (1, 16, 128, 0), (1, 16400, 256, 0), (4, 16392, 1152, 0), (3, 16385, 640, 0),   # whole tiles; 2-byte rows
+    (4, 40, 19200, 0),                                              # rows that no longer fit LDS
 ])
-def test_few_rows_in_half_tiles(mq, T, N, K):
-    """One to four rows: every work-group size, K ranges that do not divide over the waves, the
-    last half tile, strided x and y with untouched padding."""
+def test_few_rows_in_half_tiles(mq, T, N, K, waves):
+    """One to four rows: every work-group size of the half-tile form (0: whole tiles), K ranges that
+    do not divide over the waves, the last half tile, strided x and y with untouched padding."""
     rng = np.random.default_rng(T * 11 + N + K)
     wq, sc = make_weight(rng, N, K)
     xb = (rng.standard_normal((T, K + 8)) * 1.5).astype(np.float16)
     ref, mag = orc.w4g128_linear(np.ascontiguousarray(xb[:, :K]), wq, sc)
     wp = mq.w4g128_prepack(dev(pack_int4(wq)), dev(sc))
+    x = dev(xb)[:, :K]
     yb = torch.full((T, N + 3), 7.0, dtype=torch.float16, device="cuda")
     say(f"few rows T={T} N={N} K={K}")
-    mq.w4g128_gemm(dev(xb)[:, :K], wp, N, out=yb[:, :N])
+    name = kernels(lambda: mq.w4g128_gemm(x, wp, N, out=yb[:, :N]))[0]
+    assert name.startswith(f"w4g128_gemv_half_kernel<{waves}," if waves else "w4g128_gemv_kernel<"), name
     got = yb.cpu().numpy()
     check(got[:, :N], ref, mag, f"few rows {(T, N, K)}")
     assert (got[:, N:] == 7.0).all()
