@@ -501,7 +501,7 @@ typedef enum {
     MQUANT_TUNE_G128_SHAPE = 4,     /* the setting of G128_TILE over all its tiles: -1 = cost model;
                                        0 = 256x256, 1 = 96x128, 2 = 256x128, 3 = 192x128, 4 = 160x128,
                                        5 = 128x128, 6 = 64x128, 7 = 128x64, 8 = 64x64, 9 = 32x64,
-                                       10 = 64x32, 11 = 32x32 */
+                                       10 = 64x32, 11 = 32x32, 12 = 128x256, 13 = 64x256 */
     MQUANT_TUNE_GEMM_SHAPE = 5      /* -1 = cost model; else any number of rows goes to this tile of the K-sliced
                                        W4A8 GEMM: 0 = 64x128, 1 = 64x256, 2 = 192x128, 3 = 160x128,
                                        4 = 128x128, 5 = 96x128, 6 = 128x64, 7 = 64x64, 8 and 9 = 32x64

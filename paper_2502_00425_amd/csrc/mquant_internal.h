@@ -14,6 +14,29 @@ namespace mquant {
 constexpr int kWave = 64;                 // CDNA wavefront width
 constexpr int kNumCU = 256;               // compute units of an MI355X
 
+// A GEMM tile and what a launch of it costs in microseconds, over r rounds of its tiles on the
+// compute units (per_cu work-groups of a unit at a time; in a last round that leaves a unit one
+// work-group instead of two, that one runs faster):
+//   fixed + start * r + begin * tiles / CUs
+//         + K / 128 * (full * full rounds + single * single rounds + tile * tiles / CUs)
+struct TileCost {
+    int32_t bm, bn, per_cu;
+    double fixed, start, full, single, tile, begin = 0.0;
+    double us(int64_t tiles, int32_t K) const
+    {
+        static_assert(kNumCU == 256, "shift below");
+        const int shift = per_cu == 2 ? 9 : 8;              // per_cu is 1 or 2; no division on the way to a launch
+        int64_t n_full = tiles >> shift, n_single = 0;
+        const int64_t rest = tiles - (n_full << shift);
+        if (rest > 0 && (per_cu == 1 || rest > kNumCU)) ++n_full;
+        else if (rest > 0) n_single = 1;
+        const double load = static_cast<double>(tiles) * (1.0 / kNumCU);
+        return fixed + start * static_cast<double>(n_full + n_single) + begin * load +
+               static_cast<double>(K / 128) *
+                   (full * static_cast<double>(n_full) + single * static_cast<double>(n_single) + this->tile * load);
+    }
+};
+
 static inline bool aligned_to(const void *p, uintptr_t a)
 {
     return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0;
@@ -48,7 +71,7 @@ struct TuneState {
 };
 TuneState &tune_state();
 constexpr int kSlicedTiles = 11;          // tiles of the sliced W4A8 GEMM
-constexpr int kG128Tiles = 12;            // tiles of the weight-only GEMM
+constexpr int kG128Tiles = 14;            // tiles of the weight-only GEMM
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // The same for sizes and tile edges in 32 bits: the cost models ask dozens of times per call.

@@ -156,28 +156,6 @@ template <int EPI>
 int gemv_tile_dispatch(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, const Epilogue &ep,
                        hipStream_t stream);
 
-// ---- the GEMM kernels
-// A tile and what a launch of it costs in microseconds, over r rounds of its tiles on the
-// compute units (per_cu work-groups of a unit at a time; in a last round that leaves a unit one
-// work-group instead of two, that one runs faster):
-//   fixed + start * r + k-blocks * (full * full rounds + single * single rounds + tile * tiles / CUs)
-struct TileCost {
-    int32_t bm, bn, per_cu;
-    double fixed, start, full, single, tile;
-    double us(int64_t tiles, int32_t K) const
-    {
-        static_assert(kNumCU == 256, "shift below");
-        const int shift = per_cu == 2 ? 9 : 8;              // per_cu is 1 or 2; no division on the way to a launch
-        int64_t n_full = tiles >> shift, n_single = 0;
-        const int64_t rest = tiles - (n_full << shift);
-        if (rest > 0 && (per_cu == 1 || rest > kNumCU)) ++n_full;
-        else if (rest > 0) n_single = 1;
-        return fixed + start * static_cast<double>(n_full + n_single) +
-               static_cast<double>(K / 128) * (full * static_cast<double>(n_full) + single * static_cast<double>(n_single) +
-                                               this->tile * static_cast<double>(tiles) * (1.0 / kNumCU));
-    }
-};
-
 // ---- the K-sliced GEMM of w4a8_sliced.hip for the same kind of group; K % 128 == 0
 // Rows from which the GEMM kernels replace the GEMVs: 17 on few output tiles, 21 on many (weights
 // from HBM, whole decode steps, GEMV against sliced GEMM: the 7B linears at 17 rows 337 / 253 us for

@@ -655,50 +655,49 @@ int launch_g128(const __half *x, int64_t ldx, const uint8_t *wp, __half *y, int6
 using G128Launch = int (*)(const __half *, int64_t, const uint8_t *, __half *, int64_t, int32_t, int32_t, int32_t,
                            hipStream_t);
 
-// The compiled tiles and what a launch of each costs: fixed + k-tiles * (per_round * rounds +
-// per_tile * tiles / CUs), in microseconds.  The second term is the length of the longest chain
-// of tiles a compute unit walks, the third what full occupancy adds (clock, L2).  Fitted to
-// the time of every tile on the 7B and 72B projections (K 3584 .. 29568, N 3584 .. 59136) at 23
-// row counts from 9 to 2048; the tile the model picks is within 2 % of the fastest one on
-// average.  Tiles that no shape of that sweep lost by leaving out (128 x 256, 64 x 256, 32 x 128)
-// are not built.  All twelve are needed: leaving out two more costs 3 - 5 % on average and up to
-// 25 % on single shapes.
+// The compiled tiles and what they cost.  Fitted to the time of every tile on 53 matrices (K 128 ..
+// 29568, N 32 .. 59136, the 7B and 72B projections among them) at 32 row counts from 5 to 3072, weights
+// from HBM (rms 4 - 7 %): the tile the model picks is within 0.4 % of the fastest one on average.  The cost of
+// starting a tile keeps small tiles from short K (128 -> 37888 at T = 128: 64 x 32 tiles 31.6 us, 64 x 256
+// ones 7.2).
 struct G128Variant {
-    int32_t bm, bn, per_cu;               // per_cu: work-groups a compute unit holds at a time
+    TileCost cost;
     G128Launch launch;
-    double fixed, per_round, per_tile;
 };
 constexpr G128Variant kG128[] = {
-    {256, 256, 1, launch_g128<8, 8, 3>, 3.7, 1.139, 0.507}, {96, 128, 2, launch_g128<3, 4, 2>, 4.2, 0.310, 0.218},
-    {256, 128, 1, launch_g128<8, 4, 2>, 7.9, 0.579, 0.356}, {192, 128, 1, launch_g128<6, 4, 2>, 6.2, 0.461, 0.277},
-    {160, 128, 1, launch_g128<5, 4, 3>, 5.9, 0.400, 0.234}, {128, 128, 1, launch_g128<4, 4, 3>, 5.4, 0.373, 0.178},
-    {64, 128, 2, launch_g128<2, 4, 3>, 5.5, 0.250, 0.168},  {128, 64, 1, launch_g128<4, 2, 2>, 4.2, 0.227, 0.115},
-    {64, 64, 1, launch_g128<2, 2, 3>, 4.3, 0.147, 0.067},   {32, 64, 1, launch_g128<1, 2, 3>, 5.0, 0.118, 0.0},
-    {64, 32, 1, launch_g128<2, 1, 2>, 2.7, 0.115, 0.040},   {32, 32, 1, launch_g128<1, 1, 3>, 3.7, 0.072, 0.018},
+    {{256, 256, 1, 0.770, 4.517, 2.118, 0.000, 1.149, 1.963}, launch_g128<8, 8, 3>},
+    {{96, 128, 2, 2.852, 0.536, 1.017, 0.757, 0.250, 1.467}, launch_g128<3, 4, 2>},
+    {{256, 128, 1, 1.352, 4.936, 1.182, 0.000, 0.664, 1.375}, launch_g128<8, 4, 2>},
+    {{192, 128, 1, 1.336, 3.936, 0.963, 0.000, 0.479, 1.074}, launch_g128<6, 4, 2>},
+    {{160, 128, 1, 1.274, 3.627, 0.821, 0.000, 0.424, 0.929}, launch_g128<5, 4, 3>},
+    {{128, 128, 1, 1.247, 3.041, 0.758, 0.000, 0.327, 0.765}, launch_g128<4, 4, 3>},
+    {{64, 128, 2, 2.649, 0.586, 1.021, 0.611, 0.071, 1.110}, launch_g128<2, 4, 3>},
+    {{128, 64, 1, 1.416, 2.769, 0.518, 0.000, 0.139, 0.716}, launch_g128<4, 2, 2>},
+    {{64, 64, 1, 1.376, 1.828, 0.328, 0.000, 0.043, 0.631}, launch_g128<2, 2, 3>},
+    {{32, 64, 1, 2.755, 0.000, 0.268, 0.000, 0.000, 0.731}, launch_g128<1, 2, 3>},
+    {{64, 32, 1, 1.318, 2.004, 0.239, 0.000, 0.064, 0.331}, launch_g128<2, 1, 2>},
+    {{32, 32, 1, 1.165, 1.834, 0.147, 0.000, 0.017, 0.362}, launch_g128<1, 1, 3>},
+    {{128, 256, 2, 2.742, 0.427, 2.429, 1.464, 0.476, 2.571}, launch_g128<4, 8, 2>},
+    {{64, 256, 2, 2.745, 0.000, 1.828, 1.177, 0.179, 1.586}, launch_g128<2, 8, 3>},
 };
 constexpr int kG128Variants = sizeof(kG128) / sizeof(kG128[0]);
 static_assert(kG128Variants == kG128Tiles, "mquant_tune_set validates against this");
 
-const G128Variant &g128_choose(int32_t T, int32_t N, int32_t K)
+// The tile for a shape (or the forced one) and what it is expected to take.
+const G128Variant &g128_choose(int32_t T, int32_t N, int32_t K, int32_t forced, double *us_out)
 {
-    const int32_t forced = tune_state().g128_tile.load(std::memory_order_relaxed);
-    if (forced >= 0) return kG128[forced];
     int best = 0;
     double best_us = 0.0;
     for (int i = 0; i < kG128Variants; ++i) {
-        const G128Variant &v = kG128[i];
-        const int64_t tiles = static_cast<int64_t>(ceil_div32(T, v.bm)) * ceil_div32(N, v.bn);
-        const int shift = v.per_cu == 2 ? 9 : 8;          // work-groups per round: per_cu (1 or 2) x 256
-        const int64_t rounds = (tiles + (int64_t{1} << shift) - 1) >> shift;
-        const double us = v.fixed + static_cast<double>(K / kPackK) *
-                                        (v.per_round * static_cast<double>(rounds) +
-                                         v.per_tile * static_cast<double>(tiles) * (1.0 / kNumCU));
+        const TileCost &c = kG128[i].cost;
+        const double us = c.us(static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn), K);
         if (i == 0 || us < best_us) {
             best = i;
             best_us = us;
         }
     }
-    return kG128[best];
+    *us_out = best_us;
+    return kG128[forced >= 0 ? forced : best];
 }
 
 }  // namespace
@@ -744,13 +743,16 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
     const __half *xh = static_cast<const __half *>(x);
     __half *yh = static_cast<__half *>(y);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Up to twelve rows the GEMV streams the weights (the four 7B linears with weights from HBM, GEMV
-    // against GEMM: 9 rows 62 / 68 us, 16 rows 75 / 69; the 72B ones 148 / 151 and 178 / 153).  It
-    // also takes rows so far apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of
-    // them at a time.
+    // Up to twelve rows the GEMV streams the weights; from 13 to 32 it does where the GEMM is not
+    // expected to be 5 % ahead: GEMV against GEMM at 13 and 32 rows: 18944 x 3584 27.7 / 25.9 us and 46.7 /
+    // 27.2, 3584 x 18944 16.9 / 16.3 and 27.9 / 17.9, 512 x 16384 3.9 / 4.4 and 5.2 / 4.6.  It also takes rows so far
+    // apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of them at a time.
     const int32_t n_tiles32 = static_cast<int32_t>(ceil_div(N, kPackN));
-    const bool forced = tune_state().g128_tile.load(std::memory_order_relaxed) >= 0;
-    if ((T <= 12 && !forced) || ldx >= kG128MaxLdx) {
+    const int32_t forced = tune_state().g128_tile.load(std::memory_order_relaxed);
+    double gemm_us;
+    const G128Variant &gemm = g128_choose(T, N, K, forced, &gemm_us);
+    const bool gemv = forced < 0 && (T <= 12 || (T <= 32 && gemm_us > 0.95 * gemv_us(T, n_tiles32, K)));
+    if (gemv || ldx >= kG128MaxLdx) {
         const int64_t w_bytes = static_cast<int64_t>(n_tiles32) * (K / kPackK) * kPackTileBytes;
         const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
         const v4u *wt = reinterpret_cast<const v4u *>(wp);
@@ -790,5 +792,5 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
         }
         return MQUANT_OK;
     }
-    return g128_choose(T, N, K).launch(xh, ldx, wp, yh, ldy, T, N, K, st);
+    return gemm.launch(xh, ldx, wp, yh, ldy, T, N, K, st);
 }

@@ -43,3 +43,21 @@ def test_weight_only_few_rows(mq, T, N, K, name):
     """Whole tiles against half tiles at one to four rows (microseconds whole / half)."""
     got = weight_only(mq, T, N, K)
     assert len(got) == 1 and got[0].startswith(name + "<"), got
+
+
+@pytest.mark.parametrize("T,N,K,names", [
+    (13, 37888, 128, ["w4g128_gemv_kernel"]), (13, 16384, 512, ["w4g128_gemv_kernel"]),          # 4.9 us (15.3 on 64x32 tiles), 3.9 (6.9)
+    (16, 1024, 128, ["w4g128_gemv_kernel"]),                                                     # 2.6 (3.0)
+    (12, 3584, 18944, ["w4g128_gemv_kernel"]), (13, 3584, 18944, ["w4g128_gemm_kernel<1, 1, 3>"]),
+    (32, 18944, 3584, ["w4g128_gemm_kernel<1, 2, 3>"]),                                          # 17.9 (GEMV 27.9)
+    (33, 37888, 128, ["w4g128_gemm_kernel<2, 8, 3>"]),                                           # 4.7 (64x32: 16.0)
+    (128, 37888, 128, ["w4g128_gemm_kernel<2, 8, 3>", "w4g128_gemm_kernel<4, 8, 2>"]),           # 7.2 and 6.9 (64x32: 31.6)
+    (512, 4096, 128, ["w4g128_gemm_kernel<2, 8, 3>", "w4g128_gemm_kernel<2, 4, 3>"]),            # 4.6 and 4.5 (64x32: 13.1)
+    (384, 18944, 256, ["w4g128_gemm_kernel<4, 8, 2>"]),                                          # 9.2 (96x128: 17.1)
+    (1280, 37888, 3584, ["w4g128_gemm_kernel<8, 8, 3>"]), (1280, 3584, 18944, ["w4g128_gemm_kernel<5, 4, 3>"]),
+])
+def test_weight_only_rows_and_tiles(mq, T, N, K, names):
+    """GEMV against GEMM from 13 rows on, and tiles whose start cost suits the length of K
+    (microseconds measured, in brackets the kernel on the other side)."""
+    got = weight_only(mq, T, N, K)
+    assert len(got) == 1 and any(got[0].startswith(n) for n in names), got

@@ -193,7 +193,7 @@ def test_few_rows_in_half_tiles(mq, T, N, K, waves):
     assert (got[:, N:] == 7.0).all()
 
 
-@pytest.mark.parametrize("shape", range(12))
+@pytest.mark.parametrize("shape", range(14))
 def test_every_gemm_tile_on_ragged_shapes(mq, shape):
     """Each compiled tile forced on: one stage of K or fewer (K = 128 with up to eight K slices),
     slices that end a stage early (K / 64 not a multiple of the slice count), the pipeline's two
