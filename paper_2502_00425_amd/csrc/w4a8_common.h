@@ -164,7 +164,6 @@ inline bool gemm_takes(int32_t T, int32_t K, int64_t n_tiles)
 {
     return K % 128 == 0 && (T > 20 || (T > 16 && n_tiles <= kNumCU / 2));
 }
-constexpr int kPrefillTiles = 3;            // tiles of the prefill GEMM; GEMM_TILE counts on with the sliced ones
 
 template <int EPI>
 int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp, const Epilogue &ep,

@@ -862,8 +862,19 @@ int launch_gemm(const int8_t *xq, const uint8_t *wp, const void *w_scale, void *
 // granularity; 192x128 when 128x256 tiles leave a third of the CUs idle (1280 x 4608: 252 tiles
 // instead of 180; 28 us against 31 us).  Rounds of work-groups over the CUs x tile area /
 // measured relative efficiency of the tile.
+//
+// Up to 128 rows: 64-row tiles, three stages, several work-groups per CU.  With one row of 128- or
+// 256-row tiles the k-loop of a lone, mostly empty work-group per CU sets the time, and a sliced tile
+// pays for its slices where there are output channels enough to fill the chip: 64-row tiles against
+// sliced ones at T = 48: 3584 -> 18944 16.4 / 18.2 us, 3584 -> 37888 21.0 / 23.8, 1024 -> 37888 9.6 / 11.5, 384 -> 18944
+// 5.0 / 6.9; at T = 128: 1024 -> 12288 7.5 / 8.7, 2048 -> 11008 10.6 / 11.9.
 int pick_gemm_tile(int32_t T, int32_t N)
 {
+    if (T <= 128) {
+        const int64_t groups = ceil_div(T, 64) * ceil_div(N, 128);       // of 64x128 tiles
+        if (T <= 64) return groups <= kNumCU ? 3 : 4;
+        if (groups <= kNumCU + kNumCU / 4) return 3;
+    }
     const double a = static_cast<double>(ceil_div(ceil_div(T, 256) * ceil_div(N, 256), kNumCU)) *
                      256.0 * 256.0;
     const double b = static_cast<double>(ceil_div(ceil_div(T, 128) * ceil_div(N, 256), kNumCU)) *
@@ -876,17 +887,37 @@ int pick_gemm_tile(int32_t T, int32_t N)
 
 // What the plan above costs in microseconds (split-K with its reduction, or the tile), for the
 // comparison with the sliced GEMM; fitted to the same sweep as the table of w4a8_sliced.hip
-// (rms 2 - 4 %).
+// (rms 4 - 5 %).
+constexpr TileCost kPrefillCost[] = {
+    {256, 256, 1, 2.718, 4.247, 1.077, 0.000, 0.442, 3.219},
+    {128, 256, 2, 3.863, 0.597, 1.344, 0.789, 0.169, 3.013},
+    {192, 128, 1, 2.277, 2.318, 0.625, 0.000, 0.172, 1.988},
+    {64, 128, 2, 3.020, 0.000, 0.606, 0.436, 0.021, 1.298},
+    {64, 256, 2, 2.689, 0.913, 0.842, 0.499, 0.076, 1.878},
+};
+
 double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 {
     if (splits > 1)
-        return 6.62 + 1.561 * static_cast<double>(ceil_div(K / 128, splits)) +
-               1.163e-6 * splits * static_cast<double>(T) * N;
-    static constexpr TileCost cost[3] = {{256, 256, 1, 0.0, 7.34, 1.070, 0.0, 0.472},
-                                         {128, 256, 2, 2.23, 4.55, 1.023, 0.493, 0.386},
-                                         {192, 128, 1, 2.33, 1.53, 0.615, 0.0, 0.154}};
-    const TileCost &c = cost[pick_gemm_tile(T, N)];
+        return 5.885 + 1.543 * static_cast<double>(ceil_div(K / 128, splits)) +
+               1.488e-6 * splits * static_cast<double>(T) * N;
+    const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     return c.us(static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn), K);
+}
+
+// The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 12 %
+// where the tiles above fill the chip: there the clock follows power, which the sweep's short bursts do not
+// show, and the sliced 64x256 tile reads each activation fragment from LDS for one MFMA instead of two.  One
+// linear at a time switched to its sliced tile in continuous passes over the four projections, estimated
+// share of the plan's time and change of the pass: 7B, T = 1003: o 0.76 -4.6 us, down (split-K) 0.88 -8.7; T = 1280: qkv 0.96
+// +1.7, o 0.95 -1.2, down 0.95 +0.4; T = 2048: qkv 0.90 +8.2, o 0.95 +3.7; T = 3000: o 0.90 +5.6, down 0.87 -13.4;
+// 72B, T = 1003: qkv 0.87 -8.3; T = 1500: down 0.86 -38.7; T = 2048: qkv 0.92 +5.0.
+bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
+{
+    const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
+    const bool full = splits == 1 && T > 128 &&
+                      10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
+    return sliced_cost_us(T, K, grp) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
@@ -1036,20 +1067,21 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
         if (!workspace || workspace_bytes < need) return MQUANT_ERR_WORKSPACE;
         if (!aligned_to(workspace, 256)) return MQUANT_ERR_ALIGNMENT;
     }
-    // The sliced GEMM where it is expected to be clearly ahead: few tiles (T = 128: 3584 x 4608 17.1
-    // -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1 -> 15.9; T = 512: 22.8 -> 16.2 on 3584
-    // x 4608).  Closer calls go to the tiles below: where every CU is busy the clock is bound by
-    // power, and their waves, 64 columns wide, read each activation fragment from LDS for two
-    // MFMAs instead of one (T = 1280 over the four 7B projections: the sliced tiles 2 - 6 % ahead in
-    // short bursts, 3 % behind in a continuous run).
+    // The sliced GEMM on few tiles (T = 128: 3584 x 4608 17.1 -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1
+    // -> 15.9; T = 512: 22.8 -> 16.2 on 3584 x 4608) and wherever else it is expected to be ahead.
     const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
-    if (force_sliced || force_tile >= kPrefillTiles ||
-        (force_tile < 0 && sliced_cost_us(T, K, grp) < 0.88 * prefill_cost_us(T, N, K, splits)))
+    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp))))
         return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
     if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,
                                                  static_cast<int32_t *>(workspace), stream);
     const int tile = force_tile < 0 ? pick_gemm_tile(T, N) : force_tile;
+    if (tile == 3)
+        return launch_gemm<64, 128, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
+                                                nullptr, stream);
+    if (tile == 4)
+        return launch_gemm<64, 256, 1, 8, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
+                                                nullptr, stream);
     if (tile == 0)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, 1,
                                                  nullptr, stream);

@@ -347,10 +347,10 @@ int launch_sliced(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, const E
 
 using Launch = int (*)(const int8_t *, int32_t, int32_t, GemvGroup, const Epilogue &, hipStream_t);
 
-// The compiled tiles and what they cost.  Fitted to the time of every tile on the 7B and 72B
-// projections (K 3584 .. 29568, N 3584 .. 59136) at 28 row counts from 10 to 8192, one HIP graph
-// of eight launches over rotating weights: the tile the model picks is within 1 % of the fastest
-// on average and 13 % at worst.  The first two are also named by mquant_tune_set's GEMM_TILE.
+// The compiled tiles and what they cost.  Fitted to the time of every tile on 53 matrices (K 128 ..
+// 29568, N 32 .. 59136, the 7B and 72B projections among them) at 24 row counts from 33 to 3072, one HIP
+// graph over weights from HBM (rms 3 - 7 %): what the model picks, the tiles of w4a8_gemm.hip included, is within
+// 0.2 % of the fastest on average.
 struct Variant {
     TileCost cost;
     Launch launch[3];
@@ -358,17 +358,17 @@ struct Variant {
 #define MQ_SLICED(MT, NWN, NB) \
     {launch_sliced<MT, NWN, NB, kEpiStatic>, launch_sliced<MT, NWN, NB, kEpiRowScale>, launch_sliced<MT, NWN, NB, kEpiSplit>}
 constexpr Variant kSliced[] = {
-    {{64, 128, 2, 2.34, 1.99, 0.389, 0.298, 0.076}, MQ_SLICED(2, 4, 2)},
-    {{64, 256, 2, 2.14, 2.60, 0.645, 0.417, 0.145}, MQ_SLICED(2, 8, 3)},
-    {{192, 128, 1, 1.19, 6.43, 0.421, 0.000, 0.227}, MQ_SLICED(6, 4, 2)},
-    {{160, 128, 1, 1.37, 5.18, 0.371, 0.000, 0.210}, MQ_SLICED(5, 4, 2)},
-    {{128, 128, 1, 2.40, 4.13, 0.327, 0.000, 0.145}, MQ_SLICED(4, 4, 3)},
-    {{96, 128, 2, 1.95, 3.11, 0.504, 0.324, 0.096}, MQ_SLICED(3, 4, 2)},
-    {{128, 64, 1, 1.54, 3.65, 0.240, 0.000, 0.087}, MQ_SLICED(4, 2, 2)},
-    {{64, 64, 1, 2.14, 2.72, 0.126, 0.000, 0.037}, MQ_SLICED(2, 2, 3)},
-    {{32, 64, 2, 1.54, 2.10, 0.172, 0.149, 0.017}, MQ_SLICED(1, 2, 2)},
-    {{32, 64, 1, 2.07, 2.01, 0.107, 0.000, 0.008}, MQ_SLICED(1, 2, 3)},
-    {{32, 32, 1, 2.39, 2.10, 0.060, 0.000, 0.009}, MQ_SLICED(1, 1, 3)},
+    {{64, 128, 2, 2.920, 1.092, 0.377, 0.335, 0.087, 1.362}, MQ_SLICED(2, 4, 2)},
+    {{64, 256, 2, 3.403, 0.905, 0.718, 0.450, 0.081, 1.910}, MQ_SLICED(2, 8, 3)},
+    {{192, 128, 1, 1.706, 6.723, 0.510, 0.000, 0.161, 1.679}, MQ_SLICED(6, 4, 2)},
+    {{160, 128, 1, 1.991, 5.559, 0.486, 0.000, 0.135, 1.566}, MQ_SLICED(5, 4, 2)},
+    {{128, 128, 1, 1.346, 4.923, 0.331, 0.000, 0.139, 1.258}, MQ_SLICED(4, 4, 3)},
+    {{96, 128, 2, 3.702, 1.215, 0.517, 0.402, 0.080, 1.960}, MQ_SLICED(3, 4, 2)},
+    {{128, 64, 1, 1.619, 3.996, 0.257, 0.000, 0.100, 0.679}, MQ_SLICED(4, 2, 2)},
+    {{64, 64, 1, 1.523, 2.534, 0.144, 0.000, 0.033, 0.705}, MQ_SLICED(2, 2, 3)},
+    {{32, 64, 2, 1.976, 0.777, 0.165, 0.139, 0.043, 0.660}, MQ_SLICED(1, 2, 2)},
+    {{32, 64, 1, 1.422, 1.727, 0.114, 0.000, 0.028, 0.592}, MQ_SLICED(1, 2, 3)},
+    {{32, 32, 1, 1.222, 1.928, 0.064, 0.000, 0.019, 0.319}, MQ_SLICED(1, 1, 3)},
 };
 #undef MQ_SLICED
 constexpr int kVariants = sizeof(kSliced) / sizeof(kSliced[0]);
@@ -406,7 +406,6 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
                     hipStream_t stream)
 {
     int v = tune_state().gemm_sliced.load(std::memory_order_relaxed);
-    if (v < 0) v = tune_state().gemm_tile.load(std::memory_order_relaxed) - kPrefillTiles;
     if (v < 0) v = pick(T, K, grp);
     return kSliced[v].launch[EPI](xq, T, K, grp, ep, stream);
 }

@@ -61,3 +61,27 @@ def test_weight_only_rows_and_tiles(mq, T, N, K, names):
     (microseconds measured, in brackets the kernel on the other side)."""
     got = weight_only(mq, T, N, K)
     assert len(got) == 1 and any(got[0].startswith(n) for n in names), got
+
+
+def w4a8(mq, T, N, K):
+    say(f"W4A8 T={T} N={N} K={K}")
+    xq = torch.zeros((T, K), dtype=torch.int8, device="cuda")
+    wp = torch.zeros(mq.w4_prepacked_bytes(N, K), dtype=torch.uint8, device="cuda")
+    ws = torch.ones(N, dtype=torch.float16, device="cuda")
+    y = torch.empty((T, N), dtype=torch.float16, device="cuda")
+    wk = torch.empty(max(mq.w4a8_workspace_bytes(T, N, K), 256), dtype=torch.uint8, device="cuda")
+    return kernels(lambda: mq.w4a8_gemm(xq, wp, ws, N, 0, 1.0, 1.0, out=y, workspace=wk))
+
+
+@pytest.mark.parametrize("T,N,K,name", [
+    (48, 18944, 384, "w4a8_gemm_kernel<64, 128,"), (48, 37888, 3584, "w4a8_gemm_kernel<64, 256,"),    # 5.0 (6.9), 21.0 (23.8)
+    (64, 18944, 3584, "w4a8_gemm_kernel<64, 128,"), (128, 12288, 1024, "w4a8_gemm_kernel<64, 128,"),  # 16.5 (18.4), 7.5 (8.7)
+    (1280, 37888, 128, "w4a8_gemm_kernel<"),                                                          # 25.8 (33.7)
+    (48, 3584, 3584, "w4a8_sliced_kernel<"), (128, 3584, 18944, "w4a8_sliced_kernel<"),
+    (512, 4608, 3584, "w4a8_sliced_kernel<"), (64, 12288, 4096, "w4a8_sliced_kernel<"),
+])
+def test_w4a8_prompts(mq, T, N, K, name):
+    """Sliced tiles for few output channels, the large-tile kernel where the channels fill the chip
+    (microseconds measured, in brackets the sliced tile)."""
+    got = w4a8(mq, T, N, K)
+    assert len(got) == 1 and got[0].startswith(name), got
