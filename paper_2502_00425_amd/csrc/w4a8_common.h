@@ -156,14 +156,14 @@ template <int EPI>
 int gemv_tile_dispatch(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, const Epilogue &ep,
                        hipStream_t stream);
 
+constexpr int kGemvMaxT = 32;               // rows of one pass of the tile GEMV
+
+// What a launch of it is expected to take in microseconds, 17 to 32 rows on n_tiles 32-channel tiles.
+double gemv_tile_us(int32_t T, int64_t n_tiles, int32_t K);
+
 // ---- the K-sliced GEMM of w4a8_sliced.hip for the same kind of group; K % 128 == 0
-// Rows from which the GEMM kernels replace the GEMVs: 17 on few output tiles, 21 on many (weights
-// from HBM, whole decode steps, GEMV against sliced GEMM: the 7B linears at 17 rows 337 / 253 us for
-// four layers; the 72B linears at 17 rows 108.7 / 111.1, at 24 rows 120.2 / 118.1).
-inline bool gemm_takes(int32_t T, int32_t K, int64_t n_tiles)
-{
-    return K % 128 == 0 && (T > 20 || (T > 16 && n_tiles <= kNumCU / 2));
-}
+// Whether the GEMM kernels take these rows instead of the GEMVs.
+bool gemm_takes(int32_t T, int32_t K, const GemvGroup &grp);
 
 template <int EPI>
 int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp, const Epilogue &ep,

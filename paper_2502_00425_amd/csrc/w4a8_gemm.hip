@@ -775,8 +775,6 @@ __global__ __launch_bounds__(NWAVES * 64) void w4a8_decode_fused_kernel(
 
 // ------------------------------------------------------------------ host side
 
-constexpr int kGemvMaxT = 32;
-
 int check_gemm_args(const void *xq, const void *wp, const void *w_scale, const void *y,
                     int64_t ldy, int32_t T, int32_t N, int32_t K, int32_t n_vis, float s_vis,
                     float s_txt)
@@ -966,6 +964,21 @@ int workspace_splits(int32_t T, int32_t N, int32_t K)
 
 namespace mquant {
 
+// Every wave walks `steps` batches of four k-tiles, `busy` is the share of the waves that have any; sixteen
+// waves per tile below 256 tiles, eight above.  Fitted to the time on 53 matrices (K 128 .. 29568, N 32 ..
+// 59136) at 17 to 32 rows, weights from HBM (rms 5 %).
+double gemv_tile_us(int32_t T, int64_t n_tiles, int32_t K)
+{
+    const uint32_t waves = n_tiles < kNumCU ? 16 : 8, k_tiles = K / kPackK, per_wave = ceil_div32(k_tiles, waves);
+    const double steps = ceil_div32(per_wave, 4), busy = static_cast<double>(ceil_div32(k_tiles, per_wave)) / waves;
+    const double tiles = static_cast<double>(n_tiles) * (1.0 / kNumCU), q = T * (1.0 / 16);
+    if (n_tiles < kNumCU)
+        return 0.287 + 2.097 * busy + steps * (1.899 + 0.253 * q) + 0.0336 * per_wave +
+               tiles * (0.655 + k_tiles * (0.0069 + 0.0120 * q));
+    return 0.981 + 0.594 * busy + steps * (0.234 + 0.163 * q) + tiles * (0.500 + 0.0067 * k_tiles * q) +
+           static_cast<double>(ceil_div(n_tiles, kNumCU)) * (0.715 + 0.0291 * k_tiles);
+}
+
 // The tile GEMV for a group of linears that share xq (a group of one for the single-linear
 // entry points).  It handles 32 rows per pass; taller inputs (only reached for K % 128 != 0,
 // which the prefill kernel does not take) are walked in slabs of 32 rows.
@@ -1059,7 +1072,7 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     if (!force_sliced) {
         if (gemv_stream_takes(T, K, ceil_div(N, kPackN)))
             return gemv_stream_dispatch<EPI>(xq, T, K, grp, ep, stream);
-        if (!gemm_takes(T, K, ceil_div(N, kPackN))) return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);
+        if (!gemm_takes(T, K, grp)) return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);
     }
     const int splits = tune_state().gemm_nosplit.load(std::memory_order_relaxed) ? 1 : workspace_splits(T, N, K);
     if (splits > 1) {

@@ -374,22 +374,47 @@ constexpr Variant kSliced[] = {
 constexpr int kVariants = sizeof(kSliced) / sizeof(kSliced[0]);
 static_assert(kVariants == kSlicedTiles, "mquant_tune_set validates against this");
 
-double cost_us(const Variant &v, int32_t T, int32_t K, const GemvGroup &grp)
-{
-    int64_t tiles = 0;
-    for (int32_t i = 0; i < grp.n; ++i) tiles += ceil_div32(grp.p[i].N, v.cost.bn);
-    return v.cost.us(tiles * ceil_div32(T, v.cost.bm), K);
-}
+// Up to 32 rows, one row of tiles: the weights come from HBM and are what a launch waits for, so the
+// 32-row tiles have costs of their own, the part along K growing by `slope` per 16 rows beyond 16.  Same sweep at 17 to 32
+// rows (rms 5 - 8 %).
+struct ShortCost {
+    int variant;
+    TileCost cost;
+    double slope;
+};
+constexpr ShortCost kShort[] = {
+    {8, {32, 64, 2, 2.332, 0.472, 0.131, 0.156, 0.117, 1.017}, 0.052},
+    {9, {32, 64, 1, 1.702, 1.376, 0.114, 0.000, 0.067, 1.172}, 0.070},
+    {10, {32, 32, 1, 1.695, 1.493, 0.067, 0.000, 0.036, 0.979}, 0.128},
+};
+static_assert(kSliced[8].cost.bn == 64 && kSliced[9].cost.bn == 64 && kSliced[10].cost.bn == 32, "kShort names these");
 
-int pick(int32_t T, int32_t K, const GemvGroup &grp)
+struct Choice {
+    int variant;
+    double us;
+};
+
+Choice pick(int32_t T, int32_t K, const GemvGroup &grp)
 {
-    int best = 0;
-    double best_us = cost_us(kSliced[0], T, K, grp);
-    for (int i = 1; i < kVariants; ++i) {
-        const double us = cost_us(kSliced[i], T, K, grp);
-        if (us < best_us) {
-            best = i;
-            best_us = us;
+    auto tiles_n = [&](const TileCost &c) {
+        int64_t tiles = 0;
+        for (int32_t i = 0; i < grp.n; ++i) tiles += ceil_div32(grp.p[i].N, c.bn);
+        return tiles;
+    };
+    Choice best = {-1, 0.0};
+    auto consider = [&](int variant, double us) {
+        if (best.variant < 0 || us < best.us) best = {variant, us};
+    };
+    if (T <= kGemvMaxT) {
+        for (const ShortCost &s : kShort) {
+            const int64_t tiles = tiles_n(s.cost);
+            const double start = s.cost.us(tiles, 0), walk = s.cost.us(tiles, K) - start;
+            consider(s.variant, start + walk * (1.0 + s.slope * (T - 16) * (1.0 / 16)));
+        }
+    } else {
+        for (int i = 0; i < kVariants; ++i) {
+            const TileCost &c = kSliced[i].cost;
+            consider(i, c.us(tiles_n(c) * ceil_div32(T, c.bm), K));
         }
     }
     return best;
@@ -399,14 +424,29 @@ int pick(int32_t T, int32_t K, const GemvGroup &grp)
 
 namespace mquant {
 
-double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp) { return cost_us(kSliced[pick(T, K, grp)], T, K, grp); }
+double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp) { return pick(T, K, grp).us; }
+
+// From 33 rows on always.  Of 17 to 32 rows the GEMV keeps what the GEMM is not expected to do faster by 2 %,
+// or at all where the weights take 20 us and more to read (GEMV against GEMM, weights from HBM, 24 rows: 3584 ->
+// 3584 5.6 / 6.8 us, 3584 -> 37888 20.1 / 21.6, 8192 -> 8192 9.7 / 11.1; 18944 -> 3584 18.2 / 17.4, 8192 -> 59136 51.4 / 49.1, 5120 ->
+// 27648 21.7 / 18.6), and the smallest calls (128 -> 1024 3.0 / 3.3, 256 -> 4096 3.5 / 3.7).
+bool gemm_takes(int32_t T, int32_t K, const GemvGroup &grp)
+{
+    if (K % 128 != 0 || T <= 16) return false;
+    if (T > kGemvMaxT) return true;
+    int64_t n_tiles = 0;
+    for (int32_t i = 0; i < grp.n; ++i) n_tiles += ceil_div32(grp.p[i].N, kPackN);
+    if (K <= 256 && n_tiles < kNumCU) return false;
+    const double margin = n_tiles * K >= int64_t{1} << 22 ? 1.0 : 0.98;     // 64 MiB of weights
+    return sliced_cost_us(T, K, grp) < margin * gemv_tile_us(T, n_tiles, K);
+}
 
 template <int EPI>
 int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp, const Epilogue &ep,
                     hipStream_t stream)
 {
     int v = tune_state().gemm_sliced.load(std::memory_order_relaxed);
-    if (v < 0) v = pick(T, K, grp);
+    if (v < 0) v = pick(T, K, grp).variant;
     return kSliced[v].launch[EPI](xq, T, K, grp, ep, stream);
 }
 

@@ -85,3 +85,22 @@ def test_w4a8_prompts(mq, T, N, K, name):
     (microseconds measured, in brackets the sliced tile)."""
     got = w4a8(mq, T, N, K)
     assert len(got) == 1 and got[0].startswith(name), got
+
+
+@pytest.mark.parametrize("T,N,K,name", [
+    (17, 3584, 3584, "w4a8_gemv_kernel"), (24, 4608, 3584, "w4a8_gemv_kernel"),         # 5.3 us (6.6), 5.6 (6.8)
+    (32, 3584, 3584, "w4a8_gemv_kernel"), (24, 8192, 8192, "w4a8_gemv_kernel"),         # 5.7 (6.9), 9.6 (11.0)
+    (20, 37888, 3584, "w4a8_gemv_kernel"), (24, 64, 16384, "w4a8_gemv_kernel"),         # 18.5 (21.3), 10.4 (12.1)
+    (17, 1024, 128, "w4a8_gemv_kernel"),                                                # 2.8 (3.2)
+    (24, 3584, 18944, "w4a8_sliced_kernel"), (32, 10240, 8192, "w4a8_sliced_kernel"),   # 17.4 (GEMV 18.2), 14.6 (16.0)
+    (32, 59136, 8192, "w4a8_sliced_kernel"), (24, 18944, 384, "w4a8_sliced_kernel"),    # 50.8 (57.4), 4.8 (6.7)
+])
+def test_w4a8_decode_rows_above_sixteen(mq, T, N, K, name):
+    """GEMV against sliced GEMM from 17 to 32 rows (microseconds measured, in brackets the other side),
+    in the single and in the grouped entry."""
+    got = w4a8(mq, T, N, K)
+    assert len(got) == 1 and got[0].startswith(name + "<"), got
+    xq = torch.zeros((T, K), dtype=torch.int8, device="cuda")
+    wp = torch.zeros(mq.w4_prepacked_bytes(N, K), dtype=torch.uint8, device="cuda")
+    lin = [(wp, torch.ones(N, dtype=torch.float16, device="cuda"), N, torch.empty((T, N), dtype=torch.float16, device="cuda"))]
+    assert kernels(lambda: mq.w4a8_gemv_grouped(xq, lin, 0, 1.0, 1.0)) == got
