@@ -9,6 +9,8 @@ import pytest
 from oracle import mquant_oracle as orc
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
+
 pytestmark = pytest.mark.gpu
 
 TILES = 11
@@ -99,11 +101,11 @@ def test_split_epilogue(mq, forced, tile):
         assert not bad.any(), (tile, T, N, K, n_split, int(bad.sum()))
 
 
-@pytest.mark.parametrize("T", [17, 25, 32])
+@pytest.mark.parametrize("T", [5, 17, 25, 32])
 @pytest.mark.parametrize("K", [128, 3584])
 def test_group_of_linears(mq, T, K):
-    """Rows 17 to 32 of the grouped entry: four linears of different widths in one launch, every
-    tile and the library's own choice, against separate calls on the oracle."""
+    """The grouped entry: four linears of different widths in one launch, every tile (a forced one takes
+    any number of rows) and the library's own choice, against separate calls on the oracle."""
     rng = np.random.default_rng(T + K)
     xq = rng.integers(-128, 128, size=(T, K), dtype=np.int8)
     lin, want = [], []
@@ -118,7 +120,9 @@ def test_group_of_linears(mq, T, K):
             mq.tune_set(mq.TUNE_GEMM_SHAPE, tile)
             for l in lin:
                 l[3].fill_(float("nan"))
-            mq.w4a8_gemv_grouped(dev(xq), lin, T // 3, 0.07, 0.009)
+            x = dev(xq)
+            names = kernels(lambda: mq.w4a8_gemv_grouped(x, lin, T // 3, 0.07, 0.009))
+            assert len(names) == 1 and (tile < 0 or names[0].startswith("w4a8_sliced_kernel<")), (tile, names)
             for l, w in zip(lin, want):
                 assert (bits(l[3]) == w.view(np.uint16)).all(), (tile, l[2])
     finally:
