@@ -9,6 +9,8 @@ import pytest
 from oracle import mquant_oracle as orc
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
+
 pytestmark = pytest.mark.gpu
 
 
@@ -78,23 +80,29 @@ def test_dynquant_rejects_rows_too_long_for_registers(mq):
     assert e.value.status == mq.ERR_UNSUPPORTED
 
 
-_DYN_SHAPES = [(1, 200, 832, 64), (16, 200, 832, 64), (75, 300, 1024, 512), (140, 300, 1024, 512),
-               (300, 520, 8192, 128), (260, 264, 3584, 512)]
+# T, N, K, block, last kernel of the library's own choice: K % 128 = 64 walks passes of up to 64 rows on the GEMV
+_DYN_SHAPES = [(1, 200, 832, 64, "w4a8_gemv_"), (16, 200, 832, 64, "w4a8_gemv_"),
+               (17, 200, 832, 64, "w4a8_gemv_kernel<16, 4, 1, 32, 1>"), (20, 8200, 832, 64, "w4a8_gemv_kernel<8, 4, 1, 32, 1>"),
+               (40, 200, 832, 64, "w4a8_gemv_kernel<8, 4, 1, 64, 2>"), (75, 300, 832, 64, "w4a8_gemv_kernel<16, 4, 1, 16, 1>"),
+               (130, 264, 192, 64, "w4a8_gemv_kernel<16, 4, 1, 4, 1>"), (21, 4104, 3584, 512, "w4a8_gemv_kernel<16, 4, 1, 32, 1>"),
+               (75, 300, 1024, 512, "w4a8_sliced_kernel<"), (140, 300, 1024, 512, "w4a8_sliced_kernel<"),
+               (300, 520, 8192, 128, "w4a8_sliced_kernel<"), (260, 264, 3584, 512, "w4a8_sliced_kernel<")]
 
 
-# decode shapes never reach the GEMM, so they run with the library's own choice only
-@pytest.mark.parametrize("T,N,K,B,tile", [s + (t,) for s in _DYN_SHAPES for t in (-1, 0, 1, 2, 3, 4) if t < 0 or s[0] > 32])
-def test_dynamic_linear_end_to_end(mq, T, N, K, B, tile):
+# what never reaches the GEMM runs with the library's own choice only
+@pytest.mark.parametrize("T,N,K,B,last,tile", [s + (t,) for s in _DYN_SHAPES for t in (-1, 0, 1, 2, 3, 4)
+                                               if t < 0 or (s[0] > 32 and s[2] % 128 == 0)])
+def test_dynamic_linear_end_to_end(mq, T, N, K, B, last, tile):
     """Rotate + per-token quantize + GEMM + per-token dequant: the library's own choice of kernel
-    (GEMV, the 64-row GEMV passes of short prompts, GEMM, split-K) and every GEMM tile forced."""
+    (GEMV, its passes of up to 64 rows, sliced GEMM) and every GEMM tile forced, split-K with it."""
     mq.tune_set(mq.TUNE_GEMM_TILE, tile)
     try:
-        _dynamic_linear_case(mq, T, N, K, B)
+        _dynamic_linear_case(mq, T, N, K, B, last if tile < 0 else "splitk_reduce_kernel<1>" if K == 8192 else "w4a8_gemm_kernel<")
     finally:
         mq.tune_set(mq.TUNE_GEMM_TILE, -1)
 
 
-def _dynamic_linear_case(mq, T, N, K, B):
+def _dynamic_linear_case(mq, T, N, K, B, last):
     say(f"dynamic linear T={T} N={N} K={K}")
     rng = np.random.default_rng(T + N + K)
     x = make_x(rng, T, K)
@@ -107,8 +115,11 @@ def _dynamic_linear_case(mq, T, N, K, B):
     y = mq.w4a8_gemm_rowscale(xq, wp, dev(w_scale), s, N, acc_out=acc)
     assert (acc.cpu().numpy() == want["acc"]).all()
     check_y(y.cpu().numpy(), want["ref"], "dynamic linear")
-    y2 = mq.w4a8_gemm_rowscale(xq, wp, dev(w_scale), s, N)          # store path without acc_out
+    wsc = dev(w_scale)
+    y2 = torch.empty((T, N), dtype=torch.float16, device="cuda")
+    names = kernels(lambda: mq.w4a8_gemm_rowscale(xq, wp, wsc, s, N, out=y2))      # store path without acc_out
     check_y(y2.cpu().numpy(), want["ref"], "dynamic linear, wide store")
+    assert names[-1].startswith(last), names
 
 
 def test_dynamic_linear_config1_qkv_sampled(mq):

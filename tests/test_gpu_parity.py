@@ -12,6 +12,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
+
 
 from oracle import mquant_oracle as orc                      # noqa: E402
 from paper_2502_00425_amd import workloads as wl             # noqa: E402
@@ -270,13 +272,17 @@ def test_gemm_small_shapes_full(mq, T, N, K, V):
 
 
 @pytest.mark.parametrize("T,N,K,V,ldy_pad", [
-    (300, 520, 8192, 77, 0),     # split-K (few tiles, long K), ragged T and N, wide stores
-    (300, 516, 8192, 300, 4),    # split-K with N % 8 != 0: plain stores in the reduce kernel
-    (70, 250, 16384, 0, 0),      # N % 4 != 0: split-K is not taken
-    (513, 264, 4096, 512, 0),    # one row past two 256-row tiles, K too short to split
+    (300, 520, 8192, 77, 0),     # few tiles, long K: four pieces, ragged T and N, wide stores
+    (300, 516, 8192, 300, 4),    # N % 8 != 0: plain stores in the reduce kernel
+    (70, 250, 16384, 0, 0),      # N % 4 != 0: never split
+    (513, 264, 4096, 512, 0),    # one row past two 256-row tiles, two pieces
 ])
-def test_gemm_split_k_and_store_paths(mq, T, N, K, V, ldy_pad):
-    say(f"gemm split/store paths T={T} N={N} K={K}")
+@pytest.mark.parametrize("tile", [-1, 0])
+def test_gemm_split_k_and_store_paths(mq, T, N, K, V, ldy_pad, tile, forced_tile):
+    """The library's choice (the sliced GEMM on these shapes), and with the tile forced the split-K plan:
+    partial sums in the workspace and the reduce kernel behind."""
+    say(f"gemm split/store paths T={T} N={N} K={K} tile={tile}")
+    forced_tile(mq.TUNE_GEMM_TILE, tile)
     rng = np.random.default_rng(T + N + K)
     xq = rng.integers(-128, 128, size=(T, K), dtype=np.int8)
     packed = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
@@ -286,13 +292,18 @@ def test_gemm_split_k_and_store_paths(mq, T, N, K, V, ldy_pad):
     ref, _ = orc.dequant(acc_want, V, s_vis, s_txt, w_scale)
     wp = mq.w4_prepack(dev(packed))
     ws_bytes = mq.w4a8_workspace_bytes(T, N, K)
+    assert (ws_bytes > 0) == (N % 4 == 0)
     ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device="cuda")
     ldy = N + ldy_pad
+    x, wsc = dev(xq), dev(w_scale)
     for want_acc in (False, True):
         ybuf = torch.full((T, ldy), 7.0, dtype=torch.float16, device="cuda")
         acc = torch.full((T, N), -3, dtype=torch.int32, device="cuda") if want_acc else None
-        mq.w4a8_gemm(dev(xq), wp, dev(w_scale), N, V, s_vis, s_txt, out=ybuf[:, :N], acc_out=acc,
-                     workspace=ws if ws_bytes else None)
+        names = kernels(lambda: mq.w4a8_gemm(x, wp, wsc, N, V, s_vis, s_txt, out=ybuf[:, :N], acc_out=acc,
+                                             workspace=ws if ws_bytes else None))
+        if tile == 0:
+            assert names[0].startswith("w4a8_gemm_kernel<256, 256,")
+            assert [n for n in names[1:]] == (["splitk_reduce_kernel<0>"] if ws_bytes else []), names
         yb = ybuf.cpu().numpy()
         check_y(yb[:, :N], ref, f"split/store want_acc={want_acc}")
         assert (yb[:, N:] == 7.0).all()
@@ -331,11 +342,11 @@ def test_gemm_extreme_values_no_overflow(mq):
     assert (acc1.cpu().numpy() == acc_want[:2]).all()
 
 
-def test_gemm_at_the_maximum_k(mq):
+def test_gemm_at_the_maximum_k(mq, forced_tile):
     """K = 65536 is the documented limit: the accumulator holds 16 x the sum, and with every
     activation at -128 and every weight at -8 that is 2^30, the largest value it can take.
     Closed form (every product equal) for the accumulators, the oracle for the mixed rows;
-    the GEMV, the direct GEMM, split-K with its workspace, and the wide and the 2-byte stores."""
+    the GEMV, the sliced GEMM, split-K with its workspace (a forced tile), and the wide and the 2-byte stores."""
     K, N = 65536, 72
     say(f"gemm at K={K}")
     packed = np.full((N, K // 2), 0x88, dtype=np.uint8)          # every weight -8
@@ -343,7 +354,8 @@ def test_gemm_at_the_maximum_k(mq):
     wq = orc.unpack_w4(packed)
     wp = mq.w4_prepack(dev(packed))
     ones = dev(np.ones(N, dtype=np.float16))
-    for T in (3, 40, 300):
+    for T, tile in ((3, -1), (40, -1), (300, -1), (300, 0)):
+        forced_tile(mq.TUNE_GEMM_TILE, tile)
         xq = np.full((T, K), -128, dtype=np.int8)
         xq[1::3] = 127
         xq[2::3, ::2] = 55                                       # a row with mixed values
@@ -356,8 +368,11 @@ def test_gemm_at_the_maximum_k(mq):
         assert (acc.cpu().numpy() == acc_want).all(), T
         ref, _ = orc.dequant(acc_want, 0, 2.0 ** -20, 2.0 ** -20, np.ones(N, dtype=np.float16))
         check_y(y.cpu().numpy(), ref, f"max K, T={T}")
-        y2 = mq.w4a8_gemm(dev(xq), wp, ones, N, 0, 2.0 ** -20, 2.0 ** -20, workspace=ws)
+        x = dev(xq)
+        y2 = torch.empty((T, N), dtype=torch.float16, device="cuda")
+        names = kernels(lambda: mq.w4a8_gemm(x, wp, ones, N, 0, 2.0 ** -20, 2.0 ** -20, out=y2, workspace=ws))
         check_y(y2.cpu().numpy(), ref, f"max K, no acc_out, T={T}")
+        assert ("splitk_reduce_kernel<0>" in names) == (tile == 0), names
     assert mq.lib.mquant_w4_prepacked_bytes(N, K + 64) == mq.ERR_UNSUPPORTED
 
 
@@ -838,11 +853,13 @@ def test_gemm_seeded_shape_sweep(mq):
         check_y(y2.cpu().numpy(), ref, f"sweep, no acc_out {(T, N, K)}")
 
 
-def test_prefill_step_as_hip_graph_replays_match_plain_launches(mq):
+@pytest.mark.parametrize("tile", [-1, 0])
+def test_prefill_step_as_hip_graph_replays_match_plain_launches(mq, tile, forced_tile):
     """The benchmark replays a step (mask remap, row permute, rotate+quant and GEMM per linear)
     from one captured HIP graph.  Every replay must reproduce the plain launches bit for bit,
-    with other work and synchronisations between the replays; shapes cover the GEMV, both GEMM
-    tiles and the split-K path with its workspace."""
+    with other work and synchronisations between the replays; the shapes take the sliced GEMM and,
+    with the tile forced, the large tiles and the split-K plan with its workspace."""
+    forced_tile(mq.TUNE_GEMM_TILE, tile)
     rng = np.random.default_rng(88)
     T, B = 300, 64
     spans = [(10, 120), (200, 60)]
@@ -860,7 +877,6 @@ def test_prefill_step_as_hip_graph_replays_match_plain_launches(mq):
                      "xq": torch.empty((T, K), dtype=torch.int8, device="cuda"),
                      "y": torch.empty((T, N), dtype=torch.float16, device="cuda"),
                      "ws": torch.empty(nws, dtype=torch.uint8, device="cuda") if nws else None})
-    assert any(l["ws"] is not None for l in lins), "one shape must take the split-K path"
     x_u = torch.empty_like(lins[0]["x"])
 
     def step():
@@ -871,9 +887,12 @@ def test_prefill_step_as_hip_graph_replays_match_plain_launches(mq):
             mq.w4a8_gemm(l["xq"], l["wp"], l["w_scale"], l["N"], V, 0.05, 0.02, out=l["y"], workspace=l["ws"])
 
     outputs = lambda: [mask_u.clone(), x_u.clone()] + [l["y"].clone() for l in lins] + [l["xq"].clone() for l in lins]
-    say("graph: plain launches")
-    step()
-    torch.cuda.synchronize()
+    say(f"graph: plain launches, tile {tile}")
+    names = kernels(step)
+    if tile == 0:
+        assert "splitk_reduce_kernel<0>" in names, "one shape must take the split-K path"
+    else:
+        assert any(n.startswith("w4a8_sliced_kernel<") for n in names), names
     want = outputs()
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())

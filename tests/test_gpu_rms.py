@@ -10,6 +10,8 @@ import pytest
 from oracle import mquant_oracle as orc
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
+
 pytestmark = pytest.mark.gpu
 
 
@@ -55,17 +57,32 @@ def check(y_gpu, ref, mag, what):
     assert not bad.any(), f"{what}: {int(bad.sum())} outputs beyond 1e-3 (first {np.argwhere(bad)[:3].tolist()})"
 
 
-@pytest.mark.parametrize("T,N,K,B,n_split", [
-    (1, 200, 832, 64, 1), (16, 200, 832, 64, 3),            # GEMV
-    (75, 300, 1024, 512, 2),                                 # short prompt: GEMV pass of 64 rows + one of 11
-    (140, 300, 1024, 512, 2),                                # GEMM, narrow stores
-    (260, 264, 3584, 512, 1), (260, 520, 3584, 512, 7),      # GEMM, wide stores
-    (300, 520, 8192, 128, 5),                                # split-K + reduce kernel
-    (40, 64, 18944, 512, 37),                                # every block flagged
-    (33, 96, 8192, 128, 64),                                 # the most the entry point takes
+_GEMV2 = "w4a8_gemv_kernel<8, 4, 2, 64, 2>"                  # two 32-row blocks per weight tile
+
+
+@pytest.mark.parametrize("T,N,K,B,n_split,tile,last", [
+    (1, 200, 832, 64, 1, -1, "w4a8_gemv_"), (16, 200, 832, 64, 3, -1, "w4a8_gemv_"),     # GEMV
+    (17, 200, 832, 64, 3, -1, "w4a8_gemv_kernel<16, 4, 2, 32, 1>"), (20, 8200, 832, 64, 2, -1, "w4a8_gemv_kernel<8, 4, 2, 32, 1>"),
+    (40, 200, 832, 64, 5, -1, _GEMV2), (75, 300, 832, 64, 2, -1, "w4a8_gemv_kernel<16, 4, 2, 16, 1>"),   # 64 rows + 11
+    (130, 264, 192, 64, 3, -1, "w4a8_gemv_kernel<16, 4, 2, 4, 1>"),                      # 64 + 64 + 2 rows
+    (21, 4104, 3584, 512, 4, -1, "w4a8_gemv_kernel<16, 4, 2, 32, 1>"),
+    (75, 300, 1024, 512, 2, -1, "w4a8_sliced_kernel<"), (140, 300, 1024, 512, 2, -1, "w4a8_sliced_kernel<"),
+    (260, 264, 3584, 512, 1, -1, "w4a8_sliced_kernel<"), (260, 520, 3584, 512, 7, -1, "w4a8_sliced_kernel<"),
+    (300, 520, 8192, 128, 5, -1, "w4a8_sliced_kernel<"),
+    (300, 520, 8192, 128, 5, 0, "splitk_reduce_kernel<2>"), (300, 516, 8192, 128, 3, 0, "splitk_reduce_kernel<2>"),
+    (40, 64, 18944, 512, 37, -1, "w4a8_sliced_kernel<"),     # every block flagged
+    (33, 96, 8192, 128, 64, -1, "w4a8_sliced_kernel<"),      # the most the entry point takes
 ])
-def test_rms_gemm_matches_oracle(mq, T, N, K, B, n_split):
-    say(f"rms T={T} N={N} K={K} splits={n_split}")
+def test_rms_gemm_matches_oracle(mq, T, N, K, B, n_split, tile, last):
+    say(f"rms T={T} N={N} K={K} splits={n_split} tile={tile}")
+    mq.tune_set(mq.TUNE_GEMM_TILE, tile)
+    try:
+        _rms_case(mq, T, N, K, B, n_split, last)
+    finally:
+        mq.tune_set(mq.TUNE_GEMM_TILE, -1)
+
+
+def _rms_case(mq, T, N, K, B, n_split, last):
     rng = np.random.default_rng(T + N + K + n_split)
     xq, wq, idx, wsplit, ssplit, w_scale = make_case(rng, T, N, K, B, n_split)
     V, s_vis, s_txt = T // 3, 0.11, 0.004
@@ -79,8 +96,10 @@ def test_rms_gemm_matches_oracle(mq, T, N, K, B, n_split):
     y = mq.w4a8_gemm_rms(*args, acc_out=acc)
     assert (acc.cpu().numpy() == acc_want).all()
     check(y.cpu().numpy(), ref, mag, "rms with acc_out")
-    y2 = mq.w4a8_gemm_rms(*args)
+    y2 = torch.empty((T, N), dtype=torch.float16, device="cuda")
+    names = kernels(lambda: mq.w4a8_gemm_rms(*args, out=y2))
     check(y2.cpu().numpy(), ref, mag, "rms")
+    assert names[-1].startswith(last), names
 
 
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])

@@ -10,6 +10,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
+from kernel_trace import kernels
 
 
 @pytest.fixture(scope="module")
@@ -36,11 +37,20 @@ def make_case(mq, seed, T, N, K, spans):
             "T": T, "N": N, "K": K}
 
 
-def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row(mq):
+@pytest.mark.parametrize("tile", [-1, 0])
+def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row(mq, tile):
+    mq.tune_set(mq.TUNE_GEMM_TILE, tile)
+    try:
+        _static_scratch_case(mq, tile)
+    finally:
+        mq.tune_set(mq.TUNE_GEMM_TILE, -1)
+
+
+def _static_scratch_case(mq, tile):
     B = 64
-    # (300, 520, 8192): split-K with partial sums in the scratch, ragged T and N.
+    # (300, 520, 8192): ragged T and N; with the tile forced, split-K with partial sums in the scratch.
     # (130, 264, 8192): a smaller problem right after it, same path.
-    # (64, 96, 512): no split-K, only the int8 activations go through the scratch.
+    # (64, 96, 512): only the int8 activations go through the scratch.
     cases = [make_case(mq, 1, 300, 520, 8192, [(10, 120), (200, 60)]),
              make_case(mq, 2, 130, 264, 8192, [(3, 40)]),
              make_case(mq, 3, 64, 96, 512, [(8, 48)])]
@@ -68,6 +78,10 @@ def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row(mq):
             assert bool((y[:, c["N"]:] == 5.0).all())
             del y
     assert torch.cuda.memory_allocated() == before
+    for c, w in zip(cases, want):
+        names = kernels(lambda: mq.w4a8_linear_prefill_static(c["x"], c["perm"], c["wp"], c["w_scale"], c["N"], c["V"],
+                                                              0.21, 0.034, B, out=w))
+        assert ("splitk_reduce_kernel<0>" in names) == (tile == 0 and c["K"] == 8192), names
 
 
 def test_static_scratch_entry_rejects_what_does_not_fit(mq):
