@@ -195,13 +195,8 @@ int launch_remap_rows(const uint8_t *mask, uint8_t *mask_u, const int32_t *perm,
 {
     const size_t lds = static_cast<size_t>(R) * T;
     auto kern = remap_mask_rows_kernel<R>;
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                144 * 1024) != hipSuccess)
-            return MQUANT_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static LdsLimit limit;
+    if (const int st = limit.raise(reinterpret_cast<const void *>(kern), 144 * 1024); st != MQUANT_OK) return st;
     int64_t blocks = ceil_div(T, R);
     if (blocks > 8 * kNumCU) blocks = 8 * kNumCU;
     MQ_LAUNCH(kern, dim3(static_cast<unsigned>(blocks)), dim3(1024), lds, stream, mask, mask_u, perm, T);

@@ -61,6 +61,26 @@ static inline int launch_status()
     return MQUANT_ERR_HIP;
 }
 
+// Dynamic LDS beyond 64 KiB has to be allowed for a kernel before it is launched with it, and the
+// permission belongs to the kernel on the current device: one of these per kernel remembers the devices that have it.
+// Raising the limit is idempotent: threads racing here at most repeat it.
+class LdsLimit {
+    std::atomic<uint64_t> devices_{0};
+
+public:
+    int raise(const void *kernel, size_t bytes)
+    {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0) return MQUANT_ERR_HIP;
+        const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;      // later devices ask every time
+        if (devices_.load(std::memory_order_acquire) & bit) return MQUANT_OK;
+        if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)) != hipSuccess)
+            return MQUANT_ERR_HIP;
+        devices_.fetch_or(bit, std::memory_order_release);
+        return MQUANT_OK;
+    }
+};
+
 // Process-wide overrides of kernel choices (mquant_tune_set); -1 / 0 = cost model.
 struct TuneState {
     std::atomic<int32_t> gemm_tile{-1};

@@ -830,15 +830,8 @@ int launch_gemm(const int8_t *xq, const uint8_t *wp, const void *w_scale, void *
     // read by one XCD only), else equal bands of about six rows.
     const int32_t band = tiles_m <= 8 ? tiles_m
                                       : static_cast<int32_t>(ceil_div(tiles_m, ceil_div(tiles_m, 6)));
-    // Raising the dynamic LDS limit is idempotent: threads racing here at most repeat it.
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                static_cast<int>(lds)) != hipSuccess)
-            return MQUANT_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static LdsLimit limit;
+    if (const int st = limit.raise(reinterpret_cast<const void *>(kern), lds); st != MQUANT_OK) return st;
     MQ_LAUNCH(kern, dim3(tiles_m * tiles_n * splits), dim3(WM * WN * 64), lds, stream, xq,
                        reinterpret_cast<const uint4 *>(wp), static_cast<const __half *>(w_scale),
                        static_cast<__half *>(y), ldy, acc_out, T, N, K, ep, tiles_m, tiles_n, n_tiles32, splits, kb_per_split,
@@ -1277,25 +1270,15 @@ int launch_decode_fused(const __half *x, int64_t ldx, const uint4 *wp, const __h
     if (n_tiles >= 256) {
         const size_t lds = static_cast<size_t>(xq_bytes > 8 * 4096 ? xq_bytes : 8 * 4096);
         auto kern = w4a8_decode_fused_kernel<8, 4, B>;
-        static std::atomic<bool> attr_set{false};
-        if (!attr_set.load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-                return MQUANT_ERR_HIP;
-            attr_set.store(true, std::memory_order_release);
-        }
+        static LdsLimit limit;
+        if (const int st = limit.raise(reinterpret_cast<const void *>(kern), 160 * 1024); st != MQUANT_OK) return st;
         MQ_LAUNCH(kern, dim3(n_tiles), dim3(512), lds, stream, x, ldx, wp, w_scale, y, ldy, T, N, K, ep,
                   c_vis, c_txt);
     } else {
         const size_t lds = static_cast<size_t>(xq_bytes > 16 * 4096 ? xq_bytes : 16 * 4096);
         auto kern = w4a8_decode_fused_kernel<16, 4, B>;
-        static std::atomic<bool> attr_set{false};
-        if (!attr_set.load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-                return MQUANT_ERR_HIP;
-            attr_set.store(true, std::memory_order_release);
-        }
+        static LdsLimit limit;
+        if (const int st = limit.raise(reinterpret_cast<const void *>(kern), 160 * 1024); st != MQUANT_OK) return st;
         MQ_LAUNCH(kern, dim3(n_tiles), dim3(1024), lds, stream, x, ldx, wp, w_scale, y, ldy, T, N, K, ep,
                   c_vis, c_txt);
     }

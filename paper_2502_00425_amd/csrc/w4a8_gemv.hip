@@ -414,13 +414,8 @@ int launch_stream(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp, 
     const size_t red = static_cast<size_t>(WAVES) * 4 * (32 / F) * 4;
     lds = lds > red ? lds : red;
     auto kern = w4a8_gemv_stream_kernel<F, WAVES, DEPTH, NX, EPI, HB>;
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kStreamMaxLds) != hipSuccess)
-            return MQUANT_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static LdsLimit limit;
+    if (const int st = limit.raise(reinterpret_cast<const void *>(kern), kStreamMaxLds); st != MQUANT_OK) return st;
     MQ_LAUNCH(kern, dim3(static_cast<unsigned>(total_units)), dim3(WAVES * 64), lds, stream, xq, T, K, grp, ep,
               x, ldx, c_vis, c_txt);
     return launch_status();

@@ -331,14 +331,9 @@ int launch_sliced(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, const E
     constexpr int lds = sliced_lds_bytes<MT, NWN, NB, EPI>();
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     auto kern = w4a8_sliced_kernel<MT, NWN, NB, EPI>;
-    // Raising the dynamic LDS limit is idempotent: threads racing here at most repeat it.
-    static std::atomic<bool> attr_set{false};
-    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                lds) != hipSuccess)
-            return MQUANT_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static LdsLimit limit;
+    if (lds > 64 * 1024)
+        if (const int st = limit.raise(reinterpret_cast<const void *>(kern), lds); st != MQUANT_OK) return st;
     MQ_LAUNCH(kern, dim3(static_cast<unsigned>(tiles_m * tiles_n)), dim3(512), lds, stream, xq, grp, T, K, ep,
               static_cast<int32_t>(tiles_m), static_cast<int32_t>(tiles_n), band);
     return launch_status();

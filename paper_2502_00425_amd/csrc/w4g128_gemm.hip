@@ -567,14 +567,9 @@ int launch_gemv_half(const __half *x, int64_t ldx, const v4u *wt, const __half *
     auto kern = w4g128_gemv_half_kernel<NWAVES, DEPTH>;
     const int64_t xb = static_cast<int64_t>(T) * (static_cast<int64_t>(K) * 2 + 16);
     const int lds = static_cast<int>(xb > NWAVES * 1024 ? xb : NWAVES * 1024);
-    // Raising the dynamic LDS limit is idempotent: threads racing here at most repeat it.
-    static std::atomic<bool> attr_set{false};
-    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kGemvHalfLds) != hipSuccess)
-            return MQUANT_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static LdsLimit limit;
+    if (lds > 64 * 1024)
+        if (const int st = limit.raise(reinterpret_cast<const void *>(kern), kGemvHalfLds); st != MQUANT_OK) return st;
     MQ_LAUNCH(kern, dim3(static_cast<unsigned>(n_pad / 16)), dim3(NWAVES * 64), lds, stream, x, ldx, wt, sT, y, ldy, T,
               N, K, n_pad);
     return launch_status();
@@ -639,14 +634,9 @@ int launch_g128(const __half *x, int64_t ldx, const uint8_t *wp, __half *y, int6
     constexpr int lds = g128_lds_bytes<MT, NWN, NB>();
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     auto kern = w4g128_gemm_kernel<MT, NWN, NB>;
-    // Raising the dynamic LDS limit is idempotent: threads racing here at most repeat it.
-    static std::atomic<bool> attr_set{false};
-    if (lds > 64 * 1024 && !attr_set.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-            return MQUANT_ERR_HIP;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static LdsLimit limit;
+    if (lds > 64 * 1024)
+        if (const int st = limit.raise(reinterpret_cast<const void *>(kern), lds); st != MQUANT_OK) return st;
     MQ_LAUNCH(kern, dim3(tiles_m * tiles_n), dim3(512), lds, stream, x, ldx, wp, sT, y, ldy, T, N, K,
               tiles_m, tiles_n, n_tiles32, wide, band);
     return launch_status();

@@ -291,3 +291,17 @@ def test_header_is_plain_c():
                 ["g++", "-std=c++17", "-Wall", "-Werror", "-fsyntax-only", "-x", "c++", hdr]):
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert r.returncode == 0, r.stdout
+
+
+def test_lds_limits_are_raised_on_every_device(tmp_path):
+    """A kernel's dynamic LDS limit is a property of the kernel on one device: a program that moves
+    to a second device needs it raised there too (stand-in HIP calls, nothing is launched)."""
+    import shutil
+    import subprocess
+    if shutil.which("gcc") is None:
+        pytest.skip("no gcc")
+    exe = str(tmp_path / "lds_limit_driver")
+    subprocess.run(["gcc", "-std=gnu11", "-O1", "-rdynamic", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "lds_limit_driver.c"), "-o", exe, "-ldl"], check=True)
+    r = subprocess.run([exe, mq.LIB_PATH], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
