@@ -9,6 +9,7 @@ library is missing or cannot be loaded the import of this module raises.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 import struct
 from typing import Optional, Sequence, Tuple
@@ -197,7 +198,13 @@ def _linears(linears) -> bytes:
         _dense(ws, "w_scale")
         vals += (_dp(wp) or 0, _dp(ws) or 0, _dp(out) or 0, ld, N)
     n = len(linears)
-    return (_linear_packers[n] if n < len(_linear_packers) else struct.Struct("@" + "PPPqi4x" * n)).pack(*vals)
+    try:
+        return (_linear_packers[n] if n < len(_linear_packers) else struct.Struct("@" + "PPPqi4x" * n)).pack(*vals)
+    except struct.error:
+        for i, (_, _, N, _) in enumerate(linears):
+            if not -2 ** 31 <= operator.index(N) < 2 ** 31:       # index: TypeError for what is no integer
+                raise MQuantError(ERR_BAD_SHAPE, f"linear {i}: N = {N}") from None
+        raise
 
 
 # ------------------------------------------------------------------- host

@@ -305,3 +305,18 @@ def test_lds_limits_are_raised_on_every_device(tmp_path):
                     os.path.join(ROOT, "tests", "lds_limit_driver.c"), "-o", exe, "-ldl"], check=True)
     r = subprocess.run([exe, mq.LIB_PATH], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_grouped_entries_refuse_an_n_out_of_range():
+    """The descriptors hold N in 32 bits: what does not fit is refused as a bad shape, what is no
+    integer as a type error."""
+    import torch
+    x, y, ws = torch.zeros((1, 128), dtype=torch.int8), torch.zeros((1, 32), dtype=torch.float16), torch.ones(32)
+    for call in (lambda N: mq.w4a8_gemv_grouped(x, [(ws, ws, N, y)], 0, 1.0, 1.0),
+                 lambda N: mq.w4a8_linear_decode_grouped(x, [(ws, ws, 32, y), (ws, ws, N, y)], 0, 1.0, 1.0, 128)):
+        for N in (2 ** 31, -2 ** 31 - 1, 2 ** 32 + 32):
+            with pytest.raises(mq.MQuantError) as e:
+                call(N)
+            assert e.value.status == mq.ERR_BAD_SHAPE
+        with pytest.raises(TypeError):
+            call(32.0)
