@@ -477,8 +477,8 @@ int mquant_w4g128_prepack(const uint8_t *w_canonical_dev, const void *scales_dev
  *   y_dev : fp16 [T, ldy] (written: columns 0..N-1 of every row), ldy >= N; 16-byte
  *           stores are used when N % 8 == 0, ldy % 8 == 0 and y_dev is 16-byte aligned
  * Few tokens (decode) are routed to a weight-streaming GEMV kernel, many to the MFMA
- * GEMM.  The summation order is the matrix core's (and, in the GEMV, fixed across the
- * waves that split K) and is not specified; results agree with a double-precision sum
+ * GEMM.  The summation order is the matrix core's and that of the waves that split K; it
+ * depends on the kernel and tile that T, N and K are sent to and is not specified; results agree with a double-precision sum
  * to within fp32 accumulation error plus the final fp16 rounding.
  * T == 0 or N == 0 is a no-op.  Errors: ERR_BAD_SHAPE, ERR_UNSUPPORTED (K % 128 != 0 or
  * K == 0), ERR_NULL, ERR_ALIGNMENT, ERR_HIP.
@@ -491,8 +491,9 @@ int mquant_w4g128_gemm(const void *x_dev, int64_t ldx, const uint8_t *w_prepacke
  * ---------------------------------------------------------------------- */
 
 typedef enum {
-    MQUANT_TUNE_GEMM_TILE = 0,      /* -1 = cost model; 0 = 256x256, 1 = 128x256, 2 = 192x128,
-                                       3 = 64x128, 4 = 64x256 (short prompts) */
+    MQUANT_TUNE_GEMM_TILE = 0,      /* -1 = cost model; a tile of the large-tile W4A8 GEMM: 0 = 256x256,
+                                       1 = 128x256, 2 = 192x128, 3 = 64x128, 4 = 64x256 (from 33 rows on;
+                                       shapes that the split-K plan takes run it whatever the tile) */
     MQUANT_TUNE_GEMM_NOSPLIT = 1,   /* 0 = cost model; 1 = never split K */
     MQUANT_TUNE_G128_TILE = 2,      /* -1 = cost model; 0 = 256x256, 1 = 96x128 (weight-only GEMM) */
     MQUANT_TUNE_GEMV_VARIANT = 3,   /* -1 = default; 0..3 = waves per work-group x loads in flight per
@@ -502,18 +503,21 @@ typedef enum {
                                        0 = 256x256, 1 = 96x128, 2 = 256x128, 3 = 192x128, 4 = 160x128,
                                        5 = 128x128, 6 = 64x128, 7 = 128x64, 8 = 64x64, 9 = 32x64,
                                        10 = 64x32, 11 = 32x32, 12 = 128x256, 13 = 64x256 */
-    MQUANT_TUNE_GEMM_SHAPE = 5      /* -1 = cost model; else any number of rows goes to this tile of the K-sliced
-                                       W4A8 GEMM: 0 = 64x128, 1 = 64x256, 2 = 192x128, 3 = 160x128,
+    MQUANT_TUNE_GEMM_SHAPE = 5      /* -1 = cost model; else any number of rows (K % 128 == 0) goes to this tile
+                                       of the K-sliced W4A8 GEMM: 0 = 64x128, 1 = 64x256, 2 = 192x128, 3 = 160x128,
                                        4 = 128x128, 5 = 96x128, 6 = 128x64, 7 = 64x64, 8 and 9 = 32x64
                                        (two and three stages), 10 = 32x32 */
 } mquant_tune_key_t;
 
 /*
  * HOST.  Overrides one kernel choice of the library for the whole process until
- * it is set back (value -1, or 0 for NOSPLIT).  Results never depend on these
- * choices, only speed; workspace sizes reported before a change may no longer
- * match (NOSPLIT needs none).  Out-of-range keys or values: ERR_BAD_SHAPE and
- * nothing changes.  Thread-safe; calls already running keep the value they read.
+ * it is set back (value -1, or 0 for NOSPLIT).  W4A8 results never depend on these
+ * choices, only speed: their sums are integers.  Weight-only results may differ in
+ * the last bits: the tiles add K in one, two, four or eight slices, each summed in
+ * fp32 (the library's own choice varies with T, N and K in the same way).
+ * Workspace sizes reported before a change may no longer match (NOSPLIT needs
+ * none).  Out-of-range keys or values: ERR_BAD_SHAPE and nothing changes.
+ * Thread-safe; calls already running keep the value they read.
  */
 int mquant_tune_set(int32_t key, int32_t value);
 

@@ -498,8 +498,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(
 // Several linears that share xq (q/k/v, gate/up) can go into one launch: the grid is the
 // concatenation of their tiles (units = 32-channel tiles of each problem).
 //
-// MROWS = 2 (33..64 rows of a K the GEMM kernels do not take): two 32-row blocks share every weight tile -- the
-// weights are still read once, unpacked once and feed two MFMA pairs.
+// MROWS = 2 (33..64 rows of a K the GEMM kernels do not take): two 32-row blocks share every weight
+// tile -- the weights are still read once, unpacked once and feed two MFMA pairs.
 template <int NWAVES, int KT, int EPI, int AROWS, int MROWS>
 __global__ __launch_bounds__(NWAVES * 64) void w4a8_gemv_kernel(
     const int8_t *__restrict__ xq, GemvGroup grp, int32_t T, int32_t K, Epilogue ep)
@@ -857,8 +857,8 @@ int launch_gemm(const int8_t *xq, const uint8_t *wp, const void *w_scale, void *
 // Up to 128 rows: 64-row tiles, three stages, several work-groups per CU.  With one row of 128- or
 // 256-row tiles the k-loop of a lone, mostly empty work-group per CU sets the time, and a sliced tile
 // pays for its slices where there are output channels enough to fill the chip: 64-row tiles against
-// sliced ones at T = 48: 3584 -> 18944 16.4 / 18.2 us, 3584 -> 37888 21.0 / 23.8, 1024 -> 37888 9.6 / 11.5, 384 -> 18944
-// 5.0 / 6.9; at T = 128: 1024 -> 12288 7.5 / 8.7, 2048 -> 11008 10.6 / 11.9.
+// sliced ones at T = 48: 3584 -> 18944 16.4 / 18.2 us, 3584 -> 37888 21.0 / 23.8, 1024 -> 37888 9.6 /
+// 11.5, 384 -> 18944 5.0 / 6.9; at T = 128: 1024 -> 12288 7.5 / 8.7, 2048 -> 11008 10.6 / 11.9.
 int pick_gemm_tile(int32_t T, int32_t N)
 {
     if (T <= 128) {
@@ -897,12 +897,13 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 }
 
 // The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 12 %
-// where the tiles above fill the chip: there the clock follows power, which the sweep's short bursts do not
-// show, and the sliced 64x256 tile reads each activation fragment from LDS for one MFMA instead of two.  One
-// linear at a time switched to its sliced tile in continuous passes over the four projections, estimated
-// share of the plan's time and change of the pass: 7B, T = 1003: o 0.76 -4.6 us, down (split-K) 0.88 -8.7; T = 1280: qkv 0.96
-// +1.7, o 0.95 -1.2, down 0.95 +0.4; T = 2048: qkv 0.90 +8.2, o 0.95 +3.7; T = 3000: o 0.90 +5.6, down 0.87 -13.4;
-// 72B, T = 1003: qkv 0.87 -8.3; T = 1500: down 0.86 -38.7; T = 2048: qkv 0.92 +5.0.
+// where the tiles above fill the chip: in a continuous run the clock is lower than in the sweep's short
+// bursts, and the sliced 64x256 tile, which reads each activation fragment from LDS for one MFMA instead
+// of two, falls behind its estimate.  One linear at a time switched to its sliced tile in continuous
+// passes over the four projections, estimated share of the plan's time and change of the pass: 7B, T =
+// 1003: o 0.76 -4.6 us, down (split-K) 0.88 -8.7; T = 1280: qkv 0.96 +1.7, o 0.95 -1.2, down (split-K) 0.95
+// +0.4; T = 2048: qkv 0.90 +8.2, o 0.95 +3.7; T = 3000: o 0.90 +5.6, down 0.87 -13.4; 72B, T = 1003: qkv 0.87
+// -8.3; T = 1500: down 0.86 -38.7; T = 2048: qkv 0.92 +5.0.
 bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
@@ -942,7 +943,9 @@ extern "C" int mquant_w4_prepack(const uint8_t *w, uint8_t *out, int32_t N, int3
 namespace {
 
 // Pieces of the split-K plan that the caller's workspace has to hold (1: none).  Short prompts
-// on few channels ask for no workspace: the sliced GEMM is far ahead there.
+// on few channels ask for no workspace: the sliced GEMM is far ahead there.  Elsewhere the size is
+// what the plan would need, also where the sliced GEMM then runs without it: a call's route may
+// change with the library, the size it asks for does not.
 int workspace_splits(int32_t T, int32_t N, int32_t K)
 {
     if (T <= kGemvMaxT || K % 128 != 0) return 1;
@@ -973,8 +976,8 @@ double gemv_tile_us(int32_t T, int64_t n_tiles, int32_t K)
 }
 
 // The tile GEMV for a group of linears that share xq (a group of one for the single-linear
-// entry points).  It handles 32 rows per pass; taller inputs (only reached for K % 128 != 0,
-// which the prefill kernel does not take) are walked in slabs of 32 rows.
+// entry points).  Up to 32 rows are one pass; taller inputs (only reached for K % 128 != 0,
+// which the GEMM kernels do not take) are walked in passes of up to 64 rows.
 template <int EPI>
 int gemv_tile_dispatch(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, const Epilogue &ep,
                        hipStream_t stream)
@@ -986,8 +989,7 @@ int gemv_tile_dispatch(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, co
     }
     if (total <= 0 || total > 0x7fffffff) return MQUANT_ERR_BAD_SHAPE;
     const unsigned n_tiles = static_cast<unsigned>(total);
-    // 32 rows per pass, 64 with two row blocks per weight tile (rows beyond 20 come here only
-    // for K % 128 != 0)
+    // 64 rows per pass have two row blocks per weight tile
     for (int32_t t0 = 0; t0 < T;) {
         const int32_t left = T - t0;
         const int32_t tt = left > kGemvMaxT ? (left < 2 * kGemvMaxT ? left : 2 * kGemvMaxT) : left;

@@ -370,8 +370,8 @@ constexpr int kVariants = sizeof(kSliced) / sizeof(kSliced[0]);
 static_assert(kVariants == kSlicedTiles, "mquant_tune_set validates against this");
 
 // Up to 32 rows, one row of tiles: the weights come from HBM and are what a launch waits for, so the
-// 32-row tiles have costs of their own, the part along K growing by `slope` per 16 rows beyond 16.  Same sweep at 17 to 32
-// rows (rms 5 - 8 %).
+// 32-row tiles have costs of their own, the part along K growing by `slope` per 16 rows beyond 16.  Same
+// sweep at 17 to 32 rows (rms 5 - 8 %).
 struct ShortCost {
     int variant;
     TileCost cost;
@@ -421,10 +421,11 @@ namespace mquant {
 
 double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp) { return pick(T, K, grp).us; }
 
-// From 33 rows on always.  Of 17 to 32 rows the GEMV keeps what the GEMM is not expected to do faster by 2 %,
-// or at all where the weights take 20 us and more to read (GEMV against GEMM, weights from HBM, 24 rows: 3584 ->
-// 3584 5.6 / 6.8 us, 3584 -> 37888 20.1 / 21.6, 8192 -> 8192 9.7 / 11.1; 18944 -> 3584 18.2 / 17.4, 8192 -> 59136 51.4 / 49.1, 5120 ->
-// 27648 21.7 / 18.6), and the smallest calls (128 -> 1024 3.0 / 3.3, 256 -> 4096 3.5 / 3.7).
+// From 33 rows on always.  Of 17 to 32 rows the GEMV keeps what the GEMM is not expected to do faster by
+// 2 %, or at all where the weights take 10 us and more to read (GEMV against GEMM, weights from HBM, 24
+// rows: 3584 -> 3584 5.6 / 6.8 us, 3584 -> 37888 20.1 / 21.6, 8192 -> 8192 9.7 / 11.1; 18944 -> 3584 18.2 / 17.4,
+// 8192 -> 59136 51.4 / 49.1, 5120 -> 27648 21.7 / 18.6), and the smallest calls (128 -> 1024 3.0 / 3.3,
+// 256 -> 4096 3.5 / 3.7).
 bool gemm_takes(int32_t T, int32_t K, const GemvGroup &grp)
 {
     if (K % 128 != 0 || T <= 16) return false;

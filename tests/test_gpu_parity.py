@@ -460,12 +460,9 @@ def test_gemv_streamed_rows_full(mq, T, N, K):
                                    (50, 18944, 384), (64, 37888, 256), (33, 33000, 128), (100, 18944, 256),
                                    (128, 10240, 384), (128, 37888, 128)])
 def test_short_prompts_on_small_matrices(mq, T, N, K):
-    """33 to 64 rows against a matrix with few output channels (up to 128 rows against a small
-    one) run as 64-row passes of the tile GEMV, two row blocks per weight tile, the last pass
-    ragged or a plain 32-row one; one row or one tile column more runs as the prefill GEMM,
-    which takes 64-row tiles (64x128 or 64x256 by the number of work-groups) up to 128 rows.
-    Accumulators and fp16 bits of every output on both sides of each switch, the visual / text
-    boundary inside a pass."""
+    """33 to 129 rows: the sliced GEMM on few output channels, 64-row tiles of the large-tile GEMM
+    (64x128 or 64x256 by the number of work-groups) on many, which one of the two by estimate.
+    Accumulators and fp16 bits of every output, the visual / text boundary inside a tile."""
     say(f"short prompt T={T} N={N} K={K}")
     rng = np.random.default_rng(T * 7 + N + K)
     xq = rng.integers(-128, 128, size=(T, K), dtype=np.int8)

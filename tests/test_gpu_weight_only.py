@@ -73,12 +73,13 @@ def test_dequantised_weight_bit_exact_through_one_hot_rows(mq):
 
 
 @pytest.mark.parametrize("T,N,K", [
-    (1, 32, 128), (5, 200, 256), (9, 72, 1152), (16, 200, 640), (31, 40, 2176), (32, 136, 384),   # GEMV
-    (33, 64, 128), (64, 136, 384),                          # two GEMV launches
-    (50, 16400, 128),                                       # 64x128 GEMM tiles (many channels)
-    (65, 264, 512), (130, 300, 256),                        # 128x256 tiles; N % 8 != 0 -> 2-byte stores
+    (1, 32, 128), (5, 200, 256), (9, 72, 1152),             # GEMV
+    (16, 200, 640), (31, 40, 2176), (32, 136, 384),         # rows that GEMV and GEMM share by estimate
+    (33, 64, 128), (64, 136, 384),                          # the smallest tiles
+    (50, 16400, 128),                                       # 64x256 tiles (many channels)
+    (65, 264, 512), (130, 300, 256),                        # N % 8 != 0 -> 2-byte stores
     (257, 1000, 640), (300, 520, 1024),
-    (1100, 6200, 256),                                      # many tiles, ragged both ways
+    (1100, 6200, 256),                                      # many 128x256 tiles, ragged both ways
 ])
 def test_linear_matches_oracle(mq, T, N, K):
     rng = np.random.default_rng(T * 7 + N)
@@ -150,8 +151,7 @@ def test_argument_errors_and_empty_inputs(mq):
 
 @pytest.mark.parametrize("tile", [0, 1])
 def test_both_gemm_tiles_on_ragged_shapes(mq, tile):
-    """The dispatcher picks 128x256 or 96x256 from a cost model; force each (the tuning hook of
-    the library) so that both see ragged shapes whatever the model prefers."""
+    """The two tiles that G128_TILE names (256x256 and 96x128), forced, on ragged shapes."""
     mq.tune_set(mq.TUNE_G128_TILE, tile)
     try:
         rng = np.random.default_rng(70 + tile)
@@ -191,6 +191,25 @@ def test_few_rows_in_half_tiles(mq, T, N, K, waves):
     got = yb.cpu().numpy()
     check(got[:, :N], ref, mag, f"few rows {(T, N, K)}")
     assert (got[:, N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("T,N,K,name", [
+    (13, 1003, 128, "w4g128_gemv_kernel<16, 2>"), (20, 1003, 128, "w4g128_gemv_kernel<16, 2>"),
+    (17, 18951, 256, "w4g128_gemv_kernel<8, 1>"), (25, 18951, 256, "w4g128_gemv_kernel<8, 1>"),
+    (32, 16392, 512, "w4g128_gemv_kernel<8, 1>"), (13, 200, 2176, "w4g128_gemm_kernel<1, 1, 3>"),
+])
+def test_rows_between_gemv_and_gemm(mq, T, N, K, name):
+    """13 to 32 rows on both GEMV forms, every result register that can hold a row, and on the GEMM."""
+    rng = np.random.default_rng(T * 13 + N + K)
+    wq, sc = make_weight(rng, N, K)
+    x = (rng.standard_normal((T, K)) * 1.5).astype(np.float16)
+    ref, mag = orc.w4g128_linear(x, wq, sc)
+    wp, xd = mq.w4g128_prepack(dev(pack_int4(wq)), dev(sc)), dev(x)
+    say(f"rows T={T} N={N} K={K}")
+    y = torch.full((T, N), float("nan"), dtype=torch.float16, device="cuda")
+    names = kernels(lambda: mq.w4g128_gemm(xd, wp, N, out=y))
+    check(y.cpu().numpy(), ref, mag, f"rows {(T, N, K)}")
+    assert names == [name], names
 
 
 @pytest.mark.parametrize("shape", range(14))
