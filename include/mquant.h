@@ -422,7 +422,7 @@ int mquant_w4a8_linear_decode_grouped(const void *x_dev, int64_t ldx, int32_t T,
 int mquant_rope_apply(void *x_dev, int64_t ldx, const int32_t *pos_dev, int32_t T,
                       int32_t n_heads, int32_t head_dim, double base, mquant_stream_t stream);
 
-/* Workspace of mquant_aifs_attention: the transposed values and two ints per key tile. */
+/* Workspace of mquant_aifs_attention: room for the transposed values and two ints per key tile (long sequences use it). */
 int64_t mquant_aifs_attention_workspace_bytes(int32_t T, int32_t n_kv_heads, int32_t head_dim);
 
 /*

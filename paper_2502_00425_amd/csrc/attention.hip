@@ -33,16 +33,18 @@ constexpr int kHeadDim = 128;          // the only head size built (28 x 128, 64
 constexpr int kBQ = 128;               // queries per work-group (32 per wave)
 constexpr int kBK = 64;                // keys per tile
 constexpr int kAhead = 4;               // LDS fragment reads in flight ahead of the MFMA that uses them
-constexpr int kKTile = kBK * 2 * kHeadDim;   // a key tile in LDS: 64 rows of 256 bytes
-constexpr int kVTile = kHeadDim * 2 * kBK;   // a V^T tile in LDS: 128 rows (head channels) of 128 bytes
+constexpr int kTileBytes = kBK * 2 * kHeadDim;   // a key or value tile in LDS: 64 rows of 256 bytes
+constexpr int kGroupLds = 4 * kTileBytes;        // two key and two value buffers of one key group
+constexpr int kChunkTiles = 64;                  // tiles whose visibility a wave holds as bit masks, one lane each
 
 // Tiles arrive by LDS-DMA (1 KiB per wave instruction, lane i at offset 16 i), so rows cannot
-// be padded; instead the 16-byte chunks of a row are XOR-swizzled, on the global side of the
-// copy, so that the 16 lanes the LDS serves together (16 consecutive rows, one logical chunk)
-// cover the 64 banks exactly once: key rows are 256 bytes (the full bank space), V^T rows 128.
-// Chunk c of key row r sits at r * 256 + ((c ^ (r & 15)) << 4), chunk c of V^T row d at
-// d * 128 + ((c ^ ((d >> 1) & 7)) << 4).
+// be padded; instead the 16-byte chunks of a row (256 bytes, the full bank space) are XOR-swizzled, on
+// the global side of the copy.  A key fragment is one chunk of 16 consecutive rows at a time: chunk c of
+// row r sits at r * 256 + ((c ^ (r & 15)) << 4).  A value fragment is read transposed
+// (ds_read_b64_tr_b16), 32 lanes covering four rows x 64 bytes: chunk c of row r sits at
+// r * 256 + ((c ^ ((r & 3) << 2)) << 4).  Both cover the 64 banks exactly once.
 
+// V^T tiles (vt_kernel) are 128 rows of 128 bytes: chunk c of row d sits at d * 128 + ((c ^ ((d >> 1) & 7)) << 4).
 // Key order inside the V^T rows: the P V product takes its key index from the score registers
 // (operand slot i of lane group g is key 16 kk + 8 (i / 4) + 4 g + i % 4), so the transpose
 // stores every 16 keys as 0-3, 8-11, 4-7, 12-15 and an operand is one aligned 16-byte chunk.
@@ -195,36 +197,57 @@ __global__ __launch_bounds__(256) void vt_kernel(const __half *__restrict__ v, i
 
 // -------------------------------------------------------------- attention
 //
-// One work-group: 128 queries of one query head, four waves of 32 queries.
-// Per key tile (64 keys, shared through LDS):
+// One work-group: 128 queries of one query head, KG key groups of four waves of 32 queries; key
+// group kg takes every KG-th of the key tiles the work-group needs, and the groups' partial results meet in
+// LDS at the end.  V comes as it is (VT = false, at most 64 key tiles) or transposed by vt_kernel.
+// Per key tile (64 keys, shared by the four waves through LDS):
 //   S^T = K Q^T     A = K rows (keys) from LDS, B = Q^T held in registers for the whole
 //                   kernel; in the result a LANE is a query, its registers are keys, so
 //                   the softmax statistics of a query live in one lane pair
 //   P^T             the same registers, as fp16, are the B operand of
-//   O^T += V^T P^T  A = V^T rows (head channels) from LDS; the result again has a lane per
-//                   query, so the running rescale needs no cross-lane traffic.
+//   O^T += V^T P^T  A = V^T: rows (head channels) of the transposed tile, or read out of the row-major
+//                   one by the transposing LDS read (four keys of a lane's channel); the result again
+//                   has a lane per query, so the running rescale needs no cross-lane traffic.
 // Software pipeline, one tile deep inside a wave: while the exponentials of tile j run on
 // the vector ALU, the matrix core computes the scores of tile j+1 (a second score register
 // set; the two instruction streams are written interleaved and pinned), so of the three
 // parts of a tile -- scores, softmax, P V -- only two are paid in sequence.  Key tiles are
 // therefore fetched one step ahead of value tiles.  Tiles travel global -> LDS by LDS-DMA
-// (no staging registers), two buffers each for K and V^T, one barrier per tile.
+// (no staging registers), two buffers each for K and V, one barrier per tile.
 // Tiles whose smallest position exceeds the group's largest query position are skipped
 // altogether (no loads); a wave skips the arithmetic of a tile that is masked for all of its
-// 32 queries and drops the per-element compare on tiles that are visible to all of them.
-__global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
+// 32 queries and drops the per-element compare on tiles that are visible to all of them.  Which
+// tiles those are is three 64-bit masks per 64 tiles, so that walking them takes scalar arithmetic only
+// (a scalar load per tile for its bounds, in flight across the step, turned the waits for single fragments
+// into waits for everything).
+// What bounds it: at T = 8192 (28 heads on 4, 526 -> 486 us with the masks, flags and pipeline below) matrix and
+// vector pipes, each busy half of the time at a clock that power holds at 1.8 GHz; at T = 1280 (39.8 -> 27.8 us) the
+// longest work-group (20 key tiles: 2.1 us for two tiles of two key groups, of which the matrix products are 1.0)
+// and 8 us that launch, prologue and epilogue take at any T.  Measured without gain: the two key groups half a
+// step apart, so that the P V product of one runs under the exponentials of the other (T = 1280 28.5 -> 30.5 us: a
+// second barrier per step costs more); the first tile requested before the positions have arrived (28.5 ->
+// 29.5); the maximum of the next tile's scores taken under the P V product (T = 8192 +0.7 %); a raised wave priority
+// around either product (-1 .. +1 %).
+typedef __fp16 tr4 __attribute__((vector_size(8)));
+typedef tr4 __attribute__((address_space(3))) *tr4_lds_ptr;
+
+template <int KG, bool VT>
+__global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
     const __half *__restrict__ q, int64_t ldq, const __half *__restrict__ k, int64_t ldk,
-    const __half *__restrict__ vt, int32_t Tp, __half *__restrict__ o, int64_t ldo,
+    const __half *__restrict__ v, int64_t ldv, __half *__restrict__ o, int64_t ldo,
     const int32_t *__restrict__ pos, const int32_t *__restrict__ tile_min,
     const int32_t *__restrict__ tile_max, int32_t T, int32_t group, int32_t n_kv_heads, int32_t n_qblocks,
     int32_t xcds_per_kv, float scale_log2e)
 {
-    __shared__ __attribute__((aligned(1024))) uint8_t k_lds2[2][kKTile];
-    __shared__ __attribute__((aligned(1024))) uint8_t v_lds2[2][kVTile];
-    __shared__ int32_t pos_lds2[2][kBK];
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];       // KG * kGroupLds
+    __shared__ int32_t pos_lds2[KG][2][kBK];
+    __shared__ int32_t bound_lds[2][kChunkTiles];
     __shared__ int32_t wg_qmax_lds[4];
+    static_assert(kHeadDim == 128 && kBK == 64, "addressing below");
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3), kg = KG > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
+    const int tid_g = tid & 255;                           // thread of its key group
     const int l32 = lane & 31, g = lane >> 5;
     // Work-group ids are dealt round-robin to the 8 XCDs, each with its own L2.  When the
     // key/value heads divide the XCDs evenly (xcds_per_kv > 0), an XCD serves ONE key/value
@@ -247,12 +270,69 @@ __global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
     }
     const int32_t kvh = head / group;
     const int32_t q0 = qblock * kBQ + wave * 32;
-    const int32_t n_tiles = Tp / kBK;
+    const int32_t n_tiles = (T + kBK - 1) / kBK;
+
+    // ---- tile copies: 16 blocks of 1 KiB per tile, four per wave.  A copy instruction takes a
+    // wave-uniform base (scalar registers) and a 32-bit offset per lane.
+    const uint8_t *kbase = reinterpret_cast<const uint8_t *>(k + kvh * kHeadDim);
+    const uint8_t *vbase = reinterpret_cast<const uint8_t *>(v + kvh * kHeadDim * (VT ? ldv : 1));
+    const uint32_t lds0 = lds_address(smem) + kg * kGroupLds;
+    const int32_t c_row = wave * 4 + (lane >> 4);          // row of this lane in block 0 (block i: + 16 i)
+    const uint32_t k_chunk = static_cast<uint32_t>(((lane & 15) ^ (c_row & 15)) << 4);
+    const uint32_t v_chunk = static_cast<uint32_t>(((lane & 15) ^ ((c_row & 3) << 2)) << 4);
+    const uint32_t k_pitch = static_cast<uint32_t>(ldk) * 2u, v_pitch = static_cast<uint32_t>(ldv) * 2u;
+    // rows past T repeat the last row (their probabilities are masked to zero)
+    auto dma_k = [&](int32_t t, int b) {
+        const uint8_t *tile = kbase + static_cast<int64_t>(t) * kBK * ldk * 2;
+        const int32_t last = T - 1 - t * kBK;              // last valid row of this tile
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int32_t row = c_row + 16 * i;
+            row = row < last ? row : last;
+            lds_dma16_uniform_base(tile, static_cast<uint32_t>(row) * k_pitch + k_chunk,
+                                   lds0 + b * kTileBytes + (i * 4 + wave) * 1024);
+        }
+    };
+    const int32_t vt_d = wave * 8 + (lane >> 3);           // V^T: head channel of this lane in block 0 (block i: + 32 i)
+    const uint32_t vt_lane = static_cast<uint32_t>(vt_d) * v_pitch + static_cast<uint32_t>(((lane & 7) ^ ((vt_d >> 1) & 7)) << 4);
+    auto dma_v = [&](int32_t t, int b) {
+        if constexpr (VT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                lds_dma16_uniform_base(vbase + (static_cast<int64_t>(i) * 32 * ldv + static_cast<int64_t>(t) * kBK) * 2, vt_lane,
+                                       lds0 + (2 + b) * kTileBytes + (i * 4 + wave) * 1024);
+            return;
+        }
+        const uint8_t *tile = vbase + static_cast<int64_t>(t) * kBK * ldv * 2;
+        const int32_t last = T - 1 - t * kBK;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int32_t row = c_row + 16 * i;
+            row = row < last ? row : last;
+            lds_dma16_uniform_base(tile, static_cast<uint32_t>(row) * v_pitch + v_chunk,
+                                   lds0 + (2 + b) * kTileBytes + (i * 4 + wave) * 1024);
+        }
+    };
 
     // ---- this lane's query: position and Q^T fragments
     const int32_t qi = q0 + l32;
     const int32_t qrow = qi < T ? qi : T - 1;
     const int32_t my_pos = pos[qrow];
+    // Tile bounds of a short sequence: every thread folds consecutive positions, the threads of a
+    // tile meet by lane exchange.
+    constexpr bool own_bounds = !VT;
+    constexpr int PER = kChunkTiles * kBK / (KG * 256);     // positions of a thread
+    constexpr int LPT = kBK / PER;                         // lanes that share a tile
+    int32_t b_lo = INT_MAX, b_hi = INT_MIN;
+    if (own_bounds && tid * PER < T) {                     // tid * PER >= T: beyond the sequence
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int32_t t = tid * PER + i;
+            const int32_t p = pos[t < T ? t : T - 1];
+            b_lo = t < T && p < b_lo ? p : b_lo;
+            b_hi = t < T && p > b_hi ? p : b_hi;
+        }
+    }
     v8h qf[kHeadDim / 16];
     {
         const __half *qp = q + static_cast<int64_t>(qrow) * ldq + head * kHeadDim + g * 8;
@@ -262,13 +342,65 @@ __global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
     }
     int32_t qmin = my_pos, qmax = my_pos;
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
+    for (int m = 16; m >= 1; m >>= 1) {                    // lanes 32.. hold the same queries
         qmin = min(qmin, __shfl_xor(qmin, m, 64));
         qmax = max(qmax, __shfl_xor(qmax, m, 64));
     }
-    if (lane == 0) wg_qmax_lds[wave] = qmax;
+    qmin = __builtin_amdgcn_readfirstlane(qmin);
+    qmax = __builtin_amdgcn_readfirstlane(qmax);
+    if (kg == 0 && lane == 0) wg_qmax_lds[wave] = qmax;
+    if (own_bounds) {
+#pragma unroll
+        for (int m = LPT / 2; m >= 1; m >>= 1) {
+            b_lo = min(b_lo, __shfl_xor(b_lo, m, 64));
+            b_hi = max(b_hi, __shfl_xor(b_hi, m, 64));
+        }
+        if (tid % LPT == 0) {
+            bound_lds[0][tid / LPT] = b_lo;
+            bound_lds[1][tid / LPT] = b_hi;
+        }
+    }
     __syncthreads();
-    const int32_t wg_qmax = max(max(wg_qmax_lds[0], wg_qmax_lds[1]), max(wg_qmax_lds[2], wg_qmax_lds[3]));
+    const int32_t wg_qmax = __builtin_amdgcn_readfirstlane(
+        max(max(wg_qmax_lds[0], wg_qmax_lds[1]), max(wg_qmax_lds[2], wg_qmax_lds[3])));
+
+    // ---- the tiles to walk.  Masks of 64 tiles: needed by the work-group and not yet taken, needed by
+    // this wave, visible as a whole to this wave.
+    uint64_t left, needed, whole;
+    int32_t base = 0;                                      // first tile of the masks
+    auto load_masks = [&]() {
+        const int32_t t = base + lane;
+        const bool in = t < n_tiles;
+        int32_t lo = INT_MAX, hi = INT_MAX;
+        if (own_bounds) {
+            lo = bound_lds[0][lane];
+            hi = bound_lds[1][lane];
+        } else if (in) {
+            lo = tile_min[t];
+            hi = tile_max[t];
+            wait_vmcnt<0>();                               // here, not wherever their registers are used next
+        }
+        left = __ballot(in && lo <= wg_qmax);
+        needed = __ballot(in && lo <= qmax);
+        whole = __ballot(in && hi <= qmin && (t + 1) * kBK <= T);   // a tile with keys past the end is never whole
+    };
+    // Takes `n` tiles off the front; the last of them (n_tiles: none), whether this wave needs it,
+    // whether all its keys are visible to the wave.
+    const int32_t end = n_tiles * 4;
+    auto take = [&](int n) -> int32_t {
+        int bit = 0;
+        for (int i = 0; i < n; ++i) {
+            while (left == 0) {
+                if (!VT || base + kChunkTiles >= n_tiles) return end;
+                base += kChunkTiles;
+                load_masks();
+            }
+            bit = __builtin_ctzll(left);
+            left &= left - 1;
+        }
+        return (base + bit) * 4 + (static_cast<int32_t>(whole >> bit) & 1) * 2 + (static_cast<int32_t>(needed >> bit) & 1);
+    };
+    load_masks();
 
     v16f acc_o[4];
 #pragma unroll
@@ -276,56 +408,46 @@ __global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[dt][r] = 0.0f;
 
-    // ---- tile copies: 16 blocks of 1 KiB per tile, four per wave.  A copy instruction takes a
-    // wave-uniform base (scalar registers) and a 32-bit offset per lane; block i of a wave lies
-    // a fixed stride after block 0, so a lane keeps three offsets in registers and nothing more
-    // (full 64-bit addresses per copy, hoisted out of the loop, spilled to scratch memory).
-    const uint8_t *kbase = reinterpret_cast<const uint8_t *>(k + kvh * kHeadDim);
-    const uint8_t *vbase = reinterpret_cast<const uint8_t *>(vt + static_cast<int64_t>(kvh) * kHeadDim * Tp);
-    const uint32_t k_lds_addr = lds_address(&k_lds2[0][0]), v_lds_addr = lds_address(&v_lds2[0][0]);
-    const int32_t k_row = wave * 4 + (lane >> 4);          // key row of this lane in block 0 (block i: + 16 i)
-    const uint32_t k_chunk = static_cast<uint32_t>(((lane & 15) ^ (k_row & 15)) << 4);
-    const int32_t v_d = wave * 8 + (lane >> 3);            // head channel of this lane in block 0 (block i: + 32 i)
-    const uint32_t v_lane = static_cast<uint32_t>(v_d) * static_cast<uint32_t>(Tp) * 2u +
-                            static_cast<uint32_t>(((lane & 7) ^ ((v_d >> 1) & 7)) << 4);
-    const uint32_t k_pitch = static_cast<uint32_t>(ldk) * 2u;
-    auto dma_k = [&](int32_t t, int b) {                   // rows past T repeat the last row (masked later)
-        const uint8_t *tile = kbase + static_cast<int64_t>(t) * kBK * ldk * 2;
-        const int32_t last = T - 1 - t * kBK;              // last valid row of this tile
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int32_t row = k_row + 16 * i;
-            row = row < last ? row : last;
-            lds_dma16_uniform_base(tile, static_cast<uint32_t>(row) * k_pitch + k_chunk,
-                                   k_lds_addr + b * kKTile + (i * 4 + wave) * 1024);
-        }
-    };
-    auto dma_v = [&](int32_t t, int b) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            lds_dma16_uniform_base(vbase + (static_cast<int64_t>(i) * 32 * Tp + static_cast<int64_t>(t) * kBK) * 2, v_lane,
-                                   v_lds_addr + b * kVTile + (i * 4 + wave) * 1024);
-    };
-    auto key_pos = [&](int32_t t) -> int32_t {             // threads 0..63: position of key tid of tile t
-        const int32_t key = t * kBK + (tid & 63);
+    auto key_pos = [&](int32_t t) -> int32_t {             // threads 0..63 of a key group: position of key tid_g of tile t
+        const int32_t key = t * kBK + (tid_g & 63);
         return key < T ? pos[key] : INT_MAX;
-    };
-    auto next_tile = [&](int32_t t) {                     // first tile >= t the group needs, or n_tiles
-        while (t < n_tiles && tile_min[t] > wg_qmax) ++t;
-        return t;
     };
     // LDS fragments: MFMA i of the score product is (ks, kb) = (i / 2, i % 2), of the P V
     // product (kk, dt) = (i / 4, i % 4); consecutive MFMAs write different accumulators.
-    const int kswz = l32 & 15, vswz = (l32 >> 1) & 7;
-    auto kfrag = [&](const uint8_t *kb_lds, int i) {
-        return *reinterpret_cast<const v8h *>(kb_lds + ((i & 1) * 32 + l32) * 256 + ((((i >> 1) * 2 + g) ^ kswz) << 4));
+    // Operand slot s of lane group g of the P V product is the key that score register s holds there:
+    // 16 kk + 8 (s / 4) + 4 g + s % 4, two transposing reads of four keys.  Such a read takes, per 16
+    // lanes, the four rows' 32 bytes that lanes 4 r .. 4 r + 3 point at and gives lane i the four rows' channel i.
+    const int kswz = l32 & 15;
+    const int tr_row = (lane >> 2) & 3;
+    const uint32_t v_lane = g * 1024 + tr_row * 256 + (tr_row << 6) + (((lane >> 4) & 1) * 2 + ((lane >> 1) & 1)) * 16 + (lane & 1) * 8;
+    typedef const v8h __attribute__((address_space(3))) *v8h_lds_ptr;
+    uint32_t k_at[8], v_at[4];
+    for (int i = 0; i < 8; ++i) {
+        k_at[i] = lds0 + l32 * 256 + (((i * 2 + g) ^ kswz) << 4);
+        asm volatile("" : "+v"(k_at[i]));
+    }
+    auto kfrag = [&](uint32_t kb_lds, int i) {
+        return *(v8h_lds_ptr)(uintptr_t)(k_at[i >> 1] + kb_lds + (i & 1) * 8192);
     };
-    auto vfrag = [&](const uint8_t *vb_lds, int i) {
-        return *reinterpret_cast<const v8h *>(vb_lds + ((i & 3) * 32 + l32) * 128 + ((((i >> 2) * 2 + g) ^ vswz) << 4));
+    const int vswz = (l32 >> 1) & 7;
+    for (int i = 0; i < 4; ++i) {
+        v_at[i] = lds0 + (VT ? l32 * 128 + (((i * 2 + g) ^ vswz) << 4) : v_lane ^ (i << 6));
+        asm volatile("" : "+v"(v_at[i]));
+    }
+    auto vfrag = [&](uint32_t vb_lds, int i) {
+        if constexpr (VT) return *(v8h_lds_ptr)(uintptr_t)(v_at[i >> 2] + vb_lds + (i & 3) * 4096);
+        const uint32_t f = v_at[i & 3] + vb_lds + (i >> 2) * 4096;
+        union {
+            tr4 h[2];
+            v8h f8;
+        } u;
+        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4f16((tr4_lds_ptr)(uintptr_t)f);
+        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4f16((tr4_lds_ptr)(uintptr_t)(f + 2048));
+        return u.f8;
     };
     const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // scores of one tile on their own (first tile; tiles whose predecessor this wave skips)
-    auto scores = [&](const uint8_t *kb_lds, v16f (&s)[2]) {
+    auto scores = [&](uint32_t kb_lds, v16f (&s)[2]) {
         v8h fr[kAhead];
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) fr[i] = kfrag(kb_lds, i);
@@ -352,24 +474,22 @@ __global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
     // buffer par ^ 1) go to s_nxt.  On entry a barrier has published those buffers and freed
     // K buffer par (its scores are done) and V buffer par ^ 1 (its P V product is done).
     int32_t cur, nxt;
-    int32_t kmin_c, kmax_c, kmin_n, kmax_n;               // bounds of the positions of cur and nxt
     auto step = [&](v16f (&s_cur)[2], v16f (&s_nxt)[2], const int par) {
-        const int32_t nn = nxt < n_tiles ? next_tile(nxt + 1) : n_tiles;
-        if (nn < n_tiles) dma_k(nn, par);
-        if (nxt < n_tiles) dma_v(nxt, par ^ 1);
+        const int32_t nn = take(KG);
+        if (nn < end) dma_k(nn >> 2, par);
+        if (nxt < end) dma_v(nxt >> 2, par ^ 1);
         int32_t preg = INT_MAX;
-        if (tid < kBK && nxt < n_tiles) preg = key_pos(nxt);
-        // bounds of nn: requested a whole step before they decide a branch
-        const int32_t nn_c = nn < n_tiles ? nn : 0;
-        const int32_t kmin_nn = tile_min[nn_c], kmax_nn = tile_max[nn_c];
-        const uint8_t *kb_lds = k_lds2[par ^ 1], *vb_lds = v_lds2[par];
-        const int32_t *pos_lds = pos_lds2[par];
-        const bool need_cur = kmin_c <= qmax;              // else: masked for all 32 queries of the wave
-        const bool need_nxt = nxt < n_tiles && kmin_n <= qmax;
-        const bool padded = (cur + 1) * kBK > T;           // tile holds keys past the end
-        if (need_cur) {
+        if (tid_g < kBK && nxt < end) preg = key_pos(nxt >> 2);
+        // Flags held in vector registers: as wave-uniform branches the three ways to the next tile's scores
+        // were merged by copying them, 64 registers every other tile (T = 8192 538 -> 504 us without).
+        int32_t f_cur = cur & 3, f_nxt = nxt & 1;
+        asm("" : "+v"(f_cur), "+v"(f_nxt));
+        const bool need_cur = (f_cur & 1) != 0, need_nxt = f_nxt != 0;
+        const uint32_t kb_lds = (par ^ 1) * kTileBytes, vb_lds = (2 + par) * kTileBytes;
+        const int32_t *pos_lds = pos_lds2[kg][par];
+        if (need_cur) {                                    // else: masked for all 32 queries of the wave
             // ---- mask, online softmax
-            if (kmax_c > qmin || padded) {                 // wave-uniform: some (query, key) pair is hidden
+            if ((f_cur & 2) == 0) {                                  // wave-uniform: some (query, key) pair is hidden
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -420,24 +540,48 @@ __global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
             };
             v8h fr[kAhead];
             if (need_nxt) {
-                // exponentials of this tile interleaved with the score MFMAs of the next one:
-                // one MFMA, its fragment read, two exponentials per group, order pinned
+                // exponentials of this tile interleaved with the score MFMAs of the next one: one MFMA, its
+                // fragment read, two exponentials per group, order pinned.  The exponentials are a
+                // pipeline of their own (multiply-add of pair i + 2, exponentials of pair i + 1, conversion of pair
+                // i: no instruction waits for the one before it; T = 8192 500 -> 490 us).
 #pragma unroll
                 for (int i = 0; i < kAhead; ++i) fr[i] = kfrag(kb_lds, i);
+                __builtin_amdgcn_sched_barrier(0);
+                float x[2][2], y[2][2];
+                float l_two[2] = {0.0f, 0.0f};
+                auto arg = [&](int e) {
+                    x[e & 1][0] = __builtin_fmaf(s_cur[e >> 3][(e & 7) * 2], scale_log2e, neg);
+                    x[e & 1][1] = __builtin_fmaf(s_cur[e >> 3][(e & 7) * 2 + 1], scale_log2e, neg);
+                };
+                auto ex = [&](int e) {
+                    y[e & 1][0] = __builtin_amdgcn_exp2f(x[e & 1][0]);
+                    y[e & 1][1] = __builtin_amdgcn_exp2f(x[e & 1][1]);
+                };
+                arg(0);
+                ex(0);
+                arg(1);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     s_nxt[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[i % kAhead], qf[i >> 1],
                                                                           i < 2 ? zero16 : s_nxt[i & 1], 0, 0, 0);
                     if (i + kAhead < 16) fr[i % kAhead] = kfrag(kb_lds, i + kAhead);
-                    exp_pair(i, neg);
+                    if (i + 1 < 16) ex(i + 1);
+                    v2h ph;
+                    ph[0] = static_cast<_Float16>(y[i & 1][0]);
+                    ph[1] = static_cast<_Float16>(y[i & 1][1]);
+                    p[(i >> 3) * 2 + ((i & 7) >> 2)][(i & 3) * 2] = ph[0];
+                    p[(i >> 3) * 2 + ((i & 7) >> 2)][(i & 3) * 2 + 1] = ph[1];
+                    if (i + 2 < 16) arg(i + 2);
+                    l_two[i & 1] = __builtin_amdgcn_fdot2(ph, v2h{1, 1}, l_two[i & 1], false);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                l_add = l_two[0] + l_two[1];
             } else {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) exp_pair(i, neg_alone);
             }
-            // the first V^T fragments travel while the sums are exchanged
+            // the first V fragments travel while the sums are exchanged
 #pragma unroll
             for (int i = 0; i < kAhead; ++i) fr[i] = vfrag(vb_lds, i);
             __builtin_amdgcn_sched_barrier(0);
@@ -458,53 +602,99 @@ __global__ __launch_bounds__(256, 2) void aifs_attention_kernel(
         } else if (need_nxt) {
             scores(kb_lds, s_nxt);
         }
-        if (tid < kBK) pos_lds2[par ^ 1][tid] = preg;
-        wait_vmcnt<0>();                                   // K of nn and V^T of nxt have landed
+        if (tid_g < kBK) pos_lds2[kg][par ^ 1][tid_g] = preg;
+        wait_vmcnt<0>();                                   // K of nn and V of nxt have landed
         __syncthreads();
         cur = nxt;
         nxt = nn;
-        kmin_c = kmin_n, kmax_c = kmax_n;
-        kmin_n = kmin_nn, kmax_n = kmax_nn;
     };
 
-    // ---- prologue: first tile's keys, values and positions, second tile's keys
-    cur = next_tile(0);                                    // exists: every token sees itself
-    nxt = cur < n_tiles ? next_tile(cur + 1) : n_tiles;
-    if (cur < n_tiles) {
-        dma_k(cur, 0);
-        dma_v(cur, 0);
-        if (nxt < n_tiles) dma_k(nxt, 1);
-        if (tid < kBK) pos_lds2[0][tid] = key_pos(cur);
-    }
-    {
-        const int32_t c = cur < n_tiles ? cur : 0, n = nxt < n_tiles ? nxt : 0;
-        kmin_c = tile_min[c], kmax_c = tile_max[c];
-        kmin_n = tile_min[n], kmax_n = tile_max[n];
+    // ---- prologue: first tile's keys, values and positions, second tile's keys.  With two key
+    // groups the sequence has at most 64 tiles and the first group's share, the larger one, counts the steps.
+    static_assert(KG == 1 || KG == 2, "steps");
+    int32_t steps = KG == 1 ? 0 : (__builtin_popcountll(left) + KG - 1) / KG;
+    cur = take(kg + 1);                                    // group 0: exists, every token sees itself
+    nxt = cur < end ? take(KG) : end;
+    if (cur < end) {
+        dma_k(cur >> 2, 0);
+        dma_v(cur >> 2, 0);
+        if (nxt < end) dma_k(nxt >> 2, 1);
+        if (tid_g < kBK) pos_lds2[kg][0][tid_g] = key_pos(cur >> 2);
     }
     wait_vmcnt<0>();
     __syncthreads();
     v16f s_a[2], s_b[2];
-    if (cur < n_tiles && kmin_c <= qmax) scores(k_lds2[0], s_a);
+    if ((cur & 1) != 0) scores(0, s_a);
     __syncthreads();                                       // K buffer 0 is free for the third tile
-    while (cur < n_tiles) {
+    while (KG == 1 ? cur < end : steps > 0) {
         step(s_a, s_b, 0);
-        if (cur >= n_tiles) break;
+        if (KG == 1 ? cur >= end : --steps == 0) break;
         step(s_b, s_a, 1);
+        --steps;
     }
 
     // ---- normalise and store: lane = query, registers = head channels (4 consecutive per group)
-    if (qi < T) {
-        const float inv_l = 1.0f / l_run;                  // every token sees at least itself
-        __half *orow = o + static_cast<int64_t>(qi) * ldo + head * kHeadDim;
+    __half *orow = o + static_cast<int64_t>(qi) * ldo + head * kHeadDim;
+    auto store4 = [&](int dt, int r4, const float (&f)[4]) {
+        __half h[4];
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+        for (int e = 0; e < 4; ++e) h[e] = __float2half_rn(f[e]);
+        *reinterpret_cast<uint2 *>(orow + dt * 32 + r4 * 8 + g * 4) = *reinterpret_cast<const uint2 *>(h);
+    };
+    if constexpr (KG == 1) {
+        if (qi < T) {
+            const float inv_l = 1.0f / l_run;              // every token sees at least itself
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    float f[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[e] = acc_o[dt][r4 * 4 + e] * inv_l;
+                    store4(dt, r4, f);
+                }
+        }
+    } else {
+        // The two key groups of a query exchange halves of the channels: group kg finishes channels
+        // 64 kg .. 64 kg + 63.  The last barrier of the loop has freed the tile buffers.
+        float *xch = reinterpret_cast<float *>(smem);      // [8 waves][34][64]
+        float *mine = xch + (kg * 4 + wave) * (34 * 64) + lane;
+        const float *theirs = xch + ((kg ^ 1) * 4 + wave) * (34 * 64) + lane;
+        auto give = [&](const v16f &a, const v16f &b) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                mine[r * 64] = a[r];
+                mine[(16 + r) * 64] = b[r];
+            }
+        };
+        if (kg == 0) give(acc_o[2], acc_o[3]);
+        else give(acc_o[0], acc_o[1]);
+        mine[32 * 64] = m_ref;
+        mine[33 * 64] = l_run;
+        __syncthreads();
+        const float m_o = theirs[32 * 64], l_o = theirs[33 * 64];
+        const float m = fmaxf(m_ref, m_o);                 // finite: one of the groups has the token itself
+        const float a = m_ref == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_ref - m) * scale_log2e);
+        const float b = m_o == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_o - m) * scale_log2e);
+        const float inv_l = 1.0f / (l_run * a + l_o * b);
+        auto finish = [&](int dt, const v16f &acc, const float *other) {
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                __half h[4];
+                float f[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = __float2half_rn(acc_o[dt][r4 * 4 + e] * inv_l);
-                *reinterpret_cast<uint2 *>(orow + dt * 32 + r4 * 8 + g * 4) = *reinterpret_cast<const uint2 *>(h);
+                for (int e = 0; e < 4; ++e) f[e] = (acc[r4 * 4 + e] * a + other[(r4 * 4 + e) * 64] * b) * inv_l;
+                store4(dt, r4, f);
             }
+        };
+        if (qi < T) {
+            if (kg == 0) {
+                finish(0, acc_o[0], theirs);
+                finish(1, acc_o[1], theirs + 16 * 64);
+            } else {
+                finish(2, acc_o[2], theirs);
+                finish(3, acc_o[3], theirs + 16 * 64);
+            }
+        }
     }
 }
 
@@ -517,6 +707,34 @@ int check_heads(int32_t T, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_d
 }
 
 int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
+
+// Whether rows [T][w] of one array share no byte with rows [T][wo] of another: ranges apart, or column
+// slices of one buffer side by side.
+bool apart(const void *a, int64_t lda, int64_t w, const void *b, int64_t ldb, int64_t wb, int32_t T)
+{
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    if (a0 + (static_cast<uint64_t>(T - 1) * lda + w) * 2 <= b0 || b0 + (static_cast<uint64_t>(T - 1) * ldb + wb) * 2 <= a0) return true;
+    if (lda != ldb) return false;
+    const uint64_t pitch = lda * 2;
+    const uint64_t d = b0 >= a0 ? (b0 - a0) % pitch : (pitch - (a0 - b0) % pitch) % pitch;   // b's first column behind a's
+    return d >= static_cast<uint64_t>(w) * 2 && d + wb * 2 <= pitch;
+}
+
+template <int KG, bool VT>
+int launch_attention(const __half *q, int64_t ldq, const __half *k, int64_t ldk, const __half *v, int64_t ldv,
+                     __half *o, int64_t ldo, const int32_t *pos, const int32_t *tile_min, const int32_t *tile_max,
+                     int32_t T, int32_t group, int32_t n_kv_heads, int64_t groups, int32_t xcds_per_kv,
+                     float scale_log2e, hipStream_t stream)
+{
+    constexpr int lds = KG * kGroupLds;
+    static_assert(8 * 34 * 64 * 4 <= 2 * kGroupLds, "exchange of the key groups");
+    auto kern = aifs_attention_kernel<KG, VT>;
+    static LdsLimit limit;
+    if (const int st = limit.raise(reinterpret_cast<const void *>(kern), lds); st != MQUANT_OK) return st;
+    MQ_LAUNCH(kern, dim3(static_cast<unsigned>(groups)), dim3(KG * 256), lds, stream, q, ldq, k, ldk, v, ldv, o, ldo,
+              pos, tile_min, tile_max, T, group, n_kv_heads, static_cast<int32_t>(ceil_div(T, kBQ)), xcds_per_kv, scale_log2e);
+    return launch_status();
+}
 
 }  // namespace
 
@@ -580,26 +798,42 @@ extern "C" int mquant_aifs_attention(const void *q, int64_t ldq, const void *k, 
     if (!aligned_to(workspace, 256)) return MQUANT_ERR_ALIGNMENT;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
 
-    const int32_t Tp = static_cast<int32_t>(round_up(T, kBK));
-    const int32_t n_tiles = Tp / kBK;
-    __half *vt = static_cast<__half *>(workspace);
-    int32_t *tile_min = reinterpret_cast<int32_t *>(
-        static_cast<uint8_t *>(workspace) + round_up(kw * Tp * 2, 256));
-    int32_t *tile_max = tile_min + n_tiles;
-    MQ_LAUNCH(vt_kernel, dim3(n_tiles, static_cast<unsigned>(ceil_div(kw, 64))), dim3(256), 0, stream,
-              static_cast<const __half *>(v), ldv, vt, T, Tp, static_cast<int32_t>(kw), pos, tile_min,
-              tile_max);
-    int ls = launch_status();
-    if (ls != MQUANT_OK) return ls;
-    const float scale_log2e = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(head_dim)));
+    const int32_t n_tiles = static_cast<int32_t>(ceil_div(T, kBK));
     const int64_t n_qblocks = ceil_div(T, kBQ);
     const int32_t group = n_q_heads / n_kv_heads;
     const int32_t xcds_per_kv = 8 % n_kv_heads == 0 ? 8 / n_kv_heads : 0;
     const int64_t groups = xcds_per_kv > 0 ? 8 * ceil_div(n_qblocks * group, xcds_per_kv) : n_qblocks * n_q_heads;
     if (groups > 0x7fffffff) return MQUANT_ERR_UNSUPPORTED;
-    MQ_LAUNCH(aifs_attention_kernel, dim3(static_cast<unsigned>(groups)), dim3(256),
-              0, stream, static_cast<const __half *>(q), ldq, static_cast<const __half *>(k), ldk, vt, Tp,
-              static_cast<__half *>(o), ldo, pos, tile_min, tile_max, T, group, n_kv_heads,
-              static_cast<int32_t>(n_qblocks), xcds_per_kv, scale_log2e);
-    return launch_status();
+    const __half *qh = static_cast<const __half *>(q), *kh = static_cast<const __half *>(k), *vh = static_cast<const __half *>(v);
+    __half *oh = static_cast<__half *>(o);
+    const float scale_log2e = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(head_dim)));
+    // Values in place or transposed first (a launch of its own, 2 to 5 us, whose tiles the P V product then reads with
+    // half the LDS instructions: 2 % of a long sequence's time).  The line lies where the two meet: transposed / in
+    // place, 28 heads, T = 1280 35.7 / 33.6 us, 2048 55.1 / 53.0, 3500 115.2 / 114.0, 4096 138.8 / 140.2; 64 heads, T = 1280
+    // 47.6 / 44.3, 2048 87.4 / 85.1, 2500 136.5 / 138.0, 3500 238.9 / 241.5.  In place also needs an output that shares no memory
+    // with V, which every work-group reads until the last has finished, and rows close enough for 32-bit offsets.
+    const int64_t items = n_qblocks * n_q_heads;
+    if (items * n_tiles <= 48000 && n_tiles <= kChunkTiles && ldv < int64_t{1} << 24 && apart(v, ldv, kw, o, ldo, qw, T)) {
+        // Two key groups, one work-group per compute unit, where the work-groups are few: the longest one, which
+        // walks all key tiles, is what such a launch waits for.  One / two groups, 28 heads (T, work-groups): 77, 28
+        // 8.3 / 8.5 us; 256, 56 11.9 / 12.0; 512, 112 16.6 / 15.9; 1003, 224 27.5 / 24.1; 1280, 280 33.6 / 27.8; 1408, 308
+        // 37.7 / 34.6; 1792, 392 46.2 / 44.1; 2048, 448 53.0 / 50.1; 2500, 560 70.8 / 79.6; 64 heads: 512, 256 17.0 / 16.3; 640,
+        // 320 22.9 / 24.7; 1003, 512 33.5 / 40.1.  Beyond one round of work-groups it takes long ones to make up for the
+        // second prologue.
+        const bool two = n_tiles > 4 && (items <= kNumCU + kNumCU / 8 || (items <= 2 * kNumCU - kNumCU / 4 && n_tiles >= 22));
+        auto launch = two ? launch_attention<2, false> : launch_attention<1, false>;
+        return launch(qh, ldq, kh, ldk, vh, ldv, oh, ldo, pos, nullptr, nullptr, T, group, n_kv_heads, groups, xcds_per_kv,
+                      scale_log2e, stream);
+    }
+    const int32_t Tp = n_tiles * kBK;
+    __half *vt = static_cast<__half *>(workspace);
+    int32_t *tile_min = reinterpret_cast<int32_t *>(
+        static_cast<uint8_t *>(workspace) + round_up(kw * Tp * 2, 256));
+    int32_t *tile_max = tile_min + n_tiles;
+    MQ_LAUNCH(vt_kernel, dim3(n_tiles, static_cast<unsigned>(ceil_div(kw, 64))), dim3(256), 0, stream, vh, ldv, vt, T, Tp,
+              static_cast<int32_t>(kw), pos, tile_min, tile_max);
+    const int ls = launch_status();
+    if (ls != MQUANT_OK) return ls;
+    return launch_attention<1, true>(qh, ldq, kh, ldk, vt, Tp, oh, ldo, pos, tile_min, tile_max, T, group, n_kv_heads, groups,
+                                     xcds_per_kv, scale_log2e, stream);
 }

@@ -235,6 +235,55 @@ def test_attention_every_key_tile_is_visible_on_the_config_layouts(mq, name, T, 
     assert (ref == 0).any() and (ref > 1e-3).any()
 
 
+# Lengths around a tile, a query block and the 64 tiles whose visibility the kernel keeps as bit masks,
+# on head counts that take one key group, two, and the transposed values.
+@pytest.mark.parametrize("T,spans,Hq,Hkv,route", [
+    (63, [(5, 40)], 3, 1, "aifs_attention_kernel<1, false>"),
+    (256, [(0, 65)], 2, 1, "aifs_attention_kernel<1, false>"),
+    (257, [(0, 65)], 2, 1, "aifs_attention_kernel<2, false>"),       # early blocks: one key group without a tile
+    (1153, [(100, 800)], 28, 4, "aifs_attention_kernel<2, false>"),  # 280 work-groups
+    (2049, [(100, 1800)], 14, 2, "aifs_attention_kernel<2, false>"),
+    (513, [(100, 70), (300, 129)], 64, 8, "aifs_attention_kernel<1, false>"),
+    (640, [(64, 512)], 65, 5, "aifs_attention_kernel<1, false>"),
+    (4096, [(700, 1500)], 1, 1, "aifs_attention_kernel<2, false>"),
+    (4097, [(700, 1500)], 1, 1, "aifs_attention_kernel<1, true>"),   # a 65th tile of one key
+])
+def test_attention_routes(mq, T, spans, Hq, Hkv, route):
+    say(f"attention route T={T} heads={Hq}/{Hkv}")
+    rng = np.random.default_rng(T)
+    q, k, v = make_qkv(rng, T, Hq, Hkv, q_gain=0.5)
+    perm, _, V = orc.aifs_build_perm(T, spans)
+    rows = np.unique(np.r_[0, 1, min(127, T - 1), min(128, T - 1), V - 1, V, T - 2, T - 1, rng.choice(T, 24)])
+    check_attention(mq, q[perm], k[perm], v[perm], perm, Hq, Hkv, rows=rows, what=f"T={T} {route}")
+    qd, kd, vd, pd = dev(q), dev(k), dev(v), dev(perm.astype(np.int32))
+    assert kernels(lambda: mq.aifs_attention(qd, kd, vd, pd, Hq, Hkv))[-1] == route
+
+
+def test_attention_output_in_the_memory_of_v(mq):
+    """o may be v itself, or share bytes with it: V then goes through the workspace.  Column slices of one
+    buffer side by side share none."""
+    say("attention o over v")
+    rng = np.random.default_rng(13)
+    T, H, D = 150, 2, 128
+    q, k, v = make_qkv(rng, T, H, H, q_gain=0.5)
+    perm, _, _ = orc.aifs_build_perm(T, [(20, 90)])
+    perm32 = dev(perm.astype(np.int32))
+    want = mq.aifs_attention(dev(q), dev(k), dev(v), perm32, H, H).cpu().numpy()
+    buf = torch.zeros((T + 1, 4 * H * D), dtype=torch.float16, device="cuda")
+    w = H * D
+    for at, o_at, name in ((0, 0, "true"), (w, w + 64, "true"), (w, w - 64, "true"), (0, w, "false"), (w, 0, "false"),
+                           (0, 3 * w, "false")):
+        vv, oo = buf[:T, at:at + w], buf[:T, o_at:o_at + w]
+        vv.copy_(dev(v))
+        qd, kd = dev(q), dev(k)
+        run = kernels(lambda: mq.aifs_attention(qd, kd, vv, perm32, H, H, out=oo))
+        assert run[-1].endswith(f"{name}>"), (at, o_at, run)
+        vv.copy_(dev(v))
+        mq.aifs_attention(qd, kd, vv, perm32, H, H, out=oo)
+        err = np.abs(oo.cpu().numpy().astype(np.float64) - want.astype(np.float64))
+        assert (err <= 2.0 ** -9 * (np.abs(want) + 1.0)).all(), (at, o_at)
+
+
 def test_attention_argument_errors(mq):
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     pos = torch.zeros(4, dtype=torch.int32, device="cuda")
