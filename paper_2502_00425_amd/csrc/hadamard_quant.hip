@@ -3,11 +3,13 @@
 // absmax statistic used to calibrate the static scales (Algorithm 1).
 //
 // One wavefront owns 512 contiguous channels of one row (1024 when the block
-// is 1024): lane l holds channels 8l..8l+7, so index bits 0-2 live in a lane's
+// is 1024): a lane loads eight contiguous channels, so index bits 0-2 live in a lane's
 // registers and bits 3-8 across the 64 lanes.  The butterflies run in the fixed
 // stage order h = 1, 2, 4, ..., B/2, one fp32 add or subtract each, which is
-// what makes the int8 codes reproducible bit for bit.  The kernel is bound by
-// HBM traffic: 2 bytes read and 1 byte written per element.
+// what makes the int8 codes reproducible bit for bit.  HBM traffic is 2 bytes read and
+// 1 byte written per element; what bounds the kernel is the issue of vector instructions
+// (113 per segment and about 45 once per wave; T = 4096, K = 18944 52 -> 49 us, 4.75 TB/s, with
+// the exchanged stages of hadamard_segment.h and two rows to a wave).
 #include <hip/hip_fp16.h>
 #include <math.h>
 
@@ -33,14 +35,29 @@ __global__ __launch_bounds__(256) void hadamard_quant_kernel(
     float wave_max = 0.0f;
 
     if (sidx < segs_per_row) {                            // wave-uniform
-        for (int32_t i = blockIdx.y; i < T; i += gridDim.y) {
+        using Seg = Segment<B>;
+        auto row_of = [&](int32_t i) -> const __half * {
             int32_t src = i;
             if (perm != nullptr) {
                 src = perm[i];
                 src = (src < 0 || src >= T) ? 0 : src;
             }
-            Segment<B> sg;
-            sg.load_rotate(x + static_cast<int64_t>(src) * ldx, sidx, K, lane);
+            return x + static_cast<int64_t>(src) * ldx;
+        };
+        uint4 raw[Seg::C];
+        bool in_range[Seg::C];
+        auto request = [&](const __half *row) {
+#pragma unroll
+            for (int c = 0; c < Seg::C; ++c) raw[c] = Seg::template load_chunk<(B >= 512)>(row, sidx, c, K, lane, in_range[c]);
+        };
+        const int32_t step = gridDim.y;
+        if (static_cast<int32_t>(blockIdx.y) < T) request(row_of(blockIdx.y));
+        for (int32_t i = blockIdx.y; i < T; i += step) {
+            Seg sg;
+#pragma unroll
+            for (int c = 0; c < Seg::C; ++c) sg.set_chunk(c, raw[c], in_range[c]);
+            if (i + step < T) request(row_of(i + step));   // under the arithmetic of this row
+            sg.rotate(lane);
             if constexpr (ABSMAX) {
                 wave_max = sg.absmax(wave_max);
             } else {
@@ -119,7 +136,13 @@ int launch(const void *x, int64_t ldx, const int32_t *perm, int8_t *xq, int32_t 
 {
     const int32_t seg = B > 512 ? B : 512;
     const int32_t segs_per_row = static_cast<int32_t>(ceil_div(K, seg));
-    const dim3 grid(static_cast<unsigned>(ceil_div(segs_per_row, 4)), static_cast<unsigned>(T < 65535 ? T : 65535)),
+    // Two rows to a wave where there are more waves than the compute units hold at a time (8 per SIMD): the second
+    // row's segment is on its way while the first is rotated.  One / two rows, K = 3584: T = 77 2.3 / 2.7 us, 1280
+    // 6.2 / 5.9, 4096 12.7 / 12.7; K = 18944: T = 77 3.4 / 3.7, 1280 19.0 / 18.3, 4096 51.0 / 48.9; B = 128: T = 16384, K = 8192
+    // 81.2 / 77.6; B = 1024, whose segments are twice as long: T = 4096, K = 8192 22.7 / 23.8.  Four rows gain nothing more.
+    const int64_t rows = B < 1024 && static_cast<int64_t>(T) * segs_per_row > 8 * 4 * kNumCU ? ceil_div(T, 2) : T;
+    const int64_t gy = rows < 65535 ? rows : 65535;
+    const dim3 grid(static_cast<unsigned>(ceil_div(segs_per_row, 4)), static_cast<unsigned>(gy)),
         block(256);
     const __half *xh = static_cast<const __half *>(x);
     const float q_hi = static_cast<float>((1 << (bits - 1)) - 1), q_lo = -static_cast<float>(1 << (bits - 1));

@@ -3,12 +3,19 @@
 // kernels and by the decode kernel that rotates and quantizes its own input.
 //
 // One wavefront owns 512 contiguous channels of one row (1024 when the block
-// is 1024): lane l holds channels 8l..8l+7, so index bits 0-2 live in a lane's
+// is 1024): a lane loads eight contiguous channels, so index bits 0-2 live in a lane's
 // registers and bits 3-8 across the 64 lanes.  The butterflies run in the fixed
 // stage order h = 1, 2, 4, ..., B/2, one fp32 add or subtract each, which is
 // what makes the int8 codes reproducible bit for bit.  After load_rotate the registers
 // of some lanes hold the exact negative of the rotated value (lane_sign_bit); absmax
 // does not care and quant_store folds the sign into its multiplier.
+//
+// What bounds it is the issue of vector instructions, so a stage has to cost the eight it
+// cannot do without: lanes are numbered so that each stage's partner is one DPP pattern
+// away (channel_lane), the stages across rows leave the exchanged registers where they
+// are (quant_store knows where), and the first stage converts from fp16 as it adds: 80
+// instructions for the nine stages where a plain numbering with registers put back took 96 and the
+// conversion 8 more.
 #pragma once
 
 #include <hip/hip_fp16.h>
@@ -17,12 +24,30 @@
 
 namespace mquant {
 
+// The eight channels of a lane: channels 8 c .. 8 c + 7 of the wave's 512, c = channel_lane(lane).
+// Partner lanes of the stages h = 8, 16, 32, 64 are c ^ 1, 2, 4, 8.  Of the lane exchanges
+// inside a row of 16, DPP has lane ^ 1 and lane ^ 2 (quad permute), lane ^ 7 (half mirror) and
+// lane ^ 8 (rotate), but not lane ^ 4: with the two low bits of c inverted in the lanes that have bit
+// 2 set, c ^ 4 is lane ^ 7.
+__device__ __forceinline__ int channel_lane(int lane) { return lane ^ ((lane & 4) ? 3 : 0); }
+
+// Bit b of the channel lane as a sign bit.
+__device__ __forceinline__ uint32_t channel_sign(int lane, int b)
+{
+    return (static_cast<uint32_t>(channel_lane(lane)) << (31 - b)) & 0x80000000u;
+}
+
+// Whether the stages across rows leave registers and lanes exchanged (see lane_stage).  With two chunks a
+// wave's stores, twice as many then, cost more than the swaps back (B = 1024, 4096 x 8192 23.2 / 23.6 us).
+template <int B>
+constexpr bool kExchanged = B == 256 || B == 512;
+
+// Stages h = 2 and 4 inside the lane's eight contiguous channels (h = 1: Segment::set_chunk).
 template <int B>
 __device__ __forceinline__ void register_stages(float (&v)[8])
 {
-    // h = 1, 2, 4 inside the lane's eight contiguous channels.
 #pragma unroll
-    for (int h = 1; h < 8 && h < B; h <<= 1) {
+    for (int h = 2; h < 8 && h < B; h <<= 1) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             if ((j & h) == 0) {
@@ -35,15 +60,18 @@ __device__ __forceinline__ void register_stages(float (&v)[8])
 }
 
 // Lanes whose values carry a minus sign after the in-row stages (see lane_stage): the
-// parity of the lane-index bits those stages paired on.
+// parity of the channel-lane bits those stages paired on.
 template <int B>
 __device__ __forceinline__ uint32_t lane_sign_bit(int lane)
 {
-    constexpr int bits = B >= 128 ? 15 : (B >= 64 ? 7 : (B >= 32 ? 3 : (B >= 16 ? 1 : 0)));
-    return (__builtin_popcount(lane & bits) & 1) ? 0x80000000u : 0u;
+    uint32_t s = 0u;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+        if (B >= (16 << b)) s ^= channel_sign(lane, b);
+    return s;
 }
 
-// v[j] += c * (v[j] of lane ^ M) for the eight registers of a lane, one instruction per
+// v[j] += c * (v[j] of the lane whose channel lane is ^ M) for the eight registers of a lane, one instruction per
 // register: the DPP operand of v_fmac_f32 fetches the partner lane's value.  c is +-1, so
 // the product is exact and the result is the correctly rounded sum or difference, as a
 // separate add would give.  A DPP operand must not be read within two wait states of the
@@ -65,7 +93,7 @@ __device__ __forceinline__ uint32_t lane_sign_bit(int lane)
                  : "v"(c))
 
 template <int M>
-__device__ __forceinline__ void fmac_lane_xor(float (&v)[8], float c)
+__device__ __forceinline__ void fmac_partner(float (&v)[8], float c)
 {
     static_assert(M == 1 || M == 2 || M == 4 || M == 8, "in-row distance");
     if constexpr (M == 1) {
@@ -75,35 +103,7 @@ __device__ __forceinline__ void fmac_lane_xor(float (&v)[8], float c)
     } else if constexpr (M == 8) {
         MQ_FMAC8("row_ror:8");
     } else {
-        // i -> 7 - i inside each group of 8 into temporaries, then the quad reversed as the
-        // DPP operand of the multiply-add: i -> i ^ 4
-        float t[8];
-        asm volatile("s_nop 1\n\t"
-                     "v_mov_b32_dpp %0, %8 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %1, %9 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %2, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %3, %11 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %4, %12 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %5, %13 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %6, %14 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-                     "v_mov_b32_dpp %7, %15 row_half_mirror row_mask:0xf bank_mask:0xf"
-                     : "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3]), "=&v"(t[4]), "=&v"(t[5]),
-                       "=&v"(t[6]), "=&v"(t[7])
-                     : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]),
-                       "v"(v[7]));
-        asm volatile("s_nop 1\n\t"
-                     "v_fmac_f32_dpp %0, %8, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %1, %9, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %2, %10, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %3, %11, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %4, %12, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %5, %13, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %6, %14, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f32_dpp %7, %15, %16 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf"
-                     : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]),
-                       "+v"(v[6]), "+v"(v[7])
-                     : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]),
-                       "v"(t[7]), "v"(c));
+        MQ_FMAC8("row_half_mirror");
     }
 }
 #undef MQ_FMAC8
@@ -113,7 +113,7 @@ __device__ __forceinline__ void lane_stage(float (&v)[8], int lane)
 {
     if constexpr (8 * M < B) {
         if constexpr (M < 16) {
-            // Butterfly between lane l (lower index, bit M clear) and l ^ M: the lower lane
+            // Butterfly between channel lane l (lower index, bit M clear) and l ^ M: the lower lane
             // must end with a + b, the upper one with a - b, a being the lower lane's value.
             // Each lane computes mine + c * other with c = +1 (lower) or -1 (upper): the
             // lower lane gets a + b, the upper lane b - a = -(a - b).  The minus sign is
@@ -122,16 +122,17 @@ __device__ __forceinline__ void lane_stage(float (&v)[8], int lane)
             // symmetric), both partners of a later stage carry the same sign, and the
             // quantizer multiplies by a constant whose sign is flipped for those lanes
             // (lane_sign_bit).  One instruction per element and stage.
-            const float c = (lane & M) ? -1.0f : 1.0f;
-            fmac_lane_xor<M>(v, c);
+            const float c = __uint_as_float(0x3f800000u | channel_sign(lane, M == 1 ? 0 : M == 2 ? 1 : M == 4 ? 2 : 3));
+            fmac_partner<M>(v, c);
         } else {
             // Partner lanes sit in different rows (M = 16) or wave halves (M = 32).
             // The row / half swap instructions exchange the odd rows (upper half)
             // of one register with the even rows (lower half) of another: applied to
             // (v[j], v[j+4]) it leaves every lane with a complete pair (a, b) -- the
             // lower-index lanes for register j, the upper-index lanes for j+4 --
-            // so each lane does one add and one subtract, and the same swap puts the
-            // results back where they belong.  No select, no LDS.
+            // so each lane does one add and one subtract.  That has exchanged register bit 2 with
+            // the lane bit, and so it stays (kExchanged): the next stage swaps again, the store knows
+            // where channels have gone.  No select, no LDS.
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int lo = __float_as_int(v[j]), hi = __float_as_int(v[j + 4]);
@@ -145,15 +146,19 @@ __device__ __forceinline__ void lane_stage(float (&v)[8], int lane)
                     a = __int_as_float(sw[0]);
                     b = __int_as_float(sw[1]);
                 }
-                const int p = __float_as_int(a + b), q = __float_as_int(a - b);
-                if constexpr (M == 16) {
-                    const auto sw = __builtin_amdgcn_permlane16_swap(p, q, false, false);
-                    v[j] = __int_as_float(sw[0]);
-                    v[j + 4] = __int_as_float(sw[1]);
-                } else {
-                    const auto sw = __builtin_amdgcn_permlane32_swap(p, q, false, false);
-                    v[j] = __int_as_float(sw[0]);
-                    v[j + 4] = __int_as_float(sw[1]);
+                v[j] = a + b;
+                v[j + 4] = a - b;
+                if constexpr (!kExchanged<B>) {
+                    const int p = __float_as_int(v[j]), q = __float_as_int(v[j + 4]);
+                    if constexpr (M == 16) {
+                        const auto sw = __builtin_amdgcn_permlane16_swap(p, q, false, false);
+                        v[j] = __int_as_float(sw[0]);
+                        v[j + 4] = __int_as_float(sw[1]);
+                    } else {
+                        const auto sw = __builtin_amdgcn_permlane32_swap(p, q, false, false);
+                        v[j] = __int_as_float(sw[0]);
+                        v[j + 4] = __int_as_float(sw[1]);
+                    }
                 }
             }
         }
@@ -173,7 +178,9 @@ __device__ __forceinline__ void lane_stages(float (&v)[8], int lane)
 }
 
 // One wave segment: SEG = max(B, 512) consecutive channels of one row, C = SEG/512
-// chunks of 512, 8 channels per lane and chunk.  Loads fp16, rotates in fp32.
+// chunks of 512, 8 channels per lane and chunk.  Loads fp16, rotates in fp32.  Whether a lane's channels are
+// inside the row does not change when the swaps exchange lanes: K is a multiple of B, and lanes that swap
+// belong to one block.
 template <int B>
 struct Segment {
     static constexpr int C = B > 512 ? B / 512 : 1;
@@ -181,28 +188,39 @@ struct Segment {
     float v[C][8];
     bool valid[C];
 
-    // The 16 bytes (8 fp16 channels) of chunk c of segment sidx that this lane owns; zeros past K.
+    // The 16 bytes (8 fp16 channels) of chunk c of segment sidx that this lane owns; zeros past K.  WHOLE: the
+    // caller knows that the segment is all there (B >= 512 divides K).  Behind the test for it the load stays
+    // where it was written: without, the compiler moves it into the branch that uses it, behind whatever
+    // loads were to follow it (one-launch decode linear, 3584 -> 3584 3.6 -> 4.4 us).
+    template <bool WHOLE = false>
     static __device__ __forceinline__ uint4 load_chunk(const __half *row, int32_t sidx, int c, int32_t K,
                                                        int lane, bool &in_range)
     {
-        const int32_t k0 = sidx * SEG + c * 512 + lane * 8;
-        in_range = k0 < K;
+        const int32_t k0 = sidx * SEG + c * 512 + channel_lane(lane) * 8;
+        in_range = WHOLE || k0 < K;
         return in_range ? *reinterpret_cast<const uint4 *>(row + k0) : make_uint4(0u, 0u, 0u, 0u);
     }
 
+    // Converts to fp32, with the stage h = 1: the mixed-precision multiply-add by +-1 takes the two fp16
+    // channels of a dword as they are, and one rounding of the exact sum is the fp32 add of the converted values.
     __device__ __forceinline__ void set_chunk(int c, const uint4 raw, bool in_range)
     {
         valid[c] = in_range;
-        const __half2 *h2 = reinterpret_cast<const __half2 *>(&raw);
+        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float2 f = __half22float2(h2[j]);
-            v[c][2 * j] = f.x;
-            v[c][2 * j + 1] = f.y;
+            if constexpr (B > 1) {
+                asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(v[c][2 * j]) : "v"(w[j]));
+                asm("v_fma_mix_f32 %0, %1, -1.0, %1 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(v[c][2 * j + 1]) : "v"(w[j]));
+            } else {
+                const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&w[j]));
+                v[c][2 * j] = f.x;
+                v[c][2 * j + 1] = f.y;
+            }
         }
     }
 
-    // All stages h = 1 ... B/2 on the chunks set before.
+    // The stages h = 2 ... B/2 on the chunks set before.
     __device__ __forceinline__ void rotate(int lane)
     {
 #pragma unroll
@@ -276,8 +294,17 @@ struct Segment {
                     const uint32_t p23 = __builtin_amdgcn_perm(bits[4 * w + 3], bits[4 * w + 2], 0x04000c0cu);
                     packed[w] = p01 | p23;
                 }
-                const int64_t k0 = static_cast<int64_t>(sidx) * SEG + c * 512 + lane * 8;
-                *reinterpret_cast<uint2 *>(xq_row + k0) = make_uint2(packed[0], packed[1]);
+                int8_t *dst = xq_row + static_cast<int64_t>(sidx) * SEG + c * 512;
+                if constexpr (kExchanged<B>) {
+                    // channel bit 2 has gone to lane bit 4; register bit 2 holds channel bit 8 and lane bit 5 bit
+                    // 7 (two swaps, B = 512) or register bit 2 holds channel bit 7 (one swap)
+                    constexpr int kReg = B == 512 ? 256 : 128, kLane5 = B == 512 ? 128 : 256;
+                    dst += (channel_lane(lane) & 15) * 8 + ((lane >> 4) & 1) * 4 + (lane >> 5) * kLane5;
+                    *reinterpret_cast<uint32_t *>(dst) = packed[0];
+                    *reinterpret_cast<uint32_t *>(dst + kReg) = packed[1];
+                } else {
+                    *reinterpret_cast<uint2 *>(dst + channel_lane(lane) * 8) = make_uint2(packed[0], packed[1]);
+                }
             }
         }
     }

@@ -174,6 +174,26 @@ def test_hadamard_quant_bit_exact(mq, T, K, B, V, use_perm):
     assert np.abs(want.astype(np.int32)).max() > 20          # the case is not degenerate
 
 
+# A wave takes two rows where there are more than 8192 segments of 512 channels: on both sides of the line, odd
+# numbers of rows, segments that end inside a wave (B = 128), every block size with an exchange across lanes; fp16
+# subnormals, whose first sums must not be flushed.
+@pytest.mark.parametrize("T,K,B", [(1170, 3584, 512), (1171, 3584, 512), (1367, 3200, 128), (2049, 2048 + 256, 256),
+                                   (1025, 5120, 1024), (8193, 64, 64), (8195, 8, 8)])
+def test_hadamard_quant_two_rows_to_a_wave(mq, T, K, B):
+    say(f"hadamard rows T={T} K={K} B={B}")
+    rng = np.random.default_rng(T + K)
+    x = rng.standard_normal((T, K)).astype(np.float16)
+    x[::3] = (rng.integers(0, 1024, size=x[::3].shape).astype(np.uint16)
+              | (rng.integers(0, 2, size=x[::3].shape).astype(np.uint16) << 15)).view(np.float16)
+    x[1] *= np.float16(2.0 ** -14)
+    perm = rng.permutation(T).astype(np.int32)
+    V, s_vis, s_txt = T // 2, 3e-7, 0.03
+    x[perm[V:]] = rng.standard_normal((T - V, K)).astype(np.float16)     # text rows of ordinary size
+    got = mq.hadamard_quant_act(dev(x), V, s_vis, s_txt, B, perm_dev=dev(perm)).cpu().numpy()
+    want = orc.msq_quantize(orc.hadamard_rotate(x[perm], B), V, s_vis, s_txt, B)
+    assert (got == want).all()
+
+
 def test_hadamard_quant_strided_input_and_saturation(mq):
     say("hadamard_quant strided + saturation")
     rng = np.random.default_rng(77)
