@@ -708,18 +708,6 @@ int check_heads(int32_t T, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_d
 
 int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
-// Whether rows [T][w] of one array share no byte with rows [T][wo] of another: ranges apart, or column
-// slices of one buffer side by side.
-bool apart(const void *a, int64_t lda, int64_t w, const void *b, int64_t ldb, int64_t wb, int32_t T)
-{
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
-    if (a0 + (static_cast<uint64_t>(T - 1) * lda + w) * 2 <= b0 || b0 + (static_cast<uint64_t>(T - 1) * ldb + wb) * 2 <= a0) return true;
-    if (lda != ldb) return false;
-    const uint64_t pitch = lda * 2;
-    const uint64_t d = b0 >= a0 ? (b0 - a0) % pitch : (pitch - (a0 - b0) % pitch) % pitch;   // b's first column behind a's
-    return d >= static_cast<uint64_t>(w) * 2 && d + wb * 2 <= pitch;
-}
-
 template <int KG, bool VT>
 int launch_attention(const __half *q, int64_t ldq, const __half *k, int64_t ldk, const __half *v, int64_t ldv,
                      __half *o, int64_t ldo, const int32_t *pos, const int32_t *tile_min, const int32_t *tile_max,
@@ -813,7 +801,7 @@ extern "C" int mquant_aifs_attention(const void *q, int64_t ldq, const void *k, 
     // 47.6 / 44.3, 2048 87.4 / 85.1, 2500 136.5 / 138.0, 3500 238.9 / 241.5.  In place also needs an output that shares no memory
     // with V, which every work-group reads until the last has finished, and rows close enough for 32-bit offsets.
     const int64_t items = n_qblocks * n_q_heads;
-    if (items * n_tiles <= 48000 && n_tiles <= kChunkTiles && ldv < int64_t{1} << 24 && apart(v, ldv, kw, o, ldo, qw, T)) {
+    if (items * n_tiles <= 48000 && n_tiles <= kChunkTiles && ldv < int64_t{1} << 24 && rows_apart(v, ldv, kw, o, ldo, qw, T)) {
         // Two key groups, one work-group per compute unit, where the work-groups are few: the longest one, which
         // walks all key tiles, is what such a launch waits for.  One / two groups, 28 heads (T, work-groups): 77, 28
         // 8.3 / 8.5 us; 256, 56 11.9 / 12.0; 512, 112 16.6 / 15.9; 1003, 224 27.5 / 24.1; 1280, 280 33.6 / 27.8; 1408, 308

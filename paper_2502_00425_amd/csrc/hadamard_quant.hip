@@ -161,7 +161,11 @@ int launch(const void *x, int64_t ldx, const int32_t *perm, int8_t *xq, int32_t 
     return launch_status();
 }
 
-int check_common(const void *x, int64_t ldx, int32_t T, int32_t K, int32_t B)
+}  // namespace
+
+namespace mquant {
+
+int check_rotation_args(const void *x, int64_t ldx, int32_t T, int32_t K, int32_t B)
 {
     if (T < 0 || K < 0) return MQUANT_ERR_BAD_SHAPE;
     if (B < 1 || B > 1024 || (B & (B - 1)) != 0) return MQUANT_ERR_UNSUPPORTED;
@@ -173,7 +177,7 @@ int check_common(const void *x, int64_t ldx, int32_t T, int32_t K, int32_t B)
     return MQUANT_OK;
 }
 
-}  // namespace
+}  // namespace mquant
 
 extern "C" int mquant_hadamard_quant_act(const void *x, int64_t ldx, const int32_t *perm,
                                          int8_t *xq, int32_t T, int32_t K, int32_t n_vis,
@@ -190,7 +194,7 @@ extern "C" int mquant_hadamard_quant_act_bits(const void *x, int64_t ldx, const 
                                               int32_t act_bits, mquant_stream_t stream)
 {
     if (act_bits < 2 || act_bits > 8) return MQUANT_ERR_UNSUPPORTED;
-    const int st = check_common(x, ldx, T, K, had_block);
+    const int st = check_rotation_args(x, ldx, T, K, had_block);
     if (st != MQUANT_OK) return st;
     if (n_vis < 0 || n_vis > T) return MQUANT_ERR_BAD_SHAPE;
     if (!(s_vis > 0.0f) || !(s_txt > 0.0f) || !isfinite(s_vis) || !isfinite(s_txt))
@@ -223,7 +227,7 @@ extern "C" int mquant_static_scale_from_absmax(float absmax_u, int32_t had_block
 extern "C" int mquant_hadamard_absmax(const void *x, int64_t ldx, int32_t T, int32_t K,
                                       int32_t had_block, float *absmax, mquant_stream_t stream)
 {
-    const int st = check_common(x, ldx, T, K, had_block);
+    const int st = check_rotation_args(x, ldx, T, K, had_block);
     if (st != MQUANT_OK) return st;
     if (T == 0 || K == 0) return MQUANT_OK;
     if (!absmax) return MQUANT_ERR_NULL;
@@ -235,7 +239,7 @@ extern "C" int mquant_hadamard_dynquant_act(const void *x, int64_t ldx, const in
                                             int8_t *xq, float *row_scale, int32_t T, int32_t K,
                                             int32_t had_block, mquant_stream_t stream)
 {
-    const int st = check_common(x, ldx, T, K, had_block);
+    const int st = check_rotation_args(x, ldx, T, K, had_block);
     if (st != MQUANT_OK) return st;
     if (T == 0 || K == 0) return MQUANT_OK;
     if (!xq || !row_scale) return MQUANT_ERR_NULL;

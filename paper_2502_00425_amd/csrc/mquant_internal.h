@@ -42,6 +42,19 @@ static inline bool aligned_to(const void *p, uintptr_t a)
     return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0;
 }
 
+// Whether T rows of w halves, lda apart, share no byte with T rows of wb halves, ldb apart: ranges apart, or column
+// slices of one buffer side by side.
+static inline bool rows_apart(const void *a, int64_t lda, int64_t w, const void *b, int64_t ldb, int64_t wb, int32_t T)
+{
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    if (a0 + (static_cast<uint64_t>(T - 1) * lda + w) * 2 <= b0 || b0 + (static_cast<uint64_t>(T - 1) * ldb + wb) * 2 <= a0)
+        return true;
+    if (lda != ldb) return false;
+    const uint64_t pitch = static_cast<uint64_t>(lda) * 2;
+    const uint64_t d = b0 >= a0 ? (b0 - a0) % pitch : (pitch - (a0 - b0) % pitch) % pitch;    // b's first column behind a's
+    return d >= static_cast<uint64_t>(w) * 2 && d + static_cast<uint64_t>(wb) * 2 <= pitch;
+}
+
 // Kernel launch that first drops whatever error an earlier, unrelated HIP call of
 // this thread left behind (HIP keeps the last error per thread until it is read, so
 // a failed query made by the caller's framework would otherwise be reported as ours).
@@ -92,6 +105,9 @@ struct TuneState {
 TuneState &tune_state();
 constexpr int kSlicedTiles = 11;          // tiles of the sliced W4A8 GEMM
 constexpr int kG128Tiles = 14;            // tiles of the weight-only GEMM
+
+// The front end's checks of its input (hadamard_quant.hip).
+int check_rotation_args(const void *x, int64_t ldx, int32_t T, int32_t K, int32_t had_block);
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // The same for sizes and tile edges in 32 bits: the cost models ask dozens of times per call.

@@ -161,6 +161,12 @@ constexpr int kGemvMaxT = 32;               // rows of one pass of the tile GEMV
 // What a launch of it is expected to take in microseconds, 17 to 32 rows on n_tiles 32-channel tiles.
 double gemv_tile_us(int32_t T, int64_t n_tiles, int32_t K);
 
+// ---- the one-launch fused prefill linear of w4a8_small.hip, for the smallest calls
+bool small_linear_takes(int32_t T, int32_t N, int32_t K, int32_t had_block);
+int small_linear(const __half *x, int64_t ldx, const int32_t *perm, int8_t *xq, const uint4 *wp, const __half *w_scale,
+                 __half *y, int64_t ldy, int32_t T, int32_t N, int32_t K, const Epilogue &ep, int32_t had_block,
+                 float c_vis, float c_txt, hipStream_t stream);
+
 // ---- the K-sliced GEMM of w4a8_sliced.hip for the same kind of group; K % 128 == 0
 // Whether the GEMM kernels take these rows instead of the GEMVs.
 bool gemm_takes(int32_t T, int32_t K, const GemvGroup &grp);

@@ -1195,6 +1195,21 @@ extern "C" int mquant_w4a8_linear_prefill(const void *x, int64_t ldx, const int3
     int8_t *xq = static_cast<int8_t *>(workspace);
     int st = check_gemm_args(xq, wp, w_scale, y, ldy, T, N, K, n_vis, s_vis, s_txt);
     if (st != MQUANT_OK) return st;
+    // The smallest calls in one launch, whose work-groups read x while others write y already; a forced GEMM tile
+    // goes its own way.
+    const TuneState &tune = tune_state();
+    if (small_linear_takes(T, N, K, had_block) && tune.gemm_tile.load(std::memory_order_relaxed) < 0 &&
+        tune.gemm_sliced.load(std::memory_order_relaxed) < 0 && rows_apart(x, ldx, K, y, ldy, N, T)) {
+        st = check_rotation_args(x, ldx, T, K, had_block);
+        if (st != MQUANT_OK) return st;
+        const double rb = sqrt(static_cast<double>(had_block));
+        Epilogue ep = {};
+        ep.n_vis = n_vis, ep.s_vis = s_vis, ep.s_txt = s_txt, ep.K = K;
+        return small_linear(static_cast<const __half *>(x), ldx, perm, xq, reinterpret_cast<const uint4 *>(wp),
+                            static_cast<const __half *>(w_scale), static_cast<__half *>(y), ldy, T, N, K, ep, had_block,
+                            static_cast<float>(1.0 / (static_cast<double>(s_vis) * rb)),
+                            static_cast<float>(1.0 / (static_cast<double>(s_txt) * rb)), static_cast<hipStream_t>(stream));
+    }
     st = mquant_hadamard_quant_act(x, ldx, perm, xq, T, K, n_vis, s_vis, s_txt, had_block, stream);
     if (st != MQUANT_OK) return st;
     const int64_t xq_bytes = ceil_div(static_cast<int64_t>(T) * K, 256) * 256;

@@ -261,6 +261,46 @@ def test_config0_full(mq):
         assert (g["y"].cpu().numpy().view(np.uint16) == o["y"].view(np.uint16)).all()     # same two fp32 multiplies
 
 
+# The fused prefill entry in one launch: rows and channels that end inside a tile of 16 x 64, an odd N, K with an
+# uneven half and with a last segment that is not full, both blocks, and the sizes on either side of its line.
+@pytest.mark.parametrize("T,N,K,B,small", [(1, 8, 128, 128, True), (17, 72, 384, 128, True), (64, 512, 512, 512, True),
+                                           (15, 33, 896, 128, True), (100, 1000, 1024, 512, True), (256, 1024, 1024, 512, True),
+                                           (257, 1024, 1024, 512, False), (512, 1024, 512, 512, True), (513, 1024, 512, 512, False),
+                                           (33, 64, 1152, 128, False), (33, 64, 512, 256, False)])
+def test_smallest_prefill_linears(mq, T, N, K, B, small):
+    say(f"small linear T={T} N={N} K={K} B={B}")
+    rng = np.random.default_rng(T + N + K)
+    x = (rng.standard_normal((T, K)) * 3).astype(np.float16)
+    packed = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    w_scale = rng.uniform(0.005, 0.02, size=N).astype(np.float16)
+    spans = [(T // 5, T // 2)] if T > 4 else []
+    o = orc.w4a8_linear(x, spans, packed, w_scale, 0.21, 0.034, B)
+    V = o["V"]
+    xd, permd, wp, wsd = dev(x), dev(o["perm"]), mq.w4_prepack(dev(packed)), dev(w_scale)
+    ws = torch.full((mq.w4a8_linear_prefill_workspace_bytes(T, N, K) + 256,), 77, dtype=torch.uint8, device="cuda")
+    y = torch.full((T, N + 8), 7.0, dtype=torch.float16, device="cuda")
+    names = traced(lambda: mq.w4a8_linear_prefill(xd, permd, wp, wsd, N, V, 0.21, 0.034, B, ws, out=y[:, :N]))
+    if names is not None:
+        assert (len(names) == 1 and names[0].startswith("w4a8_small_kernel")) == small, names
+    check_y(y[:, :N].cpu().numpy(), o["ref"], f"small linear T={T} N={N} K={K}")
+    assert bool((y[:, N:] == 7.0).all())
+    assert (ws[:T * K].view(torch.int8).reshape(T, K).cpu().numpy() == o["xq"]).all()
+    assert bool((ws[-256:] == 77).all())
+
+
+def test_smallest_prefill_linear_in_place(mq):
+    """An output over the input: the input is read completely first, as with two launches."""
+    rng = np.random.default_rng(3)
+    T, K, B = 100, 512, 512
+    x = (rng.standard_normal((T, K)) * 3).astype(np.float16)
+    packed = rng.integers(0, 256, size=(K, K // 2), dtype=np.uint8)
+    w_scale = rng.uniform(0.0005, 0.002, size=K).astype(np.float16)
+    o = orc.w4a8_linear(x, [(8, 48)], packed, w_scale, 0.21, 0.034, B)
+    xd, permd = dev(x), dev(o["perm"])
+    y = mq.w4a8_linear_prefill_static(xd, permd, mq.w4_prepack(dev(packed)), dev(w_scale), K, o["V"], 0.21, 0.034, B, xd)
+    check_y(y.cpu().numpy(), o["ref"], "in place")
+
+
 @pytest.mark.parametrize("T,N,K,V", [
     (300, 544, 384, 120),       # two M tiles, three N tiles, ragged both ways
     (257, 100, 128, 257),       # N below one tile, T one row past a tile
