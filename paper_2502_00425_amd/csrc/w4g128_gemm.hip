@@ -21,7 +21,7 @@
 // code + 8.  (v >> 4j) & 0x000F000F then is a pair of adjacent channels in the
 // two halves of a dword; OR-ing 0x6400 into each half makes the fp16 number
 // 1024 + code + 8, from which 1032 is subtracted exactly before the multiply by
-// the scale -- two packed fp16 operations per pair and no integer->float convert.
+// the scale -- two packed fp16 operations per pair and no integer->float convert (Unpack).
 // The scale table follows the weight tiles, transposed to [K/128][N padded to 32]
 // so that the 32 lanes of a tile read consecutive halves.
 #include <hip/hip_fp16.h>
@@ -90,20 +90,49 @@ __device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t c
     return r;
 }
 
-// One dword of prepacked weights -> 8 fp16 weights (channels in ascending order),
-// each fp16(code * scale); s2 holds the scale in both halves.
-__device__ __forceinline__ v4u dequant8(uint32_t v, v2h s2, uint32_t mask, uint32_t magic)
-{
-    const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
-    v4u out;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        v2h h = __builtin_bit_cast(v2h, and_or(v >> (4 * j), mask, magic));
-        h = (h - bias) * s2;                      // the difference is exact; one rounding
-        out[j] = __builtin_bit_cast(uint32_t, h);
+// The channels 2 j, 2 j + 1 of a dword of prepacked weights as fp16(code * scale); s2 holds the scale in both
+// halves.  Both ways to the code are exact, the product is rounded once.  The odd pairs stay where they
+// are, four bits up: 0x6400 | code + 8 << 4 is 1024 + 16 (code + 8), a sixteenth of which is 64 + code + 8.  So
+// eight weights take one shift and twelve other operations.
+struct Unpack {
+    uint32_t even = 0x000F000Fu, odd = 0x00F000F0u, magic = 0x64006400u;
+    __device__ __forceinline__ Unpack()
+    {
+        asm volatile("" : "+v"(magic));       // keep it in a VGPR (third operand of v_and_or_b32)
     }
-    return out;
-}
+    __device__ __forceinline__ uint32_t pair(uint32_t v, int j, v2h s2) const
+    {
+        const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
+        const v2h sixteenth = {static_cast<_Float16>(0.0625f), static_cast<_Float16>(0.0625f)};
+        const v2h bias_odd = {static_cast<_Float16>(-72.0f), static_cast<_Float16>(-72.0f)};
+        const uint32_t t = j >= 2 ? v >> 8 : v;
+        v2h code;
+        if (j & 1) code = __builtin_elementwise_fma(__builtin_bit_cast(v2h, and_or(t, odd, magic)), sixteenth, bias_odd);
+        else code = __builtin_bit_cast(v2h, and_or(t, even, magic)) - bias;
+        return __builtin_bit_cast(uint32_t, code * s2);
+    }
+    __device__ __forceinline__ v4u eight(uint32_t v, v2h s2) const
+    {
+        v4u out;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[j] = pair(v, j, s2);
+        return out;
+    }
+    // The same with every pair shifted into place, three shifts and twelve operations: the GEMV of many tiles,
+    // which waits for its loads and not for these, takes 3 to 8 % longer with the other form (3584 ->
+    // 37888 at 8 rows 24.0 / 25.9 us).
+    __device__ __forceinline__ v4u eight_shifted(uint32_t v, v2h s2) const
+    {
+        v4u out;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
+            const v2h h = __builtin_bit_cast(v2h, and_or(v >> (4 * j), even, magic));
+            out[j] = __builtin_bit_cast(uint32_t, (h - bias) * s2);
+        }
+        return out;
+    }
+};
 
 __device__ __forceinline__ int acc_row(int r, int g) { return (r >> 2) * 8 + g * 4 + (r & 3); }
 
@@ -128,7 +157,7 @@ __device__ __forceinline__ void tile_of_group(int32_t id, int32_t tiles_m, int32
 // Prefill shapes: one work-group of eight waves computes an MT*32 x NWN*32 tile.  The waves
 // stand as NWN column waves x KS = 8 / NWN K slices: a wave owns all MT*32 rows of one
 // 32-channel column and one 64-channel k-tile of every stage, so each weight is dequantised
-// once per work-group (15 VALU operations per MT MFMAs), and the KS slices of a column are
+// once per work-group (13 VALU operations per MT MFMAs), and the KS slices of a column are
 // added through LDS at the end.
 //
 // A stage is KS k-tiles.  Everything in it arrives by LDS-DMA: the activations (KS slabs of
@@ -226,10 +255,7 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[mt][r] = 0.0f;
 
-    const uint32_t mask = 0x000F000Fu;
-    uint32_t magic = 0x64006400u;
-    asm volatile("" : "+v"(magic));           // keep it in a VGPR (third operand of v_and_or_b32)
-    const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
+    const Unpack unpack;
 
     // fragment (st, mt): chunk g * 4 + st of row mt * 32 + l32 of this wave's slab
     const uint32_t a_lane = ks * G::A_SLAB + l32 * 128 + (((g * 4) ^ ((l32 >> 1) & 7)) << 4);
@@ -242,11 +268,6 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
     auto scale = [&](uint32_t buf) {
         const _Float16 v = *reinterpret_cast<const _Float16 *>(smem + buf + G::S_OFF + wave * 256 + l32 * 2);
         return v2h{v, v};
-    };
-    auto dequant_pair = [&](uint32_t v, int j, v2h s2) -> uint32_t {
-        v2h h = __builtin_bit_cast(v2h, and_or(v >> (4 * j), mask, magic));
-        h = (h - bias) * s2;                      // the difference is exact; one rounding
-        return __builtin_bit_cast(uint32_t, h);
     };
 
     // ---- prologue: fill every buffer, wait for stage 0, first operands
@@ -269,7 +290,7 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
     for (int i = 0; i < kWin; ++i) fr[i] = afrag(0, i / MT, i % MT);
     v4u bf[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bf[0][j] = dequant_pair(bw[0], j, s2);
+    for (int j = 0; j < 4; ++j) bf[0][j] = unpack.pair(bw[0], j, s2);
 
     // A wave whose slice ends a stage early (K / 64 not a multiple of KS) leaves the loop one
     // stage early; there is no barrier in the last stage.
@@ -315,7 +336,7 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if ((MT >= 4 ? MT - 4 + j : j * MT / 4) == mt)
-                    bf[(st + 1) & 1][j] = dequant_pair(st < 3 ? bw[(st + 1) & 3] : bw_n[0], j, st < 3 ? s2 : s2_n);
+                    bf[(st + 1) & 1][j] = unpack.pair(st < 3 ? bw[(st + 1) & 3] : bw_n[0], j, st < 3 ? s2 : s2_n);
             __builtin_amdgcn_sched_barrier(0);
         }
         bw = bw_n;
@@ -418,9 +439,7 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_kernel(
     const v4u *wtile = wp + static_cast<int64_t>(ntile) * k_tiles * 64 + lane;
     const __half *xrow = x + static_cast<int64_t>(l32 < T ? l32 : T - 1) * ldx + g * 32;
     const __half *scol = sT + ntile * kPackN + l32;
-    const uint32_t mask = 0x000F000Fu;
-    uint32_t magic = 0x64006400u;
-    asm volatile("" : "+v"(magic));
+    const Unpack unpack;
 
     for (int32_t base = kt_begin; base < kt_end; base += KT) {
         v4u a[KT][4], b[KT];
@@ -448,7 +467,7 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_kernel(
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 const uint32_t code = live ? b[u][st] : 0x88888888u;
-                const v8h bf = __builtin_bit_cast(v8h, dequant8(code, s2, mask, magic));
+                const v8h bf = __builtin_bit_cast(v8h, KT == 1 ? unpack.eight_shifted(code, s2) : unpack.eight(code, s2));
                 const v8h af = __builtin_bit_cast(v8h, a[u][st]);
                 if (st & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc1, 0, 0, 0);
                 else acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc0, 0, 0, 0);
@@ -519,9 +538,7 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_half_kernel(
     __syncthreads();
 
     const uint8_t *xlane = smem + (n16 < T ? n16 : T - 1) * pitch + kg * 64;   // rows >= T are never stored
-    const uint32_t mask = 0x000F000Fu;
-    uint32_t magic = 0x64006400u;
-    asm volatile("" : "+v"(magic));
+    const Unpack unpack;
     v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains
     for (int32_t base = begin; base < end; base += DEPTH) {
 #pragma unroll
@@ -534,7 +551,7 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_half_kernel(
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 const v8h af = *reinterpret_cast<const v8h *>(xlane + (base + j) * (kGroup * 2) + st * 16);
-                const v8h bf = __builtin_bit_cast(v8h, dequant8(bw[st], s2, mask, magic));
+                const v8h bf = __builtin_bit_cast(v8h, unpack.eight(bw[st], s2));
                 acc[st & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, bf, acc[st & 1], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
