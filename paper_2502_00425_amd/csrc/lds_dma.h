@@ -13,20 +13,8 @@ namespace mquant {
 typedef const void __attribute__((address_space(1))) *global_ptr_t;
 typedef void __attribute__((address_space(3))) *lds_ptr_t;
 
-// 16 bytes per lane, global -> LDS; LDS address = wave-uniform base + lane * 16.
-__device__ __forceinline__ void lds_dma16(const uint8_t *gsrc, uint8_t *lds_wave_base)
-{
-    const uint32_t m0v =
-        __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
-            (lds_ptr_t)lds_wave_base)));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :
-                 : "s"(m0v), "v"(gsrc)
-                 : "memory", "m0");
-}
-
-// The same with a wave-uniform 64-bit base (kept in scalar registers) plus a 32-bit byte offset
-// per lane, and the LDS destination given as a byte address inside the work-group's LDS.
+// 16 bytes per lane, global -> LDS: a wave-uniform 64-bit base (kept in scalar registers) plus a 32-bit
+// byte offset per lane; LDS address = wave-uniform byte address inside the work-group's LDS + lane * 16.
 __device__ __forceinline__ void lds_dma16_uniform_base(const uint8_t *base_uniform, uint32_t lane_offset,
                                                        uint32_t lds_wave_base)
 {

@@ -94,10 +94,7 @@ __global__ __launch_bounds__(256) void prepack_kernel(
 // a 32-bank LDS would want.
 __device__ __forceinline__ int lds_a_swizzle(int row) { return (row >> 1) & 7; }
 
-__device__ __forceinline__ int lds_a_offset(int row, int chunk)
-{
-    return row * 128 + ((chunk ^ lds_a_swizzle(row)) << 4);
-}
+typedef uint32_t v4u_lds __attribute__((ext_vector_type(4)));
 
 // Work-group id -> (tm, tn).  Work-groups are dealt round-robin to the 8 XCDs,
 // each with its own L2: XCD x gets a contiguous run of the tile order, and the
@@ -148,7 +145,7 @@ __global__ __launch_bounds__(WM *WN * 64, STAGES == 2 ? 4 : 2) void w4a8_gemm_ke
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM;
     const int wn = wave / WM;
     const int l32 = lane & 31;
@@ -169,54 +166,63 @@ __global__ __launch_bounds__(WM *WN * 64, STAGES == 2 ? 4 : 2) void w4a8_gemm_ke
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mt][nt][r] = 0;
 
-    // Per-lane global source of each DMA chunk this wave copies, for k-block 0.
-    // Rows past T and n-tiles past the padded N are clamped to valid memory; the
-    // values they produce are never stored.
-    const uint8_t *src[CH];
-    int32_t src_step[CH];
+    // Copies: a chunk takes a wave-uniform base and LDS address (scalar arithmetic) and a 32-bit offset per
+    // lane, fixed for the whole loop; a wave's first A_CH / NW chunks are activations, the others weights.  Rows past
+    // T and n-tiles past the padded N are clamped to valid memory; the values they produce are never
+    // stored.  (With 64-bit lane addresses and LDS pointers converted from generic ones every copy took eight
+    // vector instructions, two of them read back to scalar registers, in front of an MFMA: passes over the four
+    // 7B projections at T = 1280 333 -> 320 us, 4096 916 -> 857, 72B at T = 16384 11.66 -> 10.87 ms.)
+    constexpr int A_PW = A_CH / NW;                   // activation chunks of a wave
+    static_assert(A_CH % NW == 0 && B_CH % NW == 0, "a chunk is of one kind for all waves");
+    const uint32_t lds0 = lds_address(smem);
+    const uint8_t *abase = reinterpret_cast<const uint8_t *>(xq) + static_cast<int64_t>(row0) * K + static_cast<int64_t>(kb0) * 128;
+    uint32_t a_off[A_PW];
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {
-        const int q = wave + j * NW;
-        if (q < A_CH) {
-            const int r = q * 8 + (lane >> 3);
-            const int logical = (lane & 7) ^ lds_a_swizzle(r);
-            int32_t row = row0 + r;
-            row = row < T ? row : T - 1;
-            src[j] = reinterpret_cast<const uint8_t *>(xq) + static_cast<int64_t>(row) * K +
-                     static_cast<int64_t>(kb0) * 128 + logical * 16;
-            src_step[j] = 128;
-        } else {
-            const int b = q - A_CH, nt = b >> 1, ks = b & 1;
-            int32_t ntile = ntile0 + nt;
-            ntile = ntile < n_tiles32 ? ntile : n_tiles32 - 1;
-            src[j] = reinterpret_cast<const uint8_t *>(wp) +
-                     ((static_cast<int64_t>(ntile) * k_tiles + kb0 * 2 + ks) * 64 + lane) * 16;
-            src_step[j] = 2 * kPackTileBytes;
-        }
+    for (int j = 0; j < A_PW; ++j) {
+        const int r = (wave + j * NW) * 8 + (lane >> 3);
+        const int32_t row = row0 + r < T ? r : T - 1 - row0;
+        a_off[j] = static_cast<uint32_t>(row) * static_cast<uint32_t>(K) + (((lane & 7) ^ lds_a_swizzle(r)) << 4);
     }
+    const uint8_t *bbase[CH - A_PW];
+#pragma unroll
+    for (int j = 0; j < CH - A_PW; ++j) {
+        const int b = wave + j * NW, ks = b & 1;
+        int32_t ntile = ntile0 + (b >> 1);
+        ntile = ntile < n_tiles32 ? ntile : n_tiles32 - 1;
+        bbase[j] = reinterpret_cast<const uint8_t *>(wp) +
+                   (static_cast<int64_t>(ntile) * k_tiles + kb0 * 2 + ks) * kPackTileBytes;
+    }
+    const uint32_t b_off = lane * 16;
     // DMA chunk j of this wave for k-block kb (relative to kb0) into stage buffer buf.
     auto dma_chunk = [&](int j, int32_t kb, int buf) {
-        lds_dma16(src[j] + static_cast<int64_t>(kb) * src_step[j],
-                  smem + buf * STAGE + (wave + j * NW) * 1024);
+        const uint32_t dst = lds0 + buf * STAGE + (wave + j * NW) * 1024;
+        if (j < A_PW)
+            lds_dma16_uniform_base(abase + static_cast<int64_t>(kb) * 128, a_off[j < A_PW ? j : 0], dst);
+        else
+            lds_dma16_uniform_base(bbase[j < A_PW ? 0 : j - A_PW] + static_cast<int64_t>(kb) * (2 * kPackTileBytes), b_off, dst);
     };
     // Fragment reads.  A k-block is consumed in four phases (ks, h) of 32 channels:
     // phase (ks, h) multiplies 16-byte chunk ks*4 + g*2 + h of every A row with half h
-    // of the unpacked B tile of k-tile ks.
+    // of the unpacked B tile of k-tile ks.  The swizzle of a row is that of l32, so a phase's fragments
+    // lie 4 KiB apart behind one lane address.
+    typedef const v4u_lds __attribute__((address_space(3))) *frag_ptr;
+    const uint32_t a_lane = lds0 + (wm * (BM / WM) + l32) * 128 + (((g * 2) ^ lds_a_swizzle(l32)) << 4);
+    const uint32_t b_lane = lds0 + A_STAGE + wn * NT * 2048 + lane * 16;
     auto read_a = [&](int buf, int ks, int h, v4i (&dst)[MT]) {
-        const uint8_t *abase = smem + buf * STAGE;
+        const uint32_t at = (a_lane ^ ((ks * 4 + h) << 4)) + buf * STAGE;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int r = wm * (BM / WM) + mt * 32 + l32;
-            dst[mt] = as_v4i(*reinterpret_cast<const uint4 *>(
-                abase + lds_a_offset(r, ks * 4 + g * 2 + h)));
+            const v4u_lds u = *(frag_ptr)(uintptr_t)(at + mt * 4096);
+            dst[mt] = __builtin_bit_cast(v4i, u);
         }
     };
     auto read_b = [&](int buf, int ks, uint4 (&dst)[NT]) {
-        const uint8_t *bbase = smem + buf * STAGE + A_STAGE;
+        const uint32_t at = b_lane + buf * STAGE;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            dst[nt] = *reinterpret_cast<const uint4 *>(
-                bbase + ((wn * NT + nt) * 2 + ks) * 1024 + lane * 16);
+        for (int nt = 0; nt < NT; ++nt) {
+            const v4u_lds u = *(frag_ptr)(uintptr_t)(at + nt * 2048 + ks * 1024);
+            dst[nt] = make_uint4(u[0], u[1], u[2], u[3]);
+        }
     };
     // One phase: MT*NT MFMAs (consecutive ones write different accumulators, a
     // dependent pair back to back would wait out the full MFMA latency) with DMA
