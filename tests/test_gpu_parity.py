@@ -111,8 +111,8 @@ def test_aifs_remap_mask_small(mq, T, spans):
 @pytest.mark.parametrize("T,spans", [(1024, [(10, 300), (500, 24), (900, 124)]), (16, [(4, 8)]), (2064, [(0, 2064)]),
                                      (18448, [(100, 9000)])])
 def test_aifs_remap_mask_staged_rows(mq, T, spans):
-    """T % 16 == 0 takes the kernel that stages source rows in LDS (8, 4 or 1 rows per group
-    depending on T); any non-zero input byte means "may attend" and comes out as 1."""
+    """Lengths that are whole 16-byte chunks, most of them in the kernel that stages source rows in LDS;
+    any non-zero input byte means "may attend" and comes out as 1."""
     say(f"mask staged rows T={T}")
     rng = np.random.default_rng(T)
     perm, _, _ = orc.aifs_build_perm(T, spans)
@@ -120,6 +120,27 @@ def test_aifs_remap_mask_staged_rows(mq, T, spans):
     got = mq.aifs_remap_mask(dev(M), dev(perm)).cpu().numpy()
     want = orc.aifs_remap_mask(M != 0, perm).astype(np.uint8)
     assert (got == want).all()
+
+
+# Lengths on either side of the lines between the forms, every T % 4 (where a row starts inside an output word) and
+# odd T (where a row starts inside a 16-byte chunk), a mask that starts inside one too; the last: one row per work-group.
+@pytest.mark.parametrize("T,offset", [(1, 3), (17, 1), (1023, 5), (1024, 0), (1025, 0), (1026, 7), (1027, 15), (1028, 2), (2559, 9),
+                                      (2560, 0), (2561, 1), (2562, 0), (2563, 11), (37103, 0)])
+def test_aifs_remap_mask_any_length(mq, T, offset):
+    say(f"mask remap T={T} offset={offset}")
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    buf = torch.randint(0, 256, (T * T + 32,), dtype=torch.uint8, device="cuda", generator=gen)
+    buf[buf < 128] = 0
+    mask = buf[offset:offset + T * T].view(T, T)
+    perm = torch.randperm(T, device="cuda", generator=gen).to(torch.int32)
+    out = torch.full((T * T + 8,), 9, dtype=torch.uint8, device="cuda")
+    got = mq.aifs_remap_mask(mask, perm, out=out[4:4 + T * T].view(T, T))
+    cols = perm.long()
+    for r in range(0, T, 4096):
+        rows = slice(r, min(r + 4096, T)) if T < 8192 else torch.arange(r, min(r + 16, T), device="cuda")
+        assert torch.equal(got[rows], (mask[cols[rows]][:, cols] != 0).to(torch.uint8))
+    assert torch.equal(got[-1], (mask[cols[-1]][cols] != 0).to(torch.uint8))
+    assert bool((out[:4] == 9).all()) and bool((out[-4:] == 9).all())
 
 
 def test_aifs_remap_mask_config2(mq):
