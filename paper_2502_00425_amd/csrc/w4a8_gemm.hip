@@ -902,20 +902,24 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
     return c.us(static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn), K);
 }
 
-// The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 12 %
+// The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 14.5 %
 // where the tiles above fill the chip: in a continuous run the clock is lower than in the sweep's short
-// bursts, and the sliced 64x256 tile, which reads each activation fragment from LDS for one MFMA instead
-// of two, falls behind its estimate.  One linear at a time switched to its sliced tile in continuous
-// passes over the four projections, estimated share of the plan's time and change of the pass: 7B, T =
-// 1003: o 0.76 -4.6 us, down (split-K) 0.88 -8.7; T = 1280: qkv 0.96 +1.7, o 0.95 -1.2, down (split-K) 0.95
-// +0.4; T = 2048: qkv 0.90 +8.2, o 0.95 +3.7; T = 3000: o 0.90 +5.6, down 0.87 -13.4; 72B, T = 1003: qkv 0.87
-// -8.3; T = 1500: down 0.86 -38.7; T = 2048: qkv 0.92 +5.0.
+// bursts, the large tiles have got faster since the sweep (scalar addresses), and the sliced 64x256 tile, which reads each
+// activation fragment from LDS for one MFMA instead of two, falls behind its estimate.  One linear at a time
+// switched from its sliced tile to the plan in continuous passes over the four projections, estimated share of the
+// plan's time and change of the pass in us: 7B, T = 850: qkv 0.77 +1.2, down (split-K) 0.89 +1.3; T = 2400: o 0.84 +2.0; T =
+// 2700: down 0.83 +6.1; T = 3000, 3072, 3300: down 0.86 -8.9, -13.0, -4.2; 72B, T = 160: gate_up 0.85 -9.5; T = 1100: o
+// 0.81 +4.3; T = 1200: o 0.87 -6.2, down 0.82 +4.4; T = 1400: o 0.88 +5.6, down 0.85 +3.7; T = 1500: down 0.86 -12.0; T = 2200:
+// o 0.88 -13.9, down 0.85 -14.0; T = 2300: down 0.86 -8.7.  And from the plan to the sliced tile: 7B, T = 1280: qkv 0.96
+// +3.6, o 0.95 +1.1; T = 2048: qkv 0.90 +3.1; 72B, T = 180: gate_up 0.89 +9.2.
+// Whole passes at 0.88 / 0.855: 7B, T = 3000 698.5 / 690, 3300 754 / 746; 72B, T = 1500 1141 / 1135, 2300 1712.5 / 1698.5, 1280
+// 1007 / 1010; at 0.845 T = 1400 loses 10.
 bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(T, K, grp) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(T, K, grp) < (full ? 0.855 : 0.94) * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
