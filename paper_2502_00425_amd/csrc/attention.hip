@@ -281,7 +281,7 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
     const uint32_t k_chunk = static_cast<uint32_t>(((lane & 15) ^ (c_row & 15)) << 4);
     const uint32_t v_chunk = static_cast<uint32_t>(((lane & 15) ^ ((c_row & 3) << 2)) << 4);
     const uint32_t k_pitch = static_cast<uint32_t>(ldk) * 2u, v_pitch = static_cast<uint32_t>(ldv) * 2u;
-    // rows past T repeat the last row (their probabilities are masked to zero)
+    // rows past T repeat the last row (their probabilities are masked to zero; values: zero_tail)
     auto dma_k = [&](int32_t t, int b) {
         const uint8_t *tile = kbase + static_cast<int64_t>(t) * kBK * ldk * 2;
         const int32_t last = T - 1 - t * kBK;              // last valid row of this tile
@@ -312,6 +312,20 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
             lds_dma16_uniform_base(tile, static_cast<uint32_t>(row) * v_pitch + v_chunk,
                                    lds0 + (2 + b) * kTileBytes + (i * 4 + wave) * 1024);
         }
+    };
+
+    // Value rows past T become zeros once the copies of the last tile have landed (every lane those it copied): a zero
+    // probability times what the last row holds is a NaN where that is infinite.  V^T has its zeros from vt_kernel.
+    typedef v4u __attribute__((address_space(3))) *v4u_lds_ptr;
+    const int32_t ragged = !VT && T % kBK != 0 ? n_tiles - 1 : -1;      // the tile that holds the end of the sequence
+    auto zero_tail = [&](int32_t t, int b) {
+        if (t != ragged) return;
+        uint32_t at = lds0 + (2 + b) * kTileBytes + wave * 1024 + lane * 16;
+        int32_t row = t * kBK + c_row;
+        asm volatile("" : "+v"(at), "+v"(row) : : "memory");   // behind the wait for the copies; made here, not kept
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (row + 16 * i >= T) *(v4u_lds_ptr)(uintptr_t)(at + i * 4096) = v4u{0, 0, 0, 0};
     };
 
     // ---- this lane's query: position and Q^T fragments
@@ -604,6 +618,7 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
         }
         if (tid_g < kBK) pos_lds2[kg][par ^ 1][tid_g] = preg;
         wait_vmcnt<0>();                                   // K of nn and V of nxt have landed
+        if constexpr (!VT) zero_tail(nxt >> 2, par ^ 1);
         __syncthreads();
         cur = nxt;
         nxt = nn;
@@ -622,6 +637,7 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
         if (tid_g < kBK) pos_lds2[kg][0][tid_g] = key_pos(cur >> 2);
     }
     wait_vmcnt<0>();
+    if constexpr (!VT) zero_tail(cur >> 2, 0);
     __syncthreads();
     v16f s_a[2], s_b[2];
     if ((cur & 1) != 0) scores(0, s_a);

@@ -284,6 +284,28 @@ def test_attention_output_in_the_memory_of_v(mq):
         assert (err <= 2.0 ** -9 * (np.abs(want) + 1.0)).all(), (at, o_at)
 
 
+@pytest.mark.parametrize("T,H,route", [(77, 1, "<1, false>"), (301, 2, "<2, false>"), (4097, 1, "<1, true>")])
+def test_attention_infinity_in_the_last_value_row(mq, T, H, route):
+    """The last tile is filled up past T, and what stands there has no part in the output: a query that
+    sees an infinite value gets that infinity, on every route."""
+    say(f"attention infinite value T={T}")
+    rng = np.random.default_rng(T)
+    q, k, v = make_qkv(rng, T, H, 1, q_gain=0.3)
+    pos = np.zeros(T, dtype=np.int32)                      # all see all
+    rows = np.unique(np.r_[0, 1, T - 2, T - 1, rng.choice(T, 16)])
+    ref = orc.aifs_attention_f64(q, k, v, pos, H, 1, rows=rows)
+    tol = attention_tolerance(q, k, v, pos, H, 1, ref, rows)
+    v[T - 1, 3], v[T - 1, 100] = np.inf, -np.inf
+    qd, kd, vd, pd = dev(q), dev(k), dev(v), dev(pos)
+    got = mq.aifs_attention(qd, kd, vd, pd, H, 1).cpu().numpy().reshape(T, H, 128)
+    assert (got[:, :, 3] == np.inf).all() and (got[:, :, 100] == -np.inf).all()
+    finite = np.r_[0:3, 4:100, 101:128]
+    err = np.abs(got[rows].astype(np.float64) - ref.reshape(-1, H, 128))
+    assert (err <= tol.reshape(-1, H, 128))[:, :, finite].all()
+    run = kernels(lambda: mq.aifs_attention(qd, kd, vd, pd, H, 1))
+    assert run[-1] == "aifs_attention_kernel" + route
+
+
 def test_attention_argument_errors(mq):
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     pos = torch.zeros(4, dtype=torch.int32, device="cuda")
