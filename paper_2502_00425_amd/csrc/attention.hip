@@ -483,6 +483,10 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
     const float lazy_raw = kLazy / scale_log2e;
     float m_ref = -INFINITY, l_run = 0.0f;
 
+    // Keys past the end have position INT_MAX, which hides them from all queries but those that are there themselves: from
+    // these by their index, in the tile `top` (-1: not this wave's concern).
+    const int32_t top = T % kBK != 0 && __any(my_pos == INT_MAX) ? n_tiles - 1 : -1;
+
     // One step of the pipeline: softmax and P V of tile `cur` (scores in s_cur, values in V
     // buffer par, positions in pos buffer par) while the scores of tile `nxt` (keys in K
     // buffer par ^ 1) go to s_nxt.  On entry a barrier has published those buffers and freed
@@ -509,6 +513,15 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         if (pos_lds[kb * 32 + acc_row(r, g)] > my_pos) s_cur[kb][r] = -INFINITY;
+                if ((cur >> 2) == top) {
+                    int32_t keys = T % kBK - 4 * g;                      // of this lane's registers, in acc_row(r, 0)
+                    asm volatile("" : "+v"(keys));                       // computed here, not kept across the loop
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (kb * 32 + acc_row(r, 0) >= keys) s_cur[kb][r] = -INFINITY;
+                }
             }
             float m_new = m_ref;
 #pragma unroll

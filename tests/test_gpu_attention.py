@@ -306,6 +306,20 @@ def test_attention_infinity_in_the_last_value_row(mq, T, H, route):
     assert run[-1] == "aifs_attention_kernel" + route
 
 
+@pytest.mark.parametrize("T,H", [(77, 1), (130, 2), (301, 2), (4097, 1)])
+def test_attention_largest_position(mq, T, H):
+    """Any position is a position: queries at INT_MAX see every key there is, and nothing past the last."""
+    say(f"attention INT_MAX T={T}")
+    rng = np.random.default_rng(T + 1)
+    q, k, v = make_qkv(rng, T, H, 1, q_gain=0.3)
+    v[T - 1] += np.float16(40.0)                           # what repeats of the last row would show
+    pos = rng.permutation(T).astype(np.int32)
+    pos[[0, T // 2, T - 1]] = np.iinfo(np.int32).max
+    pos[1] = np.iinfo(np.int32).max - 1
+    rows = np.unique(np.r_[0, 1, T // 2, T - 2, T - 1, rng.choice(T, 16)])
+    check_attention(mq, q, k, v, pos, H, 1, rows=rows, what=f"INT_MAX T={T}")
+
+
 def test_attention_argument_errors(mq):
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     pos = torch.zeros(4, dtype=torch.int32, device="cuda")
