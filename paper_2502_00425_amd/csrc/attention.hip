@@ -499,7 +499,12 @@ __global__ __launch_bounds__(KG * 256, 2) void aifs_attention_kernel(
         int32_t preg = INT_MAX;
         if (tid_g < kBK && nxt < end) preg = key_pos(nxt >> 2);
         // Flags held in vector registers: as wave-uniform branches the three ways to the next tile's scores
-        // were merged by copying them, 64 registers every other tile (T = 8192 538 -> 504 us without).
+        // were merged by copying them, 64 registers every other tile (T = 8192 538 -> 504 us without; a scalar branch
+        // around the body of need_cur alone spills more than 500 registers).  The branches below therefore narrow EXEC, which
+        // the matrix instructions do not look at: a wave that skips a tile is kept from accumulating into
+        // acc_o by the jump over the empty body, which the compiler keeps for bodies of this size with LDS reads in them.
+        // tests/test_attention_branches.py holds it to that; waves that skip what others of the work-group need run
+        // in test_attention_routes and test_attention_every_key_tile_is_visible_on_the_config_layouts.
         int32_t f_cur = cur & 3, f_nxt = nxt & 1;
         asm("" : "+v"(f_cur), "+v"(f_nxt));
         const bool need_cur = (f_cur & 1) != 0, need_nxt = f_nxt != 0;
