@@ -309,17 +309,39 @@ def test_smallest_prefill_linears(mq, T, N, K, B, small):
     assert bool((ws[-256:] == 77).all())
 
 
-def test_smallest_prefill_linear_in_place(mq):
-    """An output over the input: the input is read completely first, as with two launches."""
+def small_linear_case(mq, T=100, K=512, B=512):
     rng = np.random.default_rng(3)
-    T, K, B = 100, 512, 512
     x = (rng.standard_normal((T, K)) * 3).astype(np.float16)
     packed = rng.integers(0, 256, size=(K, K // 2), dtype=np.uint8)
     w_scale = rng.uniform(0.0005, 0.002, size=K).astype(np.float16)
     o = orc.w4a8_linear(x, [(8, 48)], packed, w_scale, 0.21, 0.034, B)
+    wp, wsd = mq.w4_prepack(dev(packed)), dev(w_scale)
+    run = lambda xd, permd, y: mq.w4a8_linear_prefill_static(xd, permd, wp, wsd, K, o["V"], 0.21, 0.034, B, y)
+    one = lambda names: names is None or [n.split("<")[0] for n in names].count("w4a8_small_kernel") == 1 == len(names)
+    none = lambda names: names is None or (len(names) >= 2 and not any(n.startswith("w4a8_small_kernel") for n in names))
+    return o, x, run, one, none
+
+
+def test_smallest_prefill_linear_in_place(mq):
+    """An output over the input: the input is read completely first, as with two launches."""
+    o, x, run, _, none = small_linear_case(mq)
     xd, permd = dev(x), dev(o["perm"])
-    y = mq.w4a8_linear_prefill_static(xd, permd, mq.w4_prepack(dev(packed)), dev(w_scale), K, o["V"], 0.21, 0.034, B, xd)
-    check_y(y.cpu().numpy(), o["ref"], "in place")
+    check_y(run(xd, permd, xd).cpu().numpy(), o["ref"], "in place")
+    names = traced(lambda: run(xd, permd, xd))
+    assert none(names), names
+
+
+@pytest.mark.parametrize("at,apart", [(512, True), (1024, True), (448, False), (8, False)])
+def test_smallest_prefill_linear_column_slices(mq, at, apart):
+    """Input and output in columns of one buffer: one launch where they lie side by side."""
+    o, x, run, one, none = small_linear_case(mq)
+    T, K = x.shape
+    permd, buf = dev(o["perm"]), torch.zeros((T, 3 * K), dtype=torch.float16, device="cuda")
+    xd, y = buf[:, :K], buf[:, at:at + K]
+    xd.copy_(dev(x))
+    check_y(run(xd, permd, y).cpu().numpy(), o["ref"], f"columns from {at}")
+    names = traced(lambda: run(xd, permd, y))
+    assert (one if apart else none)(names), names
 
 
 @pytest.mark.parametrize("T,N,K,V", [
