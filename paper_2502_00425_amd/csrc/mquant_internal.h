@@ -42,14 +42,22 @@ static inline bool aligned_to(const void *p, uintptr_t a)
     return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0;
 }
 
+static inline bool ranges_apart(const void *a, uint64_t a_bytes, const void *b, uint64_t b_bytes)
+{
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 + a_bytes <= b0 || b0 + b_bytes <= a0;
+}
+
+// Bytes from the first to behind the last of T >= 1 rows of w halves, ld apart.
+static inline uint64_t rows_bytes(int32_t T, int64_t ld, int64_t w) { return (static_cast<uint64_t>(T - 1) * ld + w) * 2; }
+
 // Whether T rows of w halves, lda apart, share no byte with T rows of wb halves, ldb apart: ranges apart, or column
 // slices of one buffer side by side.
 static inline bool rows_apart(const void *a, int64_t lda, int64_t w, const void *b, int64_t ldb, int64_t wb, int32_t T)
 {
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
-    if (a0 + (static_cast<uint64_t>(T - 1) * lda + w) * 2 <= b0 || b0 + (static_cast<uint64_t>(T - 1) * ldb + wb) * 2 <= a0)
-        return true;
+    if (ranges_apart(a, rows_bytes(T, lda, w), b, rows_bytes(T, ldb, wb))) return true;
     if (lda != ldb) return false;
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
     const uint64_t pitch = static_cast<uint64_t>(lda) * 2;
     const uint64_t d = b0 >= a0 ? (b0 - a0) % pitch : (pitch - (a0 - b0) % pitch) % pitch;    // b's first column behind a's
     return d >= static_cast<uint64_t>(w) * 2 && d + static_cast<uint64_t>(wb) * 2 <= pitch;

@@ -1205,11 +1205,12 @@ extern "C" int mquant_w4a8_linear_prefill(const void *x, int64_t ldx, const int3
     int8_t *xq = static_cast<int8_t *>(workspace);
     int st = check_gemm_args(xq, wp, w_scale, y, ldy, T, N, K, n_vis, s_vis, s_txt);
     if (st != MQUANT_OK) return st;
-    // The smallest calls in one launch, whose work-groups read x while others write y already; a forced GEMM tile
-    // goes its own way.
+    // The smallest calls in one launch, whose work-groups read x and perm while others write y already; a forced GEMM
+    // tile goes its own way.
     const TuneState &tune = tune_state();
     if (small_linear_takes(T, N, K, had_block) && tune.gemm_tile.load(std::memory_order_relaxed) < 0 &&
-        tune.gemm_sliced.load(std::memory_order_relaxed) < 0 && rows_apart(x, ldx, K, y, ldy, N, T)) {
+        tune.gemm_sliced.load(std::memory_order_relaxed) < 0 && rows_apart(x, ldx, K, y, ldy, N, T) &&
+        (perm == nullptr || ranges_apart(perm, static_cast<uint64_t>(T) * 4, y, rows_bytes(T, ldy, N)))) {
         st = check_rotation_args(x, ldx, T, K, had_block);
         if (st != MQUANT_OK) return st;
         const double rb = sqrt(static_cast<double>(had_block));

@@ -331,6 +331,17 @@ def test_smallest_prefill_linear_in_place(mq):
     assert none(names), names
 
 
+def test_smallest_prefill_linear_over_its_index_vector(mq):
+    """An output in whose memory the index vector stands: it too is read completely first."""
+    o, x, run, _, none = small_linear_case(mq)
+    y = torch.empty(x.shape, dtype=torch.float16, device="cuda")
+    xd, permd = dev(x), y.view(-1)[-2 * x.shape[0]:].view(torch.int32)
+    permd.copy_(dev(o["perm"]))
+    check_y(run(xd, permd, y).cpu().numpy(), o["ref"], "over perm")
+    names = traced(lambda: run(xd, permd, y))
+    assert none(names), names
+
+
 @pytest.mark.parametrize("at,apart", [(512, True), (1024, True), (448, False), (8, False)])
 def test_smallest_prefill_linear_column_slices(mq, at, apart):
     """Input and output in columns of one buffer: one launch where they lie side by side."""
