@@ -264,6 +264,63 @@ __global__ __launch_bounds__(NT) void remap_mask_rows_kernel(
     }
 }
 
+// Long rows that are whole 16-byte chunks of the mask: one row after the other copied by all threads.  In the kernel above the
+// conditions of chunks that reach past the mask fill the scalar registers, so that a compute unit holds one work-group of
+// sixteen waves instead of two, and its rows take one chunk more; up to 16384 columns, where eight waves a work-group are enough, it is
+// ahead nevertheless.  us, kernel above / this one: T = 12000 63 / 86, 16384 129 / 146, 18448 168 / 159, 20480 264 / 186, 32768
+// 648 / 531, 37104 838 / 618, 65536 2570 / 1769, 80000 4392 / 2670.
+template <int R>
+__global__ __launch_bounds__(1024) void remap_mask_whole_rows_kernel(
+    const uint8_t *__restrict__ mask, uint8_t *__restrict__ mask_u,
+    const int32_t *__restrict__ perm, int32_t T)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t rows[];      // R rows of T bytes
+    const int tid = threadIdx.x;
+    for (int32_t i0 = blockIdx.x * R; i0 < T; i0 += gridDim.x * R) {
+        __syncthreads();                                                 // the previous rows are consumed
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (i0 + r < T) {                                            // uniform
+                int32_t pi = perm[i0 + r];
+                pi = (pi < 0 || pi >= T) ? 0 : pi;
+                const uint4 *src = reinterpret_cast<const uint4 *>(mask + static_cast<int64_t>(pi) * T);
+                for (int32_t c = tid; c < T / 16; c += 1024)
+                    *reinterpret_cast<uint4 *>(rows + r * T + c * 16) = src[c];
+            }
+        }
+        __syncthreads();
+        for (int32_t j0 = tid * 4; j0 < T; j0 += 4096) {
+            const int4 pj = *reinterpret_cast<const int4 *>(perm + j0);
+            int32_t p[4] = {pj.x, pj.y, pj.z, pj.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) p[q] = (p[q] < 0 || p[q] >= T) ? 0 : p[q];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (i0 + r < T) {
+                    const uint8_t *row = rows + r * T;
+                    const uint32_t x = static_cast<uint32_t>(row[p[0]]) | (static_cast<uint32_t>(row[p[1]]) << 8) |
+                                       (static_cast<uint32_t>(row[p[2]]) << 16) | (static_cast<uint32_t>(row[p[3]]) << 24);
+                    // every byte -> 1 if non-zero, else 0
+                    const uint32_t nz = ((((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u) >> 7;
+                    *reinterpret_cast<uint32_t *>(mask_u + static_cast<int64_t>(i0 + r) * T + j0) = nz;
+                }
+            }
+        }
+    }
+}
+
+int64_t remap_blocks(int32_t T, int R) { return ceil_div(T, R) < 8 * kNumCU ? ceil_div(T, R) : 8 * kNumCU; }
+
+template <int R>
+int launch_remap_whole_rows(const uint8_t *mask, uint8_t *mask_u, const int32_t *perm, int32_t T, hipStream_t stream)
+{
+    auto kern = remap_mask_whole_rows_kernel<R>;
+    static LdsLimit limit;
+    if (const int st = limit.raise(reinterpret_cast<const void *>(kern), kRemapMaxLds); st != MQUANT_OK) return st;
+    MQ_LAUNCH(kern, dim3(static_cast<unsigned>(remap_blocks(T, R))), dim3(1024), static_cast<size_t>(R) * T, stream, mask, mask_u, perm, T);
+    return launch_status();
+}
+
 // A row of any alignment, in whole 16-byte chunks.
 template <int R>
 size_t remap_lds_bytes(int32_t T)
@@ -279,9 +336,7 @@ int launch_remap_rows(const uint8_t *mask, uint8_t *mask_u, const int32_t *perm,
     auto launch = [&](auto kern, LdsLimit &limit) {
         if (lds > 64 * 1024)
             if (const int st = limit.raise(reinterpret_cast<const void *>(kern), kRemapMaxLds); st != MQUANT_OK) return st;
-        int64_t blocks = ceil_div(T, R);
-        if (blocks > 8 * kNumCU) blocks = 8 * kNumCU;
-        MQ_LAUNCH(kern, dim3(static_cast<unsigned>(blocks)), dim3(NT), lds, stream, mask, mask_u, perm, T, pitch);
+        MQ_LAUNCH(kern, dim3(static_cast<unsigned>(remap_blocks(T, R))), dim3(NT), lds, stream, mask, mask_u, perm, T, pitch);
         return launch_status();
     };
     static LdsLimit words, bytes;
@@ -321,10 +376,15 @@ extern "C" int mquant_aifs_remap_mask(const uint8_t *mask, uint8_t *mask_u, cons
     // Rows through LDS where a row is longer than what the caches answer the byte gather from at once; few rows of
     // few waves for a short mask, whose work-groups have to fill the chip.  us, byte gather / 2 rows, 256 threads / 4
     // rows, 512 threads: T = 512 2.1 / 2.4 / 2.7, 1003 3.8 / 4.2 / 4.7, 1024 3.0 / 3.0 / 3.3, 1281 6.8 / 4.9 / 5.3, 2048 6.7 / 5.1
-    // / 5.2, 2501 16.2 / 8.3 / 8.6, 3072 13.0 / 7.9 / 7.9, 6001 69.8 / 27.8 / 25.3, 8192 - / 35.4 / 29.8, 16384 - / 159 / 124.
+    // / 5.2, 2501 16.2 / 8.3 / 8.6, 3072 13.0 / 7.9 / 7.9, 6001 69.8 / 27.8 / 25.3, 8192 - / 35.4 / 29.8, 16384 - / 159 / 124, 20001
+    // 1562 / - / 242, 37107, one row and 1024 threads, 5900 / 1067.
     if (T > 1024 && T <= 144 * 1024) {
         hipStream_t hs = static_cast<hipStream_t>(stream);
         if (T < 2560) return launch_remap_rows<2, 256>(mask, mask_u, perm, T, hs);
+        if (T > 16384 && T % 16 == 0 && aligned_to(mask, 16)) {
+            if (4 * static_cast<int64_t>(T) <= 144 * 1024) return launch_remap_whole_rows<4>(mask, mask_u, perm, T, hs);
+            return launch_remap_whole_rows<1>(mask, mask_u, perm, T, hs);
+        }
         if (remap_lds_bytes<4>(T) <= kRemapMaxLds) return launch_remap_rows<4, 512>(mask, mask_u, perm, T, hs);
         return launch_remap_rows<1, 1024>(mask, mask_u, perm, T, hs);
     }

@@ -111,8 +111,8 @@ def test_aifs_remap_mask_small(mq, T, spans):
 @pytest.mark.parametrize("T,spans", [(1024, [(10, 300), (500, 24), (900, 124)]), (16, [(4, 8)]), (2064, [(0, 2064)]),
                                      (18448, [(100, 9000)])])
 def test_aifs_remap_mask_staged_rows(mq, T, spans):
-    """Lengths that are whole 16-byte chunks, most of them in the kernel that stages source rows in LDS;
-    any non-zero input byte means "may attend" and comes out as 1."""
+    """Lengths that are whole 16-byte chunks, by byte gather and through LDS; any non-zero input byte means "may
+    attend" and comes out as 1."""
     say(f"mask staged rows T={T}")
     rng = np.random.default_rng(T)
     perm, _, _ = orc.aifs_build_perm(T, spans)
@@ -122,10 +122,23 @@ def test_aifs_remap_mask_staged_rows(mq, T, spans):
     assert (got == want).all()
 
 
+def remap_kernel_of(T, offset):
+    words = "true" if T % 4 == 0 else "false"
+    if T <= 1024:
+        return "remap_mask_kernel"
+    if T < 2560:
+        return f"remap_mask_rows_kernel<2, 256, {words}>"
+    if T > 16384 and T % 16 == 0 and offset % 16 == 0:
+        return f"remap_mask_whole_rows_kernel<{4 if T <= 36864 else 1}>"
+    return f"remap_mask_rows_kernel<4, 512, {words}>" if T <= 37105 else f"remap_mask_rows_kernel<1, 1024, {words}>"
+
+
 # Lengths on either side of the lines between the forms, every T % 4 (where a row starts inside an output word) and
-# odd T (where a row starts inside a 16-byte chunk), a mask that starts inside one too; the last: one row per work-group.
+# odd T (where a row starts inside a 16-byte chunk), a mask that starts inside one too; one row per work-group from
+# 37106 on, from 36880 on where rows are whole chunks.
 @pytest.mark.parametrize("T,offset", [(1, 3), (17, 1), (1023, 5), (1024, 0), (1025, 0), (1026, 7), (1027, 15), (1028, 2), (2559, 9),
-                                      (2560, 0), (2561, 1), (2562, 0), (2563, 11), (37103, 0)])
+                                      (2560, 0), (2561, 1), (2562, 0), (2563, 11), (16384, 0), (16400, 0), (16400, 8), (36864, 0),
+                                      (36880, 0), (37103, 0), (37105, 0), (37107, 3), (37108, 0)])
 def test_aifs_remap_mask_any_length(mq, T, offset):
     say(f"mask remap T={T} offset={offset}")
     gen = torch.Generator(device="cuda").manual_seed(T)
@@ -141,6 +154,7 @@ def test_aifs_remap_mask_any_length(mq, T, offset):
         assert torch.equal(got[rows], (mask[cols[rows]][:, cols] != 0).to(torch.uint8))
     assert torch.equal(got[-1], (mask[cols[-1]][cols] != 0).to(torch.uint8))
     assert bool((out[:4] == 9).all()) and bool((out[-4:] == 9).all())
+    assert traced(lambda: mq.aifs_remap_mask(mask, perm, out=out[4:4 + T * T].view(T, T))) in (None, [remap_kernel_of(T, offset)])
 
 
 def test_aifs_remap_mask_config2(mq):
