@@ -8,7 +8,7 @@
 // stage order h = 1, 2, 4, ..., B/2, one fp32 add or subtract each, which is
 // what makes the int8 codes reproducible bit for bit.  HBM traffic is 2 bytes read and
 // 1 byte written per element; what bounds the kernel is the issue of vector instructions
-// (113 per segment and about 45 once per wave; T = 4096, K = 18944 52 -> 49 us, 4.75 TB/s, with
+// (113 per segment and about 45 once per wave; T = 4096, K = 18944 53.1 -> 48.7 us from HBM with
 // the exchanged stages of hadamard_segment.h and two rows to a wave).
 #include <hip/hip_fp16.h>
 #include <math.h>
@@ -136,11 +136,16 @@ int launch(const void *x, int64_t ldx, const int32_t *perm, int8_t *xq, int32_t 
 {
     const int32_t seg = B > 512 ? B : 512;
     const int32_t segs_per_row = static_cast<int32_t>(ceil_div(K, seg));
-    // Two rows to a wave where there are more waves than the compute units hold at a time (8 per SIMD): the second
-    // row's segment is on its way while the first is rotated.  One / two rows, K = 3584: T = 77 2.3 / 2.7 us, 1280
-    // 6.2 / 5.9, 4096 12.7 / 12.7; K = 18944: T = 77 3.4 / 3.7, 1280 19.0 / 18.3, 4096 51.0 / 48.9; B = 128: T = 16384, K = 8192
-    // 81.2 / 77.6; B = 1024, whose segments are twice as long: T = 4096, K = 8192 22.7 / 23.8.  Four rows gain nothing more.
-    const int64_t rows = B < 1024 && static_cast<int64_t>(T) * segs_per_row > 8 * 4 * kNumCU ? ceil_div(T, 2) : T;
+    // Two rows to a wave, the second one on its way while the first is rotated, where the input is too long to be in the caches: eight
+    // times the segments that the compute units hold waves for (8 per SIMD).  One / two rows from HBM, block 128: T = 4096, K =
+    // 18944 50.9 / 48.6 us, 16384 x 8192 87.3 / 82.3; block 512: 2048 x 18944 27.2 / 26.4, 9500 x 3584 24.9 / 24.4.  Shorter inputs are
+    // often still in the caches, where two rows lose, and some lose both ways: block 128, 1280 x 3584 6.1 / 5.4 from HBM and 3.9 / 4.2
+    // from the caches, 450 x 18944 8.3 / 8.8 and 5.7 / 5.9; block 512 6.1 / 5.7 and 4.3 / 4.6, 8.5 / 9.4 and 6.4 / 6.9.  The
+    // absmax statistic, whose waves wait for one atomic each, takes two as soon as a second round of waves would begin
+    // (1280 x 3584 118 / 60).  Segments of the block 1024 are twice as long (4096 x 8192 22.7 / 23.8).
+    const int64_t segs = static_cast<int64_t>(T) * segs_per_row, resident = 8 * 4 * kNumCU;
+    const bool two = B < 1024 && (ABSMAX ? segs > resident : B >= 64 && segs > 8 * resident);
+    const int64_t rows = two ? ceil_div(T, 2) : T;
     const int64_t gy = rows < 65535 ? rows : 65535;
     const dim3 grid(static_cast<unsigned>(ceil_div(segs_per_row, 4)), static_cast<unsigned>(gy)),
         block(256);

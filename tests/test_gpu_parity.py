@@ -209,11 +209,12 @@ def test_hadamard_quant_bit_exact(mq, T, K, B, V, use_perm):
     assert np.abs(want.astype(np.int32)).max() > 20          # the case is not degenerate
 
 
-# A wave takes two rows where there are more than 8192 segments of 512 channels: on both sides of the line, odd
-# numbers of rows, segments that end inside a wave (B = 128), every block size with an exchange across lanes; fp16
-# subnormals, whose first sums must not be flushed.
+# A wave takes two rows where there are more than 65536 segments of 512 channels, and where as many as the chip holds waves
+# (8192) end: on both sides of these, odd numbers of rows, segments that end inside a wave (B = 128), every block size with an
+# exchange across lanes; fp16 subnormals, whose first sums must not be flushed.
 @pytest.mark.parametrize("T,K,B", [(1170, 3584, 512), (1171, 3584, 512), (1367, 3200, 128), (2049, 2048 + 256, 256),
-                                   (1025, 5120, 1024), (8193, 64, 64), (8195, 8, 8)])
+                                   (1025, 5120, 1024), (8193, 64, 64), (8195, 8, 8),
+                                   (9362, 3584, 512), (9363, 3584, 512), (5043, 6528, 128), (65537, 64, 64), (65537, 32, 32)])
 def test_hadamard_quant_two_rows_to_a_wave(mq, T, K, B):
     say(f"hadamard rows T={T} K={K} B={B}")
     rng = np.random.default_rng(T + K)
