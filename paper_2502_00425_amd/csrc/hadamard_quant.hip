@@ -44,25 +44,38 @@ __global__ __launch_bounds__(256) void hadamard_quant_kernel(
             }
             return x + static_cast<int64_t>(src) * ldx;
         };
-        uint4 raw[Seg::C];
-        bool in_range[Seg::C];
-        auto request = [&](const __half *row) {
-#pragma unroll
-            for (int c = 0; c < Seg::C; ++c) raw[c] = Seg::template load_chunk<(B >= 512)>(row, sidx, c, K, lane, in_range[c]);
-        };
-        const int32_t step = gridDim.y;
-        if (static_cast<int32_t>(blockIdx.y) < T) request(row_of(blockIdx.y));
-        for (int32_t i = blockIdx.y; i < T; i += step) {
-            Seg sg;
-#pragma unroll
-            for (int c = 0; c < Seg::C; ++c) sg.set_chunk(c, raw[c], in_range[c]);
-            if (i + step < T) request(row_of(i + step));   // under the arithmetic of this row
-            sg.rotate(lane);
+        auto finish = [&](const Seg &sg, int32_t i) {
             if constexpr (ABSMAX) {
                 wave_max = sg.absmax(wave_max);
             } else {
                 sg.quant_store((i < n_vis) ? c_vis : c_txt, xq + static_cast<int64_t>(i) * K, sidx, lane,
                                q_lo, q_hi);
+            }
+        };
+        if constexpr (B >= 64) {
+            uint4 raw[Seg::C];
+            bool in_range[Seg::C];
+            auto request = [&](const __half *row) {
+#pragma unroll
+                for (int c = 0; c < Seg::C; ++c) raw[c] = Seg::template load_chunk<(B >= 512)>(row, sidx, c, K, lane, in_range[c]);
+            };
+            const int32_t step = gridDim.y;
+            if (static_cast<int32_t>(blockIdx.y) < T) request(row_of(blockIdx.y));
+            for (int32_t i = blockIdx.y; i < T; i += step) {
+                Seg sg;
+#pragma unroll
+                for (int c = 0; c < Seg::C; ++c) sg.set_chunk(c, raw[c], in_range[c]);
+                if (i + step < T) request(row_of(i + step));   // under the arithmetic of this row
+                sg.rotate(lane);
+                finish(sg, i);
+            }
+        } else {
+            // Small blocks: that code, and the grid's size known before the loop, cost more than they save (B = 8, T = 1280, K =
+            // 18944 12.7 / 13.4 us).
+            for (int32_t i = blockIdx.y; i < T; i += gridDim.y) {
+                Seg sg;
+                sg.load_rotate(row_of(i), sidx, K, lane);
+                finish(sg, i);
             }
         }
     }
