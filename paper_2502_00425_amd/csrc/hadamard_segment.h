@@ -252,12 +252,14 @@ struct Segment {
 
     __device__ __forceinline__ void load_rotate(const __half *row, int32_t sidx, int32_t K, int lane)
     {
+        // All chunks are requested before the first is converted: the conversion is inline assembly, which the
+        // second chunk's load does not move across (dynamic scales, B = 1024, 1280 x 18432 24.9 -> 21.9 us).
+        uint4 raw[C];
+        bool in_range[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            bool in_range;
-            const uint4 raw = load_chunk(row, sidx, c, K, lane, in_range);
-            set_chunk(c, raw, in_range);
-        }
+        for (int c = 0; c < C; ++c) raw[c] = load_chunk(row, sidx, c, K, lane, in_range[c]);
+#pragma unroll
+        for (int c = 0; c < C; ++c) set_chunk(c, raw[c], in_range[c]);
         rotate(lane);
     }
 
