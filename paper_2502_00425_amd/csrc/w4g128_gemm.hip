@@ -93,43 +93,38 @@ __device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t c
 // The channels 2 j, 2 j + 1 of a dword of prepacked weights as fp16(code * scale); s2 holds the scale in both
 // halves.  Both ways to the code are exact, the product is rounded once.  The odd pairs stay where they
 // are, four bits up: 0x6400 | code + 8 << 4 is 1024 + 16 (code + 8), a sixteenth of which is 64 + code + 8.  So
-// eight weights take one shift and twelve other operations.
+// eight weights take one shift and twelve other operations.  SHIFTED: every pair shifted into place, three shifts
+// and twelve operations, for kernels that wait for their loads and not for these: the GEMV of many tiles takes 3 to 8 %
+// longer with the other form (3584 -> 37888 at 8 rows 24.0 / 25.9 us), the GEMM's 32x32 tile 1 to 3 % (18944 -> 3584 at 16
+// rows 25.3 / 26.0).
 struct Unpack {
     uint32_t even = 0x000F000Fu, odd = 0x00F000F0u, magic = 0x64006400u;
     __device__ __forceinline__ Unpack()
     {
         asm volatile("" : "+v"(magic));       // keep it in a VGPR (third operand of v_and_or_b32)
     }
+    template <bool SHIFTED>
     __device__ __forceinline__ uint32_t pair(uint32_t v, int j, v2h s2) const
     {
         const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
         const v2h sixteenth = {static_cast<_Float16>(0.0625f), static_cast<_Float16>(0.0625f)};
         const v2h bias_odd = {static_cast<_Float16>(-72.0f), static_cast<_Float16>(-72.0f)};
-        const uint32_t t = j >= 2 ? v >> 8 : v;
         v2h code;
-        if (j & 1) code = __builtin_elementwise_fma(__builtin_bit_cast(v2h, and_or(t, odd, magic)), sixteenth, bias_odd);
-        else code = __builtin_bit_cast(v2h, and_or(t, even, magic)) - bias;
+        if (SHIFTED) {
+            code = __builtin_bit_cast(v2h, and_or(v >> (4 * j), even, magic)) - bias;
+        } else {
+            const uint32_t t = j >= 2 ? v >> 8 : v;
+            if (j & 1) code = __builtin_elementwise_fma(__builtin_bit_cast(v2h, and_or(t, odd, magic)), sixteenth, bias_odd);
+            else code = __builtin_bit_cast(v2h, and_or(t, even, magic)) - bias;
+        }
         return __builtin_bit_cast(uint32_t, code * s2);
     }
+    template <bool SHIFTED>
     __device__ __forceinline__ v4u eight(uint32_t v, v2h s2) const
     {
         v4u out;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = pair(v, j, s2);
-        return out;
-    }
-    // The same with every pair shifted into place, three shifts and twelve operations: the GEMV of many tiles,
-    // which waits for its loads and not for these, takes 3 to 8 % longer with the other form (3584 ->
-    // 37888 at 8 rows 24.0 / 25.9 us).
-    __device__ __forceinline__ v4u eight_shifted(uint32_t v, v2h s2) const
-    {
-        v4u out;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
-            const v2h h = __builtin_bit_cast(v2h, and_or(v >> (4 * j), even, magic));
-            out[j] = __builtin_bit_cast(uint32_t, (h - bias) * s2);
-        }
+        for (int j = 0; j < 4; ++j) out[j] = pair<SHIFTED>(v, j, s2);
         return out;
     }
 };
@@ -256,6 +251,7 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
         for (int r = 0; r < 16; ++r) acc[mt][r] = 0.0f;
 
     const Unpack unpack;
+    constexpr bool kShifted = MT == 1 && NWN == 1;
 
     // fragment (st, mt): chunk g * 4 + st of row mt * 32 + l32 of this wave's slab
     const uint32_t a_lane = ks * G::A_SLAB + l32 * 128 + (((g * 4) ^ ((l32 >> 1) & 7)) << 4);
@@ -290,7 +286,7 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
     for (int i = 0; i < kWin; ++i) fr[i] = afrag(0, i / MT, i % MT);
     v4u bf[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bf[0][j] = unpack.pair(bw[0], j, s2);
+    for (int j = 0; j < 4; ++j) bf[0][j] = unpack.pair<kShifted>(bw[0], j, s2);
 
     // A wave whose slice ends a stage early (K / 64 not a multiple of KS) leaves the loop one
     // stage early; there is no barrier in the last stage.
@@ -336,7 +332,7 @@ __global__ __launch_bounds__(512, (g128_lds_bytes<MT, NWN, NB>() <= 80 * 1024 ? 
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if ((MT >= 4 ? MT - 4 + j : j * MT / 4) == mt)
-                    bf[(st + 1) & 1][j] = unpack.pair(st < 3 ? bw[(st + 1) & 3] : bw_n[0], j, st < 3 ? s2 : s2_n);
+                    bf[(st + 1) & 1][j] = unpack.pair<kShifted>(st < 3 ? bw[(st + 1) & 3] : bw_n[0], j, st < 3 ? s2 : s2_n);
             __builtin_amdgcn_sched_barrier(0);
         }
         bw = bw_n;
@@ -467,7 +463,7 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_kernel(
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 const uint32_t code = live ? b[u][st] : 0x88888888u;
-                const v8h bf = __builtin_bit_cast(v8h, KT == 1 ? unpack.eight_shifted(code, s2) : unpack.eight(code, s2));
+                const v8h bf = __builtin_bit_cast(v8h, unpack.eight<KT == 1>(code, s2));
                 const v8h af = __builtin_bit_cast(v8h, a[u][st]);
                 if (st & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc1, 0, 0, 0);
                 else acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc0, 0, 0, 0);
@@ -551,7 +547,7 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_half_kernel(
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 const v8h af = *reinterpret_cast<const v8h *>(xlane + (base + j) * (kGroup * 2) + st * 16);
-                const v8h bf = __builtin_bit_cast(v8h, unpack.eight(bw[st], s2));
+                const v8h bf = __builtin_bit_cast(v8h, unpack.eight<false>(bw[st], s2));
                 acc[st & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, bf, acc[st & 1], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
