@@ -27,6 +27,7 @@
 #include <hip/hip_fp16.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "lds_dma.h"
 #include "mquant_internal.h"
@@ -437,42 +438,49 @@ __global__ __launch_bounds__(NWAVES * 64) void w4g128_gemv_kernel(
     const __half *scol = sT + ntile * kPackN + l32;
     const Unpack unpack;
 
-    for (int32_t base = kt_begin; base < kt_end; base += KT) {
-        v4u a[KT][4], b[KT];
-        uint16_t sc[KT];
+    auto walk = [&](auto shifted) {
+        for (int32_t base = kt_begin; base < kt_end; base += KT) {
+            v4u a[KT][4], b[KT];
+            uint16_t sc[KT];
 #pragma unroll
-        for (int u = 0; u < KT; ++u) {
-            int32_t kt = base + u;
-            kt = kt < kt_end ? kt : kt_end - 1;
+            for (int u = 0; u < KT; ++u) {
+                int32_t kt = base + u;
+                kt = kt < kt_end ? kt : kt_end - 1;
 #pragma unroll
-            for (int st = 0; st < 4; ++st)
-                a[u][st] = *reinterpret_cast<const v4u *>(xrow + kt * kPackK + st * 8);
-        }
-#pragma unroll
-        for (int u = 0; u < KT; ++u) {
-            int32_t kt = base + u;
-            kt = kt < kt_end ? kt : kt_end - 1;
-            b[u] = __builtin_nontemporal_load(wtile + static_cast<int64_t>(kt) * 64);
-            sc[u] = __builtin_bit_cast(uint16_t, scol[static_cast<int64_t>(kt / 2) * n_pad]);
-        }
-#pragma unroll
-        for (int u = 0; u < KT; ++u) {
-            const bool live = base + u < kt_end;                     // wave-uniform
-            const _Float16 sv = __builtin_bit_cast(_Float16, sc[u]);
-            const v2h s2 = {sv, sv};
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                const uint32_t code = live ? b[u][st] : 0x88888888u;
-                const v8h bf = __builtin_bit_cast(v8h, unpack.eight<KT == 1>(code, s2));
-                const v8h af = __builtin_bit_cast(v8h, a[u][st]);
-                if (st & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc1, 0, 0, 0);
-                else acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc0, 0, 0, 0);
+                for (int st = 0; st < 4; ++st)
+                    a[u][st] = *reinterpret_cast<const v4u *>(xrow + kt * kPackK + st * 8);
             }
+#pragma unroll
+            for (int u = 0; u < KT; ++u) {
+                int32_t kt = base + u;
+                kt = kt < kt_end ? kt : kt_end - 1;
+                b[u] = __builtin_nontemporal_load(wtile + static_cast<int64_t>(kt) * 64);
+                sc[u] = __builtin_bit_cast(uint16_t, scol[static_cast<int64_t>(kt / 2) * n_pad]);
+            }
+#pragma unroll
+            for (int u = 0; u < KT; ++u) {
+                const bool live = base + u < kt_end;                     // wave-uniform
+                const _Float16 sv = __builtin_bit_cast(_Float16, sc[u]);
+                const v2h s2 = {sv, sv};
+#pragma unroll
+                for (int st = 0; st < 4; ++st) {
+                    const uint32_t code = live ? b[u][st] : 0x88888888u;
+                    const v8h bf = __builtin_bit_cast(v8h, unpack.eight<decltype(shifted)::value>(code, s2));
+                    const v8h af = __builtin_bit_cast(v8h, a[u][st]);
+                    if (st & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc1, 0, 0, 0);
+                    else acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc0, 0, 0, 0);
+                }
+            }
+            // all memory reads of the batch first, then the arithmetic
+            __builtin_amdgcn_sched_group_barrier(0x020, 6 * KT, 0);
+            __builtin_amdgcn_sched_group_barrier(0x00A, 20 * 4 * KT, 0);
         }
-        // all memory reads of the batch first, then the arithmetic
-        __builtin_amdgcn_sched_group_barrier(0x020, 6 * KT, 0);
-        __builtin_amdgcn_sched_group_barrier(0x00A, 20 * 4 * KT, 0);
-    }
+    };
+    // The form of the conversion (Unpack).  Sixteen waves over 3584 -> 3584, 18944 -> 3584 and 29568 -> 8192, one shift / three:
+    // 8 rows 6.5 / 7.2 us, 24.0 / 24.7, 40.6 / 40.8; 12 rows 7.1 / 7.6, 27.6 / 27.1, 44.6 / 42.9: from eleven rows on a long K waits for
+    // the activations as well.  The sides meet between K = 8192 (12 rows 13.0 / 13.4) and 11008 (18.0 / 17.7).
+    if (KT == 1 || (T > 10 && K > 10240)) walk(std::true_type{});
+    else walk(std::false_type{});
 
     const int rmax = T <= 8 ? 4 : (T <= 16 ? 8 : 16);     // accumulator registers that can hold a row < T
 #pragma unroll
