@@ -23,11 +23,9 @@ using namespace mquant;
 namespace {
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kHeadDim = 128;          // the only head size built (28 x 128, 64 x 128 in the paper's models)
 constexpr int kBQ = 128;               // queries per work-group (32 per wave)
@@ -220,7 +218,7 @@ __global__ __launch_bounds__(256) void vt_kernel(const __half *__restrict__ v, i
 // tiles those are is three 64-bit masks per 64 tiles, so that walking them takes scalar arithmetic only
 // (a scalar load per tile for its bounds, in flight across the step, turned the waits for single fragments
 // into waits for everything).
-// What bounds it: at T = 8192 (28 heads on 4, 526 -> 486 us with the masks, flags and pipeline below) matrix and
+// What bounds it: at T = 8192 (28 heads on 4, 514 -> 485 us with the masks, flags and pipeline below) matrix and
 // vector pipes, each busy half of the time at a clock that power holds at 1.8 GHz; at T = 1280 (39.8 -> 27.8 us) the
 // longest work-group (20 key tiles: 2.1 us for two tiles of two key groups, of which the matrix products are 1.0)
 // and 8 us that launch, prologue and epilogue take at any T.  Measured without gain: the two key groups half a
@@ -841,7 +839,10 @@ extern "C" int mquant_aifs_attention(const void *q, int64_t ldq, const void *k, 
         // 8.3 / 8.5 us; 256, 56 11.9 / 12.0; 512, 112 16.6 / 15.9; 1003, 224 27.5 / 24.1; 1280, 280 33.6 / 27.8; 1408, 308
         // 37.7 / 34.6; 1792, 392 46.2 / 44.1; 2048, 448 53.0 / 50.1; 2500, 560 70.8 / 79.6; 64 heads: 512, 256 17.0 / 16.3; 640,
         // 320 22.9 / 24.7; 1003, 512 33.5 / 40.1.  Beyond one round of work-groups it takes long ones to make up for the
-        // second prologue.
+        // second prologue, and where the line lies depends on the layout too.  Text only / one visual span / three: 28 heads, T =
+        // 1281, 308 33.7 / 34.2 / 35.1 against 28.1 / 33.2 / 32.2; 32 heads, 1281, 352 33.6 / 34.2 / 35.4 against 28.8 / 34.9 / 34.7;
+        // 40 heads, 960, 320 26.1 / 29.3 / 29.6 against 25.0 / 31.7 / 31.7; 1280, 400 34.9 / 35.8 / 36.7 against 32.8 / 39.0 / 38.9; 1281,
+        // 440 35.4 / 36.2 / 37.2 against 37.4 / 42.4 / 41.2.
         const bool two = n_tiles > 4 && (items <= kNumCU + kNumCU / 8 || (items <= 2 * kNumCU - kNumCU / 4 && n_tiles >= 22));
         auto launch = two ? launch_attention<2, false> : launch_attention<1, false>;
         return launch(qh, ldq, kh, ldk, vh, ldv, oh, ldo, pos, nullptr, nullptr, T, group, n_kv_heads, groups, xcds_per_kv,

@@ -10,7 +10,6 @@
 
 namespace mquant {
 
-typedef const void __attribute__((address_space(1))) *global_ptr_t;
 typedef void __attribute__((address_space(3))) *lds_ptr_t;
 
 // 16 bytes per lane, global -> LDS: a wave-uniform 64-bit base (kept in scalar registers) plus a 32-bit

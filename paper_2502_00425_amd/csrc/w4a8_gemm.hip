@@ -904,16 +904,18 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 
 // The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 14.5 %
 // where the tiles above fill the chip: in a continuous run the clock is lower than in the sweep's short
-// bursts, the large tiles have got faster since the sweep (scalar addresses), and the sliced 64x256 tile, which reads each
-// activation fragment from LDS for one MFMA instead of two, falls behind its estimate.  One linear at a time
+// bursts, the large tiles have got faster since the sweep (kPrefillCost and the efficiencies of pick_gemm_tile are
+// those of the kernel before its scalar addresses), and the sliced 64x256 tile, which reads each activation fragment from
+// LDS for one MFMA instead of two, falls behind its estimate.  No margin separates them: one linear at a time
 // switched from its sliced tile to the plan in continuous passes over the four projections, estimated share of the
 // plan's time and change of the pass in us: 7B, T = 850: qkv 0.77 +1.2, down (split-K) 0.89 +1.3; T = 2400: o 0.84 +2.0; T =
 // 2700: down 0.83 +6.1; T = 3000, 3072, 3300: down 0.86 -8.9, -13.0, -4.2; 72B, T = 160: gate_up 0.85 -9.5; T = 1100: o
 // 0.81 +4.3; T = 1200: o 0.87 -6.2, down 0.82 +4.4; T = 1400: o 0.88 +5.6, down 0.85 +3.7; T = 1500: down 0.86 -12.0; T = 2200:
 // o 0.88 -13.9, down 0.85 -14.0; T = 2300: down 0.86 -8.7.  And from the plan to the sliced tile: 7B, T = 1280: qkv 0.96
 // +3.6, o 0.95 +1.1; T = 2048: qkv 0.90 +3.1; 72B, T = 180: gate_up 0.89 +9.2.
-// Whole passes at 0.88 / 0.855: 7B, T = 3000 698.5 / 690, 3300 754 / 746; 72B, T = 1500 1141 / 1135, 2300 1712.5 / 1698.5, 1280
-// 1007 / 1010; at 0.845 T = 1400 loses 10.
+// Of the passes that 0.855 decides otherwise than 0.88 (medians; the runs of one side differ by 1 to 2 %): 7B, T = 3000 694 /
+// 682, 3072 699 / 691, 3300 747 / 745; 72B, T = 1003 775 / 784, 1200 980 / 990, 1280 1009 / 1008, 1350 1073 / 1065, 1400 1073 / 1070,
+// 1500 1141 / 1128, 1792 1287 / 1271, 2200 1703 / 1703, 2300 1718 / 1695; at 0.845 T = 1400 loses 10.
 bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
