@@ -198,9 +198,12 @@ def test_few_rows_in_half_tiles(mq, T, N, K, waves):
     (13, 1003, 128, "w4g128_gemv_kernel<16, 2>"), (20, 1003, 128, "w4g128_gemv_kernel<16, 2>"),
     (17, 18951, 256, "w4g128_gemv_kernel<8, 1>"), (25, 18951, 256, "w4g128_gemv_kernel<8, 1>"),
     (32, 16392, 512, "w4g128_gemv_kernel<8, 1>"), (13, 200, 2176, "w4g128_gemm_kernel<1, 1, 3>"),
+    (10, 40, 10368, "w4g128_gemv_kernel<16, 2>"), (11, 40, 10240, "w4g128_gemv_kernel<16, 2>"),     # one conversion
+    (11, 40, 10368, "w4g128_gemv_kernel<16, 2>"), (12, 72, 18944, "w4g128_gemv_kernel<16, 2>"),     # the other
 ])
 def test_rows_between_gemv_and_gemm(mq, T, N, K, name):
-    """13 to 32 rows on both GEMV forms, every result register that can hold a row, and on the GEMM."""
+    """13 to 32 rows on both GEMV forms, every result register that can hold a row, and on the GEMM; both sides of
+    the line from which on the GEMV unpacks long K the other way."""
     rng = np.random.default_rng(T * 13 + N + K)
     wq, sc = make_weight(rng, N, K)
     x = (rng.standard_normal((T, K)) * 1.5).astype(np.float16)
