@@ -916,12 +916,16 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 // Of the passes that 0.855 decides otherwise than 0.88 (medians; the runs of one side differ by 1 to 2 %): 7B, T = 3000 694 /
 // 682, 3072 699 / 691, 3300 747 / 745; 72B, T = 1003 775 / 784, 1200 980 / 990, 1280 1009 / 1008, 1350 1073 / 1065, 1400 1073 / 1070,
 // 1500 1141 / 1128, 1792 1287 / 1271, 2200 1703 / 1703, 2300 1718 / 1695; at 0.845 T = 1400 loses 10.
-bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
+// With more than three flagged channels it is 12 %: their terms, which no estimate holds, cost the large tiles several times
+// what they cost the sliced ones.  Passes with n flagged channels on down at 0.88 / 0.855: 7B, T = 3000, n = 1, 3, 4, 8, 37 808 / 739,
+// 809 / 795, 816 / 826, 826 / 947, 874 / 1727; 72B, T = 1500, n = 1, 4, 8, 16, 37 1287 / 1178, 1301 / 1249, 1309 / 1362, 1336 / 1601,
+// 1352 / 2221.
+bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp, int32_t n_split)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(T, K, grp) < (full ? 0.855 : 0.94) * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(T, K, grp) < (full ? (n_split > 3 ? 0.88 : 0.855) : 0.94) * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
@@ -1090,7 +1094,7 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     // The sliced GEMM on few tiles (T = 128: 3584 x 4608 17.1 -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1
     // -> 15.9; T = 512: 22.8 -> 16.2 on 3584 x 4608) and wherever else it is expected to be ahead.
     const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
-    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp))))
+    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp, ep.n_split))))
         return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
     if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,

@@ -2,6 +2,7 @@
 wrong side of a line was measured clearly slower.  Names come from a trace of the call."""
 import sys
 
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -104,3 +105,19 @@ def test_w4a8_decode_rows_above_sixteen(mq, T, N, K, name):
     wp = torch.zeros(mq.w4_prepacked_bytes(N, K), dtype=torch.uint8, device="cuda")
     lin = [(wp, torch.ones(N, dtype=torch.float16, device="cuda"), N, torch.empty((T, N), dtype=torch.float16, device="cuda"))]
     assert kernels(lambda: mq.w4a8_gemv_grouped(xq, lin, 0, 1.0, 1.0)) == got
+
+
+@pytest.mark.parametrize("T,N,K", [(3000, 3584, 18944), (1500, 8192, 29568)])
+def test_many_flagged_channels_stay_on_the_sliced_gemm(mq, T, N, K):
+    """Where the large tiles take a linear by a narrow margin, four flagged channels lose it in their epilogue (7B pass
+    with 3, 4, 8, 37 channels: 795, 826, 947, 1727 us on large tiles, 809, 816, 826, 874 on sliced ones)."""
+    say(f"flagged channels T={T} N={N} K={K}")
+    xq = torch.zeros((T, K), dtype=torch.int8, device="cuda")
+    wp = torch.zeros(mq.w4_prepacked_bytes(N, K), dtype=torch.uint8, device="cuda")
+    ws = torch.ones(N, dtype=torch.float16, device="cuda")
+    y = torch.empty((T, N), dtype=torch.float16, device="cuda")
+    wk = torch.empty(max(mq.w4a8_workspace_bytes(T, N, K), 256), dtype=torch.uint8, device="cuda")
+    for n, name in ((3, "w4a8_gemm_kernel<"), (4, "w4a8_sliced_kernel<")):
+        split = np.arange(n, dtype=np.int32), torch.zeros((n, N), dtype=torch.int8, device="cuda"), np.ones(n, dtype=np.float32)
+        got = kernels(lambda: mq.w4a8_gemm_rms(xq, wp, ws, N, 0, 1.0, 1.0, *split, out=y, workspace=wk))
+        assert len(got) == 1 and got[0].startswith(name), (n, got)
