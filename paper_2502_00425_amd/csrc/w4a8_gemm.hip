@@ -902,30 +902,24 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
     return c.us(static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn), K);
 }
 
-// The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 14.5 %
+// The sliced GEMM has to be expected this far ahead.  6 % covers the error of the two estimates; 12 %
 // where the tiles above fill the chip: in a continuous run the clock is lower than in the sweep's short
-// bursts, the large tiles have got faster since the sweep (kPrefillCost and the efficiencies of pick_gemm_tile are
-// those of the kernel before its scalar addresses), and the sliced 64x256 tile, which reads each activation fragment from
-// LDS for one MFMA instead of two, falls behind its estimate.  No margin separates them: one linear at a time
-// switched from its sliced tile to the plan in continuous passes over the four projections, estimated share of the
-// plan's time and change of the pass in us: 7B, T = 850: qkv 0.77 +1.2, down (split-K) 0.89 +1.3; T = 2400: o 0.84 +2.0; T =
-// 2700: down 0.83 +6.1; T = 3000, 3072, 3300: down 0.86 -8.9, -13.0, -4.2; 72B, T = 160: gate_up 0.85 -9.5; T = 1100: o
-// 0.81 +4.3; T = 1200: o 0.87 -6.2, down 0.82 +4.4; T = 1400: o 0.88 +5.6, down 0.85 +3.7; T = 1500: down 0.86 -12.0; T = 2200:
-// o 0.88 -13.9, down 0.85 -14.0; T = 2300: down 0.86 -8.7.  And from the plan to the sliced tile: 7B, T = 1280: qkv 0.96
-// +3.6, o 0.95 +1.1; T = 2048: qkv 0.90 +3.1; 72B, T = 180: gate_up 0.89 +9.2.
-// Of the passes that 0.855 decides otherwise than 0.88 (medians; the runs of one side differ by 1 to 2 %): 7B, T = 3000 694 /
-// 682, 3072 699 / 691, 3300 747 / 745; 72B, T = 1003 775 / 784, 1200 980 / 990, 1280 1009 / 1008, 1350 1073 / 1065, 1400 1073 / 1070,
-// 1500 1141 / 1128, 1792 1287 / 1271, 2200 1703 / 1703, 2300 1718 / 1695; at 0.845 T = 1400 loses 10.
-// With more than three flagged channels it is 12 %: their terms, which no estimate holds, cost the large tiles several times
-// what they cost the sliced ones.  Passes with n flagged channels on down at 0.88 / 0.855: 7B, T = 3000, n = 1, 3, 4, 8, 37 808 / 739,
-// 809 / 795, 816 / 826, 826 / 947, 874 / 1727; 72B, T = 1500, n = 1, 4, 8, 16, 37 1287 / 1178, 1301 / 1249, 1309 / 1362, 1336 / 1601,
-// 1352 / 2221.
-bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp, int32_t n_split)
+// bursts, and the sliced 64x256 tile, which reads each activation fragment from LDS for one MFMA instead
+// of two, falls behind its estimate.  One linear at a time switched to its sliced tile in continuous
+// passes over the four projections, estimated share of the plan's time and change of the pass: 7B, T =
+// 1003: o 0.76 -4.6 us, down (split-K) 0.88 -8.7; T = 1280: qkv 0.96 +1.7, o 0.95 -1.2, down (split-K) 0.95
+// +0.4; T = 2048: qkv 0.90 +8.2, o 0.95 +3.7; T = 3000: o 0.90 +5.6, down 0.87 -13.4; 72B, T = 1003: qkv 0.87
+// -8.3; T = 1500: down 0.86 -38.7; T = 2048: qkv 0.92 +5.0.
+// The large tiles have got faster since (scalar addresses; kPrefillCost and the efficiencies of pick_gemm_tile are
+// those from before), but 14.5 % was not sound: on 45 shapes drawn from those that the two margins decide differently, static
+// scales take 0.946 to 1.12 of the time with it (0.997 on average), per-row scales up to 1.44, one flagged channel 0.72 to 2.1,
+// three 0.81 to 2.9; the estimates hold neither short K nor what the epilogues cost the large tiles, most of all at odd N.
+bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(T, K, grp) < (full ? (n_split > 3 ? 0.88 : 0.855) : 0.94) * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(T, K, grp) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
@@ -1094,7 +1088,7 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     // The sliced GEMM on few tiles (T = 128: 3584 x 4608 17.1 -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1
     // -> 15.9; T = 512: 22.8 -> 16.2 on 3584 x 4608) and wherever else it is expected to be ahead.
     const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
-    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp, ep.n_split))))
+    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp))))
         return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
     if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,
