@@ -27,6 +27,13 @@ __device__ __forceinline__ void unpack_w4x16(const uint4 p, v4i &b0, v4i &b1)
     b1[3] = static_cast<int>(p.w & 0xF0F0F0F0u);
 }
 
+// Uses of v stay behind this point, and with them the wait for the load that brings it: the compiler
+// otherwise unpacks all register sets of a rolling pipeline at the top of its loop, which drains it.
+__device__ __forceinline__ void hold(uint4 &v)
+{
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+}
+
 __device__ __forceinline__ v4i as_v4i(const uint4 u)
 {
     v4i r;
@@ -177,5 +184,9 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
 
 // What its cost model expects of the tile it would pick.
 double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp);
+
+// ---- the GEMV of w4a8_walk.hip, one work-group per compute unit: several rows on many output channels
+bool gemv_walk_takes(int32_t T, int32_t K, GemvGroup grp);
+int gemv_walk_dispatch(const int8_t *xq, int32_t T, int32_t K, GemvGroup grp, const Epilogue &ep, hipStream_t stream);
 
 }  // namespace mquant

@@ -1075,6 +1075,8 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     grp.p[0].N = N;
     const bool force_sliced = tune_state().gemm_sliced.load(std::memory_order_relaxed) >= 0 && K % 128 == 0;
     if (!force_sliced) {
+        if constexpr (EPI == kEpiStatic)
+            if (gemv_walk_takes(T, K, grp)) return gemv_walk_dispatch(xq, T, K, grp, ep, stream);
         if (gemv_stream_takes(T, K, ceil_div(N, kPackN)))
             return gemv_stream_dispatch<EPI>(xq, T, K, grp, ep, stream);
         if (!gemm_takes(T, K, grp)) return gemv_tile_dispatch<EPI>(xq, T, K, grp, ep, stream);

@@ -603,6 +603,8 @@ extern "C" int mquant_w4a8_gemv_grouped(const int8_t *xq, int32_t T, int32_t K, 
     // outside the streaming kernels' range: the sliced GEMM or the tile kernel, still one launch
     // for the group
     const bool force_sliced = tune_state().gemm_sliced.load(std::memory_order_relaxed) >= 0 && K % 128 == 0;
+    if (!force_sliced && gemv_walk_takes(T, K, grp))
+        return gemv_walk_dispatch(xq, T, K, grp, ep, static_cast<hipStream_t>(stream));
     if (force_sliced || gemm_takes(T, K, grp))
         return sliced_dispatch<kEpiStatic>(xq, T, K, grp, ep, static_cast<hipStream_t>(stream));
     if (!gemv_stream_takes(T, K, group_tiles))

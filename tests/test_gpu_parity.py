@@ -558,6 +558,40 @@ def test_gemv_grouped_equals_the_oracle_per_linear(mq, T, K, Ns):
         assert bool((buf[:, N:] == 3.0).all())
 
 
+@pytest.mark.parametrize("T,K,Ns", [
+    (9, 2048, (24600,)), (16, 2048, (12296, 12280)),      # the last unit half a tile; two linears
+    (17, 2048, (24584,)), (32, 2176, (40, 16392, 8296)),  # two row blocks; waves' shares of 17 loads a unit
+    (3, 8192, (8208,)), (5, 6144, (8208,)),               # two units and three per work-group, the least loads
+    (12, 12288, (8208,)), (32, 4352, (49160,)),           # the most bytes of xq; two rounds of work-groups
+])
+def test_gemv_walk_equals_the_oracle(mq, T, K, Ns):
+    """Several rows on many output channels, a work-group per compute unit: every output of every linear, bit for
+    bit, untouched padding, and the accumulators through the single-linear entry."""
+    say(f"walk gemv T={T} K={K} Ns={Ns}")
+    rng = np.random.default_rng(T * 1000 + K + sum(Ns))
+    xq = rng.integers(-128, 128, size=(T, K), dtype=np.int8)
+    V, s_vis, s_txt = min(T, 2), 0.21, 0.034
+    lin, want, accs = [], [], []
+    for N in Ns:
+        packed = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+        w_scale = rng.uniform(0.005, 0.02, size=N).astype(np.float16)
+        out = torch.full((T, N + 8), 3.0, dtype=torch.float16, device="cuda")
+        lin.append((mq.w4_prepack(dev(packed)), dev(w_scale), N, out[:, :N]))
+        accs.append(orc.gemm_i8_i4_i32(xq, orc.unpack_w4(packed)))
+        want.append(orc.dequant(accs[-1], V, s_vis, s_txt, w_scale)[1])
+    xqd = dev(xq)
+    names = traced(lambda: mq.w4a8_gemv_grouped(xqd, lin, V, s_vis, s_txt))
+    assert names is None or (len(names) == 1 and names[0].startswith(f"w4a8_gemv_kernel<{6 if T <= 16 else 3}, ")
+                             and names[0].count(",") == 3), names
+    for (_, _, N, out), w in zip(lin, want):
+        assert (out.cpu().numpy().view(np.uint16) == w.view(np.uint16)).all(), f"N={N}"
+        assert bool((out._base[:, N:] == 3.0).all())
+    wp, ws, N, out = lin[-1]
+    acc = torch.full((T, N), -7, dtype=torch.int32, device="cuda")
+    y = mq.w4a8_gemm(xqd, wp, ws, N, V, s_vis, s_txt, acc_out=acc)
+    assert (acc.cpu().numpy() == accs[-1]).all() and torch.equal(y, out)
+
+
 @pytest.mark.parametrize("T,N,K", [(5, 200, 1024), (8, 72, 128), (11, 3584, 3584), (16, 520, 18944), (13, 16416, 256),
                                    (16, 18944, 384), (4, 264, 29568), (9, 40, 640)])
 def test_gemv_streamed_rows_full(mq, T, N, K):
