@@ -506,7 +506,8 @@ typedef enum {
     MQUANT_TUNE_GEMM_SHAPE = 5      /* -1 = cost model; else any number of rows (K % 128 == 0) goes to this tile
                                        of the K-sliced W4A8 GEMM: 0 = 64x128, 1 = 64x256, 2 = 192x128, 3 = 160x128,
                                        4 = 128x128, 5 = 96x128, 6 = 128x64, 7 = 64x64, 8 and 9 = 32x64
-                                       (two and three stages), 10 = 32x32 */
+                                       (two and three stages), 10 = 32x32, 11 = 64x128 and 12 = 96x128 with four
+                                       stages, 13 = 96x256, 14 = 128x256 */
 } mquant_tune_key_t;
 
 /*

@@ -28,8 +28,14 @@ struct SlicedTile {
     static constexpr int WIN = MT > 1 ? 4 : 2;        // A fragments requested ahead of the MFMA that uses them
     static constexpr int A_SLAB = MT * 32 * 128;
     static constexpr int B_OFF = KS * A_SLAB, STAGE = B_OFF + 8 * 2048;
-    static constexpr int CHA = MT * KS / 2;           // 1 KiB activation blocks a wave copies per stage
+    static constexpr int CHA = (MT * KS + 1) / 2;     // 1 KiB activation blocks a wave copies per stage
     static constexpr int PER = CHA + 2;               // ... and its two weight tiles
+    // Activation block i of a wave.  Where the blocks are an odd multiple of four, two waves copy each block of the
+    // last round (the same bytes to the same place), so that every wave counts the same copies.
+    static __device__ __forceinline__ int a_block(int wave, int i)
+    {
+        return ((MT * KS) % 2 != 0 && i == CHA - 1 ? wave % 4 : wave) + 8 * i;
+    }
     static constexpr int RED = NWN * MT * 4 * (KS - 1) * 1024;   // slice sums in transit
     static constexpr int CODES = RED + 8 * 32 * 80;              // ... after them the store patches
     static constexpr int SPLIT_W = CODES + kMaxSplitChannels * MT * 32;   // flagged codes [j][row], weights [j][column]
@@ -37,7 +43,6 @@ struct SlicedTile {
     {
         return epi == kEpiSplit ? SPLIT_W + kMaxSplitChannels * NWN * 32 : CODES;
     }
-    static_assert((MT * KS) % 2 == 0, "blocks must divide evenly over the waves");
 };
 
 template <int MT, int NWN, int NB, int EPI>
@@ -61,6 +66,18 @@ __device__ __forceinline__ void tile_of_group(int32_t id, int32_t tiles_m, int32
     const int32_t rows = (tiles_m - b * band) < band ? (tiles_m - b * band) : band;
     tm = b * band + in_band % rows;
     tn = in_band / rows;
+}
+
+// Waits until at most `left` stages, and no more than MOST, of PER copies each are still on their way.
+template <int MOST, int PER>
+__device__ __forceinline__ void wait_stages(int32_t left)
+{
+    if constexpr (MOST <= 0) {
+        wait_vmcnt<0>();
+    } else {
+        if (left >= MOST) wait_vmcnt<MOST * PER>();
+        else wait_stages<MOST - 1, PER>(left);
+    }
 }
 
 // Several linears that share xq can go into one launch: tiles_n counts the column tiles of all.
@@ -108,12 +125,12 @@ __global__ __launch_bounds__(512, (sliced_lds_bytes<MT, NWN, NB, kEpiStatic>() <
     uint32_t aoff[S::CHA];
 #pragma unroll
     for (int i = 0; i < S::CHA; ++i) {
-        const int r = ((wave + 8 * i) % (MT * 4)) * 8 + (lane >> 3);
+        const int r = (S::a_block(wave, i) % (MT * 4)) * 8 + (lane >> 3);
         const int32_t row = row0 + r < T ? r : T - 1 - row0;
         aoff[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(K) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
     }
     auto copy_piece = [&](int i, int32_t s, uint32_t buf) {   // buf: byte offset of the stage buffer
-        const int b = wave + 8 * i;
+        const int b = S::a_block(wave, i);
         int32_t kb = s * KS + (i < S::CHA ? b / (MT * 4) : ks);
         kb = kb < k_blocks ? kb : k_blocks - 1;
         if (i < S::CHA)
@@ -149,10 +166,7 @@ __global__ __launch_bounds__(512, (sliced_lds_bytes<MT, NWN, NB, kEpiStatic>() <
         if (s < stages)
 #pragma unroll
             for (int i = 0; i < S::PER; ++i) copy_piece(i, s, s * S::STAGE);
-    static_assert(NB == 2 || NB == 3, "waits below");
-    if (NB == 3 && stages >= 3) wait_vmcnt<2 * S::PER>();
-    else if (stages >= 2) wait_vmcnt<S::PER>();
-    else wait_vmcnt<0>();
+    wait_stages<NB - 1, S::PER>(stages - 1);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -179,8 +193,7 @@ __global__ __launch_bounds__(512, (sliced_lds_bytes<MT, NWN, NB, kEpiStatic>() <
             const int st = m / MT, mt = m % MT;
             if (m == LAND) {
                 // this wave's copies of the next stage have landed: its own weights
-                if (NB == 3 && s + 2 < stages) wait_vmcnt<S::PER>();
-                else wait_vmcnt<0>();
+                wait_stages<NB - 2, S::PER>(stages - 2 - s);
                 asm volatile("" ::: "memory");
                 bw_n[0] = btile(nxt, 0);
                 bw_n[1] = btile(nxt, 1);
@@ -345,7 +358,11 @@ using Launch = int (*)(const int8_t *, int32_t, int32_t, GemvGroup, const Epilog
 // The compiled tiles and what they cost.  Fitted to the time of every tile on 53 matrices (K 128 ..
 // 29568, N 32 .. 59136, the 7B and 72B projections among them) at 24 row counts from 33 to 3072, one HIP
 // graph over weights from HBM (rms 3 - 7 %): what the model picks, the tiles of w4a8_gemm.hip included, is within
-// 0.2 % of the fastest on average.
+// 0.2 % of the fastest on average.  The last four are one work-group to a compute unit with all of its LDS as stages, four of
+// 64 x 128 or 96 x 128 tiles: where tiles fill about one round, a lone work-group with two stages waits for its copies (us
+// before -> now: 8192 -> 10240 at T = 128 31.5 -> 24.4, 12288 -> 8192 at 192 42.0 -> 33.0, 4736 -> 27648 at 33 25.6 -> 19.7).  Fitted
+// to 92 matrices (K 512 .. 29568, N 1024 .. 59136) at thirteen row counts from 33 to 1024; of those 1196 shapes 260 go to them, in
+// 0.91 of the time on average, at worst 1.08 (2048 -> 10240 at T = 128).  Five stages are no better than four.
 struct Variant {
     TileCost cost;
     Launch launch[3];
@@ -364,8 +381,17 @@ constexpr Variant kSliced[] = {
     {{32, 64, 2, 1.976, 0.777, 0.165, 0.139, 0.043, 0.660}, MQ_SLICED(1, 2, 2)},
     {{32, 64, 1, 1.422, 1.727, 0.114, 0.000, 0.028, 0.592}, MQ_SLICED(1, 2, 3)},
     {{32, 32, 1, 1.222, 1.928, 0.064, 0.000, 0.019, 0.319}, MQ_SLICED(1, 1, 3)},
+    {{64, 128, 1, 2.529, 2.208, 0.269, 0.000, 0.027, 1.510}, MQ_SLICED(2, 4, 4)},
+    {{96, 128, 1, 2.426, 3.222, 0.303, 0.000, 0.062, 1.387}, MQ_SLICED(3, 4, 4)},
+    {{96, 256, 1, 2.685, 4.119, 0.512, 0.000, 0.164, 1.415}, MQ_SLICED(3, 8, 3)},
+    {{128, 256, 1, 2.507, 5.304, 0.602, 0.000, 0.230, 1.424}, MQ_SLICED(4, 8, 3)},
 };
 #undef MQ_SLICED
+// Up to 64 rows these take up to 20 % longer than their fit, whose rows are mostly more (every weight is then read by one
+// tile, from HBM): with the factor all of the 16 shapes of the sweep that go to them gain 10 to 30 %, without it three lose 2
+// to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).
+constexpr int kOneRound = 11;             // the first of the tiles that fill LDS
+constexpr double kFewRows = 1.14;
 constexpr int kVariants = sizeof(kSliced) / sizeof(kSliced[0]);
 static_assert(kVariants == kSlicedTiles, "mquant_tune_set validates against this");
 
@@ -409,7 +435,8 @@ Choice pick(int32_t T, int32_t K, const GemvGroup &grp)
     } else {
         for (int i = 0; i < kVariants; ++i) {
             const TileCost &c = kSliced[i].cost;
-            consider(i, c.us(tiles_n(c) * ceil_div32(T, c.bm), K));
+            const double us = c.us(tiles_n(c) * ceil_div32(T, c.bm), K);
+            consider(i, T <= 64 && i >= kOneRound ? kFewRows * us : us);
         }
     }
     return best;

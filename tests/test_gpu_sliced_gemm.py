@@ -101,6 +101,14 @@ def test_split_epilogue(mq, forced, tile):
         assert not bad.any(), (tile, T, N, K, n_split, int(bad.sum()))
 
 
+@pytest.mark.parametrize("tile", range(TILES, TILES + 4))
+def test_tiles_of_one_round(mq, forced, tile):
+    """The tiles that take a compute unit's LDS for themselves (three and four stages), the shapes above."""
+    assert mq.lib.mquant_tune_set(mq.TUNE_GEMM_SHAPE, TILES + 4) == mq.ERR_BAD_SHAPE
+    test_static_and_row_scale_bits(mq, forced, tile)
+    test_split_epilogue(mq, forced, tile)
+
+
 @pytest.mark.parametrize("T", [5, 17, 25, 32])
 @pytest.mark.parametrize("K", [128, 3584])
 def test_group_of_linears(mq, T, K):
