@@ -8,6 +8,7 @@ import hashlib
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -19,6 +20,9 @@ SOURCES = ["aifs.hip", "hadamard_quant.hip", "w4a8_gemm.hip", "w4a8_gemv.hip", "
 # The benchmark's measurement probes: their own shared object, outside the product's ABI.
 PROBES_LIB = os.path.join(LIB_DIR, "libmquant_probes.so")
 PROBES_SOURCES = ["probes.hip"]
+# The interpreter's short way to the library's launches: a CPython module without device code.
+CALL_LIB = os.path.join(LIB_DIR, "mquant_fastcall.so")
+CALL_SOURCES = ["fastcall.c"]
 HEADERS = ["mquant_internal.h", "hadamard_segment.h", "w4a8_common.h", "lds_dma.h", "probes.h"]
 
 HIPCC_FLAGS = [
@@ -59,21 +63,24 @@ def _stale(lib, srcs) -> bool:
 
 def is_stale() -> bool:
     """True when a library is missing or was built from other sources, headers or flags."""
-    return _stale(LIB, SOURCES) or _stale(PROBES_LIB, PROBES_SOURCES)
+    return _stale(LIB, SOURCES) or _stale(PROBES_LIB, PROBES_SOURCES) or _stale(CALL_LIB, CALL_SOURCES)
 
 
 def _compile(lib, srcs, verbose):
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     build_id = source_hash(srcs)
-    cmd = [hipcc, *HIPCC_FLAGS, f'-DMQUANT_BUILD_ID="{build_id}"', "-I", os.path.join(ROOT, "include"),
-           "-I", CSRC, *[os.path.join(CSRC, s) for s in srcs], "-o", lib]
+    if srcs is CALL_SOURCES:
+        cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-fPIC", "-shared", "-Wall", "-I",
+               sysconfig.get_paths()["include"]]
+    else:
+        cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, f'-DMQUANT_BUILD_ID="{build_id}"', "-I", CSRC]
+    cmd += ["-I", os.path.join(ROOT, "include"), *[os.path.join(CSRC, s) for s in srcs], "-o", lib]
     if verbose:
         print(" ".join(cmd))
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     # hipcc's host pass prints a harmless "not a recognized feature" line per file
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + out)
     if verbose and out.strip():
         print(out)
     with open(lib + ".id", "w") as f:
@@ -81,12 +88,14 @@ def _compile(lib, srcs, verbose):
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile libmquant.so and libmquant_probes.so; with force=False only what is stale."""
+    """Compile libmquant.so, libmquant_probes.so and the call module; with force=False only what is stale."""
     os.makedirs(LIB_DIR, exist_ok=True)
     if force or _stale(LIB, SOURCES):
         _compile(LIB, SOURCES, verbose)
     if force or _stale(PROBES_LIB, PROBES_SOURCES):
         _compile(PROBES_LIB, PROBES_SOURCES, verbose)
+    if force or _stale(CALL_LIB, CALL_SOURCES):
+        _compile(CALL_LIB, CALL_SOURCES, verbose)
     return LIB
 
 
