@@ -16,14 +16,14 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libmquant.so")
 SOURCES = ["aifs.hip", "hadamard_quant.hip", "w4a8_gemm.hip", "w4a8_gemv.hip", "w4a8_sliced.hip", "w4a8_small.hip", "w4a8_walk.hip", "attention.hip",
-           "w4g128_gemm.hip"]
+           "w4g128_gemm.hip", "w4g128_walk.hip"]
 # The benchmark's measurement probes: their own shared object, outside the product's ABI.
 PROBES_LIB = os.path.join(LIB_DIR, "libmquant_probes.so")
 PROBES_SOURCES = ["probes.hip"]
 # The interpreter's short way to the library's launches: a CPython module without device code.
 CALL_LIB = os.path.join(LIB_DIR, "mquant_fastcall.so")
 CALL_SOURCES = ["fastcall.c"]
-HEADERS = ["mquant_internal.h", "hadamard_segment.h", "w4a8_common.h", "lds_dma.h", "probes.h"]
+HEADERS = ["mquant_internal.h", "hadamard_segment.h", "w4a8_common.h", "w4g128_common.h", "lds_dma.h", "probes.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -31,18 +31,12 @@
 
 #include "lds_dma.h"
 #include "mquant_internal.h"
+#include "w4g128_common.h"
 
 using namespace mquant;
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-
 namespace {
 
-constexpr int kGroup = 128;               // input channels per weight scale
 constexpr int64_t kG128MaxLdx = int64_t(1) << 23;   // 255 rows of 2 * ldx bytes within 32 bits
 
 __global__ __launch_bounds__(256) void g128_prepack_kernel(
@@ -81,54 +75,6 @@ __global__ __launch_bounds__(256) void g128_prepack_kernel(
         out_s[o] = n < N ? scales[static_cast<int64_t>(n) * (K / kGroup) + kg] : __float2half(1.0f);
     }
 }
-
-// (a & mask) | c in one VALU operation (the compiler emits an AND and an OR when both
-// constants are literals: a VOP3 instruction of this ISA takes no literal operand).
-__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t c)
-{
-    uint32_t r;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(mask), "v"(c));
-    return r;
-}
-
-// The channels 2 j, 2 j + 1 of a dword of prepacked weights as fp16(code * scale); s2 holds the scale in both
-// halves.  Both ways to the code are exact, the product is rounded once.  The odd pairs stay where they
-// are, four bits up: 0x6400 | code + 8 << 4 is 1024 + 16 (code + 8), a sixteenth of which is 64 + code + 8.  So
-// eight weights take one shift and twelve other operations.  SHIFTED: every pair shifted into place, three shifts
-// and twelve operations, for kernels that wait for their loads and not for these: the GEMV of many tiles takes 3 to 8 %
-// longer with the other form (3584 -> 37888 at 8 rows 24.0 / 25.9 us), the GEMM's 32x32 tile 1 to 3 % (18944 -> 3584 at 16
-// rows 25.3 / 26.0).
-struct Unpack {
-    uint32_t even = 0x000F000Fu, odd = 0x00F000F0u, magic = 0x64006400u;
-    __device__ __forceinline__ Unpack()
-    {
-        asm volatile("" : "+v"(magic));       // keep it in a VGPR (third operand of v_and_or_b32)
-    }
-    template <bool SHIFTED>
-    __device__ __forceinline__ uint32_t pair(uint32_t v, int j, v2h s2) const
-    {
-        const v2h bias = {static_cast<_Float16>(1032.0f), static_cast<_Float16>(1032.0f)};
-        const v2h sixteenth = {static_cast<_Float16>(0.0625f), static_cast<_Float16>(0.0625f)};
-        const v2h bias_odd = {static_cast<_Float16>(-72.0f), static_cast<_Float16>(-72.0f)};
-        v2h code;
-        if (SHIFTED) {
-            code = __builtin_bit_cast(v2h, and_or(v >> (4 * j), even, magic)) - bias;
-        } else {
-            const uint32_t t = j >= 2 ? v >> 8 : v;
-            if (j & 1) code = __builtin_elementwise_fma(__builtin_bit_cast(v2h, and_or(t, odd, magic)), sixteenth, bias_odd);
-            else code = __builtin_bit_cast(v2h, and_or(t, even, magic)) - bias;
-        }
-        return __builtin_bit_cast(uint32_t, code * s2);
-    }
-    template <bool SHIFTED>
-    __device__ __forceinline__ v4u eight(uint32_t v, v2h s2) const
-    {
-        v4u out;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = pair<SHIFTED>(v, j, s2);
-        return out;
-    }
-};
 
 __device__ __forceinline__ int acc_row(int r, int g) { return (r >> 2) * 8 + g * 4 + (r & 3); }
 
@@ -768,6 +714,7 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
         const __half *sT = reinterpret_cast<const __half *>(wp + w_bytes);
         const v4u *wt = reinterpret_cast<const v4u *>(wp);
         const int32_t n_pad = n_tiles32 * kPackN;
+        if (g128_walk_takes(T, K, N)) return g128_walk(xh, ldx, wt, sT, yh, ldy, T, N, K, n_pad, st);
         // Up to four rows that fit LDS take the half-tile form with the number of waves that is expected
         // to be fastest, or the whole-tile one: half tiles against whole ones at 1 / 4 rows: 18944 x 3584
         // 11.3 / 22.5 us and 12.4 / 23.3, 3584 x 3584 4.8 / 6.6 and 5.5 / 6.9; whole ones where every

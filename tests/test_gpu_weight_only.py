@@ -194,6 +194,28 @@ def test_few_rows_in_half_tiles(mq, T, N, K, waves):
     assert names is None or (len(names) == 1 and names[0].startswith(form)), names
 
 
+@pytest.mark.parametrize("T,N,K", [
+    (5, 12299, 3584), (16, 20500, 3584),              # three units per work-group and four; the most rows
+    (2, 28700, 3584), (9, 36900, 2048),               # shares that cross units, short K
+    (12, 10250, 5120), (4, 16400, 5120),              # the fewest units; the last of half a tile
+    (2, 20500, 8192), (3, 20500, 11008),              # long K: the scales in more than one round
+])
+def test_walk_of_several_rows(mq, T, N, K):
+    """A work-group per compute unit: strided x and y with untouched padding, and the same bits again."""
+    rng = np.random.default_rng(T * 17 + N + K)
+    wq, sc = make_weight(rng, N, K)
+    xb = (rng.standard_normal((T, K + 8)) * 1.5).astype(np.float16)
+    ref, mag = orc.w4g128_linear(np.ascontiguousarray(xb[:, :K]), wq, sc)
+    wp, x = mq.w4g128_prepack(dev(pack_int4(wq)), dev(sc)), dev(xb)[:, :K]
+    yb = torch.full((T, N + 3), 7.0, dtype=torch.float16, device="cuda")
+    say(f"walk T={T} N={N} K={K}")
+    names = traced(lambda: mq.w4g128_gemm(x, wp, N, out=yb[:, :N]))
+    got = yb.cpu().numpy()
+    check(got[:, :N], ref, mag, f"walk {(T, N, K)}")
+    assert (got[:, N:] == 7.0).all() and torch.equal(mq.w4g128_gemm(x, wp, N), yb[:, :N])
+    assert names is None or (len(names) == 1 and names[0].startswith("w4g128_walk_kernel<")), names
+
+
 @pytest.mark.parametrize("T,N,K,name", [
     (13, 1003, 128, "w4g128_gemv_kernel<16, 2>"), (20, 1003, 128, "w4g128_gemv_kernel<16, 2>"),
     (17, 18951, 256, "w4g128_gemv_kernel<8, 1>"), (25, 18951, 256, "w4g128_gemv_kernel<8, 1>"),
