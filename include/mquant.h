@@ -507,7 +507,8 @@ typedef enum {
                                        of the K-sliced W4A8 GEMM: 0 = 64x128, 1 = 64x256, 2 = 192x128, 3 = 160x128,
                                        4 = 128x128, 5 = 96x128, 6 = 128x64, 7 = 64x64, 8 and 9 = 32x64
                                        (two and three stages), 10 = 32x32, 11 = 64x128 and 12 = 96x128 with four
-                                       stages, 13 = 96x256, 14 = 128x256 */
+                                       stages, 13 = 96x256, 14 = 128x256, 15 = 256x384 of the large-tile kind (14 for
+                                       flagged channels and groups) */
 } mquant_tune_key_t;
 
 /*

@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libmquant.so")
-SOURCES = ["aifs.hip", "hadamard_quant.hip", "w4a8_gemm.hip", "w4a8_gemv.hip", "w4a8_sliced.hip", "w4a8_small.hip", "w4a8_walk.hip", "attention.hip",
+SOURCES = ["aifs.hip", "hadamard_quant.hip", "w4a8_gemm.hip", "w4a8_gemv.hip", "w4a8_sliced.hip", "w4a8_wide.hip", "w4a8_small.hip", "w4a8_walk.hip", "attention.hip",
            "w4g128_gemm.hip", "w4g128_walk.hip"]
 # The benchmark's measurement probes: their own shared object, outside the product's ABI.
 PROBES_LIB = os.path.join(LIB_DIR, "libmquant_probes.so")

@@ -40,7 +40,7 @@ extern "C" int mquant_tune_set(int32_t key, int32_t value)
         t.g128_tile.store(value, std::memory_order_relaxed);
         return MQUANT_OK;
     case MQUANT_TUNE_GEMM_SHAPE:
-        if (value < -1 || value >= kSlicedTiles) return MQUANT_ERR_BAD_SHAPE;
+        if (value < -1 || value >= kGemmShapes) return MQUANT_ERR_BAD_SHAPE;
         t.gemm_sliced.store(value, std::memory_order_relaxed);
         return MQUANT_OK;
     case MQUANT_TUNE_GEMV_VARIANT:

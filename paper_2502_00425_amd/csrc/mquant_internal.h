@@ -111,7 +111,7 @@ struct TuneState {
     std::atomic<int32_t> gemm_sliced{-1};     // index into the table of w4a8_sliced.hip
 };
 TuneState &tune_state();
-constexpr int kSlicedTiles = 15;          // tiles of the sliced W4A8 GEMM
+constexpr int kGemmShapes = 16;           // tiles of the sliced W4A8 GEMM and 256 x 384
 constexpr int kG128Tiles = 14;            // tiles of the weight-only GEMM
 
 // The front end's checks of its input (hadamard_quant.hip).

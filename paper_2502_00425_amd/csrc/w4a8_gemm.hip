@@ -882,6 +882,26 @@ int pick_gemm_tile(int32_t T, int32_t N)
     return b <= c ? 1 : 2;
 }
 
+// The 256 x 384 tile's time over that of the tile above, by rounds of tiles over the CUs x tile area / relative rate.  A
+// last round of few tiles takes little over half the time of a full one, since fewer busy CUs run at a higher clock.  Estimate
+// and measured: 3584 -> 37888 at T = 1280 0.94 / 0.93 and 0.97 (two boxes), 2048 1.03 / 1.04, 4096 0.96 / 0.97; 3584 -> 4608 at
+// 4096 0.87 / 0.90; 8192 -> 10240 at 2048 0.86 / 0.89, 16384 0.96 / 0.97; 8192 -> 59136 at 16384 0.94 / 0.94 and 0.97; 8192 -> 8192
+// at 16384 1.01 / 1.02.  Short K pays for the larger tile's start (640 -> 5000 at T = 16384 79.5 / 81.6 us).
+double wide_share(int32_t T, int32_t N, int32_t K)
+{
+    if (T <= 512 || K < 1024) return 1.0;
+    auto rounds = [](int64_t tiles) {
+        const int64_t rest = tiles % kNumCU;
+        return static_cast<double>(tiles / kNumCU) + (rest > 0 ? 0.5 + rest * (0.5 / kNumCU) : 0.0);
+    };
+    const int tile = pick_gemm_tile(T, N);
+    const double old = tile == 0   ? rounds(ceil_div(T, 256) * ceil_div(N, 256)) * (256.0 * 256.0)
+                       : tile == 1 ? rounds(ceil_div(T, 128) * ceil_div(N, 256)) * (128.0 * 256.0 / 0.93)
+                                   : rounds(ceil_div(T, 192) * ceil_div(N, 128)) * (192.0 * 128.0 / 0.78);
+    return rounds(ceil_div(T, 256) * ceil_div(N, 384)) * (256.0 * 384.0 / 1.07) / old;
+}
+constexpr double kWideAhead = 0.97;
+
 // What the plan above costs in microseconds (split-K with its reduction, or the tile), for the
 // comparison with the sliced GEMM; fitted to the same sweep as the table of w4a8_sliced.hip
 // (rms 4 - 5 %).
@@ -914,12 +934,13 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 // those from before), but 14.5 % was not sound: on 45 shapes drawn from those that the two margins decide differently, static
 // scales take 0.946 to 1.12 of the time with it (0.997 on average), per-row scales up to 1.44, one flagged channel 0.72 to 2.1,
 // three 0.81 to 2.9; the estimates hold neither short K nor what the epilogues cost the large tiles, most of all at odd N.
-bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
+// `share`: of the plan's time that the 256 x 384 tile takes where it takes the linear.
+bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp, double share)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(T, K, grp) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(T, K, grp) < (full ? 0.88 : 0.94) * share * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
@@ -1090,8 +1111,12 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     // The sliced GEMM on few tiles (T = 128: 3584 x 4608 17.1 -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1
     // -> 15.9; T = 512: 22.8 -> 16.2 on 3584 x 4608) and wherever else it is expected to be ahead.
     const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
-    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp))))
+    const double wide = EPI != kEpiSplit && splits == 1 && force_tile < 0 ? wide_share(T, N, K) : 1.0;
+    const double share = wide < kWideAhead ? wide : 1.0;
+    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp, share))))
         return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
+    if constexpr (EPI != kEpiSplit)
+        if (share < 1.0) return launch_wide<EPI>(xq, T, K, grp.p[0], ep, stream);
     if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,
                                                  static_cast<int32_t *>(workspace), stream);

@@ -393,7 +393,7 @@ constexpr Variant kSliced[] = {
 constexpr int kOneRound = 11;             // the first of the tiles that fill LDS
 constexpr double kFewRows = 1.14;
 constexpr int kVariants = sizeof(kSliced) / sizeof(kSliced[0]);
-static_assert(kVariants == kSlicedTiles, "mquant_tune_set validates against this");
+static_assert(kVariants + 1 == kGemmShapes, "mquant_tune_set validates against this");
 
 // Up to 32 rows, one row of tiles: the weights come from HBM and are what a launch waits for, so the
 // 32-row tiles have costs of their own, the part along K growing by `slope` per 16 rows beyond 16.  Same
@@ -470,6 +470,11 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
 {
     int v = tune_state().gemm_sliced.load(std::memory_order_relaxed);
     if (v < 0) v = pick(T, K, grp).variant;
+    if (v == kVariants) {                    // forced: 256 x 384, or the largest tile here for what that does not take
+        if constexpr (EPI != kEpiSplit)
+            if (grp.n == 1) return launch_wide<EPI>(xq, T, K, grp.p[0], ep, stream);
+        v = kVariants - 1;
+    }
     return kSliced[v].launch[EPI](xq, T, K, grp, ep, stream);
 }
 

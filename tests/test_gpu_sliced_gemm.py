@@ -101,12 +101,35 @@ def test_split_epilogue(mq, forced, tile):
         assert not bad.any(), (tile, T, N, K, n_split, int(bad.sum()))
 
 
-@pytest.mark.parametrize("tile", range(TILES, TILES + 4))
-def test_tiles_of_one_round(mq, forced, tile):
-    """The tiles that take a compute unit's LDS for themselves (three and four stages), the shapes above."""
-    assert mq.lib.mquant_tune_set(mq.TUNE_GEMM_SHAPE, TILES + 4) == mq.ERR_BAD_SHAPE
+@pytest.mark.parametrize("tile", range(TILES, TILES + 5))
+def test_tiles_that_fill_lds(mq, forced, tile):
+    """The tiles that take a compute unit's LDS for themselves (three and four stages; 256 x 384), the shapes above."""
+    assert mq.lib.mquant_tune_set(mq.TUNE_GEMM_SHAPE, TILES + 5) == mq.ERR_BAD_SHAPE
     test_static_and_row_scale_bits(mq, forced, tile)
     test_split_epilogue(mq, forced, tile)
+
+
+@pytest.mark.parametrize("T,N,K", [(661, 21872, 1024), (772, 18764, 1152), (1031, 14530, 1024)])
+def test_wide_tiles_by_choice(mq, T, N, K):
+    """Few rows and short K that the library itself sends to 256 x 384 tiles (2-byte stores; eight and nine
+    stages, the last rows and columns inside a tile), static and per-token scales, padding untouched."""
+    rng = np.random.default_rng(T + N + K)
+    xq = rng.integers(-128, 128, size=(T, K), dtype=np.int8)
+    packed = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    w_scale = rng.uniform(0.005, 0.02, size=N).astype(np.float16)
+    acc = orc.gemm_i8_i4_i32(xq, orc.unpack_w4(packed))
+    _, want = orc.dequant(acc, T // 3, 0.07, 0.009, w_scale)
+    rows = rng.uniform(0.004, 0.1, size=T).astype(np.float32)
+    _, want_r = orc.dequant_rows(acc, rows, w_scale)
+    wp, ws, xd, rd = mq.w4_prepack(dev(packed)), dev(w_scale), dev(xq), dev(rows)
+    buf = torch.full((T, N + 8), 3.0, dtype=torch.float16, device="cuda")
+    say(f"wide T={T} N={N} K={K}")
+    for call, w in ((lambda: mq.w4a8_gemm(xd, wp, ws, N, T // 3, 0.07, 0.009, out=buf[:, :N]), want),
+                    (lambda: mq.w4a8_gemm_rowscale(xd, wp, ws, rd, N, out=buf[:, :N]), want_r)):
+        names = traced(call)
+        assert names is None or (len(names) == 1 and names[0].startswith("w4a8_wide_kernel<")), names
+        assert (bits(buf[:, :N].contiguous()) == w.view(np.uint16)).all()
+        assert bool((buf[:, N:] == 3.0).all())
 
 
 @pytest.mark.parametrize("T", [5, 17, 25, 32])
