@@ -359,6 +359,95 @@ __global__ __launch_bounds__(WM *WN * 64, STAGES == 2 ? 4 : 2) void w4a8_gemm_ke
         return;
     }
 
+    constexpr int ROWB = NT * 64 + 16;                 // padded row pitch of a wave's store patch, bytes
+    constexpr int LPR = NT * 64 / 16;                  // lanes per patch row on the way out
+    constexpr int RPI = 64 / LPR;                      // patch rows per store instruction
+    auto store_patch = [&](const uint8_t *patch, int mt) {        // 32 rows x (NT*32) columns, 16 bytes per lane
+#pragma unroll
+        for (int q = 0; q < 32 / RPI; ++q) {
+            const int rl = q * RPI + lane / LPR;
+            const int c = lane % LPR;
+            const uint4 v = *reinterpret_cast<const uint4 *>(patch + rl * ROWB + c * 16);
+            const int32_t row = wave_row0 + mt * 32 + rl;
+            const int32_t n = wave_n0 + c * 8;
+            if (row < T && n < N)                                  // N % 8 == 0 on this path
+                *reinterpret_cast<uint4 *>(y + static_cast<int64_t>(row) * ldy + n) = v;
+        }
+    };
+
+    // ---- flagged channels: the codes of the tile's rows and the split weights of its columns go to LDS once, four rows
+    // are dequantised at a time (same terms and order as Epilogue::dequant).  Read from memory for every output the
+    // terms took longer than the product: 18944 -> 3584 with 37 channels at T = 3600 1424 -> 311 us (205 with one), 3584 -> 37888
+    // with four at 1280 452 -> 195, with 37 1751 -> 407 (264 of it the issue of the five operations a term takes).
+    if constexpr (EPI == kEpiSplit) {
+        constexpr int CODES = NW * 32 * ROWB, SPLIT_W = CODES + kMaxSplitChannels * BM;    // [j][row], [j][column]
+        static_assert(SPLIT_W + kMaxSplitChannels * BN <= STAGES * STAGE, "epilogue must fit the stage buffers");
+        const bool wide = wide_store && acc_out == nullptr;
+        __syncthreads();                               // every wave is done with the stage buffers
+        for (int32_t e = tid; e < ep.n_split * BM; e += NW * 64) {
+            const int32_t j = e / BM, row = row0 + e % BM;
+            smem[CODES + e] = static_cast<uint8_t>(ep.xq[static_cast<int64_t>(row < T ? row : T - 1) * K + ep.split_idx[j]]);
+        }
+        for (int32_t e = tid; e < ep.n_split * BN; e += NW * 64) {
+            const int32_t j = e / BN, n = tn * BN + e % BN;
+            smem[SPLIT_W + e] = static_cast<uint8_t>(ep.split_w[static_cast<int64_t>(j) * N + (n < N ? n : N - 1)]);
+        }
+        __syncthreads();
+        uint8_t *patch = smem + wave * (32 * ROWB);
+        float ws[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int32_t n = wave_n0 + nt * 32 + l32;
+            ws[nt] = __half2float(w_scale[n < N ? n : N - 1]);
+        }
+        const uint8_t *codes = smem + CODES + wm * (BM / WM) + g * 4;
+        const uint8_t *weights = smem + SPLIT_W + wn * NT * 32 + l32;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {              // registers 4 q .. 4 q + 3: rows q * 8 + g * 4 ..
+                float s_row[4], v[NT][4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int32_t row = wave_row0 + mt * 32 + q * 8 + g * 4 + e;
+                    s_row[e] = ep.scale_of<EPI>(row < T ? row : T - 1);            // rows past T are never stored
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        v[nt][e] = (static_cast<float>(acc[mt][nt][q * 4 + e] >> 4) * s_row[e]) * ws[nt];
+                }
+                for (int32_t j = 0; j < ep.n_split; ++j) {
+                    const uint32_t c4 = *reinterpret_cast<const uint32_t *>(codes + j * BM + mt * 32 + q * 8);
+                    const float sc = ep.split_scale[j];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const int32_t w = static_cast<int8_t>(weights[j * BN + nt * 32]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int32_t p = static_cast<int32_t>(static_cast<int8_t>(c4 >> (8 * e))) * w;
+                            v[nt][e] = v[nt][e] + (static_cast<float>(p) * s_row[e]) * sc;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const __half h = half_of_rounded_f32(v[nt][e]);
+                        const int rl = q * 8 + g * 4 + e;
+                        const int32_t row = wave_row0 + mt * 32 + rl, n = wave_n0 + nt * 32 + l32;
+                        if (wide) {
+                            *reinterpret_cast<__half *>(patch + rl * ROWB + (nt * 32 + l32) * 2) = h;
+                        } else if (row < T && n < N) {
+                            y[static_cast<int64_t>(row) * ldy + n] = h;
+                            if (acc_out) acc_out[static_cast<int64_t>(row) * N + n] = acc[mt][nt][q * 4 + e] >> 4;
+                        }
+                    }
+            }
+            if (wide) store_patch(patch, mt);
+        }
+        return;
+    }
+
     // ---- epilogue: scale select by row span, per-channel scale, fp16
     if (!wide_store || acc_out != nullptr) {
         // plain path: every lane stores its own 2-byte results
@@ -383,9 +472,6 @@ __global__ __launch_bounds__(WM *WN * 64, STAGES == 2 ? 4 : 2) void w4a8_gemm_ke
     // 2 bytes per lane.  Each wave instead turns 32 rows x (NT*32) columns through
     // its own LDS patch and stores 16 bytes per lane, whole rows of the patch
     // (NT*64 contiguous bytes) at a time.
-    constexpr int ROWB = NT * 64 + 16;                 // padded row pitch of the patch, bytes
-    constexpr int LPR = NT * 64 / 16;                  // lanes per patch row on the way out
-    constexpr int RPI = 64 / LPR;                      // patch rows per store instruction
     static_assert(NW * 32 * ROWB <= STAGES * STAGE, "epilogue patch must fit the stage buffers");
     __syncthreads();                                   // every wave is done with the stage buffers
     uint8_t *patch = smem + wave * (32 * ROWB);
@@ -413,16 +499,7 @@ __global__ __launch_bounds__(WM *WN * 64, STAGES == 2 ? 4 : 2) void w4a8_gemm_ke
                     half_of_rounded_f32(v);
             }
         }
-#pragma unroll
-        for (int q = 0; q < 32 / RPI; ++q) {
-            const int rl = q * RPI + lane / LPR;
-            const int c = lane % LPR;
-            const uint4 v = *reinterpret_cast<const uint4 *>(patch + rl * ROWB + c * 16);
-            const int32_t row = wave_row0 + mt * 32 + rl;
-            const int32_t n = wave_n0 + c * 8;
-            if (row < T && n < N)                                  // N % 8 == 0 on this path
-                *reinterpret_cast<uint4 *>(y + static_cast<int64_t>(row) * ldy + n) = v;
-        }
+        store_patch(patch, mt);
     }
 }
 

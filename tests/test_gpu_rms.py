@@ -128,6 +128,28 @@ def test_rms_on_every_gemm_tile(mq, tile):
         mq.tune_set(mq.TUNE_GEMM_TILE, -1)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+def test_rms_terms_staged_in_lds(mq, tile):
+    """The most flagged channels and one, second tiles of rows and columns that end inside, 16-byte and 2-byte stores: each
+    tile gives the bits of the sliced GEMM, which adds the same terms in the same order."""
+    for T, N, K, n_split in [(300, 520, 256, 64), (259, 516, 128, 1), (41, 264, 384, 64)]:
+        rng = np.random.default_rng(170 + tile + n_split)
+        xq, wq, idx, wsplit, ssplit, w_scale = make_case(rng, T, N, K, 4, n_split)
+        args = (dev(xq), mq.w4_prepack(dev(pack_int4(wq))), dev(w_scale), N, T // 3, 0.11, 0.004, idx, dev(wsplit), ssplit)
+        say(f"rms staged tile {tile} T={T} N={N} K={K} splits={n_split}")
+        out = []
+        for key, value in ((mq.TUNE_GEMM_SHAPE, 7), (mq.TUNE_GEMM_TILE, tile)):
+            mq.tune_set(key, value)
+            try:
+                y = torch.full((T, N), float("nan"), dtype=torch.float16, device="cuda")
+                names = traced(lambda: mq.w4a8_gemm_rms(*args, out=y))
+                assert names is None or names[-1].startswith("w4a8_sliced" if key == mq.TUNE_GEMM_SHAPE else "w4a8_gemm_kernel<"), names
+            finally:
+                mq.tune_set(key, -1)
+            out.append(y.cpu().numpy().view(np.uint16))
+        assert (out[0] == out[1]).all(), (tile, T, N, K)
+
+
 def test_rms_without_split_channels_equals_plain_gemm(mq):
     rng = np.random.default_rng(9)
     T, N, K = 70, 264, 1024
