@@ -182,9 +182,10 @@ template <int EPI>
 int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp, const Epilogue &ep,
                     hipStream_t stream);
 
-// ---- 256 x 384 tiles (w4a8_wide.hip): one linear, K % 128 == 0, no flagged channels
+// ---- large tiles (w4a8_wide.hip): 0 = 256 x 384, 1 = 192 x 256, 2 = 128 x 384, 3 = 128 x 256; one linear, K % 128 == 0,
+// no flagged channels
 template <int EPI>
-int launch_wide(const int8_t *xq, int32_t T, int32_t K, const GemvProblem &pr, const Epilogue &ep, hipStream_t stream);
+int launch_wide(int tile, const int8_t *xq, int32_t T, int32_t K, const GemvProblem &pr, const Epilogue &ep, hipStream_t stream);
 
 // What its cost model expects of the tile it would pick.
 double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp);

@@ -979,6 +979,28 @@ double wide_share(int32_t T, int32_t N, int32_t K)
 }
 constexpr double kWideAhead = 0.97;
 
+// Where 256 x 384 is not ahead: the tile of w4a8_wide.hip (its index there) that is expected ahead of the tile above, or -1, by
+// the same rounds with 0.7 of a full one for a last round of few tiles: rates and that share with the least regret over 168
+// shapes at T = 520 .. 8192 (0.2 % on average, 7.7 % at most).  us, the tile above / this: 8192 -> 10240 at T = 900 82.9 / 68.2,
+// 3584 -> 4608 at 2048 38.6 / 32.7, 3584 -> 3584 at 3000 39.9 / 35.0; at worst, 2048 -> 11008 at 1440, 35.8 / 37.2.  They take
+// linears from that tile only: the margin of the sliced GEMM covers errors of its estimate on them that were not measured.
+int smaller_wide(int32_t T, int32_t N, int32_t K)
+{
+    if (T <= 512 || K < 1024) return -1;
+    auto time = [&](int32_t bm, int32_t bn, double rate) {
+        const int64_t tiles = ceil_div(T, bm) * ceil_div(N, bn), rest = tiles % kNumCU;
+        const double rounds = static_cast<double>(tiles / kNumCU) + (rest > 0 ? 0.7 + rest * (0.3 / kNumCU) : 0.0);
+        return rounds * bm * bn / rate;
+    };
+    const double of[] = {time(192, 256, 0.95), time(128, 384, 0.95), time(128, 256, 0.96)};
+    int best = 0;
+    for (int i = 1; i < 3; ++i)
+        if (of[i] < of[best]) best = i;
+    const int tile = pick_gemm_tile(T, N);
+    const double plan = tile == 0 ? time(256, 256, 1.0) : tile == 1 ? time(128, 256, 0.93) : time(192, 128, 0.815);
+    return of[best] < kWideAhead * plan ? best + 1 : -1;
+}
+
 // What the plan above costs in microseconds (split-K with its reduction, or the tile), for the
 // comparison with the sliced GEMM; fitted to the same sweep as the table of w4a8_sliced.hip
 // (rms 4 - 5 %).
@@ -1193,7 +1215,10 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp, share))))
         return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
     if constexpr (EPI != kEpiSplit)
-        if (share < 1.0) return launch_wide<EPI>(xq, T, K, grp.p[0], ep, stream);
+        if (splits == 1 && force_tile < 0) {
+            const int tile = share < 1.0 ? 0 : smaller_wide(T, N, K);
+            if (tile >= 0) return launch_wide<EPI>(tile, xq, T, K, grp.p[0], ep, stream);
+        }
     if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,
                                                  static_cast<int32_t *>(workspace), stream);

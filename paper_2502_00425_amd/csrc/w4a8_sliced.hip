@@ -472,7 +472,7 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
     if (v < 0) v = pick(T, K, grp).variant;
     if (v == kVariants) {                    // forced: 256 x 384, or the largest tile here for what that does not take
         if constexpr (EPI != kEpiSplit)
-            if (grp.n == 1) return launch_wide<EPI>(xq, T, K, grp.p[0], ep, stream);
+            if (grp.n == 1) return launch_wide<EPI>(0, xq, T, K, grp.p[0], ep, stream);
         v = kVariants - 1;
     }
     return kSliced[v].launch[EPI](xq, T, K, grp, ep, stream);

@@ -132,6 +132,19 @@ def test_wide_tiles_by_choice(mq, T, N, K):
         assert bool((buf[:, N:] == 3.0).all())
 
 
+@pytest.mark.parametrize("T,N,K,tile", [(1150, 7676, 1024, "<3, 2,"), (1150, 7672, 1152, "<3, 2,"),
+                                        (1010, 10236, 1024, "<2, 3,"), (1010, 10232, 1152, "<2, 3,"),
+                                        (526, 10900, 1152, "<2, 2,"), (527, 10912, 1024, "<2, 2,")])
+def test_smaller_wide_tiles_by_choice(mq, T, N, K, tile):
+    """192 x 256, 128 x 384 and 128 x 256, each with 2-byte and with 16-byte stores, as above."""
+    test_wide_tiles_by_choice(mq, T, N, K)
+    xq = torch.zeros((T, K), dtype=torch.int8, device="cuda")
+    wp = torch.zeros(mq.w4_prepacked_bytes(N, K), dtype=torch.uint8, device="cuda")
+    ws = torch.ones(N, dtype=torch.float16, device="cuda")
+    names = traced(lambda: mq.w4a8_gemm(xq, wp, ws, N, T // 3, 0.07, 0.009))
+    assert names is None or (len(names) == 1 and names[0].startswith("w4a8_wide_kernel" + tile)), names
+
+
 @pytest.mark.parametrize("T", [5, 17, 25, 32])
 @pytest.mark.parametrize("K", [128, 3584])
 def test_group_of_linears(mq, T, K):
