@@ -982,8 +982,9 @@ constexpr double kWideAhead = 0.97;
 // Where 256 x 384 is not ahead: the tile of w4a8_wide.hip (its index there) that is expected ahead of the tile above, or -1, by
 // the same rounds with 0.7 of a full one for a last round of few tiles: rates and that share with the least regret over 168
 // shapes at T = 520 .. 8192 (0.2 % on average, 7.7 % at most).  us, the tile above / this: 8192 -> 10240 at T = 900 82.9 / 68.2,
-// 3584 -> 4608 at 2048 38.6 / 32.7, 3584 -> 3584 at 3000 39.9 / 35.0; at worst, 2048 -> 11008 at 1440, 35.8 / 37.2.  They take
-// linears from that tile only: the margin of the sliced GEMM covers errors of its estimate on them that were not measured.
+// 3584 -> 4608 at 2048 38.6 / 32.7, 3584 -> 3584 at 3000 39.9 / 35.0.  On short K the first two take one
+// round only: nothing hides the start of the next (1536 -> 8960 at 4096, three rounds: 58.0 / 62.7; 2048 -> 11008 at 1440, two:
+// 35.8 / 37.2).  They take linears from that tile only: the margin of the sliced GEMM covers errors of its estimate on them that were not measured.
 int smaller_wide(int32_t T, int32_t N, int32_t K)
 {
     if (T <= 512 || K < 1024) return -1;
@@ -993,9 +994,10 @@ int smaller_wide(int32_t T, int32_t N, int32_t K)
         return rounds * bm * bn / rate;
     };
     const double of[] = {time(192, 256, 0.95), time(128, 384, 0.95), time(128, 256, 0.96)};
-    int best = 0;
-    for (int i = 1; i < 3; ++i)
-        if (of[i] < of[best]) best = i;
+    const int64_t groups[] = {ceil_div(T, 192) * ceil_div(N, 256), ceil_div(T, 128) * ceil_div(N, 384)};
+    int best = 2;
+    for (int i = 0; i < 2; ++i)
+        if (of[i] < of[best] && (K >= 3072 || groups[i] <= kNumCU)) best = i;
     const int tile = pick_gemm_tile(T, N);
     const double plan = tile == 0 ? time(256, 256, 1.0) : tile == 1 ? time(128, 256, 0.93) : time(192, 128, 0.815);
     return of[best] < kWideAhead * plan ? best + 1 : -1;
