@@ -2,7 +2,7 @@
 // binding.py does for them in Python and ctypes, in C.  A call passes the same checks on the same methods
 // of its tensors (shape, stride, data_ptr, is_contiguous), reads the stream through the same functions of
 // torch and releases the interpreter lock while the library runs.  Anything out of the ordinary -- a
-// method that raises, a number that is not a plain int or float, a layout the checks refuse --
+// method that raises an error, a number that is not a plain int or float, a layout the checks refuse --
 // returns NotImplemented before the library is called, and binding.py goes its own way, which also
 // words the errors.  Nothing is kept from one call for another.
 //
@@ -36,10 +36,11 @@ typedef struct {
     int (*weight_only)(const void *, int64_t, const uint8_t *, void *, int64_t, int32_t, int32_t, int32_t, mquant_stream_t);
 } State;
 
-// ---- readers: 1 on success, 0 (no exception set) where the slow way has to look
+// ---- readers: 1 on success, 0 where the slow way has to look.  An interrupt, an exit and exhausted memory are nobody's
+// layout: they stay set, and the call raises them.
 static int no(void)
 {
-    PyErr_Clear();
+    if (PyErr_ExceptionMatches(PyExc_Exception) && !PyErr_ExceptionMatches(PyExc_MemoryError)) PyErr_Clear();
     return 0;
 }
 
@@ -159,7 +160,13 @@ static int read_linears(PyObject *list, mquant_linear_t *lin, int32_t *n)
     return 1;
 }
 
-#define SLOW_WAY Py_RETURN_NOTIMPLEMENTED
+#define SLOW_WAY return slow_way()
+static PyObject *slow_way(void)
+{
+    if (PyErr_Occurred()) return NULL;
+    Py_RETURN_NOTIMPLEMENTED;
+}
+
 #define LAUNCH(...)                     \
     int st;                             \
     Py_BEGIN_ALLOW_THREADS              \

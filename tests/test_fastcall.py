@@ -121,3 +121,32 @@ def test_errors_of_the_library_are_raised(both):
     with pytest.raises(mq.MQuantError) as e:
         calls()["weight_only"]()
     assert e.value.status == mq.ERR_BAD_SHAPE
+
+
+@pytest.mark.parametrize("where", ["initialized", "device", "stream", "shape", "stride", "data_ptr", "is_contiguous"])
+@pytest.mark.parametrize("error,raised", [(KeyboardInterrupt, True), (SystemExit, True), (MemoryError, True), (RuntimeError, False)])
+def test_interrupts_are_not_swallowed(both, where, error, raised):
+    """What a program raises over a call (Ctrl-C surfaces in the functions of torch that the module calls) reaches the
+    caller, as it does through ctypes; an error of a method leaves the call to the other way.  Nothing is launched."""
+    mod, seen, _ = both
+
+    def fail(*a):
+        raise error
+
+    class X:
+        shape = property(fail) if where == "shape" else (3, 512)
+        stride = fail if where == "stride" else lambda self: (512, 1)
+        data_ptr = fail if where == "data_ptr" else lambda self: 4096
+        is_contiguous = fail if where == "is_contiguous" else lambda self: True
+    mod.setup(fail if where == "initialized" else lambda: True, fail if where == "device" else lambda: 0,
+              fail if where == "stream" else lambda d: STREAM, *[1] * 7)
+    t = X()
+    calls = [lambda: mod.quant(t, 1, 0.5, 0.1, 512, t, t), lambda: mod.prefill_static(t, t, t, t, 256, 2, 0.5, 0.1, 512, t),
+             lambda: mod.gemv_grouped(t, [(t, t, 256, t)], 1, 0.5, 0.1)]
+    for call in calls:
+        if raised:
+            with pytest.raises(error):
+                call()
+        else:
+            assert call() is NotImplemented
+    assert not seen
