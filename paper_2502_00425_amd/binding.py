@@ -14,6 +14,7 @@ import importlib.util
 import operator
 import os
 import struct
+import sysconfig
 from typing import Optional, Sequence, Tuple
 
 import numpy as np
@@ -25,7 +26,7 @@ import torch  # noqa: F401
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libmquant.so")
-FAST_PATH = os.path.join(_HERE, "lib", "mquant_fastcall.so")
+FAST_PATH = os.path.join(_HERE, "lib", "mquant_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 EXPORTS = (
     "mquant_version", "mquant_status_string", "mquant_aifs_build_perm", "mquant_aifs_permute",
@@ -188,19 +189,21 @@ def _stream() -> Optional[int]:
     return _raw_stream(_device()) or None
 
 
+class _SlowWay:
+    """In the place of the call module: takes no call."""
+    def __getattr__(self, _):
+        return lambda *_: NotImplemented
+
+
 def _load_fast():
     """The module of csrc/fastcall.c, whose functions take the ordinary calls to the library (2.3 us less of the
-    host's time each); where it cannot, they return NotImplemented and the caller goes on through ctypes."""
-    if not os.path.exists(FAST_PATH):
-        raise ImportError(f"{FAST_PATH} is missing: build it with `python -m paper_2502_00425_amd.build`")
+    host's time each); where it cannot, they return NotImplemented and the caller goes on through ctypes, as all
+    calls do where this interpreter has no such module built."""
+    if not os.path.exists(FAST_PATH) or _raw_stream is None or _device is None:
+        return _SlowWay()
     loader = importlib.machinery.ExtensionFileLoader("mquant_fastcall", FAST_PATH)
     mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location("mquant_fastcall", FAST_PATH, loader=loader))
     loader.exec_module(mod)
-    if _raw_stream is None or _device is None:
-        class SlowWay:
-            def __getattr__(self, _):
-                return lambda *_: NotImplemented
-        return SlowWay()
     mod.setup(torch.cuda.is_initialized, _device, _raw_stream, *(
         ctypes.cast(getattr(lib, "mquant_" + f), ctypes.c_void_p).value
         for f in ("w4a8_linear_prefill", "w4a8_linear_prefill_static", "w4a8_linear_decode", "w4a8_linear_decode_grouped",

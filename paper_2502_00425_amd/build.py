@@ -6,6 +6,8 @@ operations; packed-fp32 instructions are switched off.
 """
 import hashlib
 import os
+import shlex
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -20,8 +22,9 @@ SOURCES = ["aifs.hip", "hadamard_quant.hip", "w4a8_gemm.hip", "w4a8_gemv.hip", "
 # The benchmark's measurement probes: their own shared object, outside the product's ABI.
 PROBES_LIB = os.path.join(LIB_DIR, "libmquant_probes.so")
 PROBES_SOURCES = ["probes.hip"]
-# The interpreter's short way to the library's launches: a CPython module without device code.
-CALL_LIB = os.path.join(LIB_DIR, "mquant_fastcall.so")
+# The interpreter's short way to the library's launches: a CPython module without device code, under the name that
+# this interpreter's ABI gives its modules.  Calls go through ctypes where it is not built.
+CALL_LIB = os.path.join(LIB_DIR, "mquant_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 CALL_SOURCES = ["fastcall.c"]
 HEADERS = ["mquant_internal.h", "hadamard_segment.h", "w4a8_common.h", "w4g128_common.h", "lds_dma.h", "probes.h"]
 
@@ -31,6 +34,7 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wextra", "-Wno-unused-parameter", "-Wno-inline-asm",
 ]
+CC_FLAGS = ["-O2", "-std=gnu11", "-fPIC", "-shared", "-Wall"]
 
 
 def sources():
@@ -38,15 +42,18 @@ def sources():
 
 
 def _deps(srcs):
-    return ([os.path.join(CSRC, s) for s in srcs] + [os.path.join(CSRC, h) for h in HEADERS]
+    headers = [] if srcs is CALL_SOURCES else HEADERS
+    return ([os.path.join(CSRC, s) for s in srcs] + [os.path.join(CSRC, h) for h in headers]
             + [os.path.join(ROOT, "include", "mquant.h")])
 
 
 def source_hash(srcs=None) -> str:
-    """Hash of the sources, headers and compiler flags a library is built from.  It is
-    compiled into libmquant.so (mquant_build_id) and written next to each library, so that
-    staleness is judged by content: file times do not survive every copy of the tree."""
-    h = hashlib.sha256(" ".join(HIPCC_FLAGS).encode())
+    """Hash of the sources, headers and compiler flags a library is built from, for the call module
+    of the interpreter's ABI too.  It is compiled into libmquant.so (mquant_build_id) and written
+    next to each library, so that staleness is judged by content: file times do not survive every
+    copy of the tree."""
+    flags = CC_FLAGS + [sysconfig.get_config_var("SOABI")] if srcs is CALL_SOURCES else HIPCC_FLAGS
+    h = hashlib.sha256(" ".join(flags).encode())
     for d in _deps(SOURCES if srcs is None else srcs):
         h.update(os.path.basename(d).encode())
         with open(d, "rb") as f:
@@ -61,16 +68,32 @@ def _stale(lib, srcs) -> bool:
         return f.read().strip() != source_hash(srcs)
 
 
+def _cc():
+    return shlex.split(os.environ.get("CC") or "gcc")
+
+
+def _can_build_call() -> bool:
+    return shutil.which(_cc()[0]) is not None and os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h"))
+
+
+def _call_stale() -> bool:
+    """The call module can be done without, but not be another build's."""
+    return _stale(CALL_LIB, CALL_SOURCES) and (os.path.exists(CALL_LIB) or _can_build_call())
+
+
+def _hip_stale() -> bool:
+    return _stale(LIB, SOURCES) or _stale(PROBES_LIB, PROBES_SOURCES)
+
+
 def is_stale() -> bool:
     """True when a library is missing or was built from other sources, headers or flags."""
-    return _stale(LIB, SOURCES) or _stale(PROBES_LIB, PROBES_SOURCES) or _stale(CALL_LIB, CALL_SOURCES)
+    return _hip_stale() or _call_stale()
 
 
 def _compile(lib, srcs, verbose):
     build_id = source_hash(srcs)
     if srcs is CALL_SOURCES:
-        cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-fPIC", "-shared", "-Wall", "-I",
-               sysconfig.get_paths()["include"]]
+        cmd = [*_cc(), *CC_FLAGS, "-I", sysconfig.get_paths()["include"]]
     else:
         cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, f'-DMQUANT_BUILD_ID="{build_id}"', "-I", CSRC]
     cmd += ["-I", os.path.join(ROOT, "include"), *[os.path.join(CSRC, s) for s in srcs], "-o", lib]
@@ -94,8 +117,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
         _compile(LIB, SOURCES, verbose)
     if force or _stale(PROBES_LIB, PROBES_SOURCES):
         _compile(PROBES_LIB, PROBES_SOURCES, verbose)
-    if force or _stale(CALL_LIB, CALL_SOURCES):
+    if (force or _stale(CALL_LIB, CALL_SOURCES)) and _can_build_call():
         _compile(CALL_LIB, CALL_SOURCES, verbose)
+    elif _call_stale():
+        os.remove(CALL_LIB)                          # of other sources, and nothing here to build it with
     return LIB
 
 
@@ -103,12 +128,10 @@ def ensure_fresh() -> str:
     """What tests, the smoke run and the benchmark call before loading the library: rebuild
     when the sources differ from what the binary was built from, so an edited kernel is never
     checked against an older build.  Where no compiler is present a stale library is an error."""
+    if _hip_stale() and not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")):
+        raise RuntimeError("libmquant.so is missing or stale and there is no hipcc to build it")
     if is_stale():
-        hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-        if os.path.exists(hipcc):
-            build(force=False)
-        else:
-            raise RuntimeError("libmquant.so is missing or stale and there is no hipcc to build it")
+        build(force=False)
     return LIB
 
 

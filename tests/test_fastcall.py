@@ -150,3 +150,41 @@ def test_interrupts_are_not_swallowed(both, where, error, raised):
         else:
             assert call() is NotImplemented
     assert not seen
+
+
+def test_without_the_module(both, monkeypatch, tmp_path):
+    """An interpreter for which it is not built: every call takes the other way."""
+    mod, seen, mp = both
+    mp.setattr(mq, "FAST_PATH", str(tmp_path / "none.so"))
+    mp.setattr(mq, "_fast", mq._load_fast())
+    for name, call in calls().items():
+        call()
+        assert seen.pop()[0] == name
+
+
+def test_the_module_belongs_to_one_build_and_interpreter(monkeypatch, tmp_path):
+    from paper_2502_00425_amd import build as hip_build
+    assert hip_build.CALL_LIB == mq.FAST_PATH and not hip_build.is_stale()
+    assert hip_build.sysconfig.get_config_var("SOABI") in mq.FAST_PATH
+    ids = {hip_build.source_hash(hip_build.CALL_SOURCES)}
+    with monkeypatch.context() as m:
+        m.setattr(hip_build, "CC_FLAGS", hip_build.CC_FLAGS + ["-g"])
+        ids.add(hip_build.source_hash(hip_build.CALL_SOURCES))
+    with monkeypatch.context() as m:
+        m.setattr(hip_build.sysconfig, "get_config_var", lambda _: "cpython-399-other")
+        ids.add(hip_build.source_hash(hip_build.CALL_SOURCES))
+    assert len(ids) == 3
+    # no compiler: the libraries are whole without the module, and one of other sources does not stay
+    monkeypatch.setattr(hip_build, "CALL_LIB", str(tmp_path / "m.so"))
+    monkeypatch.setenv("CC", "no-such-compiler")
+    monkeypatch.setenv("HIPCC", "/no/such/hipcc")
+    assert not hip_build.is_stale() and hip_build.ensure_fresh() == hip_build.LIB
+    (tmp_path / "m.so").write_bytes(b"")
+    assert hip_build.is_stale()
+    hip_build.ensure_fresh()
+    assert not (tmp_path / "m.so").exists() and not hip_build.is_stale()
+    # with one the module is built without hipcc
+    monkeypatch.delenv("CC")
+    assert hip_build.is_stale()
+    hip_build.ensure_fresh()
+    assert (tmp_path / "m.so").exists() and not hip_build.is_stale()
