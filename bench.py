@@ -233,7 +233,7 @@ class Bench:
             breakdown[p] = {"gemm_us": stats(per_proj[p], 2), "tops": round(ops / gemm_us[p] / 1e6, 1),
                             "frac": round(ops / gemm_us[p] / 1e6 / INT8_MFMA_PEAK_TOPS, 4)}
         alg_bytes = sum(l["K"] * l["N"] / 2 + T * l["K"] + 2 * T * l["N"] + 2 * l["N"] for l in lin.values())
-        roof = {"bound": "mfma", "kernel": "w4a8_gemm_kernel", "achieved": round(gemm_tops, 1),
+        roof = {"bound": "mfma", "kernel": "W4A8 GEMM: w4a8_gemm_kernel, w4a8_sliced_kernel or w4a8_wide_kernel, by shape", "achieved": round(gemm_tops, 1),
                 "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s", "frac": round(gemm_tops / INT8_MFMA_PEAK_TOPS, 4),
                 "traffic": None, "algorithmic_bytes_per_launch": alg_bytes / n_launch,
                 "avg_launch_us": round(gemm_total_us / n_launch, 2),
@@ -243,6 +243,7 @@ class Bench:
         tr = traffic.get(f"c{st['cfg']}") if traffic else None
         if tr is not None:
             roof["traffic"] = tr["bytes_per_gemm_launch"]
+            roof["kernel"] = ", ".join(tr["kernels"])                # those the counter run saw
             roof["traffic_over_algorithmic"] = round(tr["bytes_per_gemm_launch"] / (alg_bytes / n_launch), 3)
         elif traffic is not None:
             roof["traffic_note"] = "no counter run of this configuration on this build"

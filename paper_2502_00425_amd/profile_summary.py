@@ -36,6 +36,8 @@ from collections import defaultdict
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "gemm_hbm_traffic.json")
 GIB_KIB = 1048576.0
+# The kernels that compute a prefill linear, one launch each (split-K adds its reduction).
+GEMM_KERNELS = ("w4a8_gemm_kernel", "w4a8_sliced_kernel", "w4a8_wide_kernel")
 
 
 def read_counter(directory: str, counter: str):
@@ -107,7 +109,7 @@ def trace_table(directory: str, projections=None,
     for _, name, wgs, us in rows:
         label = ""
         if projections:
-            kind = "gemm" if name.startswith(("w4a8_gemm_kernel", "w4a8_sliced_kernel")) else ("quant" if name.startswith("hadamard_quant_kernel") and "false" in name else None)
+            kind = "gemm" if name.startswith(GEMM_KERNELS) else ("quant" if name.startswith("hadamard_quant_kernel") and "false" in name else None)
             if kind:
                 label = projections[seen[kind] % len(projections)]
                 seen[kind] += 1
@@ -194,6 +196,7 @@ def main():
     rows = []
     gemm_bytes = 0.0
     gemm_launches = 0
+    gemm_kernels = set()
     for key in sorted(set(fetch) | set(write)):
         name, grid, wg = key
         fv, wv = fetch.get(key, []), write.get(key, [])
@@ -201,10 +204,11 @@ def main():
         f_avg = sum(fv) / len(fv) * ff if fv else 0.0
         w_avg = sum(wv) / len(wv) * wf if wv else 0.0
         rows.append((name, grid // wg, n, f_avg, w_avg))
-        if name.startswith(("w4a8_gemm_kernel", "w4a8_sliced_kernel", "splitk_reduce_kernel")):
+        if name.startswith(GEMM_KERNELS + ("splitk_reduce_kernel",)):
             gemm_bytes += (f_avg + w_avg) * 1024.0 * n
             if not name.startswith("splitk_reduce_kernel"):
                 gemm_launches += n
+                gemm_kernels.add(name.split("<")[0])
     if gemm_launches == 0:
         raise SystemExit("no GEMM dispatch in the counter output")
     per_launch = gemm_bytes / gemm_launches
@@ -219,7 +223,7 @@ def main():
     data["fetch_factor"], data["write_factor"] = round(ff, 4), round(wf, 4)
     data["configs"][f"c{args.config}"] = {
         "bytes_per_gemm_launch": round(per_launch, 1), "bytes_per_step": round(per_step, 1),
-        "gemm_launches_counted": gemm_launches, "steps": args.steps,
+        "gemm_launches_counted": gemm_launches, "steps": args.steps, "kernels": sorted(gemm_kernels),
         "includes": "GEMM kernel fetch + write, plus the split-K reduce kernel's",
     }
     os.makedirs(os.path.dirname(args.json), exist_ok=True)
