@@ -188,7 +188,7 @@ template <int EPI>
 int launch_wide(int tile, const int8_t *xq, int32_t T, int32_t K, const GemvProblem &pr, const Epilogue &ep, hipStream_t stream);
 
 // What its cost model expects of the tile it would pick.
-double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp);
+double sliced_cost_us(int epi, int32_t T, int32_t K, const GemvGroup &grp);
 
 // ---- the GEMV of w4a8_walk.hip, one work-group per compute unit: several rows on many output channels
 bool gemv_walk_takes(int32_t T, int32_t K, GemvGroup grp);

@@ -1036,12 +1036,12 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 // scales take 0.946 to 1.12 of the time with it (0.997 on average), per-row scales up to 1.44, one flagged channel 0.72 to 2.1,
 // three 0.81 to 2.9; the estimates hold neither short K nor what the epilogues cost the large tiles, most of all at odd N.
 // `share`: of the plan's time that the 256 x 384 tile takes where it takes the linear.
-bool sliced_ahead(int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp, double share)
+bool sliced_ahead(int epi, int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp, double share)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(T, K, grp) < (full ? 0.88 : 0.94) * share * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(epi, T, K, grp) < (full ? 0.88 : 0.94) * share * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
@@ -1214,7 +1214,7 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
     const double wide = EPI != kEpiSplit && splits == 1 && force_tile < 0 ? wide_share(T, N, K) : 1.0;
     const double share = wide < kWideAhead ? wide : 1.0;
-    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(T, N, K, splits, grp, share))))
+    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(EPI, T, N, K, splits, grp, share))))
         return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
     if constexpr (EPI != kEpiSplit)
         if (splits == 1 && force_tile < 0) {

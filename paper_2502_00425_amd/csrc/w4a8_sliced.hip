@@ -358,11 +358,11 @@ using Launch = int (*)(const int8_t *, int32_t, int32_t, GemvGroup, const Epilog
 // The compiled tiles and what they cost.  Fitted to the time of every tile on 53 matrices (K 128 ..
 // 29568, N 32 .. 59136, the 7B and 72B projections among them) at 24 row counts from 33 to 3072, one HIP
 // graph over weights from HBM (rms 3 - 7 %): what the model picks, the tiles of w4a8_gemm.hip included, is within
-// 0.2 % of the fastest on average.  The last four are one work-group to a compute unit with all of its LDS as stages, four of
-// 64 x 128 or 96 x 128 tiles: where tiles fill about one round, a lone work-group with two stages waits for its copies (us
-// before -> now: 8192 -> 10240 at T = 128 31.5 -> 24.4, 12288 -> 8192 at 192 42.0 -> 33.0, 4736 -> 27648 at 33 25.6 -> 19.7).  Fitted
-// to 92 matrices (K 512 .. 29568, N 1024 .. 59136) at thirteen row counts from 33 to 1024; of those 1196 shapes 260 go to them, in
-// 0.91 of the time on average, at worst 1.08 (2048 -> 10240 at T = 128).  Five stages are no better than four.
+// 0.2 % of the fastest on average.  The last four have a compute unit to themselves (128, 160, 84 and 96 KiB of
+// stages) and three or four stages: where tiles fill about one round, a lone work-group with two stages waits for its
+// copies (us before -> now: 8192 -> 10240 at T = 128 31.5 -> 24.4, 12288 -> 8192 at 192 42.0 -> 33.0, 4736 -> 27648 at 33
+// 25.6 -> 19.7).  Fitted to 92 matrices (K 512 .. 29568, N 1024 .. 59136) at thirteen row counts from 33 to 1024.  Five
+// stages are no better than four.
 struct Variant {
     TileCost cost;
     Launch launch[3];
@@ -387,12 +387,22 @@ constexpr Variant kSliced[] = {
     {{128, 256, 1, 2.507, 5.304, 0.602, 0.000, 0.230, 1.424}, MQ_SLICED(4, 8, 3)},
 };
 #undef MQ_SLICED
-// Up to 64 rows these take up to 20 % longer than their fit, whose rows are mostly more (every weight is then read by one
-// tile, from HBM): with the factor all of the 16 shapes of the sweep that go to them gain 10 to 30 %, without it three lose 2
-// to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).
-constexpr int kOneRound = 11;             // the first of the tiles that fill LDS
-constexpr double kFewRows = 1.14;
+// What the estimates of the last four are multiplied by against all others.  They hold within a few percent, while those of
+// the tiles that share a compute unit, of split-K and of the large tiles are up to 15 % above what these take by now,
+// most of all over several rounds.  8000 shapes that the bare estimates send to the four (K 384 .. 29696, T 33 .. 8192): a
+// quarter of them 2 to 24 % slower (static 16640 -> 2624 at T = 3394 147 -> 165 us, 28288 -> 24456 at 213 172 -> 197, 1152 ->
+// 16448 at 65 1.24 times), 0.941 of the time on average; with 1.07 one in a hundred more than 2 % slower, 9 % at most, 0.933
+// on average; with 1.03 one in ten, with 1.1 0.943 on average.  Up to 64 rows the four take up to 20 % longer than their
+// fit, whose rows are mostly more (every weight is then read by one tile, from HBM): with 1.14 all of the 16 shapes of the
+// sweep that go to them gain 10 to 30 %, without it three lose 2 to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).
+constexpr int kOneRound = 11;             // the first of the tiles that have a compute unit to themselves
+constexpr double kAlone = 1.07, kFewRows = 1.14;
+// The operands of flagged channels push two work-groups of this tile off a compute unit, and its estimate does not know: the
+// four are then taken wherever their bare estimates are ahead of it (0.73 .. 0.95 of its time).
+constexpr int kCrowded = 5;
+static_assert(sliced_lds_bytes<3, 4, 2, kEpiStatic>() <= 80 * 1024 && sliced_lds_bytes<3, 4, 2, kEpiSplit>() > 80 * 1024, "kCrowded");
 constexpr int kVariants = sizeof(kSliced) / sizeof(kSliced[0]);
+static_assert(kSliced[kCrowded].cost.bm == 96 && kSliced[kCrowded].cost.per_cu == 2, "kCrowded");
 static_assert(kVariants + 1 == kGemmShapes, "mquant_tune_set validates against this");
 
 // Up to 32 rows, one row of tiles: the weights come from HBM and are what a launch waits for, so the
@@ -415,7 +425,7 @@ struct Choice {
     double us;
 };
 
-Choice pick(int32_t T, int32_t K, const GemvGroup &grp)
+Choice pick(int epi, int32_t T, int32_t K, const GemvGroup &grp)
 {
     auto tiles_n = [&](const TileCost &c) {
         int64_t tiles = 0;
@@ -433,11 +443,19 @@ Choice pick(int32_t T, int32_t K, const GemvGroup &grp)
             consider(s.variant, start + walk * (1.0 + s.slope * (T - 16) * (1.0 / 16)));
         }
     } else {
-        for (int i = 0; i < kVariants; ++i) {
+        auto us_of = [&](int i) {
             const TileCost &c = kSliced[i].cost;
-            const double us = c.us(tiles_n(c) * ceil_div32(T, c.bm), K);
-            consider(i, T <= 64 && i >= kOneRound ? kFewRows * us : us);
+            return c.us(tiles_n(c) * ceil_div32(T, c.bm), K);
+        };
+        for (int i = 0; i < kOneRound; ++i) consider(i, us_of(i));
+        const double factor = T <= 64 ? kFewRows : kAlone;
+        const double bar = best.us * (epi == kEpiSplit && best.variant == kCrowded ? factor : 1.0);
+        Choice alone = {-1, bar};
+        for (int i = kOneRound; i < kVariants; ++i) {
+            const double us = factor * us_of(i);
+            if (us < alone.us) alone = {i, us};
         }
+        if (alone.variant >= 0) best = {alone.variant, alone.us < best.us ? alone.us : best.us};
     }
     return best;
 }
@@ -446,7 +464,7 @@ Choice pick(int32_t T, int32_t K, const GemvGroup &grp)
 
 namespace mquant {
 
-double sliced_cost_us(int32_t T, int32_t K, const GemvGroup &grp) { return pick(T, K, grp).us; }
+double sliced_cost_us(int epi, int32_t T, int32_t K, const GemvGroup &grp) { return pick(epi, T, K, grp).us; }
 
 // From 33 rows on always.  Of 17 to 32 rows the GEMV keeps what the GEMM is not expected to do faster by
 // 2 %, or at all where the weights take 10 us and more to read (GEMV against GEMM, weights from HBM, 24
@@ -461,7 +479,7 @@ bool gemm_takes(int32_t T, int32_t K, const GemvGroup &grp)
     for (int32_t i = 0; i < grp.n; ++i) n_tiles += ceil_div32(grp.p[i].N, kPackN);
     if (K <= 256 && n_tiles < kNumCU) return false;
     const double margin = n_tiles * K >= int64_t{1} << 22 ? 1.0 : 0.98;     // 64 MiB of weights
-    return sliced_cost_us(T, K, grp) < margin * gemv_tile_us(T, n_tiles, K);
+    return sliced_cost_us(kEpiStatic, T, K, grp) < margin * gemv_tile_us(T, n_tiles, K);
 }
 
 template <int EPI>
@@ -469,7 +487,7 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
                     hipStream_t stream)
 {
     int v = tune_state().gemm_sliced.load(std::memory_order_relaxed);
-    if (v < 0) v = pick(T, K, grp).variant;
+    if (v < 0) v = pick(EPI, T, K, grp).variant;
     if (v == kVariants) {                    // forced: 256 x 384, or the largest tile here for what that does not take
         if constexpr (EPI != kEpiSplit)
             if (grp.n == 1) return launch_wide<EPI>(0, xq, T, K, grp.p[0], ep, stream);

@@ -123,3 +123,33 @@ def test_sliced_gemm_keeps_narrow_margins(mq, T, N, K):
                  lambda: mq.w4a8_gemm_rms(xq, wp, ws, N, 0, 1.0, 1.0, *split, out=y, workspace=wk)):
         got = kernels(call)
         assert len(got) == 1 and got[0].startswith("w4a8_sliced_kernel<"), got
+
+
+def w4a8_as(mq, epi, T, N, K):
+    """Kernels of one linear with static scales, per-row scales or that many flagged channels."""
+    say(f"W4A8 {epi} T={T} N={N} K={K}")
+    xq = torch.zeros((T, K), dtype=torch.int8, device="cuda")
+    wp = torch.zeros(mq.w4_prepacked_bytes(N, K), dtype=torch.uint8, device="cuda")
+    ws, rs = torch.ones(N, dtype=torch.float16, device="cuda"), torch.ones(T, device="cuda")
+    y = torch.empty((T, N), dtype=torch.float16, device="cuda")
+    wk = torch.empty(max(mq.w4a8_workspace_bytes(T, N, K), 256), dtype=torch.uint8, device="cuda")
+    if epi == "static":
+        return kernels(lambda: mq.w4a8_gemm(xq, wp, ws, N, 0, 1.0, 1.0, out=y, workspace=wk))
+    if epi == "row":
+        return kernels(lambda: mq.w4a8_gemm_rowscale(xq, wp, ws, rs, N, out=y, workspace=wk))
+    split = np.arange(epi, dtype=np.int32), torch.zeros((epi, N), dtype=torch.int8, device="cuda"), np.ones(epi, dtype=np.float32)
+    return kernels(lambda: mq.w4a8_gemm_rms(xq, wp, ws, N, 0, 1.0, 1.0, *split, out=y, workspace=wk))
+
+
+@pytest.mark.parametrize("epi,T,N,K,name", [
+    ("static", 65, 16448, 1152, "w4a8_gemm_kernel<64, 128,"), ("static", 2863, 3072, 10624, "w4a8_sliced_kernel<3, 4, 2,"),   # 1.24, 1.19
+    ("row", 7763, 1425, 12288, "w4a8_sliced_kernel<3, 4, 2,"), ("static", 495, 11712, 27264, "w4a8_gemm_kernel<256, 256,"),   # 1.19, 1.15
+    (1, 985, 6016, 28672, "w4a8_gemm_kernel<256, 256,"), ("row", 1217, 3792, 5760, "w4a8_sliced_kernel<5, 4, 2,"),            # 1.14, 1.10
+    (1, 329, 11904, 12416, "w4a8_sliced_kernel<3, 8, 3,"), ("row", 40, 23936, 5120, "w4a8_sliced_kernel<2, 4, 4,"),           # 0.64, 0.75
+    ("static", 763, 2285, 18944, "w4a8_sliced_kernel<2, 4, 4,"), ("static", 144, 12480, 11776, "w4a8_sliced_kernel<3, 4, 4,"),  # 0.76, 0.80
+])
+def test_tiles_that_have_a_compute_unit_alone(mq, epi, T, N, K, name):
+    """The sliced tiles with three and four stages against all others (their time over the other side's: over 1 they are not
+    taken)."""
+    got = w4a8_as(mq, epi, T, N, K)
+    assert got[0].startswith(name) and (len(got) == 1 or got[1].startswith("splitk_reduce_kernel")), got
