@@ -959,25 +959,43 @@ int pick_gemm_tile(int32_t T, int32_t N)
     return b <= c ? 1 : 2;
 }
 
-// The 256 x 384 tile's time over that of the tile above, by rounds of tiles over the CUs x tile area / relative rate.  A
-// last round of few tiles takes little over half the time of a full one, since fewer busy CUs run at a higher clock.  Estimate
-// and measured: 3584 -> 37888 at T = 1280 0.94 / 0.93 and 0.97 (two boxes), 2048 1.03 / 1.04, 4096 0.96 / 0.97; 3584 -> 4608 at
-// 4096 0.87 / 0.90; 8192 -> 10240 at 2048 0.86 / 0.89, 16384 0.96 / 0.97; 8192 -> 59136 at 16384 0.94 / 0.94 and 0.97; 8192 -> 8192
-// at 16384 1.01 / 1.02.  Short K pays for the larger tile's start (640 -> 5000 at T = 16384 79.5 / 81.6 us).
-double wide_share(int32_t T, int32_t N, int32_t K)
+// What a linear of more than 512 rows and at least 1024 channels takes on the 256 x 384 tile and on the tiles above: a TileCost
+// and, for every round (128 x 256: every tile / CUs), what per-row scales and stores of two bytes add; the epilogue of a
+// work-group that has its unit alone runs under nobody's main loop.  Fitted to 3700 shapes (K 1024 .. 29696, N 512 .. 60000, T
+// 513 .. 8192, half of them drawn from those an earlier rule sent to 256 x 384) with weights from HBM, rms 3 - 4 %.
+struct LargeCost {
+    TileCost cost;
+    double row, narrow, narrow_row;
+};
+constexpr LargeCost kWide = {{256, 384, 1, 3.601, 5.233, 1.094, 0.000, 0.952, 4.589}, 1.938, 9.239, 13.396};
+constexpr LargeCost kLarge[] = {
+    {{256, 256, 1, 2.060, 7.054, 0.777, 0.000, 0.663}, 0.440, 5.528, 9.724},
+    {{128, 256, 2, 4.567, 0.000, 0.839, 0.517, 0.326, 2.534}, 0.534, 2.392, 3.463},
+    {{192, 128, 1, 2.772, 3.611, 0.306, 0.000, 0.361}, 0.290, 1.873, 4.011},
+};
+
+double large_us(const LargeCost &c, int epi, int32_t T, int32_t N, int32_t K, bool narrow)
 {
-    if (T <= 512 || K < 1024) return 1.0;
-    auto rounds = [](int64_t tiles) {
-        const int64_t rest = tiles % kNumCU;
-        return static_cast<double>(tiles / kNumCU) + (rest > 0 ? 0.5 + rest * (0.5 / kNumCU) : 0.0);
-    };
-    const int tile = pick_gemm_tile(T, N);
-    const double old = tile == 0   ? rounds(ceil_div(T, 256) * ceil_div(N, 256)) * (256.0 * 256.0)
-                       : tile == 1 ? rounds(ceil_div(T, 128) * ceil_div(N, 256)) * (128.0 * 256.0 / 0.93)
-                                   : rounds(ceil_div(T, 192) * ceil_div(N, 128)) * (192.0 * 128.0 / 0.78);
-    return rounds(ceil_div(T, 256) * ceil_div(N, 384)) * (256.0 * 384.0 / 1.07) / old;
+    const int64_t tiles = ceil_div(T, c.cost.bm) * ceil_div(N, c.cost.bn);
+    const double times = c.cost.per_cu == 1 ? static_cast<double>(ceil_div(tiles, kNumCU)) : static_cast<double>(tiles) * (1.0 / kNumCU);
+    const bool row = epi == kEpiRowScale;
+    return c.cost.us(tiles, K) + times * ((row ? c.row : 0.0) + (narrow ? c.narrow : 0.0) + (row && narrow ? c.narrow_row : 0.0));
 }
-constexpr double kWideAhead = 0.97;
+
+// Whether 256 x 384 takes a linear from the sliced GEMM or from the tile above, `narrow`: with stores of two bytes.  Its time
+// over theirs on the 3700 shapes: 0.970 on average where it is taken by the present margins, seven of 1840 more than 2 % slower (1.035 at
+// worst); by rounds of tiles and one rate for each tile, without short K, the stores and the rows, 0.979 with 480 of 2560 (1536
+// -> 13814 at T = 7730 176 -> 223 us, 1152 -> 24077 at 3487 with per-row scales 1.36 times, 1024 -> 17105 at 948 1.6).  On 641
+// others that the two rules send elsewhere this one takes 0.931 of that one's time.
+// 256 x 256 never was more than 1.5 % ahead where the estimates are even.
+constexpr double kWideAhead = 0.97, kWideAheadOfLargest = 0.99;
+bool wide_ahead(int epi, int32_t T, int32_t N, int32_t K, bool narrow, bool sliced, const GemvGroup &grp)
+{
+    const double wide = large_us(kWide, epi, T, N, K, narrow);
+    if (sliced) return wide < kWideAhead * sliced_cost_us(epi, T, K, grp);
+    const int tile = pick_gemm_tile(T, N);
+    return wide < (tile == 0 ? kWideAheadOfLargest : kWideAhead) * large_us(kLarge[tile], epi, T, N, K, narrow);
+}
 
 // Where 256 x 384 is not ahead: the tile of w4a8_wide.hip (its index there) that is expected ahead of the tile above, or -1, by
 // the same rounds with 0.7 of a full one for a last round of few tiles: rates and that share with the least regret over 168
@@ -987,7 +1005,6 @@ constexpr double kWideAhead = 0.97;
 // 35.8 / 37.2).  They take linears from that tile only: the margin of the sliced GEMM covers errors of its estimate on them that were not measured.
 int smaller_wide(int32_t T, int32_t N, int32_t K)
 {
-    if (T <= 512 || K < 1024) return -1;
     auto time = [&](int32_t bm, int32_t bn, double rate) {
         const int64_t tiles = ceil_div(T, bm) * ceil_div(N, bn), rest = tiles % kNumCU;
         const double rounds = static_cast<double>(tiles / kNumCU) + (rest > 0 ? 0.7 + rest * (0.3 / kNumCU) : 0.0);
@@ -1000,7 +1017,7 @@ int smaller_wide(int32_t T, int32_t N, int32_t K)
         if (of[i] < of[best] && (K >= 3072 || groups[i] <= kNumCU)) best = i;
     const int tile = pick_gemm_tile(T, N);
     const double plan = tile == 0 ? time(256, 256, 1.0) : tile == 1 ? time(128, 256, 0.93) : time(192, 128, 0.815);
-    return of[best] < kWideAhead * plan ? best + 1 : -1;
+    return of[best] < 0.97 * plan ? best + 1 : -1;
 }
 
 // What the plan above costs in microseconds (split-K with its reduction, or the tile), for the
@@ -1035,13 +1052,12 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 // those from before), but 14.5 % was not sound: on 45 shapes drawn from those that the two margins decide differently, static
 // scales take 0.946 to 1.12 of the time with it (0.997 on average), per-row scales up to 1.44, one flagged channel 0.72 to 2.1,
 // three 0.81 to 2.9; the estimates hold neither short K nor what the epilogues cost the large tiles, most of all at odd N.
-// `share`: of the plan's time that the 256 x 384 tile takes where it takes the linear.
-bool sliced_ahead(int epi, int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp, double share)
+bool sliced_ahead(int epi, int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(epi, T, K, grp) < (full ? 0.88 : 0.94) * share * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(epi, T, K, grp) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace
@@ -1212,15 +1228,14 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     // The sliced GEMM on few tiles (T = 128: 3584 x 4608 17.1 -> 9.9 us, 18944 x 3584 38.6 -> 22.3, 8192 x 8192 27.1
     // -> 15.9; T = 512: 22.8 -> 16.2 on 3584 x 4608) and wherever else it is expected to be ahead.
     const int force_tile = tune_state().gemm_tile.load(std::memory_order_relaxed);
-    const double wide = EPI != kEpiSplit && splits == 1 && force_tile < 0 ? wide_share(T, N, K) : 1.0;
-    const double share = wide < kWideAhead ? wide : 1.0;
-    if (force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(EPI, T, N, K, splits, grp, share))))
-        return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
+    const bool sliced = force_sliced || (force_tile < 0 && (T <= kGemvMaxT || sliced_ahead(EPI, T, N, K, splits, grp)));
     if constexpr (EPI != kEpiSplit)
-        if (splits == 1 && force_tile < 0) {
-            const int tile = share < 1.0 ? 0 : smaller_wide(T, N, K);
+        if (!force_sliced && force_tile < 0 && splits == 1 && T > 512 && K >= 1024) {
+            const bool narrow = N % 8 != 0 || ldy % 8 != 0 || !aligned_to(y, 16) || acc_out != nullptr;
+            const int tile = wide_ahead(EPI, T, N, K, narrow, sliced, grp) ? 0 : sliced ? -1 : smaller_wide(T, N, K);
             if (tile >= 0) return launch_wide<EPI>(tile, xq, T, K, grp.p[0], ep, stream);
         }
+    if (sliced) return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
     if (splits > 1)
         return launch_gemm<256, 256, 2, 4, 3, EPI>(xq, wp, w_scale, y, ldy, acc_out, T, N, K, ep, splits,
                                                  static_cast<int32_t *>(workspace), stream);

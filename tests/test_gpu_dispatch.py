@@ -153,3 +153,18 @@ def test_tiles_that_have_a_compute_unit_alone(mq, epi, T, N, K, name):
     taken)."""
     got = w4a8_as(mq, epi, T, N, K)
     assert got[0].startswith(name) and (len(got) == 1 or got[1].startswith("splitk_reduce_kernel")), got
+
+
+@pytest.mark.parametrize("epi,T,N,K,name", [
+    ("row", 948, 17105, 1024, "w4a8_sliced_kernel<"), ("static", 772, 18764, 1152, "w4a8_sliced_kernel<"),    # 1.62, 1.35
+    ("row", 3487, 24077, 1152, "w4a8_wide_kernel<2, 2,"), ("static", 7730, 13814, 1536, "w4a8_wide_kernel<2, 2,"),   # 1.36, 1.27
+    ("row", 4523, 3861, 1152, "w4a8_gemm_kernel<192, 128,"), ("row", 5691, 14208, 1792, "w4a8_wide_kernel<2, 2,"),   # 1.10, 1.14
+    ("static", 1280, 37888, 3584, "w4a8_wide_kernel<4, 3,"), ("row", 1280, 37888, 3584, "w4a8_wide_kernel<4, 3,"),   # 0.94, 0.96
+    ("static", 4096, 4608, 3584, "w4a8_wide_kernel<4, 3,"), ("row", 2048, 10240, 8192, "w4a8_wide_kernel<4, 3,"),    # 0.90, 0.90
+    ("static", 4096, 37888, 3584, "w4a8_wide_kernel<4, 3,"),                                                  # 0.96
+])
+def test_largest_tile(mq, epi, T, N, K, name):
+    """256 x 384 against the sliced GEMM and the tiles of one and two work-groups to a compute unit (its time over the other
+    side's: over 1 it is not taken)."""
+    got = w4a8_as(mq, epi, T, N, K)
+    assert len(got) == 1 and got[0].startswith(name), got
