@@ -998,12 +998,15 @@ bool wide_ahead(int epi, int32_t T, int32_t N, int32_t K, bool narrow, bool slic
 }
 
 // Where 256 x 384 is not ahead: the tile of w4a8_wide.hip (its index there) that is expected ahead of the tile above, or -1, by
-// the same rounds with 0.7 of a full one for a last round of few tiles: rates and that share with the least regret over 168
-// shapes at T = 520 .. 8192 (0.2 % on average, 7.7 % at most).  us, the tile above / this: 8192 -> 10240 at T = 900 82.9 / 68.2,
+// rounds of tiles over the CUs x tile area / rate, a last round of few tiles counted as 0.7 of a full one: rates and that share
+// with the least regret over 168 shapes at T = 520 .. 8192.  us, the tile above / this: 8192 -> 10240 at T = 900 82.9 / 68.2,
 // 3584 -> 4608 at 2048 38.6 / 32.7, 3584 -> 3584 at 3000 39.9 / 35.0.  On short K the first two take one
 // round only: nothing hides the start of the next (1536 -> 8960 at 4096, three rounds: 58.0 / 62.7; 2048 -> 11008 at 1440, two:
 // 35.8 / 37.2).  They take linears from that tile only: the margin of the sliced GEMM covers errors of its estimate on them that were not measured.
-int smaller_wide(int32_t T, int32_t N, int32_t K)
+//   From 128 x 256, two of which hide each other's start and end on a unit, the first two take long K only (with stores of two bytes
+// longer K) and what is 9 % ahead: 224 such shapes 0.951 of that tile's time on average, 1.025 at worst, the 150 others 0.986 with
+// 1.09 at worst (3968 -> 52928 at T = 1329, per-row scales).  128 x 256 here takes those instead, at 0.968.
+int smaller_wide(int32_t T, int32_t N, int32_t K, bool narrow)
 {
     auto time = [&](int32_t bm, int32_t bn, double rate) {
         const int64_t tiles = ceil_div(T, bm) * ceil_div(N, bn), rest = tiles % kNumCU;
@@ -1012,11 +1015,14 @@ int smaller_wide(int32_t T, int32_t N, int32_t K)
     };
     const double of[] = {time(192, 256, 0.95), time(128, 384, 0.95), time(128, 256, 0.96)};
     const int64_t groups[] = {ceil_div(T, 192) * ceil_div(N, 256), ceil_div(T, 128) * ceil_div(N, 384)};
-    int best = 2;
-    for (int i = 0; i < 2; ++i)
-        if (of[i] < of[best] && (K >= 3072 || groups[i] <= kNumCU)) best = i;
     const int tile = pick_gemm_tile(T, N);
     const double plan = tile == 0 ? time(256, 256, 1.0) : tile == 1 ? time(128, 256, 0.93) : time(192, 128, 0.815);
+    auto allowed = [&](int i) {
+        return tile == 1 ? K >= (narrow ? 8192 : 4096) && of[i] < 0.91 * plan : K >= 3072 || groups[i] <= kNumCU;
+    };
+    int best = 2;
+    for (int i = 0; i < 2; ++i)
+        if (of[i] < of[best] && allowed(i)) best = i;
     return of[best] < 0.97 * plan ? best + 1 : -1;
 }
 
@@ -1232,7 +1238,7 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     if constexpr (EPI != kEpiSplit)
         if (!force_sliced && force_tile < 0 && splits == 1 && T > 512 && K >= 1024) {
             const bool narrow = N % 8 != 0 || ldy % 8 != 0 || !aligned_to(y, 16) || acc_out != nullptr;
-            const int tile = wide_ahead(EPI, T, N, K, narrow, sliced, grp) ? 0 : sliced ? -1 : smaller_wide(T, N, K);
+            const int tile = wide_ahead(EPI, T, N, K, narrow, sliced, grp) ? 0 : sliced ? -1 : smaller_wide(T, N, K, narrow);
             if (tile >= 0) return launch_wide<EPI>(tile, xq, T, K, grp.p[0], ep, stream);
         }
     if (sliced) return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);

@@ -168,3 +168,14 @@ def test_largest_tile(mq, epi, T, N, K, name):
     side's: over 1 it is not taken)."""
     got = w4a8_as(mq, epi, T, N, K)
     assert len(got) == 1 and got[0].startswith(name), got
+
+
+@pytest.mark.parametrize("epi,T,N,K,name", [
+    ("row", 1329, 52928, 3968, "w4a8_wide_kernel<2, 2,"), ("static", 1289, 16796, 3584, "w4a8_wide_kernel<2, 2,"),   # 1.09, 1.06
+    ("row", 1795, 18020, 3072, "w4a8_wide_kernel<2, 2,"), ("row", 6579, 4992, 3456, "w4a8_wide_kernel<2, 2,"),       # 1.07, 1.07
+    ("static", 900, 10240, 8192, "w4a8_wide_kernel<3, 2,"), ("static", 2048, 4608, 3584, "w4a8_wide_kernel<2, 3,"),  # 0.82, 0.85
+])
+def test_smaller_large_tiles(mq, epi, T, N, K, name):
+    """192 x 256 and 128 x 384 against 128 x 256 (their time over the other side's: over 1 they are not taken)."""
+    got = w4a8_as(mq, epi, T, N, K)
+    assert len(got) == 1 and got[0].startswith(name), got
