@@ -95,6 +95,7 @@ def test_w4a8_prompts(mq, T, N, K, name):
     (17, 1024, 128, "w4a8_gemv_kernel"),                                                # 2.8 (3.2)
     (24, 3584, 18944, "w4a8_sliced_kernel"), (32, 10240, 8192, "w4a8_sliced_kernel"),   # 17.4 (GEMV 18.2), 14.6 (16.0)
     (32, 59136, 8192, "w4a8_sliced_kernel"), (24, 18944, 384, "w4a8_sliced_kernel"),    # 50.8 (57.4), 4.8 (6.7)
+    (32, 32437, 4608, "w4a8_sliced_kernel"),                                            # 18.6 (walking kernel in two rounds 21.4)
 ])
 def test_w4a8_decode_rows_above_sixteen(mq, T, N, K, name):
     """GEMV against sliced GEMM from 17 to 32 rows (microseconds measured, in brackets the other side),
