@@ -19,7 +19,7 @@
 
 using namespace mquant;
 
-namespace mquant::walk {
+namespace {
 
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
@@ -30,7 +30,7 @@ constexpr int kWalkMaxLds = 160 * 1024;
 
 // RB: blocks of 16 rows; NX: pieces of xq per thread.  Every wave has at least DEPTH loads.
 template <int DEPTH, int RB, int NX, int EPI>
-__global__ __launch_bounds__(kWalkWaves * 64) void w4a8_gemv_kernel(
+__global__ __launch_bounds__(kWalkWaves * 64) void w4a8_walk_kernel(
     const int8_t *__restrict__ xq, int32_t T, int32_t K, GemvGroup grp, int32_t total_units, Epilogue ep,
     uint32_t row_magic)
 {
@@ -186,12 +186,6 @@ __global__ __launch_bounds__(kWalkWaves * 64) void w4a8_gemv_kernel(
     }
 }
 
-}  // namespace mquant::walk
-
-namespace {
-
-using walk::kWalkMaxLds, walk::kWalkMaxXq, walk::kWalkPieces, walk::kWalkWaves;
-
 // Loads in flight per wave, by the rows: two row blocks leave registers for three.
 constexpr int walk_depth(int32_t T) { return T > 16 ? 3 : 6; }
 
@@ -228,7 +222,7 @@ template <int DEPTH, int RB, int NX>
 int launch_walk(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp, int32_t units, int32_t groups,
                 const Epilogue &ep, hipStream_t stream)
 {
-    auto kern = walk::w4a8_gemv_kernel<DEPTH, RB, NX, kEpiStatic>;
+    auto kern = w4a8_walk_kernel<DEPTH, RB, NX, kEpiStatic>;
     static LdsLimit limit;
     if (const int st = limit.raise(reinterpret_cast<const void *>(kern), kWalkMaxLds); st != MQUANT_OK) return st;
     const uint32_t vecs = static_cast<uint32_t>(K / 16);

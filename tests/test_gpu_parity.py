@@ -581,8 +581,7 @@ def test_gemv_walk_equals_the_oracle(mq, T, K, Ns):
         want.append(orc.dequant(accs[-1], V, s_vis, s_txt, w_scale)[1])
     xqd = dev(xq)
     names = traced(lambda: mq.w4a8_gemv_grouped(xqd, lin, V, s_vis, s_txt))
-    assert names is None or (len(names) == 1 and names[0].startswith(f"w4a8_gemv_kernel<{6 if T <= 16 else 3}, ")
-                             and names[0].count(",") == 3), names
+    assert names is None or (len(names) == 1 and names[0].startswith(f"w4a8_walk_kernel<{6 if T <= 16 else 3}, ")), names
     for (_, _, N, out), w in zip(lin, want):
         assert (out.cpu().numpy().view(np.uint16) == w.view(np.uint16)).all(), f"N={N}"
         assert bool((out._base[:, N:] == 3.0).all())
