@@ -145,6 +145,23 @@ def test_smaller_wide_tiles_by_choice(mq, T, N, K, tile):
     assert names is None or (len(names) == 1 and names[0].startswith("w4a8_wide_kernel" + tile)), names
 
 
+@pytest.mark.parametrize("T,N,K,tile", [(1150, 7672, 1024, "<3, 2,"), (1010, 10232, 1024, "<2, 3,"), (526, 10904, 1152, "<2, 2,")])
+def test_accumulators_of_the_smaller_wide_tiles(mq, T, N, K, tile):
+    rng = np.random.default_rng(T + N)
+    xq = rng.integers(-128, 128, size=(T, K), dtype=np.int8)
+    packed = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    w_scale = rng.uniform(0.005, 0.02, size=N).astype(np.float16)
+    want = orc.gemm_i8_i4_i32(xq, orc.unpack_w4(packed))
+    xd, wp, ws = dev(xq), mq.w4_prepack(dev(packed)), dev(w_scale)
+    acc = torch.full((T, N), -7, dtype=torch.int32, device="cuda")
+    y = torch.empty((T, N), dtype=torch.float16, device="cuda")
+    say(f"wide accumulators T={T} N={N} K={K}")
+    names = traced(lambda: mq.w4a8_gemm(xd, wp, ws, N, T // 3, 0.07, 0.009, out=y, acc_out=acc))
+    assert names is None or (len(names) == 1 and names[0].startswith("w4a8_wide_kernel" + tile)), names
+    assert (acc.cpu().numpy() == want).all()
+    assert (bits(y) == orc.dequant(want, T // 3, 0.07, 0.009, w_scale)[1].view(np.uint16)).all()
+
+
 @pytest.mark.parametrize("T", [5, 17, 25, 32])
 @pytest.mark.parametrize("K", [128, 3584])
 def test_group_of_linears(mq, T, K):
@@ -159,7 +176,7 @@ def test_group_of_linears(mq, T, K):
         want.append(orc.dequant(orc.gemm_i8_i4_i32(xq, orc.unpack_w4(packed)), T // 3, 0.07, 0.009, w_scale)[1])
         lin.append((mq.w4_prepack(dev(packed)), dev(w_scale), N, torch.empty((T, N), dtype=torch.float16, device="cuda")))
     try:
-        for tile in range(-1, TILES):
+        for tile in range(-1, TILES + 5):                # the last, 256 x 384, leaves a group to the one before
             say(f"group T={T} K={K} tile {tile}")
             mq.tune_set(mq.TUNE_GEMM_SHAPE, tile)
             for l in lin:
