@@ -1057,7 +1057,8 @@ double prefill_cost_us(int32_t T, int32_t N, int32_t K, int32_t splits)
 // The large tiles have got faster since (scalar addresses; kPrefillCost and the efficiencies of pick_gemm_tile are
 // those from before), but 14.5 % was not sound: on 45 shapes drawn from those that the two margins decide differently, static
 // scales take 0.946 to 1.12 of the time with it (0.997 on average), per-row scales up to 1.44, one flagged channel 0.72 to 2.1,
-// three 0.81 to 2.9; the estimates hold neither short K nor what the epilogues cost the large tiles, most of all at odd N.
+// three 0.81 to 2.9; the estimates hold neither short K nor what the epilogues cost the large tiles, most of all at odd N.  (The
+// large tiles read the terms of flagged channels from memory then; staged in LDS they take a quarter of that time.)
 bool sliced_ahead(int epi, int32_t T, int32_t N, int32_t K, int32_t splits, const GemvGroup &grp)
 {
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];

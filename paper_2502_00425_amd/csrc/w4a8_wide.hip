@@ -1,8 +1,9 @@
 // W4A8 GEMM with 256 x 384 tiles and three smaller ones: the largest prefill linears, and shapes whose tiles of one of these
 // sizes fill the compute units' rounds better than those of w4a8_gemm.hip.
 //
-// What bounds the largest is power, and a large part of it goes into bringing operands to the matrix cores.  Per
-// multiply-add the 256 x 384 tile takes 22 % fewer bytes out of the L2 and 27 % fewer out of LDS than 256 x 256 with
+// What bounds the largest is power (8192 -> 59136 at T = 16384: the matrix pipes hold an MFMA in 84 % of the busy cycles, 78 % with
+// 256 x 256, at 1.70 GHz where the rotation beside it runs at 2.0), and a large part of it goes into bringing operands to the matrix
+// cores.  Per multiply-add the 256 x 384 tile takes 22 % fewer bytes out of the L2 and 27 % fewer out of LDS than 256 x 256 with
 // 128 x 64 wave tiles: eight waves, two rows of four, hold 128 x 96 each, 192 accumulator registers.  The 64 that
 // are left do not take two sets of operands, so the fragments of the activations go through a ring of four, each requested
 // nine MFMAs ahead and used for three; a weight operand is unpacked again into its own registers as soon as the last of its

@@ -64,7 +64,7 @@ struct Unpack {
     }
 };
 
-// ---- the GEMV of w4g128_walk.hip, one work-group per compute unit, up to sixteen rows that fit LDS
+// ---- the GEMV of w4g128_walk.hip, one work-group per compute unit, two to sixteen rows that fit LDS
 bool g128_walk_takes(int32_t T, int32_t K, int32_t N);
 int g128_walk(const __half *x, int64_t ldx, const v4u *wt, const __half *sT, __half *y, int64_t ldy, int32_t T, int32_t N,
               int32_t K, int32_t n_pad, hipStream_t stream);

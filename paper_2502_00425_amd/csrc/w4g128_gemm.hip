@@ -700,8 +700,8 @@ extern "C" int mquant_w4g128_gemm(const void *x, int64_t ldx, const uint8_t *wp,
     const __half *xh = static_cast<const __half *>(x);
     __half *yh = static_cast<__half *>(y);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // Up to twelve rows the GEMV streams the weights; from 13 to 32 it does where the GEMM is not
-    // expected to be 5 % ahead: GEMV against GEMM at 13 and 32 rows: 18944 x 3584 27.7 / 25.9 us and 46.7 /
+    // Up to twelve rows a GEMV streams the weights; from 13 to 32 one does where the GEMM is not
+    // expected to be 5 % ahead of the GEMV with a work-group per tile (the walking one is not weighed here): GEMV against GEMM at 13 and 32 rows: 18944 x 3584 27.7 / 25.9 us and 46.7 /
     // 27.2, 3584 x 18944 16.9 / 16.3 and 27.9 / 17.9, 512 x 16384 3.9 / 4.4 and 5.2 / 4.6.  It also takes rows so far
     // apart that the GEMM's 32-bit offsets inside a tile would not reach, 32 of them at a time.
     const int32_t n_tiles32 = static_cast<int32_t>(ceil_div(N, kPackN));

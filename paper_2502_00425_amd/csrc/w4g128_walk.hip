@@ -1,5 +1,7 @@
-// Weight-only W4 GEMV for up to sixteen rows: one work-group of sixteen waves per compute unit walks a
-// contiguous run of 16-channel units (halves of the prepacked tiles).
+// Weight-only W4 GEMV for two to sixteen rows: one work-group of sixteen waves per compute unit walks a
+// contiguous run of 16-channel units (halves of the prepacked tiles).  From thirteen rows on it is asked only where the
+// GEMM is not expected ahead of the GEMV with a work-group per tile (3584 -> 37888: 26.7 -> 20.6 us at twelve rows, at sixteen the
+// GEMM keeps its 27).
 //
 // The rows and the scales of the run go to LDS once; the weights of the run are one stream whose 1 KiB
 // wave-loads (16 channels x one scale group) are dealt to the waves in even contiguous shares, DEPTH of
