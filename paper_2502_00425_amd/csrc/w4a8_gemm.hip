@@ -982,22 +982,27 @@ double large_us(const LargeCost &c, int epi, int32_t T, int32_t N, int32_t K, bo
     return c.cost.us(tiles, K) + times * ((row ? c.row : 0.0) + (narrow ? c.narrow : 0.0) + (row && narrow ? c.narrow_row : 0.0));
 }
 
-// Whether 256 x 384 takes a linear from the sliced GEMM or from the tile above, `narrow`: with stores of two bytes.  Its time
-// over theirs on the 3700 shapes: 0.970 on average where it is taken by the present margins, seven of 1840 more than 2 % slower (1.035 at
-// worst); by rounds of tiles and one rate for each tile, without short K, the stores and the rows, 0.979 with 480 of 2560 (1536
-// -> 13814 at T = 7730 176 -> 223 us, 1152 -> 24077 at 3487 with per-row scales 1.36 times, 1024 -> 17105 at 948 1.6).  On 641
-// others that the two rules send elsewhere this one takes 0.931 of that one's time.
-// 256 x 256 never was more than 1.5 % ahead where the estimates are even.
-constexpr double kWideAhead = 0.97, kWideAheadOfLargest = 0.99;
-bool wide_ahead(int epi, int32_t T, int32_t N, int32_t K, bool narrow, bool sliced, const GemvGroup &grp)
+// Whether 256 x 384 takes a linear from the sliced GEMM or from the tile above; `narrow`: with stores of two bytes.  The margins are
+// from 420 shapes around the line, each side in a run of its own of 90 ms: there the larger tile, which spends less power on its
+// operands, gains 3 % on the costs, whose shapes were timed with the others in turn (0.959 of the time on average over
+// all 420, one of 249 that are taken more than 1 % slower, 1.02; without that 3 % 0.972).  It also leaves the clock higher for what
+// comes next: 3584 -> 37888 at T = 1003 takes 118 us either way, and a pass of four such linears 278 instead of 285.
+// By rounds of tiles and one rate for each tile, without short K, the stores and the rows, 480 of 2560 drawn shapes were more than
+// 2 % slower (1536 -> 13814 at T = 7730 176 -> 223 us, 1152 -> 24077 at 3487 with per-row scales 1.36 times, 1024 -> 17105 at
+// 948 1.6).
+// Where 192 x 256 or 128 x 384 would be taken instead (`smaller`, as smaller_wide numbers them), which are 5 to 15 % ahead of the tile
+// above, 256 x 384 has to be so too.
+constexpr double kWideMargin[] = {1.01, 1.035, 1.02}, kWideMarginSliced = 1.02, kWideMarginSmaller = 0.97;
+bool wide_ahead(int epi, int32_t T, int32_t N, int32_t K, bool narrow, bool sliced, int smaller, const GemvGroup &grp)
 {
     const double wide = large_us(kWide, epi, T, N, K, narrow);
-    if (sliced) return wide < kWideAhead * sliced_cost_us(epi, T, K, grp);
+    if (sliced) return wide < kWideMarginSliced * sliced_cost_us(epi, T, K, grp);
     const int tile = pick_gemm_tile(T, N);
-    return wide < (tile == 0 ? kWideAheadOfLargest : kWideAhead) * large_us(kLarge[tile], epi, T, N, K, narrow);
+    const double margin = smaller == 1 || smaller == 2 ? kWideMarginSmaller : kWideMargin[tile];
+    return wide < margin * large_us(kLarge[tile], epi, T, N, K, narrow);
 }
 
-// Where 256 x 384 is not ahead: the tile of w4a8_wide.hip (its index there) that is expected ahead of the tile above, or -1, by
+// Beside 256 x 384: the tile of w4a8_wide.hip (its index there) that is expected ahead of the tile above, or -1, by
 // rounds of tiles over the CUs x tile area / rate, a last round of few tiles counted as 0.7 of a full one: rates and that share
 // with the least regret over 168 shapes at T = 520 .. 8192.  us, the tile above / this: 8192 -> 10240 at T = 900 82.9 / 68.2,
 // 3584 -> 4608 at 2048 38.6 / 32.7, 3584 -> 3584 at 3000 39.9 / 35.0.  On short K the first two take one
@@ -1239,7 +1244,8 @@ int gemm_dispatch(const int8_t *xq, const uint8_t *wp, const void *w_scale, void
     if constexpr (EPI != kEpiSplit)
         if (!force_sliced && force_tile < 0 && splits == 1 && T > 512 && K >= 1024) {
             const bool narrow = N % 8 != 0 || ldy % 8 != 0 || !aligned_to(y, 16) || acc_out != nullptr;
-            const int tile = wide_ahead(EPI, T, N, K, narrow, sliced, grp) ? 0 : sliced ? -1 : smaller_wide(T, N, K, narrow);
+            const int smaller = sliced ? -1 : smaller_wide(T, N, K, narrow);
+            const int tile = wide_ahead(EPI, T, N, K, narrow, sliced, smaller, grp) ? 0 : smaller;
             if (tile >= 0) return launch_wide<EPI>(tile, xq, T, K, grp.p[0], ep, stream);
         }
     if (sliced) return sliced_dispatch<EPI>(xq, T, K, grp, ep, stream);
