@@ -68,17 +68,30 @@ __device__ __forceinline__ void tile_of_group(int32_t id, int32_t tiles_m, int32
     tn = in_band / rows;
 }
 
-// Waits for this wave's copies of stage s, PER of them: at most MOST of the stages behind it may still be on their way.  (Given the
-// number of those that are left instead, the per-row-scale kernel of 64 x 256 was compiled to 2 % more time on average,
-// 9 % at worst.)
+// Waits for a stage of this wave's copies, PER of them: at most MOST of the stages behind it, and of these the `left` that there
+// are, may still be on their way.
 template <int MOST, int PER>
-__device__ __forceinline__ void wait_stages(int32_t s, int32_t stages)
+__device__ __forceinline__ void wait_left(int32_t left)
+{
+    if constexpr (MOST <= 0) {
+        wait_vmcnt<0>();
+    } else {
+        if (left >= MOST) wait_vmcnt<MOST * PER>();
+        else wait_left<MOST - 1, PER>(left);
+    }
+}
+
+// The same for stage s of `stages`.  The two are compiled to different loops: by the count the per-row-scale kernel of 64 x 256 takes
+// 1 to 2 % longer on average, 9 % at worst, the others of up to three stages 0.5 %; this way those of four stages and those
+// of 256 columns with flagged channels take up to 1.5 % longer.
+template <int MOST, int PER>
+__device__ __forceinline__ void wait_stage(int32_t s, int32_t stages)
 {
     if constexpr (MOST <= 0) {
         wait_vmcnt<0>();
     } else {
         if (s + MOST < stages) wait_vmcnt<MOST * PER>();
-        else wait_stages<MOST - 1, PER>(s, stages);
+        else wait_stage<MOST - 1, PER>(s, stages);
     }
 }
 
@@ -168,7 +181,9 @@ __global__ __launch_bounds__(512, (sliced_lds_bytes<MT, NWN, NB, kEpiStatic>() <
         if (s < stages)
 #pragma unroll
             for (int i = 0; i < S::PER; ++i) copy_piece(i, s, s * S::STAGE);
-    wait_stages<NB - 1, S::PER>(0, stages);
+    constexpr bool COUNT_LEFT = NB > 3 || (EPI == kEpiSplit && NWN == 8);
+    if constexpr (COUNT_LEFT) wait_left<NB - 1, S::PER>(stages - 1);
+    else wait_stage<NB - 1, S::PER>(0, stages);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -195,7 +210,8 @@ __global__ __launch_bounds__(512, (sliced_lds_bytes<MT, NWN, NB, kEpiStatic>() <
             const int st = m / MT, mt = m % MT;
             if (m == LAND) {
                 // this wave's copies of the next stage have landed: its own weights
-                wait_stages<NB - 2, S::PER>(s + 1, stages);
+                if constexpr (COUNT_LEFT) wait_left<NB - 2, S::PER>(stages - 2 - s);
+                else wait_stage<NB - 2, S::PER>(s + 1, stages);
                 asm volatile("" ::: "memory");
                 bw_n[0] = btile(nxt, 0);
                 bw_n[1] = btile(nxt, 1);
