@@ -405,17 +405,21 @@ constexpr Variant kSliced[] = {
     {{128, 256, 1, 2.507, 5.304, 0.602, 0.000, 0.230, 1.424}, MQ_SLICED(4, 8, 3)},
 };
 #undef MQ_SLICED
-// What the estimates of the last four are multiplied by against all others.  They hold within a few percent, while those of
-// the tiles that share a compute unit, of split-K and of the large tiles are up to 15 % above what these take by now,
-// most of all over several rounds.  8000 shapes that the bare estimates send to the four (K 384 .. 29696, T 33 .. 8192): a
-// quarter of them 2 to 24 % slower (static 16640 -> 2624 at T = 3394 147 -> 165 us, 28288 -> 24456 at 213 172 -> 197, 1152 ->
-// 16448 at 65 1.24 times), 0.941 of the time on average; with 1.07 one in a hundred more than 2 % slower, 9 % at most, 0.933
-// on average; with 1.03 one in ten, with 1.1 0.943 on average.  Up to 64 rows the four take up to 20 % longer than their
-// fit, whose rows are mostly more (every weight is then read by one tile, from HBM): with 1.14 all of the 16 shapes of the
-// sweep that go to them gain 10 to 30 %, without it three lose 2 to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).
+// What the estimates of the last four are multiplied by.  They hold within a few percent, while those of the 96 x 128 tile that
+// shares a compute unit, of split-K and of the large tiles are up to 15 % above what these take by now, most of all over several
+// rounds.  By the bare estimates a quarter of 5000 drawn shapes that went to the four (K 384 .. 29696, T 33 .. 8192) was 2 to 24 %
+// slower (static 16640 -> 2624 at T = 3394 147 -> 165 us, 28288 -> 24456 at 213 172 -> 197, 1152 -> 16448 at 65 1.24 times),
+// 0.941 of the time on average.  With these factors 0.930 and one in fifteen, mostly 128 x 256 against 64 x 256, which gain on
+// one box (0.95 with each side in a run of its own) and lose on another (1.03 in turns).
+//   up to 64 rows: 1.14.  There the four take up to 20 % longer than their fit, whose rows are mostly more (every weight is then
+//     read by one tile, from HBM): all of the 16 shapes of the sweep that go to them gain 10 to 30 %, without it three lose 2
+//     to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).
+//   against 96 x 128: 1.07 (between 0.92 and 0.95 of its estimate there is no shape; above, 1.00 to 1.19 of its time)
+//   against the other sliced tiles: 1.02 (0.98 .. 1.0 of their estimates 1.01 of their time)
+//   against the plan: 1.07, four stages of 64 x 128 1.04 (split-K at 0.88 .. 0.91 of its estimate: 0.97 of its time, with 128 x 256 1.05)
 constexpr int kOneRound = 11;             // the first of the tiles that have a compute unit to themselves
-constexpr double kAlone = 1.07, kFewRows = 1.14;
-// The operands of flagged channels push two work-groups of this tile off a compute unit, and its estimate does not know: the
+constexpr double kFewRows = 1.14, kAgainstSliced = 1.02, kAgainst96 = 1.07, kAgainstPlan = 1.07, kAgainstPlan64 = 1.04;
+// The operands of flagged channels push two work-groups of 96 x 128 off a compute unit, and its estimate does not know: the
 // four are then taken wherever their bare estimates are ahead of it (0.73 .. 0.95 of its time).
 constexpr int kCrowded = 5;
 static_assert(sliced_lds_bytes<3, 4, 2, kEpiStatic>() <= 80 * 1024 && sliced_lds_bytes<3, 4, 2, kEpiSplit>() > 80 * 1024, "kCrowded");
@@ -466,14 +470,17 @@ Choice pick(int epi, int32_t T, int32_t K, const GemvGroup &grp)
             return c.us(tiles_n(c) * ceil_div32(T, c.bm), K);
         };
         for (int i = 0; i < kOneRound; ++i) consider(i, us_of(i));
-        const double factor = T <= 64 ? kFewRows : kAlone;
-        const double bar = best.us * (epi == kEpiSplit && best.variant == kCrowded ? factor : 1.0);
-        Choice alone = {-1, bar};
+        double factor = T <= 64 ? kFewRows : best.variant == kCrowded ? kAgainst96 : kAgainstSliced;
+        if (epi == kEpiSplit && best.variant == kCrowded) factor = 1.0;
+        Choice alone = {-1, best.us / factor};
         for (int i = kOneRound; i < kVariants; ++i) {
-            const double us = factor * us_of(i);
+            const double us = us_of(i);
             if (us < alone.us) alone = {i, us};
         }
-        if (alone.variant >= 0) best = {alone.variant, alone.us < best.us ? alone.us : best.us};
+        if (alone.variant >= 0) {
+            const double us = alone.us * (T <= 64 ? kFewRows : alone.variant == kOneRound ? kAgainstPlan64 : kAgainstPlan);
+            best = {alone.variant, us < best.us ? us : best.us};
+        }
     }
     return best;
 }
