@@ -7,7 +7,7 @@
 // words the errors.  Nothing is kept from one call for another.
 //
 // A call through this file costs the host 1.0 us beside the launch, through ctypes 3.3 (512 -> 512 at T = 64, a 3.8 us
-// kernel: 6.0 -> 4.0, 6.4 -> 5.0 and 6.8 -> 4.9 us a call on three boxes).
+// kernel: 6.0 -> 4.0, 6.4 -> 5.0 and 6.8 -> 4.9 us a call on three machines).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

@@ -410,7 +410,7 @@ constexpr Variant kSliced[] = {
 // rounds.  By the bare estimates a quarter of 5000 drawn shapes that went to the four (K 384 .. 29696, T 33 .. 8192) was 2 to 24 %
 // slower (static 16640 -> 2624 at T = 3394 147 -> 165 us, 28288 -> 24456 at 213 172 -> 197, 1152 -> 16448 at 65 1.24 times),
 // 0.941 of the time on average.  With these factors 0.930 and one in fifteen, mostly 128 x 256 against 64 x 256, which gain on
-// one box (0.95 with each side in a run of its own) and lose on another (1.03 in turns).
+// one card (0.95 with each side in a run of its own) and lose on another (1.03 in turns).
 //   up to 64 rows: 1.14.  There the four take up to 20 % longer than their fit, whose rows are mostly more (every weight is then
 //     read by one tile, from HBM): all of the 16 shapes of the sweep that go to them gain 10 to 30 %, without it three lose 2
 //     to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).

@@ -2,7 +2,7 @@
 // sizes fill the compute units' rounds better than those of w4a8_gemm.hip.
 //
 // What bounds the largest is power (8192 -> 59136 at T = 16384: the matrix pipes hold an MFMA in 84 % of the busy cycles, 78 % with
-// 256 x 256, at 1.70 GHz where the rotation beside it runs at 2.0), and a large part of it goes into bringing operands to the matrix
+// 256 x 256, at 1.6 to 1.7 GHz where the rotation beside it runs at 1.9), and a large part of it goes into bringing operands to the matrix
 // cores.  Per multiply-add the 256 x 384 tile takes 22 % fewer bytes out of the L2 and 27 % fewer out of LDS than 256 x 256 with
 // 128 x 64 wave tiles: eight waves, two rows of four, hold 128 x 96 each, 192 accumulator registers.  The 64 that
 // are left do not take two sets of operands, so the fragments of the activations go through a ring of four, each requested
@@ -18,7 +18,7 @@
 // barrier a stage, three fragments before its end, where its last operands are in registers.  (Stages of 64 channels, five of
 // them: rows of 64 bytes and twice the barriers cost what the tile gains.)
 //
-// us, 256 x 256 -> 256 x 384, two boxes: 8192 -> 59136 at T = 16384 6158 -> 5770, 3584 -> 37888 at 1280 154 -> 143 and 149 -> 145, at
+// us, 256 x 256 -> 256 x 384, two cards: 8192 -> 59136 at T = 16384 6158 -> 5770, 3584 -> 37888 at 1280 154 -> 143 and 149 -> 145, at
 // 16384 1889 -> 1780; against 128 x 256 3584 -> 4608 at 4096 71.7 -> 64.6, 8192 -> 10240 at 2048 158 -> 141.
 // 192 x 256 and 128 x 384, against what was taken before them: 8192 -> 10240 at 900 82.9 -> 68.2, 6912 -> 5120 at 2048 74.1 -> 62.1,
 // 5120 -> 5120 at 2048 53.6 -> 46.6, 3584 -> 4608 at 2048 38.6 -> 32.7, 3584 -> 3584 at 3000 39.9 -> 35.0.
