@@ -187,8 +187,8 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
 template <int EPI>
 int launch_wide(int tile, const int8_t *xq, int32_t T, int32_t K, const GemvProblem &pr, const Epilogue &ep, hipStream_t stream);
 
-// What its cost model expects of the tile it would pick.
-double sliced_cost_us(int epi, int32_t T, int32_t K, const GemvGroup &grp);
+// What its cost model expects of the tile it would pick, for the comparison with a plan of `splits` pieces of K.
+double sliced_cost_us(int epi, int32_t T, int32_t K, const GemvGroup &grp, int32_t splits);
 
 // ---- the GEMV of w4a8_walk.hip, one work-group per compute unit: several rows on many output channels
 bool gemv_walk_takes(int32_t T, int32_t K, GemvGroup grp);

@@ -996,7 +996,7 @@ constexpr double kWideMargin[] = {1.01, 1.035, 1.02}, kWideMarginSliced = 1.02, 
 bool wide_ahead(int epi, int32_t T, int32_t N, int32_t K, bool narrow, bool sliced, int smaller, const GemvGroup &grp)
 {
     const double wide = large_us(kWide, epi, T, N, K, narrow);
-    if (sliced) return wide < kWideMarginSliced * sliced_cost_us(epi, T, K, grp);
+    if (sliced) return wide < kWideMarginSliced * sliced_cost_us(epi, T, K, grp, 1);
     const int tile = pick_gemm_tile(T, N);
     const double margin = smaller == 1 || smaller == 2 ? kWideMarginSmaller : kWideMargin[tile];
     return wide < margin * large_us(kLarge[tile], epi, T, N, K, narrow);
@@ -1069,7 +1069,7 @@ bool sliced_ahead(int epi, int32_t T, int32_t N, int32_t K, int32_t splits, cons
     const TileCost &c = kPrefillCost[pick_gemm_tile(T, N)];
     const bool full = splits == 1 && T > 128 &&
                       10 * static_cast<int64_t>(ceil_div32(T, c.bm)) * ceil_div32(N, c.bn) >= 7 * kNumCU;
-    return sliced_cost_us(epi, T, K, grp) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
+    return sliced_cost_us(epi, T, K, grp, splits) < (full ? 0.88 : 0.94) * prefill_cost_us(T, N, K, splits);
 }
 
 }  // namespace

@@ -416,9 +416,12 @@ constexpr Variant kSliced[] = {
 //     to 7 % (2048 -> 27648 at T = 64 11.3 -> 12.2).
 //   against 96 x 128: 1.07 (between 0.92 and 0.95 of its estimate there is no shape; above, 1.00 to 1.19 of its time)
 //   against the other sliced tiles: 1.02 (0.98 .. 1.0 of their estimates 1.01 of their time)
-//   against the plan: 1.07, four stages of 64 x 128 1.04 (split-K at 0.88 .. 0.91 of its estimate: 0.97 of its time, with 128 x 256 1.05)
+//   against the plan: 1.07 (at 0.88 .. 0.94 of its estimate 1.01 to 1.07 of its time); four stages of 64 x 128 1.04, with
+//     flagged channels nothing (64-row tiles at 0.88 .. 0.90: 0.99 of their time, 0.94); against six pieces of K and more
+//     nothing (0.95 to 0.99 there; 18944 -> 3584 at T = 577 .. 734 0.98)
 constexpr int kOneRound = 11;             // the first of the tiles that have a compute unit to themselves
 constexpr double kFewRows = 1.14, kAgainstSliced = 1.02, kAgainst96 = 1.07, kAgainstPlan = 1.07, kAgainstPlan64 = 1.04;
+constexpr int kManyPieces = 6;
 // The operands of flagged channels push two work-groups of 96 x 128 off a compute unit, and its estimate does not know: the
 // four are then taken wherever their bare estimates are ahead of it (0.73 .. 0.95 of its time).
 constexpr int kCrowded = 5;
@@ -447,7 +450,8 @@ struct Choice {
     double us;
 };
 
-Choice pick(int epi, int32_t T, int32_t K, const GemvGroup &grp)
+// `splits`: pieces of K in the plan that the estimate will be compared with
+Choice pick(int epi, int32_t T, int32_t K, const GemvGroup &grp, int32_t splits)
 {
     auto tiles_n = [&](const TileCost &c) {
         int64_t tiles = 0;
@@ -478,7 +482,9 @@ Choice pick(int epi, int32_t T, int32_t K, const GemvGroup &grp)
             if (us < alone.us) alone = {i, us};
         }
         if (alone.variant >= 0) {
-            const double us = alone.us * (T <= 64 ? kFewRows : alone.variant == kOneRound ? kAgainstPlan64 : kAgainstPlan);
+            const bool rows64 = alone.variant == kOneRound;
+            const double plan = splits >= kManyPieces || (rows64 && epi == kEpiSplit) ? 1.0 : rows64 ? kAgainstPlan64 : kAgainstPlan;
+            const double us = alone.us * (T <= 64 ? kFewRows : plan);
             best = {alone.variant, us < best.us ? us : best.us};
         }
     }
@@ -489,7 +495,7 @@ Choice pick(int epi, int32_t T, int32_t K, const GemvGroup &grp)
 
 namespace mquant {
 
-double sliced_cost_us(int epi, int32_t T, int32_t K, const GemvGroup &grp) { return pick(epi, T, K, grp).us; }
+double sliced_cost_us(int epi, int32_t T, int32_t K, const GemvGroup &grp, int32_t splits) { return pick(epi, T, K, grp, splits).us; }
 
 // From 33 rows on always.  Of 17 to 32 rows the GEMV keeps what the GEMM is not expected to do faster by
 // 2 %, or at all where the weights take 10 us and more to read (GEMV against GEMM, weights from HBM, 24
@@ -504,7 +510,7 @@ bool gemm_takes(int32_t T, int32_t K, const GemvGroup &grp)
     for (int32_t i = 0; i < grp.n; ++i) n_tiles += ceil_div32(grp.p[i].N, kPackN);
     if (K <= 256 && n_tiles < kNumCU) return false;
     const double margin = n_tiles * K >= int64_t{1} << 22 ? 1.0 : 0.98;     // 64 MiB of weights
-    return sliced_cost_us(kEpiStatic, T, K, grp) < margin * gemv_tile_us(T, n_tiles, K);
+    return sliced_cost_us(kEpiStatic, T, K, grp, 1) < margin * gemv_tile_us(T, n_tiles, K);
 }
 
 template <int EPI>
@@ -512,7 +518,7 @@ int sliced_dispatch(const int8_t *xq, int32_t T, int32_t K, const GemvGroup &grp
                     hipStream_t stream)
 {
     int v = tune_state().gemm_sliced.load(std::memory_order_relaxed);
-    if (v < 0) v = pick(EPI, T, K, grp).variant;
+    if (v < 0) v = pick(EPI, T, K, grp, 1).variant;
     if (v == kVariants) {                    // forced: 256 x 384, or the largest tile here for what that does not take
         if constexpr (EPI != kEpiSplit)
             if (grp.n == 1) return launch_wide<EPI>(0, xq, T, K, grp.p[0], ep, stream);

@@ -148,6 +148,7 @@ def w4a8_as(mq, epi, T, N, K):
     (1, 985, 6016, 28672, "w4a8_gemm_kernel<256, 256,"), ("row", 1217, 3792, 5760, "w4a8_sliced_kernel<5, 4, 2,"),            # 1.14, 1.10
     (1, 329, 11904, 12416, "w4a8_sliced_kernel<3, 8, 3,"), ("row", 40, 23936, 5120, "w4a8_sliced_kernel<2, 4, 4,"),           # 0.64, 0.75
     ("static", 763, 2285, 18944, "w4a8_sliced_kernel<2, 4, 4,"), ("static", 144, 12480, 11776, "w4a8_sliced_kernel<3, 4, 4,"),  # 0.76, 0.80
+    ("row", 662, 3584, 18944, "w4a8_sliced_kernel<3, 4, 4,"), ("static", 457, 13856, 5120, "w4a8_sliced_kernel<4, 8, 3,"),      # 0.96, 0.95
 ])
 def test_tiles_that_have_a_compute_unit_alone(mq, epi, T, N, K, name):
     """The sliced tiles with three and four stages against all others (their time over the other side's: over 1 they are not
