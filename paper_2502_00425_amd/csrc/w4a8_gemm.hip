@@ -990,9 +990,10 @@ double large_us(const LargeCost &c, int epi, int32_t T, int32_t N, int32_t K, bo
 // By rounds of tiles and one rate for each tile, without short K, the stores and the rows, 480 of 2560 drawn shapes were more than
 // 2 % slower (1536 -> 13814 at T = 7730 176 -> 223 us, 1152 -> 24077 at 3487 with per-row scales 1.36 times, 1024 -> 17105 at
 // 948 1.6).
-// Where 192 x 256 or 128 x 384 would be taken instead (`smaller`, as smaller_wide numbers them), which are 5 to 15 % ahead of the tile
-// above, 256 x 384 has to be so too.
-constexpr double kWideMargin[] = {1.01, 1.035, 1.02}, kWideMarginSliced = 1.02, kWideMarginSmaller = 0.97;
+// Where 192 x 256 or 128 x 384 would be taken instead (`smaller`, as smaller_wide numbers them), which are ahead of the tile above
+// themselves, 256 x 384 has to be 1 % ahead of it by the costs (8192 -> 10240 at T = 3300, estimate 1.02: 233 us against 222; 8192 ->
+// 59136 at 2460, 0.97: 907 against 922).
+constexpr double kWideMargin[] = {1.01, 1.035, 1.02}, kWideMarginSliced = 1.02, kWideMarginSmaller = 0.99;
 bool wide_ahead(int epi, int32_t T, int32_t N, int32_t K, bool narrow, bool sliced, int smaller, const GemvGroup &grp)
 {
     const double wide = large_us(kWide, epi, T, N, K, narrow);
